@@ -2,7 +2,9 @@
 
 The forward kernel is instantiated once per large-kernel size in a translation unit of
 its own (esc_variants.hip with -DESC_KS=<Ks>), so the units compile in parallel; the
-host side and the C ABI are esc_api.hip.
+host side and the C ABI are esc_api.hip.  The Python binding's argument handling
+(esc_native.cpp) is host code against torch's headers, a module of its own that links the
+library.
 """
 from __future__ import annotations
 
@@ -10,12 +12,14 @@ import concurrent.futures
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(CSRC, "_build")
 LIB = os.path.join(CSRC, "libesc_convattn.so")
+NATIVE = os.path.join(HERE, "_native.so")
 
 KERNEL_SIZES = (0,) + tuple(range(1, 32, 2))
 
@@ -41,6 +45,21 @@ def _units(extra_sources=()):
     return units
 
 
+def _native_commands():
+    """(compile, link) command lines of the binding's native half."""
+    import torch
+    from torch.utils import cpp_extension
+    obj = os.path.join(OBJ_DIR, "esc_native.o")
+    inc = [f"-I{d}" for d in (os.path.join(ROOT, "include"), *cpp_extension.include_paths(), sysconfig.get_paths()["include"],
+                               "/opt/rocm/include")]
+    cxx = ["g++", "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+    libs = [f"-L{d}" for d in cpp_extension.library_paths()]
+    return ([*cxx, *inc, "-c", "-o", obj, os.path.join(CSRC, "esc_native.cpp")],
+            ["g++", "-shared", "-fPIC", "-o", NATIVE, obj, f"-L{CSRC}", "-lesc_convattn", "-Wl,-rpath,$ORIGIN/csrc",
+             *libs, "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"])
+
+
 def build(verbose: bool = False, extra=(), jobs: int | None = None) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     os.makedirs(OBJ_DIR, exist_ok=True)
@@ -48,20 +67,23 @@ def build(verbose: bool = False, extra=(), jobs: int | None = None) -> str:
                      if f.endswith(".hip") and f not in ("esc_api.hip", "esc_variants.hip")]
     jobs = jobs or min(8, os.cpu_count() or 1)
 
-    def compile_one(unit):
-        src, defs, obj = unit
-        cmd = [hipcc, *HIPCC_FLAGS, *extra, *defs, "-c", "-o", os.path.join(OBJ_DIR, obj), src]
+    def run(cmd):
         if verbose:
             print(" ".join(cmd), flush=True)
         subprocess.run(cmd, check=True)
+
+    def compile_one(unit):
+        src, defs, obj = unit
+        run([hipcc, *HIPCC_FLAGS, *extra, *defs, "-c", "-o", os.path.join(OBJ_DIR, obj), src])
         return os.path.join(OBJ_DIR, obj)
 
+    native_compile, native_link = _native_commands()
     with concurrent.futures.ThreadPoolExecutor(max_workers=jobs) as pool:
+        native = pool.submit(run, native_compile)
         objs = list(pool.map(compile_one, _units(extra_sources)))
-    cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
+        native.result()
+    run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs])
+    run(native_link)
     return LIB
 
 
