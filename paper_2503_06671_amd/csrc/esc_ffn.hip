@@ -15,6 +15,7 @@
 #include <stdint.h>
 
 #include "esc_ffn.hpp"
+#include "esc_gelu.hpp"
 
 namespace esc {
 namespace {
@@ -23,26 +24,6 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kFbThreads = 256;
 constexpr int kFbRows = 4;  // rows of a thread's strip
-
-// GELU of ConvFFN, v * Phi(v) with the erf of Phi evaluated by the rational approximation
-// 7.1.26 of Abramowitz and Stegun's handbook (|error| <= 1.5e-7 in erf, i.e. <= 1e-7 |v| in the
-// result: a hundredth of the fp32 parity bar): erf(a) = 1 - (a1 t + ... + a5 t^5) exp(-a^2),
-// t = 1 / (1 + p a), a = |v| / sqrt(2).  A reciprocal, an exponential and a dozen multiply-adds,
-// no branch - a third of the library erf's instructions, which at one GELU per hidden element
-// twice over were most of the vector units' time in these kernels.
-__device__ __forceinline__ float fb_gelu(float v)
-{
-    const float a = fabsf(v) * 0.70710678118654752440f;
-    const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, a, 1.f));
-    float q = fmaf(1.061405429f, t, -1.453152027f);
-    q = fmaf(q, t, 1.421413741f);
-    q = fmaf(q, t, -0.284496736f);
-    q = fmaf(q, t, 0.254829592f);
-    const float e = __builtin_amdgcn_exp2f(a * a * -1.44269504088896340736f);
-    const float erf_a = fmaf(-q * t, e, 1.f);          // erf(|v| / sqrt 2) >= 0
-    const float h = 0.5f * v;
-    return fmaf(fabsf(h), erf_a, h);                   // 0.5 v (1 + sign(v) erf_a)
-}
 
 __device__ __forceinline__ uint16_t fb_f32_to_bf16(float f)
 {
@@ -142,7 +123,7 @@ __global__ __launch_bounds__(kFbThreads) void ffn_branch_kernel(const FfnBranchP
                 s = fmaf(k[0], ra[j], s), s = fmaf(k[1], ra[j + 1], s), s = fmaf(k[2], ra[j + 2], s);
                 s = fmaf(k[3], rb[j], s), s = fmaf(k[4], rb[j + 1], s), s = fmaf(k[5], rb[j + 2], s);
                 s = fmaf(k[6], rc[j], s), s = fmaf(k[7], rc[j + 1], s), s = fmaf(k[8], rc[j + 2], s);
-                o[j] = rb[j + 1] + fb_gelu(s);
+                o[j] = rb[j + 1] + ffn_gelu(s);
             }
             T *dst = vp + (size_t)y * p.W + x0;
             if constexpr (VEC) {
@@ -400,7 +381,7 @@ __global__ __launch_bounds__(kFsThreads, 2) void ffn_stream_kernel(const FfnStre
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 const int m = 8 * (i >> 2) + (i & 3);   // (+ 4 half: in ur and b1p)
-                const float u = fb_gelu(acc[i] + b1v[i]);
+                const float u = ffn_gelu(acc[i] + b1v[i]);
                 ur[m * kFsPitch] = live ? u : 0.f;
             }
         }
@@ -426,7 +407,7 @@ __global__ __launch_bounds__(kFsThreads, 2) void ffn_stream_kernel(const FfnStre
                 s = fmaf(kd[0], a[0][j], s), s = fmaf(kd[1], a[0][j + 1], s), s = fmaf(kd[2], a[0][j + 2], s);
                 s = fmaf(kd[3], a[1][j], s), s = fmaf(kd[4], a[1][j + 1], s), s = fmaf(kd[5], a[1][j + 2], s);
                 s = fmaf(kd[6], a[2][j], s), s = fmaf(kd[7], a[2][j + 1], s), s = fmaf(kd[8], a[2][j + 2], s);
-                vv[j] = a[1][j + 1] + fb_gelu(s);
+                vv[j] = a[1][j + 1] + ffn_gelu(s);
             }
             __builtin_amdgcn_wave_barrier();  // every lane has read the oldest row before any lane overwrites it
             float *vr = ring + vslot * (kFsCh * kFsPitch) + chb * kFsPitch + 16 * half;
@@ -659,7 +640,7 @@ __global__ __launch_bounds__(kFsThreads, 2) void ffn_stream_bf16_kernel(const Ff
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 const int m = 8 * (i >> 2) + (i & 3);
-                const float u = fb_gelu(acc[i] + b1v[i]);
+                const float u = ffn_gelu(acc[i] + b1v[i]);
                 ur[m * kFsPitch] = live ? u : 0.f;
             }
         }
@@ -685,7 +666,7 @@ __global__ __launch_bounds__(kFsThreads, 2) void ffn_stream_bf16_kernel(const Ff
                 s = fmaf(kd[0], a[0][j], s), s = fmaf(kd[1], a[0][j + 1], s), s = fmaf(kd[2], a[0][j + 2], s);
                 s = fmaf(kd[3], a[1][j], s), s = fmaf(kd[4], a[1][j + 1], s), s = fmaf(kd[5], a[1][j + 2], s);
                 s = fmaf(kd[6], a[2][j], s), s = fmaf(kd[7], a[2][j + 1], s), s = fmaf(kd[8], a[2][j + 2], s);
-                vv[j] = a[1][j + 1] + fb_gelu(s);
+                vv[j] = a[1][j + 1] + ffn_gelu(s);
             }
 #pragma unroll
             for (int j = 0; j < 16; j += 2) {
