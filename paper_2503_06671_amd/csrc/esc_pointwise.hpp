@@ -27,7 +27,7 @@ struct PointwiseParams {
     int gelu;           // != 0: GELU on the product plus bias (ConvFFN's first layer)
 };
 
-constexpr int kPointwiseMaxK = 240;  // input channels the kernel's LDS staging holds
+constexpr int kPointwiseMaxK = 240;  // channels of x the entry points take
 
 hipError_t launch_pointwise(const PointwiseParams &p, bool bf16, hipStream_t s);
 
