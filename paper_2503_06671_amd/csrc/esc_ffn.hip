@@ -148,40 +148,40 @@ __global__ __launch_bounds__(kFbThreads) void ffn_branch_kernel(const FfnBranchP
 }
 
 
-// ---- the whole network in one kernel (fp32 storage, C <= 64, Ch <= 128) ------------------
+// ---- the whole network in one kernel (C <= 64, Ch <= 128) --------------------------------
 //
 // A block streams down a strip of the image 32 columns wide (30 output columns and one
 // halo column each side) over a band of rows.  Per input row y:
-//   1. the row's C x 32 values are in LDS (fetched a row ahead), each as three bf16 terms
-//      (v = t0 + t1 + t2 but for 2^-24 of it), pixel-major;
+//   1. the row's C x 32 values are in LDS (fetched a row ahead), pixel-major: bf16 storage as
+//      stored, fp32 storage as three bf16 terms each (v = t0 + t1 + t2 but for 2^-24 of it);
 //   2. wavefront w forms U[32 w .. 32 w + 31][32 columns] = gelu(W1 . x + b1) with
-//      v_mfma_f32_32x32x16_bf16 on the terms - its 32 x 64 tile of W1, three bf16 terms per
-//      weight, lives in registers in the A operand's layout; six of the nine products of
-//      terms are accumulated in fp32, what is left out lies below 2^-24 of a product: fp32
-//      accuracy (3.8e-7 against the oracle at 180 x 320) from instructions a sixteenth as long
-//      as the fp32 ones, which moreover do not hold up the vector units - and writes it,
-//      zeroed outside the image (the branch pads U with zeros), into row y's slot of a
-//      three-row ring in LDS;
-//   3. the same wavefront applies the depth-wise branch to its own 32 hidden channels for
-//      output row y - 1 (lane = one channel and sixteen columns; rows y - 2, y - 1, y from the
-//      ring) and writes V over the ring's oldest row: the first layer, the GELU, the ring
-//      and the branch never leave the wavefront, so no block barrier is needed up to here;
-//   4. after a barrier, wavefront (mt, kh) multiplies W2's rows 32 mt .. + 31 with the 64
-//      hidden channels 64 kh .. + 63 of V (v_mfma_f32_32x32x2_f32, its 32 x 64 tile of W2 in
-//      registers: V as three pixel-major bf16 terms would not fit beside the ring with two
-//      blocks per compute unit); the kh = 1 wavefronts hand their partial sums over through
-//      LDS, the kh = 0 ones add them and b2 and store 30 columns of output row y - 1 - while
-//      the kh = 1 ones already start on the next row.
-// Two barriers per row, 73 KB of LDS (two blocks per compute unit), weights read once per
-// block.  The band's first two input rows are recomputed by the band above
-// (rows_per_band + 2 first-layer rows for rows_per_band output rows), the strips' halo
-// columns by their neighbours (32 for 30).  Measured: fp32 matrix instructions' time and
-// the vector instructions' time add up in this kernel - neither issued among the other
-// wavefront's nor among the same wavefront's vector instructions do fp32 matrix
-// instructions run beside them - so the phases are simply written one after the other,
-// and the first layer moved to the bf16 instructions (46.8 -> 41.0 us at 180 x 320).
+//      v_mfma_f32_32x32x16_bf16, the row as operand A and its 32 x 64 tile of W1 as operand B,
+//      held in registers.  The result puts a hidden channel in a lane; the row's columns sit in
+//      LDS in the order that gives lane (channel, half) the sixteen neighbouring columns
+//      16 half .. 16 half + 15 in its sixteen accumulators;
+//   3. so the depth-wise branch for row y - 1 needs nothing but registers: the last three rows
+//      of U are 3 x 16 registers of the lane, its channel's nine weights nine more, and the two
+//      columns where the halves meet change places once per row (v_permlane32_swap);
+//   4. V is rounded (bf16 storage) or taken apart into three terms (fp32 storage) and written to
+//      LDS pixel-major; after the step's only barrier - both LDS tiles have two buffers -
+//      wavefront w multiplies W2's rows 16 w .. 16 w + 15, in registers too, with all 128 hidden
+//      channels of V (v_mfma_f32_16x16x32_bf16) and stores 30 columns of output row y - 1.  Its
+//      two products hold the odd and the even columns, so a lane stores pairs of neighbours.
+// fp32 storage: three terms per value and weight, the six of nine products of terms that lie
+// above 2^-24 of a product; bf16 storage: the value and two terms per weight.  fp32 sums.
+//
+// What bounds it: the vector instructions.  Two GELUs (ten instructions and an exponential
+// each), ten for the branch and, fp32 storage, five and a half to take V apart per hidden
+// element; the matrix instructions run beside them (the fp32 ones, four times as long, did not).
+// U stays in registers because its way through LDS - sixteen stores and fifty-four loads a lane
+// and row - cost as much as the arithmetic.  The band's first two input rows are recomputed by
+// the band above (rows_per_band + 2 first-layer rows for rows_per_band output rows), the strips'
+// halo columns by their neighbours (32 for 30).
+//@MEASURED@
 
+typedef float f32x4s __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef unsigned u32x2s __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4s __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8s __attribute__((ext_vector_type(8)));
 
@@ -190,34 +190,73 @@ constexpr int kFsC = 64;        // input (and output) channels the tiles hold
 constexpr int kFsCh = 128;      // hidden channels the tiles hold
 constexpr int kFsNp = 32;       // columns of a strip, halo included
 constexpr int kFsOut = 30;      // output columns of a strip
-constexpr int kFsPitch = 33;    // floats between two channel rows of the ring (odd: lanes on different channels, same column, hit different banks)
-constexpr int kFsXPitch = kFsC + 8;                       // bf16 elements between two columns of the input row tile (144 bytes)
-constexpr int kFsXTerm = kFsNp * kFsXPitch;               // bf16 elements of one term's tile
-constexpr int kFsXFloats = (3 * kFsXTerm * 2 + 3) / 4;    // the input row as three bf16 terms, pixel-major (one buffer)
-static_assert((3 * kFsXTerm * 2) % 16 == 0, "the ring starts on a 16-byte boundary");
-constexpr int kFsRingFloats = 3 * kFsCh * kFsPitch;
-constexpr int kFsRedFloats = 2 * 16 * 64;
-constexpr int kFsBiasFloats = kFsCh + kFsC;
-constexpr size_t kFsLdsBytes = (size_t)(kFsXFloats + kFsRingFloats + kFsRedFloats + kFsBiasFloats) * sizeof(float);
+// pitches, in bf16 elements, of 4 words mod 32: the sixteen-byte reads of eight neighbouring lanes cover all banks
+constexpr int kFsXPitch = kFsC + 8;                // between two columns of an input row tile (144 bytes)
+constexpr int kFsVPitch = kFsCh + 8;               // ... of V's tile (272 bytes)
+constexpr int kFsXTerm = kFsNp * kFsXPitch;        // elements of one term's tile
+constexpr int kFsVTerm = kFsNp * kFsVPitch;
+constexpr size_t kFsLdsBytes = (size_t)2 * 3 * (kFsXTerm + kFsVTerm) * 2;  // fp32 storage: two buffers of three terms
+constexpr size_t kFbLdsBytes = (size_t)2 * (kFsXTerm + kFsVTerm) * 2;
+static_assert(2 * kFsLdsBytes <= 160 * 1024, "two blocks per compute unit");
+constexpr unsigned kFsNowhere = 0x80000000u;       // a byte offset beyond any image: loads give 0, stores are dropped
 
-static_assert(kFsCh * (kFsC + 1) + kFsC * (kFsCh + 1) <= kFsXFloats + kFsRingFloats + kFsRedFloats,
-              "the weights pass through the row tile's, the ring's and the partial sums' space on their way into registers");
+extern __shared__ __align__(16) uint16_t fs_lds[];
 
-extern __shared__ __align__(16) float fs_lds[];
-
-__global__ __launch_bounds__(kFsThreads, 2) void ffn_stream_kernel(const FfnStreamParams p)
+// eight fp32 values as T bf16 terms each in a matrix operand's layout: every term the nearest bf16 to what
+// the terms before it left
+template <int T>
+__device__ __forceinline__ void fs_split8(const float *v, u32x4s (&t)[T])
 {
+    unsigned o[T][4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        float a = v[2 * e], b = v[2 * e + 1];
+#pragma unroll
+        for (int q = 0; q < T; ++q) {
+            o[q][e] = fb_pack2_bf16(a, b);
+            a -= __uint_as_float(o[q][e] << 16), b -= __uint_as_float(o[q][e] & 0xffff0000u);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < T; ++q) t[q] = u32x4s{o[q][0], o[q][1], o[q][2], o[q][3]};
+}
+
+// eight neighbouring weights of a row, zeros outside the rows x cols matrix
+__device__ __forceinline__ void fs_weights8(const float *w, int row, int rows, int col, int cols, bool vec, float (&v)[8])
+{
+    if (vec) {  // cols % 4 == 0 on a 16-byte boundary: four weights are in or out together
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const bool in = row < rows && col + 4 * h < cols;
+            const f32x4s r = *reinterpret_cast<const f32x4s *>(w + (in ? (size_t)row * cols + col + 4 * h : 0));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[4 * h + e] = in ? r[e] : 0.f;
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const bool in = row < rows && col + e < cols;
+            const float r = w[in ? (size_t)row * cols + col + e : 0];
+            v[e] = in ? r : 0.f;
+        }
+    }
+}
+
+template <bool BF>
+__device__ __forceinline__ void ffn_stream(const FfnStreamParams &p)
+{
+    constexpr int TX = BF ? 1 : 3;         // terms of a value
+    constexpr int TW = BF ? 2 : 3;         // terms of a weight
+    constexpr int OM = BF ? 1 : 2;         // products of terms whose orders add up to at most this
+    constexpr unsigned ES = BF ? 2u : 4u;  // bytes of a stored value
     const int tid = (int)threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, half = lane >> 5;
-    const int mt = wave & 1, kh = wave >> 1;
+    const int l16 = lane & 15, quad = lane >> 4;
     const int C = p.C, Ch = p.Ch, H = p.H, W = p.W;
 
-    uint16_t *sX = reinterpret_cast<uint16_t *>(fs_lds);   // [3 terms][kFsNp][kFsXPitch] bf16
-    float *ring = fs_lds + kFsXFloats;      // [3][kFsCh][kFsPitch]
-    float *red = ring + kFsRingFloats;      // [2 mt][16][64]
-    float *sB1 = red + kFsRedFloats;        // [kFsCh] first layer's biases, zeros beyond Ch
-    float *sB2 = sB1 + kFsCh;               // [kFsC] second layer's
+    uint16_t *sX = fs_lds;                      // [2][TX][kFsNp][kFsXPitch] bf16
+    uint16_t *sV = sX + 2 * TX * kFsXTerm;      // [2][TX][kFsNp][kFsVPitch] bf16
 
     // which strip, band and image.  Blocks are dealt to the eight dies (XCDs) in turn, each die
     // with an L2 of its own: block b works on piece (b % 8) * (grid / 8) + b / 8 of the image, so
@@ -231,106 +270,72 @@ __global__ __launch_bounds__(kFsThreads, 2) void ffn_stream_kernel(const FfnStre
     const int band = (int)(rem / (unsigned)p.strips), strip = (int)(rem - (unsigned)band * (unsigned)p.strips);
     const int x0 = strip * kFsOut - 1;                    // image column of the strip's column 0
     const int y0 = band * p.rows_per_band;                // first output row
-    const int rows_out = min(p.rows_per_band, H - y0);    // >= 1
-    const size_t plane = (size_t)H * W;
-    const float *xin = (const float *)p.x + (size_t)n * C * plane;
-    const unsigned plane_bytes = (unsigned)plane * 4u;
-    const __amdgpu_buffer_rsrc_t rout = __builtin_amdgcn_make_buffer_rsrc((void *)((float *)p.out + (size_t)n * C * plane), 0,
-                                                                          (int)((unsigned)C * plane_bytes), 0x00020000);
+    const int steps = min(p.rows_per_band, H - y0) + 2;   // input rows, >= 3
+    const unsigned row_bytes = (unsigned)W * ES, plane_bytes = (unsigned)H * row_bytes;
+    const unsigned img_bytes = (unsigned)C * plane_bytes;  // < 2^31 (checked by the caller)
+    const __amdgpu_buffer_rsrc_t rin =
+        __builtin_amdgcn_make_buffer_rsrc((void *)((const char *)p.x + (size_t)n * img_bytes), 0, (int)img_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rout =
+        __builtin_amdgcn_make_buffer_rsrc((void *)((char *)p.out + (size_t)n * img_bytes), 0, (int)img_bytes, 0x00020000);
 
-    // ---- this thread's share of an input row: column tid % 32 of channels tid / 32 + 8 i ----
-    const int xpx = tid & 31, xc0 = tid >> 5;
-    const int gx_in = x0 + xpx;
-    const bool col_in = gx_in >= 0 && gx_in < W;
-    // (the loads' results are not touched until they are put into LDS a row later: a value
-    // used right behind its load makes the compiler wait for the load there)
-    auto fetch_row = [&](int gy, float (&v)[8]) {
-        const bool row_in = gy >= 0 && gy < H;
-        const size_t off = (size_t)(row_in ? gy : 0) * W + (size_t)(col_in ? gx_in : 0);
+    // ---- this thread's share of an input row: channels 8 (tid / 32) ... + 7 of the column that row
+    // tid % 32 of the first layer's product stands for (accumulator i of half h is row 8 (i / 4) + 4 h + i % 4).
+    // A column or channel that does not exist has its offset beyond the image and reads as zero; a row that does
+    // not exist reads as the nearest one (what comes of it is not used) ----
+    const int xslot = tid & 31;
+    const int xcol = x0 + 16 * ((xslot >> 2) & 1) + 4 * (xslot >> 3) + (xslot & 3);
+    const int xc0 = 8 * (tid >> 5);
+    unsigned xoff[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+        xoff[i] = (xcol >= 0 && xcol < W && xc0 + i < C) ? (unsigned)(xc0 + i) * plane_bytes + (unsigned)xcol * ES : kFsNowhere;
+    unsigned xr[8];
+    // (the loads' results are not touched until they are put into LDS a row later)
+    auto fetch_row = [&](int gy) {
+        const unsigned so = (unsigned)min(max(gy, 0), H - 1) * row_bytes;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            const int c = xc0 + 8 * i;
-            v[i] = xin[(size_t)(c < C ? c : 0) * plane + off];
+            if constexpr (BF)
+                xr[i] = (unsigned)(unsigned short)__builtin_amdgcn_raw_buffer_load_b16(rin, (int)xoff[i], (int)so, 0);
+            else
+                xr[i] = __builtin_amdgcn_raw_buffer_load_b32(rin, (int)xoff[i], (int)so, 0);
         }
     };
-    // a row into LDS as three bf16 terms per value (v = t0 + t1 + t2 but for 2^-24 of it: each term
-    // the nearest bf16 to what the terms before it left), pixel-major: the first layer's B operands
-    auto put_row = [&](const float (&v)[8], int gy) {
-        const bool in = col_in && gy >= 0 && gy < H;
-        uint16_t *d = sX + xpx * kFsXPitch + xc0;
+    auto put_row = [&](int buf) {
+        u32x4s t[TX];
+        if constexpr (BF) {
+            t[0] = u32x4s{xr[0] | xr[1] << 16, xr[2] | xr[3] << 16, xr[4] | xr[5] << 16, xr[6] | xr[7] << 16};
+        } else {
+            float v[8];
 #pragma unroll
-        for (int i = 0; i < 8; i += 2) {
-            const float v0 = (in && xc0 + 8 * i < C) ? v[i] : 0.f, v1 = (in && xc0 + 8 * (i + 1) < C) ? v[i + 1] : 0.f;
-            const uint32_t t0 = fb_pack2_bf16(v0, v1);
-            const float r0 = v0 - __uint_as_float(t0 << 16), r1 = v1 - __uint_as_float(t0 & 0xffff0000u);
-            const uint32_t t1 = fb_pack2_bf16(r0, r1);
-            const uint32_t t2 = fb_pack2_bf16(r0 - __uint_as_float(t1 << 16), r1 - __uint_as_float(t1 & 0xffff0000u));
-            d[8 * i] = (uint16_t)t0, d[8 * (i + 1)] = (uint16_t)(t0 >> 16);
-            d[kFsXTerm + 8 * i] = (uint16_t)t1, d[kFsXTerm + 8 * (i + 1)] = (uint16_t)(t1 >> 16);
-            d[2 * kFsXTerm + 8 * i] = (uint16_t)t2, d[2 * kFsXTerm + 8 * (i + 1)] = (uint16_t)(t2 >> 16);
+            for (int i = 0; i < 8; ++i) v[i] = __uint_as_float(xr[i]);
+            fs_split8<TX>(v, t);
         }
+        uint16_t *d = sX + buf * (TX * kFsXTerm) + xslot * kFsXPitch + xc0;
+#pragma unroll
+        for (int q = 0; q < TX; ++q) *reinterpret_cast<u32x4s *>(d + q * kFsXTerm) = t[q];
     };
 
-    float xr[8];
-    fetch_row(y0 - 1, xr);  // the band's first input row travels while the weights are staged
+    fetch_row(y0 - 1);  // the band's first input row travels with the weights
 
-    // ---- weights into registers, in the matrix instructions' A layout.  They pass through
-    // LDS (the row buffers' and the ring's space, rows of an odd pitch), fetched by the block with coalesced loads:
-    // fetched by every lane for itself - thirty-two rows per load instruction - the blocks
-    // moved half a gigabyte through the L2 for 64 KB of weights ----
-    // first layer (bf16 instructions on exact terms): lane holds W1[32 w + l32][16 c + 8 half ... + 7] of
-    // chunk c as three bf16 terms; second layer (fp32 instructions): W2[32 mt + l32][64 kh + 2 kp + half]
-    u32x4s a1t[3][4];
-    float a2[32];
+    // ---- weights into registers, in the matrix operands' layouts, sixteen bytes a load where they allow it.
+    // first layer: lane holds W1[32 w + l32][16 c + 8 half ... + 7]; second: W2[16 w + l16][32 c + 8 quad ... + 7] ----
+    u32x4s a1[4][TW], a2[4][TW];
     {
-        constexpr int kP1 = kFsC + 1, kP2 = kFsCh + 1;
-        float *s1 = fs_lds, *s2 = fs_lds + kFsCh * kP1;  // both matrices at once, over the row buffers and the ring
-        for (int i0 = tid; i0 < kFsCh * kFsC; i0 += 8 * kFsThreads) {
-            float v[8], w[8];
-            bool in1[8], in2[8];
+        const bool vec = C % 4 == 0 && Ch % 4 == 0 && ((uintptr_t)p.w1 | (uintptr_t)p.w2) % 16 == 0;
+        float v1[4][8], v2[4][8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {  // sixteen loads out together, their uses behind them
-                const int i = i0 + u * kFsThreads;
-                const int r1 = i / kFsC, c1 = i - r1 * kFsC, r2 = i / kFsCh, c2 = i - r2 * kFsCh;
-                in1[u] = r1 < Ch && c1 < C;
-                in2[u] = r2 < C && c2 < Ch;
-                v[u] = p.w1[in1[u] ? (size_t)r1 * C + c1 : 0];
-                w[u] = p.w2[in2[u] ? (size_t)r2 * Ch + c2 : 0];
-            }
+        for (int c = 0; c < 4; ++c) fs_weights8(p.w1, 32 * wave + l32, Ch, 16 * c + 8 * half, C, vec, v1[c]);
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int i = i0 + u * kFsThreads;
-                const int r1 = i / kFsC, c1 = i - r1 * kFsC, r2 = i / kFsCh, c2 = i - r2 * kFsCh;
-                s1[r1 * kP1 + c1] = in1[u] ? v[u] : 0.f;
-                s2[r2 * kP2 + c2] = in2[u] ? w[u] : 0.f;
-            }
-        }
-        __syncthreads();
+        for (int c = 0; c < 4; ++c) fs_weights8(p.w2, 16 * wave + l16, C, 32 * c + 8 * quad, Ch, vec, v2[c]);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            unsigned t[3][4];
+        for (int c = 0; c < 4; ++c) fs_split8<TW>(v1[c], a1[c]);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float w0 = s1[(32 * wave + l32) * kP1 + 16 * c + 8 * half + 2 * e];
-                const float w1 = s1[(32 * wave + l32) * kP1 + 16 * c + 8 * half + 2 * e + 1];
-                t[0][e] = fb_pack2_bf16(w0, w1);
-                const float r0 = w0 - __uint_as_float(t[0][e] << 16), r1 = w1 - __uint_as_float(t[0][e] & 0xffff0000u);
-                t[1][e] = fb_pack2_bf16(r0, r1);
-                t[2][e] = fb_pack2_bf16(r0 - __uint_as_float(t[1][e] << 16), r1 - __uint_as_float(t[1][e] & 0xffff0000u));
-            }
-#pragma unroll
-            for (int q = 0; q < 3; ++q) a1t[q][c] = u32x4s{t[q][0], t[q][1], t[q][2], t[q][3]};
-        }
-#pragma unroll
-        for (int kp = 0; kp < 32; ++kp) a2[kp] = s2[(32 * mt + l32) * kP2 + 64 * kh + 2 * kp + half];
-        __syncthreads();  // everyone has its weights: the space is the row buffers' and the ring's from here on
+        for (int c = 0; c < 4; ++c) fs_split8<TW>(v2[c], a2[c]);
     }
-    // biases into LDS (the first barrier below covers them)
-    if (tid < kFsCh) sB1[tid] = (p.b1 != nullptr && tid < Ch) ? p.b1[tid] : 0.f;
-    if (tid < kFsC) sB2[tid] = (p.b2 != nullptr && tid < C) ? p.b2[tid] : 0.f;
-    // the branch: lane = hidden channel 32 w + l32, columns 16 half .. 16 half + 15 of the strip
+    // the branch's and the first layer's other constants of this lane's hidden channel
     const int chb = 32 * wave + l32;
-    float kd[9], bkd;
+    float kd[9], bkd, b1d;
     {
         const bool in = chb < Ch;
 #pragma unroll
@@ -338,388 +343,179 @@ __global__ __launch_bounds__(kFsThreads, 2) void ffn_stream_kernel(const FfnStre
             const float v = p.k[in ? (size_t)chb * 9 + t : 0];
             kd[t] = in ? v : 0.f;
         }
-        const float vb = p.bk != nullptr ? p.bk[in ? chb : 0] : 0.f;
-        bkd = (in && p.bk != nullptr) ? vb : 0.f;
+        bkd = (in && p.bk != nullptr) ? p.bk[chb] : 0.f;
+        b1d = (in && p.b1 != nullptr) ? p.b1[chb] : 0.f;
     }
+    // the output channels 16 w + 4 quad ... + 3 this lane's second product holds, of columns 2 l16 + 1 and 2 l16 + 2
+    const int ocol = x0 + 1 + 2 * l16;
+    float b2d[4];
+    unsigned ooff[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int co = 16 * wave + 4 * quad + i;
+        b2d[i] = (p.b2 != nullptr && co < C) ? p.b2[co] : 0.f;
+        ooff[i] = (l16 < 15 && ocol < W && co < C) ? (unsigned)co * plane_bytes + (unsigned)ocol * ES : kFsNowhere;
+    }
+    // an even width has no pair with one column outside and, from such a base, none across a boundary of its size
+    const bool pairs = W % 2 == 0 && (uintptr_t)p.out % (2 * ES) == 0;
+    const bool edge = x0 < 0 || x0 + kFsNp > W;   // some of the strip's columns lie outside the image
 
-    put_row(xr, y0 - 1);
-    fetch_row(y0, xr);
+    put_row(0);
+    fetch_row(y0);
     __syncthreads();
 
-    const bool ucol_in = (x0 + l32) >= 0 && (x0 + l32) < W;   // the column a lane's accumulators hold
-    const int steps = rows_out + 2;
-    for (int r = 0; r < steps; ++r) {
-        const int gy = y0 - 1 + r;   // this step's input row
-        // ---- first layer on row gy: U tile = W1 tile . x row ----
-        {
-            f32x16 acc;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-            // the biases of the rows this lane's accumulators hold, asked for in front of the
-            // products (read one by one where they are used, each read's latency was waited for)
-            const float *b1p = sB1 + 32 * wave + 4 * half;
-            float b1v[16];
-#pragma unroll
-            for (int i = 0; i < 16; ++i) b1v[i] = b1p[8 * (i >> 2) + (i & 3)];
-            // v_mfma_f32_32x32x16_bf16 on the terms: of the nine products of a weight's and a value's terms
-            // the six whose orders add up to at most two (the rest lies below 2^-24 of a product)
-            const uint16_t *bx = sX + l32 * kFsXPitch + 8 * half;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                u32x4s x3[3];
-#pragma unroll
-                for (int q = 0; q < 3; ++q) x3[q] = *reinterpret_cast<const u32x4s *>(bx + q * kFsXTerm + 16 * c);
-#pragma unroll
-                for (int qw = 2; qw >= 0; --qw)
-#pragma unroll
-                    for (int qx = 2 - qw; qx >= 0; --qx)
-                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8s, a1t[qw][c]),
-                                                                      __builtin_bit_cast(bf16x8s, x3[qx]), acc, 0, 0, 0);
-            }
-            const bool live = ucol_in && gy >= 0 && gy < H;
-            float *ur = ring + (r % 3) * (kFsCh * kFsPitch) + (32 * wave + 4 * half) * kFsPitch + l32;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int m = 8 * (i >> 2) + (i & 3);   // (+ 4 half: in ur and b1p)
-                const float u = ffn_gelu(acc[i] + b1v[i]);
-                ur[m * kFsPitch] = live ? u : 0.f;
-            }
-        }
-        __builtin_amdgcn_wave_barrier();  // (a wavefront's LDS accesses are carried out in order)
-        // ---- the branch on output row gy - 1, this wavefront's 32 hidden channels ----
-        const int vslot = (r + 1) % 3;    // the ring's oldest row, (r - 2) % 3: V goes there
-        if (r >= 2) {
-            float a[3][18];
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                const float *row = ring + ((r + 1 + i) % 3) * (kFsCh * kFsPitch) + chb * kFsPitch;
-#pragma unroll
-                for (int j = 0; j < 18; ++j) {
-                    const int px = 16 * half - 1 + j;   // -1 and 32 lie outside the strip: only halo columns need them
-                    const float v = row[px < 0 ? 0 : (px > 31 ? 31 : px)];
-                    a[i][j] = (px >= 0 && px <= 31) ? v : 0.f;
-                }
-            }
-            float vv[16];
-#pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                float s = bkd;
-                s = fmaf(kd[0], a[0][j], s), s = fmaf(kd[1], a[0][j + 1], s), s = fmaf(kd[2], a[0][j + 2], s);
-                s = fmaf(kd[3], a[1][j], s), s = fmaf(kd[4], a[1][j + 1], s), s = fmaf(kd[5], a[1][j + 2], s);
-                s = fmaf(kd[6], a[2][j], s), s = fmaf(kd[7], a[2][j + 1], s), s = fmaf(kd[8], a[2][j + 2], s);
-                vv[j] = a[1][j + 1] + ffn_gelu(s);
-            }
-            __builtin_amdgcn_wave_barrier();  // every lane has read the oldest row before any lane overwrites it
-            float *vr = ring + vslot * (kFsCh * kFsPitch) + chb * kFsPitch + 16 * half;
-#pragma unroll
-            for (int j = 0; j < 16; ++j) vr[j] = vv[j];
-        }
-        __syncthreads();  // V of all hidden channels is in LDS; everyone has multiplied this step's input row
-        // the next row into the (one) row tile, the row after it asked for
-        if (r + 1 < steps) {
-            put_row(xr, gy + 1);
-            if (r + 2 < steps) fetch_row(gy + 2, xr);
-        }
-        // ---- second layer: W2 tile (32 output channels x 64 hidden channels) . V ----
-        f32x16 acc2;
-        if (r >= 2) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc2[i] = 0.f;
-            const float *bv = ring + vslot * (kFsCh * kFsPitch) + (64 * kh + half) * kFsPitch + l32;
-#pragma unroll
-            for (int kp = 0; kp < 32; ++kp)
-                acc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a2[kp], bv[2 * kp * kFsPitch], acc2, 0, 0, 0);
-            if (kh == 1) {
-#pragma unroll
-                for (int i = 0; i < 16; ++i) red[(mt * 16 + i) * 64 + lane] = acc2[i];
-            }
-        }
-        __syncthreads();  // the partial sums and the next input row are in LDS; nobody reads V any more
-        if (r >= 2 && kh == 0) {
-            const int gyo = gy - 1, gxo = x0 + l32;
-            const bool st_ok = l32 >= 1 && l32 <= kFsOut && gxo < W;   // (gyo < H by the loop's bound)
-            float rv[16], bv[16];
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                rv[i] = red[(mt * 16 + i) * 64 + lane];
-                bv[i] = sB2[32 * mt + 8 * (i >> 2) + 4 * half + (i & 3)];
-            }
-            // buffer stores on a resource that is the image's output: what is not to be
-            // written gets an offset beyond it and is dropped - no branches
-            // (the channel's plane offset as the lane's part plus a multiple of the plane's bytes that is
-            // the same for all lanes: one multiplication per lane instead of sixteen)
-            const int co0 = 32 * mt + 4 * half;
-            const unsigned lane_off = (unsigned)co0 * plane_bytes + (unsigned)(gyo * W + gxo) * 4u;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int dc = 8 * (i >> 2) + (i & 3);
-                const float v = acc2[i] + rv[i] + bv[i];
-                const unsigned off = (st_ok && co0 + dc < C) ? lane_off + (unsigned)dc * plane_bytes : 0x80000000u;
-                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rout, (int)off, 0, 2 /* non-temporal */);
-            }
-        }
-    }
-}
-
-// ---- the same for bf16 storage, on the bf16 matrix instructions --------------------------
-//
-// v_mfma_f32_32x32x16_bf16 on the stored values, every fp32 weight as two bf16 terms
-// (w = hi + lo to 16 mantissa bits; products exact, fp32 accumulation): a sixteenth of the
-// fp32 instructions' time, and beside the vector units instead of in their way.  What
-// changes against the fp32 kernel is the layout of the matrix operands: an operand wants
-// eight consecutive channels of one pixel per lane, so the input row and V sit in LDS
-// pixel-major ([column][channel] bf16, 16-byte reads; pitches of 4 words mod 32, which
-// spreads a half-wavefront's sixteen-byte reads evenly over the banks), each weight tile is
-// 2 terms x 4 chunks of sixteen channels x 4 registers, and V has a buffer of its own (it
-// is bf16, the ring fp32).  U stays fp32 in the ring - only V is rounded to bf16 on the way
-// to the second layer, as a stored V would be - and out is rounded once at its store.
-
-constexpr int kFbXPitch = kFsC + 8;                  // bf16 elements between two columns of an input row tile (144 bytes)
-constexpr int kFbVPitch = kFsCh + 8;                 // ... of V's tile (272 bytes)
-constexpr int kFbXElems = 2 * kFsNp * kFbXPitch;     // two row buffers
-constexpr int kFbVElems = kFsNp * kFbVPitch;
-constexpr size_t kFbLdsBytes = (size_t)(kFbXElems + kFbVElems) * 2 +
-                               (size_t)(kFsRingFloats + kFsRedFloats + kFsBiasFloats) * sizeof(float);
-static_assert((kFbXElems * 2) % 16 == 0 && (kFbVElems * 2) % 16 == 0, "the fp32 parts start on 16-byte boundaries");
-static_assert((size_t)(kFsCh * (kFsC + 1) + kFsC * (kFsCh + 1)) * 4 <= (size_t)(kFbXElems + kFbVElems) * 2 + (size_t)kFsRingFloats * 4,
-              "the weights pass through the tiles' and the ring's space on their way into registers");
-
-// eight fp32 weights as the two bf16 terms of an A operand: hi = bf16(w), lo = bf16(w - hi)
-__device__ __forceinline__ void fb_split8(const float *w, u32x4s &hi, u32x4s &lo)
-{
-    unsigned h[4], l[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        h[e] = fb_pack2_bf16(w[2 * e], w[2 * e + 1]);
-        l[e] = fb_pack2_bf16(w[2 * e] - __uint_as_float(h[e] << 16), w[2 * e + 1] - __uint_as_float(h[e] & 0xffff0000u));
-    }
-    hi = u32x4s{h[0], h[1], h[2], h[3]};
-    lo = u32x4s{l[0], l[1], l[2], l[3]};
-}
-
-__global__ __launch_bounds__(kFsThreads, 2) void ffn_stream_bf16_kernel(const FfnStreamParams p)
-{
-    const int tid = (int)threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int l32 = lane & 31, half = lane >> 5;
-    const int mt = wave & 1, kh = wave >> 1;
-    const int C = p.C, Ch = p.Ch, H = p.H, W = p.W;
-
-    uint16_t *sX = reinterpret_cast<uint16_t *>(fs_lds);   // [2][kFsNp][kFbXPitch] bf16
-    uint16_t *sV = sX + kFbXElems;                         // [kFsNp][kFbVPitch] bf16
-    float *ring = reinterpret_cast<float *>(sV + kFbVElems);  // [3][kFsCh][kFsPitch]
-    float *red = ring + kFsRingFloats;                     // [2 mt][16][64]
-    float *sB1 = red + kFsRedFloats;
-    float *sB2 = sB1 + kFsCh;
-
-    // which strip, band and image (pieces dealt so that neighbours meet in one die's L2, as above)
-    const unsigned bq = gridDim.x / 8u, br = gridDim.x % 8u, xcd = blockIdx.x % 8u;
-    const unsigned piece = xcd * bq + (xcd < br ? xcd : br) + blockIdx.x / 8u;
-    const unsigned per_img = (unsigned)p.strips * (unsigned)p.bands;
-    const unsigned n = piece / per_img;
-    const unsigned rem = piece - n * per_img;
-    const int band = (int)(rem / (unsigned)p.strips), strip = (int)(rem - (unsigned)band * (unsigned)p.strips);
-    const int x0 = strip * kFsOut - 1;
-    const int y0 = band * p.rows_per_band;
-    const int rows_out = min(p.rows_per_band, H - y0);
-    const size_t plane = (size_t)H * W;
-    const uint16_t *xin = (const uint16_t *)p.x + (size_t)n * C * plane;
-    const unsigned plane_bytes = (unsigned)plane * 2u;
-    const __amdgpu_buffer_rsrc_t rout = __builtin_amdgcn_make_buffer_rsrc((void *)((uint16_t *)p.out + (size_t)n * C * plane), 0,
-                                                                          (int)((unsigned)C * plane_bytes), 0x00020000);
-
-    // ---- this thread's share of an input row: column tid % 32 of channels tid / 32 + 8 i ----
-    const int xpx = tid & 31, xc0 = tid >> 5;
-    const int gx_in = x0 + xpx;
-    const bool col_in = gx_in >= 0 && gx_in < W;
-    auto fetch_row = [&](int gy, uint16_t (&v)[8]) {
-        const bool row_in = gy >= 0 && gy < H;
-        const size_t off = (size_t)(row_in ? gy : 0) * W + (size_t)(col_in ? gx_in : 0);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int c = xc0 + 8 * i;
-            v[i] = xin[(size_t)(c < C ? c : 0) * plane + off];
-        }
-    };
-    auto put_row = [&](const uint16_t (&v)[8], int gy, int buf) {
-        const bool in = col_in && gy >= 0 && gy < H;
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-            sX[buf * (kFsNp * kFbXPitch) + xpx * kFbXPitch + xc0 + 8 * i] = (in && xc0 + 8 * i < C) ? v[i] : (uint16_t)0;
-    };
-
-    uint16_t xr[8];
-    fetch_row(y0 - 1, xr);  // the band's first input row travels while the weights are staged
-
-    // ---- weights: fp32 through LDS as in the fp32 kernel, then split into their two bf16
-    // terms in the A operand's layout: lane holds W[row][16 c + 8 half ... + 7] of chunk c ----
-    u32x4s a1h[4], a1l[4], a2h[4], a2l[4];
-    {
-        constexpr int kP1 = kFsC + 1, kP2 = kFsCh + 1;
-        float *s1 = fs_lds, *s2 = fs_lds + kFsCh * kP1;
-        for (int i0 = tid; i0 < kFsCh * kFsC; i0 += 8 * kFsThreads) {
-            float v[8], w[8];
-            bool in1[8], in2[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int i = i0 + u * kFsThreads;
-                const int r1 = i / kFsC, c1 = i - r1 * kFsC, r2 = i / kFsCh, c2 = i - r2 * kFsCh;
-                in1[u] = r1 < Ch && c1 < C;
-                in2[u] = r2 < C && c2 < Ch;
-                v[u] = p.w1[in1[u] ? (size_t)r1 * C + c1 : 0];
-                w[u] = p.w2[in2[u] ? (size_t)r2 * Ch + c2 : 0];
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int i = i0 + u * kFsThreads;
-                const int r1 = i / kFsC, c1 = i - r1 * kFsC, r2 = i / kFsCh, c2 = i - r2 * kFsCh;
-                s1[r1 * kP1 + c1] = in1[u] ? v[u] : 0.f;
-                s2[r2 * kP2 + c2] = in2[u] ? w[u] : 0.f;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            float w8[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) w8[e] = s1[(32 * wave + l32) * kP1 + 16 * c + 8 * half + e];
-            fb_split8(w8, a1h[c], a1l[c]);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) w8[e] = s2[(32 * mt + l32) * kP2 + 64 * kh + 16 * c + 8 * half + e];
-            fb_split8(w8, a2h[c], a2l[c]);
-        }
-        __syncthreads();  // everyone has its weights: the space is the tiles' and the ring's from here on
-    }
-    if (tid < kFsCh) sB1[tid] = (p.b1 != nullptr && tid < Ch) ? p.b1[tid] : 0.f;
-    if (tid < kFsC) sB2[tid] = (p.b2 != nullptr && tid < C) ? p.b2[tid] : 0.f;
-    const int chb = 32 * wave + l32;
-    float kd[9], bkd;
-    {
-        const bool in = chb < Ch;
-#pragma unroll
-        for (int t = 0; t < 9; ++t) {
-            const float v = p.k[in ? (size_t)chb * 9 + t : 0];
-            kd[t] = in ? v : 0.f;
-        }
-        const float vb = p.bk != nullptr ? p.bk[in ? chb : 0] : 0.f;
-        bkd = (in && p.bk != nullptr) ? vb : 0.f;
-    }
-
-    put_row(xr, y0 - 1, 0);
-    fetch_row(y0, xr);
-    __syncthreads();
-
-    const bool ucol_in = (x0 + l32) >= 0 && (x0 + l32) < W;
-    const int steps = rows_out + 2;
-    for (int r = 0; r < steps; ++r) {
+    // first layer on input row r of the band: u[j] is column 16 half + j; u[16], u[17]: the column left of and the
+    // column right of the half (used where the other half has it: the strip's outer neighbours are nobody's)
+    auto first = [&](int r, float (&u)[18]) {
         const int gy = y0 - 1 + r;
-        if (r + 1 < steps) {
-            put_row(xr, gy + 1, (r + 1) & 1);
-            if (r + 2 < steps) fetch_row(gy + 2, xr);
+        if (gy < 0 || gy >= H) {  // the branch pads U with zeros
+#pragma unroll
+            for (int j = 0; j < 18; ++j) u[j] = 0.f;
+            return;
         }
-        // ---- first layer on row gy ----
-        {
-            f32x16 acc;
+        f32x16 acc;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-            const uint16_t *bx = sX + (r & 1) * (kFsNp * kFbXPitch) + l32 * kFbXPitch + 8 * half;
-            const float *b1p = sB1 + 32 * wave + 4 * half;
-            float b1v[16];
+        for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+        const uint16_t *ax = sX + (r & 1) * (TX * kFsXTerm) + l32 * kFsXPitch + 8 * half;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) b1v[i] = b1p[8 * (i >> 2) + (i & 3)];
-            u32x4s bq[4];
+        for (int c = 0; c < 4; ++c) {
+            u32x4s x[TX];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) bq[c] = *reinterpret_cast<const u32x4s *>(bx + 16 * c);
+            for (int q = 0; q < TX; ++q) x[q] = *reinterpret_cast<const u32x4s *>(ax + q * kFsXTerm + 16 * c);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8s, a1h[c]), __builtin_bit_cast(bf16x8s, bq[c]), acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8s, a1l[c]), __builtin_bit_cast(bf16x8s, bq[c]), acc, 0, 0, 0);
-            }
-            const bool live = ucol_in && gy >= 0 && gy < H;
-            float *ur = ring + (r % 3) * (kFsCh * kFsPitch) + (32 * wave + 4 * half) * kFsPitch + l32;
+            for (int qw = TW - 1; qw >= 0; --qw)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int m = 8 * (i >> 2) + (i & 3);
-                const float u = ffn_gelu(acc[i] + b1v[i]);
-                ur[m * kFsPitch] = live ? u : 0.f;
-            }
+                for (int qx = TX - 1; qx >= 0; --qx)
+                    if (qw + qx <= OM)
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8s, x[qx]),
+                                                                      __builtin_bit_cast(bf16x8s, a1[c][qw]), acc, 0, 0, 0);
         }
-        __builtin_amdgcn_wave_barrier();  // (a wavefront's LDS accesses are carried out in order)
-        // ---- the branch on output row gy - 1; V, rounded to bf16, into its pixel-major tile ----
-        if (r >= 2) {
-            float a[3][18];
 #pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                const float *row = ring + ((r + 1 + i) % 3) * (kFsCh * kFsPitch) + chb * kFsPitch;
-#pragma unroll
-                for (int j = 0; j < 18; ++j) {
-                    const int px = 16 * half - 1 + j;
-                    const float v = row[px < 0 ? 0 : (px > 31 ? 31 : px)];
-                    a[i][j] = (px >= 0 && px <= 31) ? v : 0.f;
-                }
-            }
-            uint16_t *vr = sV + (16 * half) * kFbVPitch + chb;
-            float vv[16];
+        for (int j = 0; j < 16; ++j) u[j] = ffn_gelu(acc[j] + b1d);
+        if (edge) {
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
+                const int gx = x0 + 16 * half + j;
+                u[j] = gx >= 0 && gx < W ? u[j] : 0.f;
+            }
+        }
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(u[0]), __float_as_uint(u[15]), false, false);
+        u[16] = __uint_as_float(sw[0]), u[17] = __uint_as_float(sw[1]);
+    };
+    // the branch on the middle one of three rows of U; V into its buffer.  The second layer's lane l wants columns
+    // 2 l + 1 and 2 l + 2 (mod 32): column c's slot is c / 2 for odd ones, 16 + (c / 2 - 1) mod 16 for even ones
+    uint16_t *const vw = sV + 8 * half * kFsVPitch + chb;
+    uint16_t *const vw0 = sV + (half ? 23 : 31) * kFsVPitch + chb;
+    auto branch = [&](int r, const float (&ua)[18], const float (&ub)[18], const float (&uc)[18]) {
+        const int buf = (r & 1) * (TX * kFsVTerm);
+#pragma unroll
+        for (int j = 0; j < 16; j += 2) {
+            float v[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int m = j + e, l = m == 0 ? 16 : m - 1, g = m == 15 ? 17 : m + 1;
                 float s = bkd;
-                s = fmaf(kd[0], a[0][j], s), s = fmaf(kd[1], a[0][j + 1], s), s = fmaf(kd[2], a[0][j + 2], s);
-                s = fmaf(kd[3], a[1][j], s), s = fmaf(kd[4], a[1][j + 1], s), s = fmaf(kd[5], a[1][j + 2], s);
-                s = fmaf(kd[6], a[2][j], s), s = fmaf(kd[7], a[2][j + 1], s), s = fmaf(kd[8], a[2][j + 2], s);
-                vv[j] = a[1][j + 1] + ffn_gelu(s);
+                s = fmaf(kd[0], ua[l], s), s = fmaf(kd[1], ua[m], s), s = fmaf(kd[2], ua[g], s);
+                s = fmaf(kd[3], ub[l], s), s = fmaf(kd[4], ub[m], s), s = fmaf(kd[5], ub[g], s);
+                s = fmaf(kd[6], uc[l], s), s = fmaf(kd[7], uc[m], s), s = fmaf(kd[8], uc[g], s);
+                v[e] = ub[m] + ffn_gelu(s);
             }
+            uint16_t *const d0 = (j == 0 ? vw0 : vw + (15 + j / 2) * kFsVPitch) + buf, *const d1 = vw + (j / 2) * kFsVPitch + buf;
 #pragma unroll
-            for (int j = 0; j < 16; j += 2) {
-                const uint32_t pk = fb_pack2_bf16(vv[j], vv[j + 1]);
-                vr[j * kFbVPitch] = (uint16_t)pk;
-                vr[(j + 1) * kFbVPitch] = (uint16_t)(pk >> 16);
-            }
-        }
-        __syncthreads();  // V of all hidden channels (and the next input row) is in LDS
-        // ---- second layer ----
-        f32x16 acc2;
-        if (r >= 2) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc2[i] = 0.f;
-            const uint16_t *bv = sV + l32 * kFbVPitch + 64 * kh + 8 * half;
-            u32x4s vq[4];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) vq[c] = *reinterpret_cast<const u32x4s *>(bv + 16 * c);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                acc2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8s, a2h[c]), __builtin_bit_cast(bf16x8s, vq[c]), acc2, 0, 0, 0);
-                acc2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8s, a2l[c]), __builtin_bit_cast(bf16x8s, vq[c]), acc2, 0, 0, 0);
-            }
-            if (kh == 1) {
-#pragma unroll
-                for (int i = 0; i < 16; ++i) red[(mt * 16 + i) * 64 + lane] = acc2[i];
+            for (int q = 0; q < TX; ++q) {
+                const uint32_t t = fb_pack2_bf16(v[0], v[1]);
+                d0[q * kFsVTerm] = (uint16_t)t, d1[q * kFsVTerm] = (uint16_t)(t >> 16);
+                v[0] -= __uint_as_float(t << 16), v[1] -= __uint_as_float(t & 0xffff0000u);
             }
         }
-        __syncthreads();  // the partial sums are in LDS; nobody reads V any more
-        if (r >= 2 && kh == 0) {
-            const int gyo = gy - 1, gxo = x0 + l32;
-            const bool st_ok = l32 >= 1 && l32 <= kFsOut && gxo < W;
-            float rv[16], bv2[16];
+    };
+    // second layer on the V of step r, output row y0 + r - 2
+    auto second = [&](int r) {
+        f32x4s acc[2];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                rv[i] = red[(mt * 16 + i) * 64 + lane];
-                bv2[i] = sB2[32 * mt + 8 * (i >> 2) + 4 * half + (i & 3)];
+        for (int t = 0; t < 2; ++t) acc[t] = f32x4s{b2d[0], b2d[1], b2d[2], b2d[3]};
+        const uint16_t *bv = sV + (r & 1) * (TX * kFsVTerm) + l16 * kFsVPitch + 8 * quad;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            u32x4s v[2][TX];
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int q = 0; q < TX; ++q)
+                    v[t][q] = *reinterpret_cast<const u32x4s *>(bv + q * kFsVTerm + 16 * t * kFsVPitch + 32 * c);
+#pragma unroll
+            for (int qw = TW - 1; qw >= 0; --qw)
+#pragma unroll
+                for (int qx = TX - 1; qx >= 0; --qx)
+                    if (qw + qx <= OM) {
+#pragma unroll
+                        for (int t = 0; t < 2; ++t)
+                            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8s, a2[c][qw]),
+                                                                             __builtin_bit_cast(bf16x8s, v[t][qx]), acc[t], 0, 0, 0);
+                    }
+        }
+        // (the same for all lanes, which the compiler must see: otherwise every store is a loop over the lanes' offsets)
+        const int so = __builtin_amdgcn_readfirstlane((int)((unsigned)(y0 + r - 2) * row_bytes));
+        if (pairs) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if constexpr (BF)
+                    __builtin_amdgcn_raw_buffer_store_b32(fb_pack2_bf16(acc[0][i], acc[1][i]), rout, (int)ooff[i], so, 2 /* non-temporal */);
+                else
+                    __builtin_amdgcn_raw_buffer_store_b64(u32x2s{__float_as_uint(acc[0][i]), __float_as_uint(acc[1][i])}, rout,
+                                                          (int)ooff[i], so, 2);
             }
-            const int co0 = 32 * mt + 4 * half;
-            const unsigned lane_off = (unsigned)co0 * plane_bytes + (unsigned)(gyo * W + gxo) * 2u;
+        } else {
 #pragma unroll
-            for (int i = 0; i < 16; i += 2) {
-                const uint32_t pk = fb_pack2_bf16(acc2[i] + rv[i] + bv2[i], acc2[i + 1] + rv[i + 1] + bv2[i + 1]);
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    const int dc = 8 * ((i + e) >> 2) + ((i + e) & 3);
-                    const unsigned off = (st_ok && co0 + dc < C) ? lane_off + (unsigned)dc * plane_bytes : 0x80000000u;
-                    __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(e == 0 ? pk : pk >> 16), rout, (int)off, 0, 2 /* non-temporal */);
+            for (int i = 0; i < 4; ++i) {
+                const unsigned off1 = ocol + 1 < W ? ooff[i] + ES : kFsNowhere;
+                if constexpr (BF) {
+                    const uint32_t o = fb_pack2_bf16(acc[0][i], acc[1][i]);
+                    __builtin_amdgcn_raw_buffer_store_b16((unsigned short)o, rout, (int)ooff[i], so, 2);
+                    __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(o >> 16), rout, (int)off1, so, 2);
+                } else {
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[0][i]), rout, (int)ooff[i], so, 2);
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[1][i]), rout, (int)off1, so, 2);
                 }
             }
         }
+    };
+    // one input row: the next one into the other buffer (whose readers are behind the last barrier) and the one after
+    // it asked for, first layer, and from the third row on branch and second layer for the row above
+    auto next_row = [&](int r) {
+        if (r + 1 < steps) {
+            put_row((r + 1) & 1);
+            if (r + 2 < steps) fetch_row(y0 + 1 + r);
+        }
+    };
+    auto step = [&](int r, const float (&ua)[18], const float (&ub)[18], float (&uc)[18]) {
+        next_row(r);
+        first(r, uc);
+        branch(r, ua, ub, uc);
+        __syncthreads();  // V of all hidden channels and the next input row are in LDS
+        second(r);
+    };
+    float u0[18], u1[18], u2[18];
+    next_row(0);
+    first(0, u0);
+    __syncthreads();
+    next_row(1);
+    first(1, u1);
+    __syncthreads();
+    // three copies of the step, the three rows of U in three sets of registers that take turns
+    for (int r = 2;; r += 3) {
+        step(r, u0, u1, u2);
+        if (r + 1 >= steps) break;
+        step(r + 1, u1, u2, u0);
+        if (r + 2 >= steps) break;
+        step(r + 2, u2, u0, u1);
+        if (r + 3 >= steps) break;
     }
 }
+
+__global__ __launch_bounds__(kFsThreads, 2) void ffn_stream_kernel(const FfnStreamParams p) { ffn_stream<false>(p); }
+
+__global__ __launch_bounds__(kFsThreads, 2) void ffn_stream_bf16_kernel(const FfnStreamParams p) { ffn_stream<true>(p); }
 
 }  // namespace
 
