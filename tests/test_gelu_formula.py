@@ -28,26 +28,32 @@ def test_rational_erf_keeps_gelu_within_its_stated_error():
 
 
 def test_power_of_two_form_keeps_gelu_within_its_stated_error():
-    # the form the kernels evaluate (csrc/esc_gelu.hpp): max(v, 0) - |v| 2^-(1 + |v| P(|v|)), every multiply-add
-    # rounded once.  Its own bars: 8e-8 |v| (the fit's 1e-8 and three roundings of 2^-25 to 2^-24 relative to |v|) and
-    # half an ulp of the largest argument, 2^-21, absolutely; P must not turn down beyond the fitted range.
+    # the form the kernels evaluate (csrc/esc_gelu.hpp): h + |h| (1 - 2^-(|v| P(|v|))), h = v / 2.  Bars: relative to |v|
+    # the fit's 1e-8, half a rounding of 1 - e (2^-26), half an ulp of the exponential (2^-25) and the last
+    # rounding (2^-24), together 1.2e-7; half an ulp of the largest argument, 2^-21, absolutely; P must not
+    # turn down beyond the fitted range.  Infinities as in the definition evaluated in floating point.
     f = np.float32
     v = np.concatenate([np.linspace(-12.0, 12.0, 600001), np.logspace(1, 38, 2000), -np.logspace(1, 38, 2000)]).astype(f)
-    t = np.abs(v)
 
     def fma(a, b, c):
         return (np.asarray(a, np.float64) * b + c).astype(f)
 
-    with np.errstate(over="ignore"):
-        q = fma(f(2.834909764715121e-06), t.astype(np.float64), np.float64(f(-3.937766086892225e-05)))
-        for c in (0.0001861801283666864, 0.0001369366073049605, -0.0070634204894304276, 0.052496179938316345,
-                  0.4592081904411316, 1.1511051654815674):
-            q = fma(q, t.astype(np.float64), np.float64(f(c)))
-        e = np.exp2(fma(-q.astype(np.float64), t.astype(np.float64), -1.0).astype(np.float64)).astype(f)
-    g = fma(-t.astype(np.float64), e.astype(np.float64), np.maximum(v, 0).astype(np.float64)).astype(np.float64)
+    def gelu(v):
+        t = np.abs(v).astype(np.float64)
+        with np.errstate(over="ignore", invalid="ignore"):
+            q = fma(f(2.834909764715121e-06), t, np.float64(f(-3.937766086892225e-05)))
+            for c in (0.0001861801283666864, 0.0001369366073049605, -0.0070634204894304276, 0.052496179938316345,
+                      0.4592081904411316, 1.1511051654815674):
+                q = fma(q, t, np.float64(f(c)))
+            e = np.exp2((-q * t).astype(f).astype(np.float64)).astype(f)
+            h = f(0.5) * v
+            return fma(np.abs(h), (f(1) - e).astype(np.float64), h.astype(np.float64))
+
+    g, t = gelu(v).astype(np.float64), np.abs(v).astype(np.float64)
     ref = np.array([0.5 * x * math.erfc(-x / math.sqrt(2.0)) for x in v.astype(np.float64)])
     err = np.abs(g - ref)
-    near = t <= 12
-    assert err[near].max() <= 2.0 ** -21, err[near].max()
-    assert (err <= 8e-8 * np.maximum(t.astype(np.float64), 1e-2)).all()
+    assert err[t <= 12].max() <= 2.0 ** -21, err[t <= 12].max()
+    assert (err <= 1.2e-7 * np.maximum(t, 1e-2)).all()
     assert g[t == 0].tolist() == [0.0] * int((t == 0).sum())
+    special = gelu(np.array([np.inf, -np.inf, np.nan], f))
+    assert np.isposinf(special[0]) and np.isnan(special[1]) and np.isnan(special[2])
