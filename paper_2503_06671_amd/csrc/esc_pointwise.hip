@@ -337,6 +337,40 @@ __device__ __forceinline__ void pointwise_body(const PointwiseParams &p)
                 }
             }
         }
+
+    // An infinite value, or one beyond the largest bf16, has no three terms: its products come out NaN, and so does
+    // every output channel of that pixel.  Those elements - none in an ordinary image: one comparison for two
+    // accumulators - are summed again in plain fp32, which gives what fp32 arithmetic gives.
+    if constexpr (F) {
+        bool bad = false;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+#pragma unroll
+                for (int t = 0; t < NT; t += 2) bad |= __builtin_isunordered(acc[mt][t][i], acc[mt][NT > 1 ? t + 1 : t][i]);
+        if (!bad || px >= P) return;
+        const float *b1 = (const float *)p.src1 + (size_t)n * p.src1_img_stride + pxc;
+        const float *b2 = (const float *)p.src2 + (size_t)n * p.src2_img_stride + pxc;
+        const float *br = (const float *)p.res + (size_t)n * p.res_img_stride + pxc;
+        float *bd = (float *)p.dst + (size_t)n * p.dst_img_stride + pxc;
+#pragma unroll 1
+        for (int i = 0; i < 16 * MT; ++i) {
+            const int m = m0 + 32 * (i >> 4) + 8 * ((i & 15) >> 2) + 4 * half + (i & 3);
+            if (m >= M) continue;
+#pragma unroll 1
+            for (int t = 0; t < NT; ++t) {
+                float *d = bd + (size_t)m * P + t;
+                // this lane's own store, or the same bits from the lane whose pixels overlap
+                if (!__builtin_isnan(__hip_atomic_load(d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) continue;
+                float s = p.bias != nullptr ? p.bias[m] : 0.f;
+                if (!GELU && p.res != nullptr) s += br[(size_t)m * P + t];
+                for (int k = 0; k < K; ++k)
+                    s = fmaf(p.w[(size_t)m * p.w_ld + k], k < K1 ? b1[(size_t)k * P + t] : b2[(size_t)(k - K1) * P + t], s);
+                *d = GELU ? ffn_gelu(s) : s;
+            }
+        }
+    }
 }
 
 // 64 pixels per wavefront.
