@@ -558,18 +558,28 @@ __attribute__((visibility("hidden"))) hipError_t launch_ffn_stream(const FfnStre
     }
     FfnStreamParams q = p;
     q.strips = (p.W + kFsOut - 1) / kFsOut;
-    // a block lasts as long whatever the image's size (its weights' way into registers, then six
-    // rows one after the other): with too few blocks to fill the chip the three launches are faster
-    if ((long)p.N * q.strips * ((p.H + 3) / 4) < 3L * cus / 2) return hipErrorNotSupported;
-    // ... and a last strip that is mostly empty costs as much as a full one: widths that fill less than
-    // four fifths of their strips keep the three launches too (64 columns are 30 + 30 + 4)
-    if (5L * p.W < 4L * q.strips * kFsOut) return hipErrorNotSupported;
+    // Which problems take one launch (C = 64, Ch = 128, the residual step around it; three launches -> one):
+    //  * small ones, whose four-row bands fit on the chip in one round, at widths that fill at least half of their
+    //    strips and nearly all of the kernel's channels (it always works for 64 and 128: with 32 and 64 the three
+    //    launches are as fast).  64 x 64 fp32 38 -> 27 us, bf16 34 -> 24; 135 x 240 50 -> 43, 43 -> 36; 8 x 64 x 64
+    //    50 -> 46, 42 -> 37; 2000 x 8, a quarter of a strip: 50 -> 53.
+    //  * large ones at widths that fill at least four fifths of their strips: a last strip that is mostly empty costs
+    //    as much as a full one (180 x 320 fp32 68 -> 50, 16 x 72 x 72 107 -> 86; 32 x 64 x 64 bf16, whose 64
+    //    columns are 30 + 30 + 4: 72 -> 74).
+    const long quads = (long)p.N * q.strips * ((p.H + 3) / 4), width = (long)q.strips * kFsOut;
+    const bool small = quads <= 2L * cus && 2L * p.W >= width && 4L * p.C * p.Ch >= 3L * kFsC * kFsCh;
+    const bool large = 2 * quads >= 3L * cus && 5L * p.W >= 4 * width;
+    if (!small && !large) return hipErrorNotSupported;
     // the band height that needs the fewest row steps one after the other: a block takes its rows + 2
-    // steps and about a step and a half to get its weights; the blocks run in rounds of two per compute unit
+    // steps and about a step and a half to get its weights; the blocks run in rounds of two per compute unit.
+    // Bands of less than four rows where they leave half of the compute units to a single block (64 x 64 fp32:
+    // one row 27 us, two 30, four 35; 135 x 240: 360 blocks of three rows 43, 272 of four 47; 8 x 64 x 64: 528 of three
+    // 47, 384 of four 46)
     q.rows_per_band = 4;
     double best = 0.0;
-    for (int rb = 4; rb <= 32; rb *= 2) {
+    for (int rb : {4, 1, 2, 3, 8, 16, 32}) {
         const long blocks = (long)p.N * q.strips * ((p.H + rb - 1) / rb);
+        if (rb < 4 && (!small || 2 * blocks > 3L * cus)) continue;
         const long rounds = (blocks + 2L * cus - 1) / (2L * cus);
         const double cost = (double)rounds * (rb + 3.5);
         if (rb == 4 || cost < best) {
