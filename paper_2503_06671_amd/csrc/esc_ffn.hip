@@ -154,6 +154,12 @@ __global__ __launch_bounds__(kFbThreads) void ffn_branch_kernel(const FfnBranchP
 // fp32 storage: three terms per value and weight, the six of nine products of terms that lie
 // above 2^-24 of a product; bf16 storage: the value and two terms per weight.  fp32 sums.
 //
+// With fp32 storage an infinite value, and one of x or a weight beyond the largest bf16, has no three
+// terms (inf - inf is left for the second): its products come out NaN.  Elements of U and of out that
+// do - none in an ordinary image: twelve comparisons a lane and row - are summed again in fp32, U from x
+// in memory and out from V's terms in LDS, which gives what fp32 arithmetic gives - unless a NaN among
+// their values or weights (the first terms tell) makes them NaN for good.  V's first term is cut off, not rounded, so that every finite V has three terms and an infinite
+// first term means an infinite V.
 // What bounds it: the vector instructions.  Two GELUs (ten instructions and an exponential
 // each), ten for the branch and, fp32 storage, five and a half to take V apart per hidden
 // element; the matrix instructions run beside them (the fp32 ones, four times as long, did not).
@@ -161,7 +167,6 @@ __global__ __launch_bounds__(kFbThreads) void ffn_branch_kernel(const FfnBranchP
 // and row - cost as much as the arithmetic.  The band's first two input rows are recomputed by
 // the band above (rows_per_band + 2 first-layer rows for rows_per_band output rows), the strips'
 // halo columns by their neighbours (32 for 30).
-//@MEASURED@
 
 typedef float f32x4s __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -203,6 +208,16 @@ __device__ __forceinline__ void fs_split8(const float *v, u32x4s (&t)[T])
     }
 #pragma unroll
     for (int q = 0; q < T; ++q) t[q] = u32x4s{o[q][0], o[q][1], o[q][2], o[q][3]};
+}
+
+// whether one of eight first terms is NaN (which it is where the value is)
+__device__ __forceinline__ bool fs_any_nan(u32x4s t)
+{
+    bool n = false;
+    asm volatile("" : "+v"(t));  // (not to be known ahead of the rare case that asks)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) n |= (t[e] & 0x7fffu) > 0x7f80u || (t[e] & 0x7fff0000u) > 0x7f800000u;
+    return n;
 }
 
 // eight neighbouring weights of a row, zeros outside the rows x cols matrix
@@ -374,6 +389,41 @@ __device__ __forceinline__ void ffn_stream(const FfnStreamParams &p)
                         acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8s, x[qx]),
                                                                       __builtin_bit_cast(bf16x8s, a1[c][qw]), acc, 0, 0, 0);
         }
+        if constexpr (!BF) {
+            bool bad = false;
+#pragma unroll
+            for (int j = 0; j < 16; j += 2) bad |= __builtin_isunordered(acc[j], acc[j + 1]);
+            if (__builtin_amdgcn_ballot_w64(bad) != 0) {  // (see above)
+                bool xn = false, wn = false;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) xn |= fs_any_nan(*reinterpret_cast<const u32x4s *>(ax + 16 * c)), wn |= fs_any_nan(a1[c][0]);
+                const uint64_t xm = __builtin_amdgcn_ballot_w64(xn), wm = __builtin_amdgcn_ballot_w64(wn);
+                const unsigned slots = ~(unsigned)(xm | xm >> 32) >> 4 * half;   // columns of x without a NaN
+                const bool row = chb < Ch && ((unsigned)(wm | wm >> 32) >> l32 & 1u) == 0;
+                unsigned todo = 0;
+#pragma unroll
+                for (int j = 0; j < 16; ++j) {
+                    if (chb >= Ch || (__builtin_isnan(acc[j]) && row && (slots >> (8 * (j >> 2) + (j & 3)) & 1u) != 0))
+                        acc[j] = 0.f, todo |= 1u << j;
+                }
+                if (chb >= Ch) todo = 0;
+                int gx0 = x0 + 16 * half;
+                asm volatile("" : "+v"(gx0));  // (nothing of this is to be computed ahead and kept)
+#pragma unroll 1
+                for (int c = 0; c < C && todo != 0; ++c) {
+                    const float w = p.w1[(size_t)chb * C + c];
+                    const unsigned line = (unsigned)c * plane_bytes + (unsigned)gy * row_bytes;
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) {
+                        if (todo >> j & 1u) {  // (what a column outside the image gives is not used)
+                            const unsigned off = line + (unsigned)min(max(gx0 + j, 0), W - 1) * ES;
+                            acc[j] = fmaf(__uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rin, (int)off, 0, 0)), w, acc[j]);
+                            if (__builtin_isnan(acc[j])) todo &= ~(1u << j);
+                        }
+                    }
+                }
+            }
+        }
 #pragma unroll
         for (int j = 0; j < 16; ++j) u[j] = ffn_gelu(acc[j] + b1d);
         if (edge) {
@@ -407,7 +457,9 @@ __device__ __forceinline__ void ffn_stream(const FfnStreamParams &p)
             uint16_t *const d0 = (j == 0 ? vw0 : vw + (15 + j / 2) * kFsVPitch) + buf, *const d1 = vw + (j / 2) * kFsVPitch + buf;
 #pragma unroll
             for (int q = 0; q < TX; ++q) {
-                const uint32_t t = fb_pack2_bf16(v[0], v[1]);
+                // (fp32 storage: the first term is the value's upper half, so that every finite value has its three)
+                const uint32_t t = BF || q > 0 ? fb_pack2_bf16(v[0], v[1])
+                                               : __builtin_amdgcn_perm(__float_as_uint(v[1]), __float_as_uint(v[0]), 0x07060302u);
                 d0[q * kFsVTerm] = (uint16_t)t, d1[q * kFsVTerm] = (uint16_t)(t >> 16);
                 v[0] -= __uint_as_float(t << 16), v[1] -= __uint_as_float(t & 0xffff0000u);
             }
@@ -415,9 +467,10 @@ __device__ __forceinline__ void ffn_stream(const FfnStreamParams &p)
     };
     // second layer on the V of step r, output row y0 + r - 2
     auto second = [&](int r) {
-        f32x4s acc[2];
+        // (fp32 storage: the small products in sums of their own, so that they are not rounded at the large ones' size)
+        f32x4s acc[2], low[2];
 #pragma unroll
-        for (int t = 0; t < 2; ++t) acc[t] = f32x4s{b2d[0], b2d[1], b2d[2], b2d[3]};
+        for (int t = 0; t < 2; ++t) acc[t] = f32x4s{b2d[0], b2d[1], b2d[2], b2d[3]}, low[t] = f32x4s{0.f, 0.f, 0.f, 0.f};
         const uint16_t *bv = sV + (r & 1) * (TX * kFsVTerm) + l16 * kFsVPitch + 8 * quad;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
@@ -433,10 +486,60 @@ __device__ __forceinline__ void ffn_stream(const FfnStreamParams &p)
                 for (int qx = TX - 1; qx >= 0; --qx)
                     if (qw + qx <= OM) {
 #pragma unroll
-                        for (int t = 0; t < 2; ++t)
-                            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8s, a2[c][qw]),
-                                                                             __builtin_bit_cast(bf16x8s, v[t][qx]), acc[t], 0, 0, 0);
+                        for (int t = 0; t < 2; ++t) {
+                            f32x4s &sum = !BF && qw + qx > 0 ? low[t] : acc[t];
+                            sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8s, a2[c][qw]),
+                                                                          __builtin_bit_cast(bf16x8s, v[t][qx]), sum, 0, 0, 0);
+                        }
                     }
+        }
+        if constexpr (!BF) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t) acc[t] += low[t];
+        }
+        if constexpr (!BF) {
+            bool bad = false;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) bad |= __builtin_isunordered(acc[0][i], acc[1][i]);
+            if (__builtin_amdgcn_ballot_w64(bad && l16 < 15) != 0) {  // (see above; V is in LDS, its first term alone where that is infinite)
+                bool vn[2] = {false, false}, wn = false;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    wn |= fs_any_nan(a2[c][0]);
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) vn[t] |= fs_any_nan(*reinterpret_cast<const u32x4s *>(bv + 16 * t * kFsVPitch + 32 * c));
+                }
+                auto fold = [](bool b) {  // of the four lanes l16, l16 + 16, ... : bit l16
+                    const uint64_t m = __builtin_amdgcn_ballot_w64(b);
+                    const unsigned h = (unsigned)m | (unsigned)(m >> 32);
+                    return h | h >> 16;
+                };
+                const unsigned cols[2] = {fold(vn[0]) >> l16, fold(vn[1]) >> l16}, rows = fold(wn) >> 4 * quad;
+                unsigned todo = 0;
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (__builtin_isnan(acc[t][i]) && l16 < 15 && 16 * wave + 4 * quad + i < C && ((cols[t] | rows >> i) & 1u) == 0)
+                            acc[t][i] = b2d[i], todo |= 1u << (4 * t + i);
+                int at = (r & 1) * (TX * kFsVTerm) + l16 * kFsVPitch, co = 16 * wave + 4 * quad;
+                asm volatile("" : "+v"(at), "+v"(co));
+#pragma unroll 1
+                for (int ch = 0; ch < Ch && todo != 0; ++ch) {
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        const uint16_t *e = sV + at + 16 * t * kFsVPitch + ch;
+                        const float t0 = __uint_as_float((uint32_t)e[0] << 16), t1 = __uint_as_float((uint32_t)e[kFsVTerm] << 16);
+                        const float v = __builtin_isinf(t0) ? t0 : t0 + t1 + __uint_as_float((uint32_t)e[2 * kFsVTerm] << 16);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (todo >> (4 * t + i) & 1u) {
+                                acc[t][i] = fmaf(p.w2[(size_t)(co + i) * Ch + ch], v, acc[t][i]);
+                                if (__builtin_isnan(acc[t][i])) todo &= ~(1u << (4 * t + i));
+                            }
+                    }
+                }
+            }
         }
         // (the same for all lanes, which the compiler must see: otherwise every store is a loop over the lanes' offsets)
         const int so = __builtin_amdgcn_readfirstlane((int)((unsigned)(y0 + r - 2) * row_bytes));
