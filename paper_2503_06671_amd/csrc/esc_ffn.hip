@@ -393,7 +393,7 @@ __device__ __forceinline__ void ffn_stream(const FfnStreamParams &p)
             bool bad = false;
 #pragma unroll
             for (int j = 0; j < 16; j += 2) bad |= __builtin_isunordered(acc[j], acc[j + 1]);
-            if (__builtin_amdgcn_ballot_w64(bad) != 0) {  // (see above)
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(bad) != 0, 0)) {  // (see above)
                 bool xn = false, wn = false;
 #pragma unroll
                 for (int c = 0; c < 4; ++c) xn |= fs_any_nan(*reinterpret_cast<const u32x4s *>(ax + 16 * c)), wn |= fs_any_nan(a1[c][0]);
@@ -501,7 +501,7 @@ __device__ __forceinline__ void ffn_stream(const FfnStreamParams &p)
             bool bad = false;
 #pragma unroll
             for (int i = 0; i < 4; ++i) bad |= __builtin_isunordered(acc[0][i], acc[1][i]);
-            if (__builtin_amdgcn_ballot_w64(bad && l16 < 15) != 0) {  // (see above; V is in LDS, its first term alone where that is infinite)
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(bad && l16 < 15) != 0, 0)) {  // (see above; V is in LDS, its first term alone where that is infinite)
                 bool vn[2] = {false, false}, wn = false;
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
