@@ -340,7 +340,10 @@ __device__ __forceinline__ void pointwise_body(const PointwiseParams &p)
 
     // An infinite value, or one beyond the largest bf16, has no three terms: its products come out NaN, and so does
     // every output channel of that pixel.  Those elements - none in an ordinary image: one comparison for two
-    // accumulators - are summed again in plain fp32, which gives what fp32 arithmetic gives.
+    // accumulators - are summed again in plain fp32, which gives what fp32 arithmetic gives.  Not those that are NaN
+    // for good because their row of W or their pixel holds one (found first, each read once): all-NaN
+    // inputs must not cost many times an ordinary call (the fused call at 339 x 511: 78 us, with x all NaN 105; 2010
+    // with every element of it summed again).
     if constexpr (F) {
         bool bad = false;
 #pragma unroll
@@ -349,26 +352,56 @@ __device__ __forceinline__ void pointwise_body(const PointwiseParams &p)
             for (int i = 0; i < 16; ++i)
 #pragma unroll
                 for (int t = 0; t < NT; t += 2) bad |= __builtin_isunordered(acc[mt][t][i], acc[mt][NT > 1 ? t + 1 : t][i]);
-        if (!bad || px >= P) return;
+        bad = bad && px < P;
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(bad) == 0, 1)) return;
+        uint64_t todo = 0;   // this lane's elements, bit NT (16 mt + i) + t
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+                    if (bad && __builtin_isnan(acc[mt][t][i])) todo |= (uint64_t)1 << (NT * (16 * mt + i) + t);
+        bool nan = false;
+        const int wm = m0 + (lane & (32 * MT - 1));
+        const float *wrow = p.w + (wm < M ? (size_t)wm * p.w_ld : 0);
+#pragma unroll 1
+        for (int k = 0; k < K; k += 8)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) nan |= __builtin_isnan(wrow[min(k + e, K - 1)]);
+        const uint64_t nan_rows = __builtin_amdgcn_ballot_w64(nan);   // bit r: row m0 + r of W
         const float *b1 = (const float *)p.src1 + (size_t)n * p.src1_img_stride + pxc;
         const float *b2 = (const float *)p.src2 + (size_t)n * p.src2_img_stride + pxc;
         const float *br = (const float *)p.res + (size_t)n * p.res_img_stride + pxc;
         float *bd = (float *)p.dst + (size_t)n * p.dst_img_stride + pxc;
+        auto value = [&](int k, int t) { return k < K1 ? b1[(size_t)k * P + t] : b2[(size_t)(k - K1) * P + t]; };
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const uint64_t of_t = NT == 1 ? ~(uint64_t)0 : (uint64_t)0x5555555555555555u << t;
+            nan = (todo & of_t) == 0;
 #pragma unroll 1
-        for (int i = 0; i < 16 * MT; ++i) {
-            const int m = m0 + 32 * (i >> 4) + 8 * ((i & 15) >> 2) + 4 * half + (i & 3);
-            if (m >= M) continue;
+            for (int k = 0; k < K && !nan; k += 8)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) nan |= __builtin_isnan(value(min(k + e, K - 1), t));
+            if (nan) todo &= ~of_t;
+        }
 #pragma unroll 1
-            for (int t = 0; t < NT; ++t) {
-                float *d = bd + (size_t)m * P + t;
-                // this lane's own store, or the same bits from the lane whose pixels overlap
-                if (!__builtin_isnan(__hip_atomic_load(d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) continue;
-                float s = p.bias != nullptr ? p.bias[m] : 0.f;
-                if (!GELU && p.res != nullptr) s += br[(size_t)m * P + t];
-                for (int k = 0; k < K; ++k)
-                    s = fmaf(p.w[(size_t)m * p.w_ld + k], k < K1 ? b1[(size_t)k * P + t] : b2[(size_t)(k - K1) * P + t], s);
-                *d = GELU ? ffn_gelu(s) : s;
+        while (todo != 0) {
+            const int bit = __builtin_ctzll(todo), i = bit / NT, t = bit % NT;
+            todo &= todo - 1;
+            const int row = 32 * (i >> 4) + 8 * ((i & 15) >> 2) + 4 * half + (i & 3), m = m0 + row;
+            if (m >= M || (nan_rows >> row & 1) != 0) continue;
+            float s = p.bias != nullptr ? p.bias[m] : 0.f;
+            if (!GELU && p.res != nullptr) s += br[(size_t)m * P + t];
+#pragma unroll 1
+            for (int k = 0; k < K && !__builtin_isnan(s); k += 8) {
+                float w[8], v[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) w[e] = p.w[(size_t)m * p.w_ld + min(k + e, K - 1)], v[e] = value(min(k + e, K - 1), t);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) s = k + e < K ? fmaf(w[e], v[e], s) : s;
             }
+            bd[(size_t)m * P + t] = GELU ? ffn_gelu(s) : s;
         }
     }
 }

@@ -2,8 +2,9 @@
 against the CPU oracle; the bars are the fused call's (tests/test_gpu_fused.py)."""
 import numpy as np
 import pytest
+import torch
 
-from paper_2503_06671_amd import workloads as wk
+from paper_2503_06671_amd import binding, workloads as wk
 from tests.test_gpu_fused import check_fused, pointwise_weights, residual_for, run_fused
 
 pytestmark = pytest.mark.gpu
@@ -57,3 +58,37 @@ def test_values_that_have_no_three_bf16_terms(N):
         fin = np.isfinite(want)
         assert np.array_equal(have[~fin & ~np.isnan(want)], want[~fin & ~np.isnan(want)])
         assert np.allclose(have[fin], want[fin], rtol=1e-5, atol=0)
+
+
+@pytest.mark.parametrize("what", ["x", "last channel", "w1", "w2", "one weight"])
+def test_nan_costs_no_more_than_a_few_ordinary_calls(what):
+    # fp32 storage: an element that is NaN because a value or weight of it is must not be summed again
+    # (three launches, 16 x 96 -> 192 -> 96 channels of 64 x 64: it took 55 to 80 times an ordinary call so, and takes
+    # about twice as long with the rows and pixels found first; the bar is five times)
+    N, C, H, W, Ch = 16, 96, 64, 64, 192
+    g = torch.Generator(device="cuda")
+    g.manual_seed(960)
+    r = lambda *s: torch.randn(s, generator=g, device="cuda") * 0.1
+    x, w1, k, w2 = r(N, C, H, W), r(Ch, C), r(Ch, 3, 3), r(C, Ch)
+    ws, out = binding.new_convffn_workspace(N, Ch, H, W, torch.float32), torch.empty_like(x)
+
+    def us():
+        times = []
+        for _ in range(7):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                binding.convffn_forward(x, w1, k, w2, ws, out=out)
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b) * 200.0)
+        return sorted(times)[3]
+
+    print(f"[case] cost of NaN: {what}", flush=True)
+    ordinary = us()
+    assert torch.isfinite(out).all()
+    {"x": x, "last channel": x[:, -1], "w1": w1, "w2": w2, "one weight": w1[7, -1]}[what].fill_(float("nan"))
+    with_nan = us()
+    print(f"{what}: {ordinary:.1f} us, with NaN {with_nan:.1f} us", flush=True)
+    assert torch.isnan(out).all()
+    assert with_nan <= 5 * ordinary
