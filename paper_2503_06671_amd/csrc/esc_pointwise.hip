@@ -353,7 +353,7 @@ __device__ __forceinline__ void pointwise_body(const PointwiseParams &p)
 #pragma unroll
                 for (int t = 0; t < NT; t += 2) bad |= __builtin_isunordered(acc[mt][t][i], acc[mt][NT > 1 ? t + 1 : t][i]);
         bad = bad && px < P;
-        if (__builtin_expect(__builtin_amdgcn_ballot_w64(bad) == 0, 1)) return;
+        if (__builtin_amdgcn_ballot_w64(bad) == 0) return;
         uint64_t todo = 0;   // this lane's elements, bit NT (16 mt + i) + t
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
