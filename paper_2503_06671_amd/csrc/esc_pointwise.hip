@@ -23,8 +23,12 @@
 // loads of one channel row each bring it (32 lanes on a run of 32 NT pixels: whole cache
 // lines), so the inputs go from memory into the operand's registers without passing LDS,
 // two stages of 32 channels ahead.  Only the weights pass LDS, split into their terms there by
-// the block, a stage at a time in two buffers and one barrier a stage.  The accumulators start
-// from the residual, so that all of a wavefront's reads are in flight at once.  Nothing here
+// the block, a stage at a time in two buffers and one barrier a stage.  The residual's first row
+// block is on its way with them, its second takes an input buffer as that falls free; it is added to
+// the finished sums: one rounding at its size, where sums started from it are rounded there by every
+// matrix instruction (64 -> 64 channels, fp32, a residual ten times the products: error against
+// float64 3.2e-8, started from it 1.7e-7; the fused call 339 x 511 83.4 us, started from it 81.2,
+// with the whole residual in freed buffers 88).  Nothing here
 // asks for alignment: a lane's two pixels are one access wherever they lie (a plane of odd size
 // costs 4 %, where the kernel before this one went element by element).
 //
@@ -204,27 +208,26 @@ __device__ __forceinline__ void pointwise_body(const PointwiseParams &p)
     wfetch(0, wr);
     fetch(0, ra);
     if (stages > 1) fetch(1, rb);
-    // the residual, in the accumulators' layout: lane l of tile t of row block mt holds output channel
+    // the accumulators' layout: lane l of tile t of row block mt holds output channel
     // m0 + 32 mt + 8 (i / 4) + 4 half + i % 4 of pixel px + t in element i
     const unsigned out_off = (unsigned)(m0 + 4 * half) * pb + pxc * (unsigned)sizeof(T);
     auto row_of = [](int mt, int i) { return (unsigned)(32 * mt + 8 * (i >> 2) + (i & 3)); };
-    Raw rv[MT][16];
-    if (!GELU && p.res != nullptr) {
-        const Rsrc rres = __builtin_amdgcn_make_buffer_rsrc((void *)((const T *)p.res + (size_t)n * p.res_img_stride), 0,
-                                                            (int)((unsigned)M * pb), kRawBuffer);
+    // the residual: row block 0's is on its way from the start, row block 1's takes the first input buffer once nothing
+    // will be fetched into it any more
+    const bool has_res = !GELU && p.res != nullptr;
+    const Rsrc rres = __builtin_amdgcn_make_buffer_rsrc((void *)((const T *)p.res + (size_t)n * p.res_img_stride), 0,
+                                                        (int)((unsigned)M * pb), kRawBuffer);
+    auto rfetch = [&](int mt, Raw (&r)[16]) {
+        int m = m0 + 4 * half;
+        asm volatile("" : "+v"(m));  // (not to be computed ahead of the loop and kept through it)
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const unsigned row = row_of(mt, i);
-                rv[mt][i] = load(rres, m0 + 4 * half + (int)row < M ? out_off + row * pb : kBeyond, 0);
-            }
-    } else {
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) rv[mt][i] = Raw{};
-    }
+        for (int i = 0; i < 16; ++i) {
+            const unsigned row = row_of(mt, i);
+            r[i] = load(rres, m + (int)row < M ? out_off : kBeyond, row * pb);
+        }
+    };
+    Raw rv[16];
+    if (has_res) rfetch(0, rv);
     float *s_bias = reinterpret_cast<float *>(pw_lds + 2 * 2 * MT * TW * 64);
     if (tid < 32 * MT) s_bias[tid] = (p.bias != nullptr && m0 + tid < M) ? p.bias[m0 + tid] : 0.f;
     wput(0, wr);
@@ -237,20 +240,11 @@ __device__ __forceinline__ void pointwise_body(const PointwiseParams &p)
             for (int g = 0; g < 4; ++g) {
                 const f32x4 b = *reinterpret_cast<const f32x4 *>(s_bias + 32 * mt + 8 * g + 4 * half);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const Raw r = rv[mt][4 * g + e];
-                    if constexpr (F && NT == 2) {
-                        acc[mt][0][4 * g + e] = __uint_as_float(r.x) + b[e];
-                        acc[mt][1][4 * g + e] = __uint_as_float(r.y) + b[e];
-                    } else if constexpr (F) {
-                        acc[mt][0][4 * g + e] = __uint_as_float(r) + b[e];
-                    } else {
-                        acc[mt][0][4 * g + e] = __uint_as_float(r << 16) + b[e];
-                        if constexpr (NT == 2) acc[mt][NT - 1][4 * g + e] = __uint_as_float(r & 0xffff0000u) + b[e];
-                    }
-                }
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) acc[mt][t][4 * g + e] = b[e];
             }
-    auto body = [&](int st, Raw (&raw)[16]) {
+    auto body = [&](int st, Raw (&raw)[16], bool first) {
         if (st + 1 < stages) wfetch(st + 1, wr);
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
@@ -279,7 +273,12 @@ __device__ __forceinline__ void pointwise_body(const PointwiseParams &p)
                     if constexpr (NT == 2) b[NT - 1][0][e] = __builtin_amdgcn_perm(x1, x0, 0x07060302u);  // the high ones
                 }
             }
-            if (c == 1 && st + 2 < stages) fetch(st + 2, raw);
+            if (c == 1 || st * kPwStage + 16 >= K) {
+                if (st + 2 < stages)
+                    fetch(st + 2, raw);
+                else if (has_res && MT > 1 && first)
+                    rfetch(1, raw);
+            }
             const u32x4 *wa = pw_lds + (((st & 1) * 2 + c) * MT * TW) * 64 + lane;
             u32x4 a[MT][TW];
 #pragma unroll
@@ -306,11 +305,28 @@ __device__ __forceinline__ void pointwise_body(const PointwiseParams &p)
         }
     };
     for (int st = 0; st < stages; st += 2) {
-        body(st, ra);
-        if (st + 1 < stages) body(st + 1, rb);
+        body(st, ra, true);
+        if (st + 1 < stages) body(st + 1, rb, false);
+    }
+    if (has_res) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const Raw r = mt == 0 ? rv[i] : ra[i];
+                if constexpr (F && NT == 2) {
+                    acc[mt][0][i] += __uint_as_float(r.x);
+                    acc[mt][NT - 1][i] += __uint_as_float(r.y);
+                } else if constexpr (F) {
+                    acc[mt][0][i] += __uint_as_float(r);
+                } else {
+                    acc[mt][0][i] += __uint_as_float(r << 16);
+                    if constexpr (NT == 2) acc[mt][NT - 1][i] += __uint_as_float(r & 0xffff0000u);
+                }
+            }
     }
 
-    // (taken afresh: kept from the residual's loads, the offsets would fill the registers through the loop)
+    // (taken afresh: kept from the residual's loads, the offsets would fill registers)
     unsigned st_off = out_off;
     asm volatile("" : "+v"(st_off));
     const Rsrc rdst = __builtin_amdgcn_make_buffer_rsrc((void *)((T *)p.dst + (size_t)n * p.dst_img_stride), 0,
@@ -392,7 +408,8 @@ __device__ __forceinline__ void pointwise_body(const PointwiseParams &p)
             const int row = 32 * (i >> 4) + 8 * ((i & 15) >> 2) + 4 * half + (i & 3), m = m0 + row;
             if (m >= M || (nan_rows >> row & 1) != 0) continue;
             float s = p.bias != nullptr ? p.bias[m] : 0.f;
-            if (!GELU && p.res != nullptr) s += br[(size_t)m * P + t];
+            const float r = has_res ? br[(size_t)m * P + t] : 0.f;
+            if (__builtin_isnan(r)) continue;
 #pragma unroll 1
             for (int k = 0; k < K && !__builtin_isnan(s); k += 8) {
                 float w[8], v[8];
@@ -401,7 +418,7 @@ __device__ __forceinline__ void pointwise_body(const PointwiseParams &p)
 #pragma unroll
                 for (int e = 0; e < 8; ++e) s = k + e < K ? fmaf(w[e], v[e], s) : s;
             }
-            bd[(size_t)m * P + t] = GELU ? ffn_gelu(s) : s;
+            bd[(size_t)m * P + t] = GELU ? ffn_gelu(s) : s + r;
         }
     }
 }

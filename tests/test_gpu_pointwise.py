@@ -30,6 +30,18 @@ def test_tile_edges(oracle, dtype, N, C, H, W, Ca):
     check_fused(wl, oracle, w_fuse, b_fuse, lkc, residual_for(wl, 902), what=f"{N}x{C}x{H}x{W} Ca={Ca}")
 
 
+@pytest.mark.parametrize("N,C", [(1, 20), (1, 40), (1, 64), (1, 96), (600, 24), (600, 32), (600, 64), (600, 70)])  # one to three stages of channels, one and two row blocks and pixels per lane
+def test_residual_is_rounded_once(N, C):
+    # fp32 storage: the residual is added to the finished sums, so that one far larger than they are costs them no
+    # more than the one rounding of that addition
+    H, W, Ca = 3, 15, 8
+    wl = wk.make_random(930 + C, N, C, H, W, Ca, 3, dtype=F32, x_mean=0.3)
+    w_fuse, b_fuse, _ = pointwise_weights(931, C, Ca)
+    res = 100 * residual_for(wl, 932)
+    print(f"[case] residual added once N={N} C={C}", flush=True)
+    assert np.array_equal(run_fused(wl, w_fuse, b_fuse, None, res), run_fused(wl, w_fuse, b_fuse) + res)
+
+
 @pytest.mark.parametrize("N", [1, 600])   # one and two pixels per lane
 def test_values_that_have_no_three_bf16_terms(N):
     # fp32 storage: an infinite pixel gives an infinity of each weight's sign, one beyond the largest bf16 its
