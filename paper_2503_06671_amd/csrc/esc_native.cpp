@@ -14,8 +14,8 @@
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
-#include <initializer_list>
 #include <string>
+#include <vector>
 
 #include "esc_convattn.h"
 
@@ -155,6 +155,7 @@ Ws workspace(PyObject *o)
 struct Gen {
     esc_gen_params p;
     int64_t n_w_down, n_b_down, n_w_up, n_b_up;  // elements, -1 where there is no tensor
+    std::vector<int64_t> sizes[4];               // in that order
 };
 constexpr const char *kGenCapsule = "esc_gen";
 
@@ -278,7 +279,9 @@ PyObject *gen_handle(PyObject *const *a, Py_ssize_t n)
     const char *const names[4] = {"w_down", "b_down", "w_up", "b_up"};
     for (int i = 0; i < 4; ++i) t[i] = dev_f32(a[1 + i], names[i]);
     auto count = [](const at::Tensor *p) { return p != nullptr ? p->numel() : (int64_t)-1; };
-    Gen *g = new Gen{{integer(a[0]), ptr(t[0]), ptr(t[1]), ptr(t[2]), ptr(t[3])}, count(t[0]), count(t[1]), count(t[2]), count(t[3])};
+    Gen *g = new Gen{{integer(a[0]), ptr(t[0]), ptr(t[1]), ptr(t[2]), ptr(t[3])}, count(t[0]), count(t[1]), count(t[2]), count(t[3]), {}};
+    for (int i = 0; i < 4; ++i)
+        if (t[i] != nullptr) g->sizes[i] = t[i]->sizes().vec();
     PyObject *cap = PyCapsule_New(g, kGenCapsule, [](PyObject *c) { delete static_cast<Gen *>(PyCapsule_GetPointer(c, kGenCapsule)); });
     if (cap == nullptr) {
         delete g;
@@ -494,23 +497,17 @@ PyObject *convattn_backward(PyObject *const *a, Py_ssize_t n)
     float *gdk = need("grad_dk", {s.N, Ca, 3, 3}, false);
     esc_gen_grads gg{};
     if (g != nullptr) {
-        // (shaped like the weights, which binding.GenParams keeps)
-        PyObject *ts = PyObject_GetAttrString(a[5], "tensors");
-        if (ts == nullptr) throw PyError{};
-        struct Ref {
-            PyObject *o;
-            ~Ref() { Py_DECREF(o); }
-        } ref{ts};
-        auto sizes = [&](int i) { return THPVariable_Unpack(PyTuple_GET_ITEM(ts, i)).sizes(); };
         auto brought = [&](const char *name) -> float * {  // (the gradient of a bias that is not there)
             PyObject *v = item(grads.d, name);
             return v != nullptr ? static_cast<float *>(dev_f32_required(v, name).data_ptr()) : nullptr;
         };
-        gg.w_up = need("grad_w_up", sizes(2), zero);
-        gg.b_up = g->n_b_up >= 0 ? need("grad_b_up", sizes(3), zero) : brought("grad_b_up");
+        // (shaped like the weights; an estimator without w_up is the library's to refuse, but has no shape to allocate)
+        if (g->n_w_up < 0 && item(grads.d, "grad_w_up") == nullptr) fail(PyExc_TypeError, "the estimator needs w_up");
+        gg.w_up = need("grad_w_up", g->sizes[2], zero);
+        gg.b_up = g->n_b_up >= 0 ? need("grad_b_up", g->sizes[3], zero) : brought("grad_b_up");
         if (g->p.hidden > 0) {
-            gg.w_down = need("grad_w_down", sizes(0), zero);
-            gg.b_down = g->n_b_down >= 0 ? need("grad_b_down", sizes(1), zero) : brought("grad_b_down");
+            gg.w_down = need("grad_w_down", g->sizes[0], zero);
+            gg.b_down = g->n_b_down >= 0 ? need("grad_b_down", g->sizes[1], zero) : brought("grad_b_down");
         }
     }
     // every other buffer the caller put into the dict is held to the same rule

@@ -33,6 +33,23 @@ def test_refuses(error, change):
         call(**change())
 
 
+def backward(**change):
+    a = dict(x=torch.randn(1, 6, 9, 8, device="cuda"), grad_out=torch.randn(1, 6, 9, 8, device="cuda"), Ca=CA,
+             lk=torch.randn(CA, KS, KS, device="cuda"), workspace=binding.new_backward_workspace(1, CA, 9, 8, KS, 0))
+    a.update(change)
+    return binding.convattn_backward(**a)
+
+
+def test_refuses_an_estimator_without_w_up():
+    gen = binding.GenParams(None)
+    with pytest.raises(binding.EscError):
+        call(gen=gen)
+    with pytest.raises(TypeError):
+        backward(gen=gen)
+    with pytest.raises(binding.EscError):   # nothing to allocate: the library sees the missing weight
+        backward(gen=gen, grads={"grad_w_up": torch.zeros(9 * CA, CA, device="cuda")})
+
+
 def test_streams_and_given_outputs():
     x = torch.randn(1, 6, 9, 8, device="cuda")
     lk, ws, out = torch.randn(KS, KS, device="cuda"), binding.new_workspace(1, CA, 9, 8), torch.empty_like(x)
