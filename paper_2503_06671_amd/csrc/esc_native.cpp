@@ -461,10 +461,14 @@ PyObject *convattn_backward(PyObject *const *a, Py_ssize_t n)
     const int acc = PyObject_IsTrue(a[7]);
     if (acc < 0) throw PyError{};
     struct Dict {
-        PyObject *d = PyDict_New();
+        PyObject *d;
         ~Dict() { Py_XDECREF(d); }
-    } grads;
-    if (grads.d == nullptr || (given(a[8]) && PyDict_Update(grads.d, a[8]) != 0)) throw PyError{};
+    } grads{nullptr};
+    const int brought_any = given(a[8]) ? PyObject_IsTrue(a[8]) : 0;
+    if (brought_any < 0) throw PyError{};
+    // (whatever dict() takes: a mapping, or pairs)
+    grads.d = brought_any != 0 ? PyObject_CallFunctionObjArgs((PyObject *)&PyDict_Type, a[8], nullptr) : PyDict_New();
+    if (grads.d == nullptr) throw PyError{};
     // Buffers the caller did not bring.  A call writes every element of the parameter gradients, so
     // they need no zeros first - unless it adds to them, or has no attention channels to write any.
     const bool zero = acc != 0 || Ca == 0;

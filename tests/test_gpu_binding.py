@@ -50,6 +50,16 @@ def test_refuses_an_estimator_without_w_up():
         backward(gen=gen, grads={"grad_w_up": torch.zeros(9 * CA, CA, device="cuda")})
 
 
+@pytest.mark.parametrize("form", [dict, lambda d: list(d.items()), lambda d: tuple(d.items())])
+def test_gradient_buffers_as_a_mapping_or_as_pairs(form):
+    mine = {"grad_x": torch.empty(1, 6, 9, 8, device="cuda"), "grad_dk": None}
+    given = form(mine)
+    got = backward(grads=given)
+    assert got["grad_x"] is mine["grad_x"] and set(got) == {"grad_x", "grad_lk", "grad_dk"}
+    assert mine["grad_dk"] is None and given == form(mine)   # the caller's own is left as it was
+    assert set(backward(grads=form({}))) == {"grad_x", "grad_lk", "grad_dk"}
+
+
 def test_streams_and_given_outputs():
     x = torch.randn(1, 6, 9, 8, device="cuda")
     lk, ws, out = torch.randn(KS, KS, device="cuda"), binding.new_workspace(1, CA, 9, 8), torch.empty_like(x)
