@@ -55,20 +55,23 @@ const at::Tensor &tensor(PyObject *o, const char *name)
     return THPVariable_Unpack(o);
 }
 
-int integer(PyObject *o)
+// whatever int() takes, as the callers may pass numpy integers or floats
+long whole_number(PyObject *o)
 {
     const long v = PyLong_AsLong(o);
-    if (v == -1 && PyErr_Occurred()) {
-        // whatever int() takes, as the callers may pass numpy integers or floats
-        PyErr_Clear();
-        PyObject *i = PyNumber_Long(o);
-        if (i == nullptr) throw PyError{};
-        const long w = PyLong_AsLong(i);
-        Py_DECREF(i);
-        if (w == -1 && PyErr_Occurred()) throw PyError{};
-        if (w != (long)(int)w) fail(PyExc_OverflowError, "integer argument out of range");
-        return (int)w;
-    }
+    if (v != -1 || !PyErr_Occurred()) return v;
+    PyErr_Clear();
+    PyObject *i = PyNumber_Long(o);
+    if (i == nullptr) throw PyError{};
+    const long w = PyLong_AsLong(i);
+    Py_DECREF(i);
+    if (w == -1 && PyErr_Occurred()) throw PyError{};
+    return w;
+}
+
+int integer(PyObject *o)
+{
+    const long v = whole_number(o);
     if (v != (long)(int)v) fail(PyExc_OverflowError, "integer argument out of range");
     return (int)v;
 }
@@ -200,8 +203,7 @@ Lk lk_checked(PyObject *o, int Ca, PyObject *ks = nullptr, PyObject *stride = nu
     if (given(ks) || given(stride)) {
         if (!given(ks) || !given(stride)) fail(PyExc_ValueError, "give ks and lk_channel_stride together");
         const int k = integer(ks);
-        const long st = PyLong_AsLong(stride);
-        if (st == -1 && PyErr_Occurred()) throw PyError{};
+        const long st = whole_number(stride);
         const int64_t need = (st != 0 && Ca > 0) ? (int64_t)(Ca - 1) * st + (int64_t)k * k : (int64_t)k * k;
         if (t.numel() < need)
             fail(PyExc_ValueError, "lk holds " + std::to_string(t.numel()) + " values, Ks = " + std::to_string(k) +

@@ -1,4 +1,5 @@
 """The binding's native half: what it refuses, with which exception, and the gradient buffers it allocates."""
+import numpy as np
 import pytest
 import torch
 
@@ -48,6 +49,15 @@ def test_refuses_an_estimator_without_w_up():
         backward(gen=gen)
     with pytest.raises(binding.EscError):   # nothing to allocate: the library sees the missing weight
         backward(gen=gen, grads={"grad_w_up": torch.zeros(9 * CA, CA, device="cuda")})
+
+
+@pytest.mark.parametrize("number", [int, float, np.int64, np.float32, str])
+def test_whole_numbers_of_any_type(number):
+    # the integer arguments are what int() makes of them
+    lk = torch.randn(CA * 11, device="cuda")
+    x = torch.randn(1, 6, 9, 8, device="cuda")
+    want = call(x=x, lk=torch.stack([lk[11 * c:11 * c + 9].view(KS, KS) for c in range(CA)]))
+    assert torch.equal(call(x=x, Ca=number(CA), lk=lk, ks=number(KS), lk_channel_stride=number(11)), want)
 
 
 @pytest.mark.parametrize("form", [dict, lambda d: list(d.items()), lambda d: tuple(d.items())])
