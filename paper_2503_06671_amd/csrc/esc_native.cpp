@@ -204,10 +204,11 @@ Lk lk_checked(PyObject *o, int Ca, PyObject *ks = nullptr, PyObject *stride = nu
         if (!given(ks) || !given(stride)) fail(PyExc_ValueError, "give ks and lk_channel_stride together");
         const int k = integer(ks);
         const long st = whole_number(stride);
-        const int64_t need = (st != 0 && Ca > 0) ? (int64_t)(Ca - 1) * st + (int64_t)k * k : (int64_t)k * k;
+        // (128 bits: the product of any two such numbers, which must not wrap round to a small one)
+        const __int128 need = ((st != 0 && Ca > 0) ? (__int128)(Ca - 1) * st : 0) + (__int128)k * k;
         if (t.numel() < need)
             fail(PyExc_ValueError, "lk holds " + std::to_string(t.numel()) + " values, Ks = " + std::to_string(k) +
-                                       " with channel stride " + std::to_string(st) + " reads " + std::to_string(need));
+                                       " with channel stride " + std::to_string(st) + " reads more");
         return Lk{p, k, st};
     }
     if (t.dim() == 2 && t.size(0) == t.size(1)) return Lk{p, (int)t.size(0), 0};

@@ -23,6 +23,7 @@ def call(**change):
     (TypeError, lambda: dict(lk=torch.randn(CA, KS, KS))),
     (ValueError, lambda: dict(lk=torch.randn(CA + 1, KS, KS, device="cuda"))),
     (ValueError, lambda: dict(lk=torch.randn(8, device="cuda"), ks=3, lk_channel_stride=9)),
+    (ValueError, lambda: dict(lk=torch.randn(36, device="cuda"), ks=3, lk_channel_stride=2 ** 64 // 3)),  # three times that is -1 in 64 bits
     (ValueError, lambda: dict(ks=3)),
     (ValueError, lambda: dict(dk_in=torch.randn(1, CA, 3, device="cuda"))),
     (ValueError, lambda: dict(gen=binding.GenParams(torch.randn(9 * CA, CA + 1, device="cuda")))),
