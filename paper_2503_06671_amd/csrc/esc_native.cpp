@@ -489,8 +489,9 @@ PyObject *convattn_backward(PyObject *const *a, Py_ssize_t n)
     void *gxp;
     if (PyObject *v = item(grads.d, "grad_x")) {
         const at::Tensor &t = tensor(v, "grad_x");
-        if (!t.is_cuda() || t.scalar_type() != x.scalar_type() || t.numel() != x.numel() || !t.is_contiguous())
-            fail(PyExc_TypeError, "grad_x must match x in dtype and size and be a contiguous device tensor");
+        // (a buffer to write into, as a pool of bytes may hold it: its own type and shape are the caller's business)
+        if (!t.is_cuda() || t.nbytes() < x.nbytes() || !t.is_contiguous())
+            fail(PyExc_TypeError, "grad_x must be a contiguous device tensor with room for x's gradient");
         gxp = t.data_ptr();
     } else {
         const at::Tensor t = at::empty(x.sizes(), x.options());

@@ -71,6 +71,17 @@ def test_gradient_buffers_as_a_mapping_or_as_pairs(form):
     assert set(backward(grads=form({}))) == {"grad_x", "grad_lk", "grad_dk"}
 
 
+def test_gradient_of_x_into_any_buffer_with_room():
+    x, go, lk = torch.randn(1, 6, 9, 8, device="cuda"), torch.randn(1, 6, 9, 8, device="cuda"), torch.randn(CA, KS, KS, device="cuda")
+    want = backward(x=x, grad_out=go, lk=lk)["grad_x"]
+    for buf in (torch.empty(500, device="cuda"), torch.empty(2000, dtype=torch.uint8, device="cuda")):
+        assert backward(x=x, grad_out=go, lk=lk, grads={"grad_x": buf})["grad_x"] is buf
+        assert torch.equal(buf.view(torch.float32)[:432].view(1, 6, 9, 8), want)
+    for small in (torch.empty(431, device="cuda"), torch.empty(1, 6, 9, 8, dtype=torch.bfloat16, device="cuda")):
+        with pytest.raises(TypeError):
+            backward(x=x, grad_out=go, lk=lk, grads={"grad_x": small})
+
+
 def test_streams_and_given_outputs():
     x = torch.randn(1, 6, 9, 8, device="cuda")
     lk, ws, out = torch.randn(KS, KS, device="cuda"), binding.new_workspace(1, CA, 9, 8), torch.empty_like(x)
