@@ -155,7 +155,12 @@ class GenParams:
                         _dev_f32(w_up, "w_up"), _dev_f32(b_up, "b_up"))
         self.hidden = int(hidden)
         self.c = _GenParams(self.hidden, *[_ptr(t) for t in self.tensors])
-        self.handle = _native.gen_handle(self.hidden, *self.tensors)
+
+    def __getattr__(self, name):
+        # the native half's view of the weights, made at the first call that needs it (one, whichever thread is first)
+        if name == "handle":
+            return self.__dict__.setdefault(name, _native.gen_handle(self.hidden, *self.tensors))
+        raise AttributeError(name)
 
     def check(self, Ca: int) -> None:
         """The library reads these buffers by the sizes C_a and hidden imply: refuse others."""
