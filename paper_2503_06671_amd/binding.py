@@ -17,6 +17,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "csrc", "libesc_convattn.so")
+NATIVE_PATH = os.path.join(_HERE, "_native.so")
 
 ESC_F32 = 0
 ESC_BF16 = 1
@@ -52,11 +53,10 @@ class _NativeModule:
     def __getattr__(self, name):
         global _native
         load_library()
-        try:
-            _native = importlib.import_module("paper_2503_06671_amd._native")
-        except ImportError as e:
-            raise FileNotFoundError("paper_2503_06671_amd/_native.so is not built; run `python -m paper_2503_06671_amd.build` "
-                                    "(or __graft_entry__.build()) first") from e
+        if not os.path.exists(NATIVE_PATH):
+            raise FileNotFoundError(f"{NATIVE_PATH} is not built; run `python -m paper_2503_06671_amd.build` "
+                                    "(or __graft_entry__.build()) first")
+        _native = importlib.import_module("paper_2503_06671_amd._native")  # (one that is there and does not load says why)
         return getattr(_native, name)
 
 
