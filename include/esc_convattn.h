@@ -146,13 +146,18 @@ esc_status esc_convattn_forward(const void *x, esc_dtype dt, int N, int C, int H
  *                                            the tensor the module's result is added to)
  *
  * The concat is never written: Conv_fuse reads F_res from the workspace and the identity
- * channels from x, on the matrix cores: with fp32 storage fp32 products and fp32
- * accumulation; with bf16 storage bf16 matrix instructions on the stored values, each fp32
- * weight applied as the sum of two bf16 terms (w = hi + lo to 16 mantissa bits; products
- * exact, accumulation fp32).  F_res (and F_pw) pass through the workspace in the storage
- * type, so with bf16 storage they are rounded to bf16 on the way, as a network's tensors
- * would be; out is rounded once more at its store.  out must not overlap x, residual or
- * the workspace.  The workspace is larger than esc_convattn_forward's
+ * channels from x, on the bf16 matrix instructions with fp32 accumulation.  fp32 storage:
+ * every value and weight as three bf16 terms (v = t0 + t1 + t2, exact down to magnitudes of
+ * 2^-110; below, what the third term cannot hold is lost, at most 2^-134 of a value), the six
+ * products of terms whose orders add up to at most two (what is left out lies below 2^-24 of
+ * a product: fp32 accuracy); sums that an infinite value, or one beyond the largest bf16
+ * (3.39e38), turns into NaN this way are made again in fp32, so that NaN and Inf appear
+ * exactly where fp32 arithmetic gives them.  bf16 storage: the stored values, each fp32 weight
+ * as the sum of two bf16 terms (w = hi + lo to 16 mantissa bits; products exact).  The
+ * residual is added to the finished sums.  F_res (and F_pw) pass through the workspace in the
+ * storage type, so with bf16 storage they are rounded to bf16 on the way, as a network's
+ * tensors would be; out is rounded once more at its store.  out must not overlap x, residual
+ * or the workspace.  The workspace is larger than esc_convattn_forward's
  * (esc_fused_workspace_bytes; with_lk_c != 0 when lk_c will be given), prepared with the
  * same esc_workspace_init, and serves esc_convattn_forward / esc_dynkernel_gen calls of
  * the same shape as well.  Limits as above, and C <= 240.  Two to four launches on `stream`.
@@ -172,7 +177,8 @@ esc_status esc_convattn_fused_forward(const void *x, esc_dtype dt, int N, int C,
  * depth-wise convolution branch between them:
  *
  *   U   = gelu(w1 . x + b1)            w1 [C_h, C] row-major, b1 [C_h] or NULL; the erf form of
- *                                      GELU (not its tanh approximation), erf evaluated to 1.5e-7
+ *                                      GELU (not its tanh approximation), evaluated to 3.4e-7
+ *                                      and 8.1e-8 of its argument
  *   V   = U + gelu(k_dw (*) U + b_dw)  k_dw [C_h, 3, 3] depth-wise, cross-correlation, zero
  *                                      padding 1; b_dw [C_h] or NULL
  *   out = w2 . V + b2                  w2 [C, C_h] row-major, b2 [C] or NULL
@@ -180,20 +186,19 @@ esc_status esc_convattn_fused_forward(const void *x, esc_dtype dt, int N, int C,
  *   x, out    [N,C,H,W] in the storage type (device); out must not overlap x or the workspace
  *   C_h       width of the hidden layer (the paper does not print its ratio to C)
  * All weights are device pointers to fp32, read-only.  The point-wise layers run on the
- * matrix cores as in esc_convattn_fused_forward (fp32 storage: fp32 products; bf16 storage:
- * bf16 instructions on the stored values, each fp32 weight as two bf16 terms), the branch
- * in fp32 on the vector units.  With C <= 64, C_h <= 128, an image (or batch) large enough
- * to fill the chip with 30-column strips and a width that fills at least four fifths of its
- * strips, the call takes ONE launch in which U and V
- * never leave the chip (the workspace is not touched; with bf16 storage U stays fp32 and V
- * is rounded to bf16 once, as the second layer's operand); everything else takes three
+ * matrix cores as in esc_convattn_fused_forward (bf16 instructions, fp32 accumulation: fp32
+ * storage with three terms a value and weight, bf16 storage with two terms a weight), the
+ * branch in fp32 on the vector units.  With C <= 64 and C_h <= 128 the call takes ONE launch,
+ * where that is the faster way: large images (or batches) whose width fills at least four
+ * fifths of the 30-column strips it is cut into, and small ones that fill at least half of
+ * their strips and whose C * C_h is at least three quarters of 64 * 128.  There U and V never
+ * leave the chip (the workspace is not touched; with bf16 storage U stays fp32 and V is
+ * rounded to bf16 once, as the second layer's operand).  Everything else takes three
  * launches, U and V passing through the workspace in the storage type, so that with bf16
  * storage both are rounded to bf16 on the way.  out is rounded once at its store.
  * The workspace (esc_convffn_workspace_bytes, 256-byte aligned) is plain scratch: it needs
  * no esc_workspace_init and its contents are undefined after the call.  Limits: C <= 240,
- * C_h <= 960, C_h*H*W*element size < 2 GiB.  A hidden layer of more than 224 channels is
- * multiplied by w2 224 channels at a time, each launch adding to out (with bf16 storage the
- * partial sums are rounded to bf16 between the launches).  The whole residual step is this call followed by
+ * C_h <= 960, C_h*H*W*element size < 2 GiB.  The whole residual step is this call followed by
  * esc_convattn_fused_forward on its output with residual = x.
  */
 size_t esc_convffn_workspace_bytes(int N, int C_h, int H, int W, esc_dtype dt);
@@ -213,7 +218,7 @@ esc_status esc_convffn_forward(const void *x, esc_dtype dt, int N, int C, int H,
  * not overlap f_in or the workspace.  The workspace (esc_residual_step_workspace_bytes;
  * with_lk_c != 0 when lk_c will be given) is prepared once with esc_workspace_init; it begins
  * with the fused call's workspace, so esc_workspace_errors applies to it.  All arguments are
- * checked before anything is enqueued.  Launches: those of the two calls (three to eight).
+ * checked before anything is enqueued.  Launches: those of the two calls (three to seven).
  */
 size_t esc_residual_step_workspace_bytes(int N, int C, int H, int W, int C_a, int C_h, esc_dtype dt, int with_lk_c);
 esc_status esc_residual_step_forward(const void *f_in, esc_dtype dt, int N, int C, int H, int W, int C_h,

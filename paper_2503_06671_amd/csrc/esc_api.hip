@@ -816,9 +816,8 @@ esc_status esc_convffn_forward(const void *x, esc_dtype dt, int N, int C, int H,
     const bool bf16 = dt == ESC_BF16;
     char *u = (char *)workspace, *v = u + need / 2;
     {
-        // up to 64 channels and a hidden layer of up to 128, on an image (or batch) large enough to
-        // fill the chip: the whole network in one launch, U and V staying on the chip (the workspace
-        // is not touched)
+        // up to 64 channels and a hidden layer of up to 128, where the sizes suit it (launch_ffn_stream): the
+        // whole network in one launch, U and V staying on the chip (the workspace is not touched)
         FfnStreamParams fs{};
         fs.x = x;
         fs.out = out;

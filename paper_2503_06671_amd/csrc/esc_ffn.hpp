@@ -22,8 +22,9 @@ hipError_t launch_ffn_branch(const FfnBranchParams &p, bool bf16, hipStream_t s)
 
 // The whole network in one launch for C <= 64 and Ch <= 128 (neither U nor V
 // leaves the chip): out = w2 . V + b2, V = U + gelu(k (*) U + bk), U = gelu(w1 . x + b1).
-// Returns hipErrorNotSupported, with nothing launched, for other shapes and for problems of
-// too few strips and bands to fill the chip.
+// Returns hipErrorNotSupported, with nothing launched, for other shapes and for those that three
+// launches take in less time: small ones that fill few of the strips' columns or of the tiles'
+// channels, and large ones whose last strip is mostly empty.
 struct FfnStreamParams {
     const void *x;         // storage type: fp32, or bf16 bit patterns (bf16 != 0)
     void *out;
