@@ -368,14 +368,16 @@ def test_dense_bf16_kernels_fit_two_blocks_per_cu_without_scratch(lib):
 def test_convffn_kernels_use_no_scratch(lib):
     # ffn_stream_kernel runs two blocks per compute unit (256 registers a lane; its 76 KB of LDS
     # are dynamic) with nothing in the private segment; so do the depth-wise branch kernel's four
-    # instantiations and the point-wise kernel's eight (storage type x 16-byte fetches x GELU)
+    # instantiations and the point-wise kernel's sixteen (storage type x pixels a lane x row blocks x GELU)
     found = {}
     for name, scratch, vgprs, lds in kernel_notes():
-        for key in ("ffn_stream_kernel", "ffn_stream_bf16_kernel", "ffn_branch_kernel", "pointwise_kernel", "pointwise_bf16_kernel"):
+        for key in ("ffn_stream_kernel", "ffn_stream_bf16_kernel", "ffn_branch_kernel", "pointwise_kernel", "pointwise_bf16_kernel",
+                    "pointwise_single_kernel"):
             if key + "E" in name or key + "I" in name:
                 found.setdefault(key, []).append((name, scratch, vgprs))
     assert {k: len(v) for k, v in found.items()} == {"ffn_stream_kernel": 1, "ffn_stream_bf16_kernel": 1, "ffn_branch_kernel": 4,
-                                                     "pointwise_kernel": 4, "pointwise_bf16_kernel": 4}, found
+                                                     "pointwise_kernel": 4, "pointwise_bf16_kernel": 4,
+                                                     "pointwise_single_kernel": 8}, found
     for key, items in found.items():
         for name, scratch, vgprs in items:
             assert scratch == 0 and vgprs <= 256, (name, scratch, vgprs)

@@ -93,6 +93,22 @@ def test_streams_and_given_outputs():
     assert torch.equal(out, want)
 
 
+def test_the_current_stream_is_the_one_used():
+    # no stream given: the call belongs behind what the current stream still has to do, here to fill x
+    x, lk, ws = torch.zeros(1, 6, 9, 8, device="cuda"), torch.randn(KS, KS, device="cuda"), binding.new_workspace(1, CA, 9, 8)
+    later, big = torch.randn(1, 6, 9, 8, device="cuda"), torch.randn(4096, 4096, device="cuda")
+    want = binding.convattn_forward(later, CA, lk, ws)
+    torch.cuda.synchronize()
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        for _ in range(10):   # some milliseconds
+            big = big @ big * 1e-4
+        x.copy_(later)
+        got = binding.convattn_forward(x, CA, lk, ws)
+    s.synchronize()
+    assert torch.equal(got, want)
+
+
 @pytest.mark.parametrize("hidden", [0, 5])
 def test_backward_writes_every_gradient_it_allocates(hidden):
     # the buffers are not cleared first: two calls with different junk in the allocator's memory agree
