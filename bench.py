@@ -177,24 +177,32 @@ def roofline_of(wl, sec):
 FP32_MFMA_PEAK_TFLOPS = 157.3         # dense fp32 matrix-core peak
 
 
+def terms_per_product(wl) -> float:
+    """bf16 matrix instructions the point-wise layers issue per block of products: fp32 storage has every
+    value and weight in three bf16 terms and multiplies six of the nine pairs, bf16 storage has every weight in two."""
+    return 2.0 if wl.elem_bytes == 2 else 6.0
+
+
 def fused_roofline_of(wl, sec, lkc, residual):
     """The fused call: x read once (plus the residual), out written once; the depth-wise taps on
-    the vector units, Conv_fuse (and LK^c) on the matrix cores in fp32 - with bf16 storage both
-    on the bf16 matrix cores (taps: Ks <= 17), whose peak is then the one that counts."""
+    the vector units (bf16 storage with Ks <= 17: the bf16 matrix cores), Conv_fuse (and LK^c) on the
+    bf16 matrix cores: `achieved` counts the instructions issued (`terms_per_product` times the
+    algorithmic flops, which hold each product once)."""
     P = wl.N * wl.H * wl.W
     b_alg = (3.0 if residual else 2.0) * P * wl.C * wl.elem_bytes
     f_vec = 2.0 * wl.Ks * wl.Ks * P * wl.Ca
     f_mat = 2.0 * wl.C * wl.C * P + (2.0 * wl.Ca * wl.Ca * P if lkc else 0.0)
     taps_peak = BF16_MFMA_PEAK_TFLOPS if taps_on_matrix_cores(wl) else FP32_VECTOR_PEAK_TFLOPS
-    mat_peak = BF16_MFMA_PEAK_TFLOPS if wl.elem_bytes == 2 else FP32_MFMA_PEAK_TFLOPS
-    t = {"hbm": b_alg / (HBM_PEAK_GBS * 1e9), "alu": f_vec / (taps_peak * 1e12), "mfma": f_mat / (mat_peak * 1e12)}
+    issued = terms_per_product(wl)
+    t = {"hbm": b_alg / (HBM_PEAK_GBS * 1e9), "alu": f_vec / (taps_peak * 1e12),
+         "mfma": issued * f_mat / (BF16_MFMA_PEAK_TFLOPS * 1e12)}
     bound = max(t, key=t.get)
-    ach = {"hbm": b_alg / sec / 1e9, "alu": f_vec / sec / 1e12, "mfma": f_mat / sec / 1e12}[bound]
-    peak = {"hbm": HBM_PEAK_GBS, "alu": taps_peak, "mfma": mat_peak}[bound]
+    ach = {"hbm": b_alg / sec / 1e9, "alu": f_vec / sec / 1e12, "mfma": issued * f_mat / sec / 1e12}[bound]
+    peak = {"hbm": HBM_PEAK_GBS, "alu": taps_peak, "mfma": BF16_MFMA_PEAK_TFLOPS}[bound]
     return {"bound": bound, "achieved": ach, "peak": peak, "unit": "GB/s" if bound == "hbm" else "TFLOP/s",
             "frac": ach / peak, "algorithmic_bytes": b_alg, "algorithmic_flops_vector": f_vec,
-            "algorithmic_flops_matrix": f_mat, "hbm_gbps": b_alg / sec / 1e9, "alu_tflops": f_vec / sec / 1e12,
-            "mfma_tflops": f_mat / sec / 1e12}
+            "algorithmic_flops_matrix": f_mat, "terms_per_product": issued, "hbm_gbps": b_alg / sec / 1e9,
+            "alu_tflops": f_vec / sec / 1e12, "mfma_tflops": f_mat / sec / 1e12}
 
 
 def dense_roofline_of(wl, sec):
@@ -249,32 +257,30 @@ def backward_roofline_of(wl, sec):
 
 def ffn_roofline_of(wl, sec, with_module):
     """ConvFFN (hidden width 2 C): x read once, out written once; the two point-wise layers on the
-    matrix cores (fp32 instructions for fp32 storage; bf16 storage: bf16 instructions, two per product
-    block because every weight is two bf16 terms - `achieved` counts those), the 3 x 3 branch and the
-    two GELUs per hidden element on the vector units.  with_module: the whole residual step, the fused module's work and bytes added
+    bf16 matrix cores (`achieved` counts the instructions issued, `terms_per_product` per block of products),
+    the 3 x 3 branch and the two GELUs per hidden element on the vector units.  with_module: the whole residual step, the fused module's work and bytes added
     (the tensor between the two calls is written and read once more: it is an output and an input)."""
     P = wl.N * wl.H * wl.W
     Ch = 2 * wl.C
     b_alg = 2.0 * P * wl.C * wl.elem_bytes
     f_mat = 4.0 * wl.C * Ch * P
     # the branch's nine multiply-adds and two GELUs per hidden element; an erf-form GELU is priced at the
-    # operation count of the evaluation the kernels use (rational erf: a reciprocal, an exponential,
-    # nine multiply-adds, six other operations): 30 flops
-    f_vec = (18.0 + 2.0 * 30.0) * Ch * P
+    # operation count of the evaluation the kernels use (eight multiply-adds, an exponential, two
+    # multiplications, a subtraction): 20 flops
+    f_vec = (18.0 + 2.0 * 20.0) * Ch * P
     if with_module:
         b_alg += 3.0 * P * wl.C * wl.elem_bytes
         f_mat += 2.0 * wl.C * wl.C * P
         f_taps = 2.0 * wl.Ks * wl.Ks * P * wl.Ca
     else:
         f_taps = 0.0
-    issued = 2.0 if wl.elem_bytes == 2 else 1.0
-    mat_peak = BF16_MFMA_PEAK_TFLOPS if wl.elem_bytes == 2 else FP32_MFMA_PEAK_TFLOPS
+    issued = terms_per_product(wl)
     taps_peak = BF16_MFMA_PEAK_TFLOPS if taps_on_matrix_cores(wl) else FP32_VECTOR_PEAK_TFLOPS
-    t = {"hbm": b_alg / (HBM_PEAK_GBS * 1e9), "mfma": issued * f_mat / (mat_peak * 1e12),
+    t = {"hbm": b_alg / (HBM_PEAK_GBS * 1e9), "mfma": issued * f_mat / (BF16_MFMA_PEAK_TFLOPS * 1e12),
          "alu": f_vec / (FP32_VECTOR_PEAK_TFLOPS * 1e12) + f_taps / (taps_peak * 1e12)}
     bound = max(t, key=t.get)
     ach = {"hbm": b_alg / sec / 1e9, "mfma": issued * f_mat / sec / 1e12, "alu": (f_vec + f_taps) / sec / 1e12}[bound]
-    peak = {"hbm": HBM_PEAK_GBS, "mfma": mat_peak, "alu": FP32_VECTOR_PEAK_TFLOPS}[bound]
+    peak = {"hbm": HBM_PEAK_GBS, "mfma": BF16_MFMA_PEAK_TFLOPS, "alu": FP32_VECTOR_PEAK_TFLOPS}[bound]
     return {"bound": bound, "achieved": ach, "peak": peak, "unit": "GB/s" if bound == "hbm" else "TFLOP/s",
             "frac": t[bound] / sec, "algorithmic_bytes": b_alg, "algorithmic_flops_matrix": f_mat,
             "algorithmic_flops_vector": f_vec + f_taps, "terms_per_product": issued, "hidden_channels": Ch,
