@@ -467,10 +467,11 @@ __device__ __forceinline__ void ffn_stream(const FfnStreamParams &p)
     };
     // second layer on the V of step r, output row y0 + r - 2
     auto second = [&](int r) {
-        // (fp32 storage: the small products in sums of their own, so that they are not rounded at the large ones' size)
+        // (fp32 storage: the small products in sums of their own, so that they are not rounded at the large ones' size; the
+        // bias is added to the finished sums for the same reason)
         f32x4s acc[2], low[2];
 #pragma unroll
-        for (int t = 0; t < 2; ++t) acc[t] = f32x4s{b2d[0], b2d[1], b2d[2], b2d[3]}, low[t] = f32x4s{0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < 2; ++t) acc[t] = low[t] = f32x4s{0.f, 0.f, 0.f, 0.f};
         const uint16_t *bv = sV + (r & 1) * (TX * kFsVTerm) + l16 * kFsVPitch + 8 * quad;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
@@ -493,9 +494,10 @@ __device__ __forceinline__ void ffn_stream(const FfnStreamParams &p)
                         }
                     }
         }
-        if constexpr (!BF) {
 #pragma unroll
-            for (int t = 0; t < 2; ++t) acc[t] += low[t];
+        for (int t = 0; t < 2; ++t) {
+            if constexpr (!BF) acc[t] += low[t];
+            acc[t] += f32x4s{b2d[0], b2d[1], b2d[2], b2d[3]};
         }
         if constexpr (!BF) {
             bool bad = false;

@@ -37,6 +37,20 @@ def test_small_images(oracle, dtype, N, C, H, W, Ch):
     check_ffn(oracle, 400 + H * W, N, C, H, W, Ch, dtype)
 
 
+@pytest.mark.parametrize("N,C,H,W,Ch", [
+    (1, 64, 9, 31, 128),   # bands of one row
+    (16, 6, 37, 100, 10),  # more bands and strips
+])
+def test_output_bias_is_rounded_once(N, C, H, W, Ch):
+    # one launch, fp32 storage: b2 is added to the finished sums, so that one far larger than they are costs them no
+    # more than that addition
+    x = np.random.default_rng(480 + N + C).standard_normal((N, C, H, W)).astype(np.float32)
+    p = wk.make_ffn_params(481 + C, C, Ch)
+    b2 = 1000 * p["b2"]
+    print(f"[case] output bias added once {N}x{C}x{H}x{W} Ch={Ch}", flush=True)
+    assert np.array_equal(run_ffn(x, wk.F32, dict(p, b2=b2)), run_ffn(x, wk.F32, dict(p, b2=None)) + b2[:, None, None])
+
+
 @pytest.mark.parametrize("what", ["values", "weight"])
 @pytest.mark.parametrize("N,C,H,W,Ch", [
     (1, 64, 9, 31, 128),   # one launch, bands of one row
