@@ -503,7 +503,7 @@ def main():
                    "dense_bf16_kernel / dense_kernel (implicit GEMM on the matrix cores, DK taps, pass-through share) after the estimator launch and the weight rearrangement"
                    if args.dense else
                    "forward_kernel (F_res into the workspace) + pointwise_kernel (Conv_fuse on the matrix cores)"
-                   + ("; with LK^c also the estimator launch and a second pointwise_kernel" if args.lkc else "")),
+                   + ("; with LK^c also a second pointwise_kernel" if args.lkc else "")),
         "traffic": traffic, "traffic_source": traffic_src,
         # one step is one launch of the single forward kernel, so the per-launch duration is
         # the HIP-event time of a timed region divided by the number of launches in it

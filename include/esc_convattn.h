@@ -160,7 +160,7 @@ esc_status esc_convattn_forward(const void *x, esc_dtype dt, int N, int C, int H
  * or the workspace.  The workspace is larger than esc_convattn_forward's
  * (esc_fused_workspace_bytes; with_lk_c != 0 when lk_c will be given), prepared with the
  * same esc_workspace_init, and serves esc_convattn_forward / esc_dynkernel_gen calls of
- * the same shape as well.  Limits as above, and C <= 240.  Two to four launches on `stream`.
+ * the same shape as well.  Limits as above, and C <= 240.  Two launches on `stream`, with LK^c three.
  */
 size_t esc_fused_workspace_bytes(int N, int C_a, int H, int W, esc_dtype dt, int with_lk_c);
 esc_status esc_convattn_fused_forward(const void *x, esc_dtype dt, int N, int C, int H, int W, int C_a,
@@ -218,7 +218,7 @@ esc_status esc_convffn_forward(const void *x, esc_dtype dt, int N, int C, int H,
  * not overlap f_in or the workspace.  The workspace (esc_residual_step_workspace_bytes;
  * with_lk_c != 0 when lk_c will be given) is prepared once with esc_workspace_init; it begins
  * with the fused call's workspace, so esc_workspace_errors applies to it.  All arguments are
- * checked before anything is enqueued.  Launches: those of the two calls (three to seven).
+ * checked before anything is enqueued.  Launches: those of the two calls (three to six).
  */
 size_t esc_residual_step_workspace_bytes(int N, int C, int H, int W, int C_a, int C_h, esc_dtype dt, int with_lk_c);
 esc_status esc_residual_step_forward(const void *f_in, esc_dtype dt, int N, int C, int H, int W, int C_h,

@@ -148,18 +148,22 @@ Plan plan_items(FwdParams &p, int Ks, int blocks_per_cu, int carry_grains)
     // gen items still fit beside all conv items (fused pooling).  Otherwise the conv items
     // run the estimator themselves (direct mode).  Measured at 180 x 320, the hop is the
     // faster of the two for every Ks.
+    // Pooling another tensor than the one convolved, there are pool items in any case, in front of the
+    // gen items, which then wait for them alone.
+    const bool pool_own = p.pool_x == p.x;
+    const unsigned pool_die = pool_own ? 0u : per_die_of(p.n_pool);
     if (p.pool_mode == kPoolItems && p.dk_mode == kDkDirect && p.n_conv > 0 &&
-        per_die_of(p.n_conv) + per_die_of((u64)p.N) <= Smax) {
+        (!pool_own || per_die_of(p.n_conv) + per_die_of((u64)p.N) <= Smax)) {
         p.dk_mode = kDkBoxes;
         p.n_gen = (unsigned)p.N;
     }
 
     // all conv items (and the gen items they wait for) in the first round => fused pooling
-    const bool one_round = p.n_conv > 0 && per_die_of(p.n_conv) + per_die_of(p.n_gen) <= Smax;
-    if (p.pool_mode == kPoolItems && one_round) {
+    const bool one_round = p.n_conv > 0 && per_die_of(p.n_conv) + per_die_of(p.n_gen) + pool_die <= Smax;
+    if (p.pool_mode == kPoolItems && one_round && pool_own) {
         p.pool_mode = kPoolFused;
         p.n_pool = 0;
-    } else if (p.dk_mode == kDkMeans) {
+    } else if (p.dk_mode == kDkMeans && !one_round) {
         // Longer calls: a conv item that runs the estimator itself pays for it (mailboxes,
         // barriers) in every one of a block's items, while the hop it saves is waited for once
         // per call: one gen item per image publishes DK instead (measured at 540 x 960).
@@ -339,9 +343,9 @@ esc_status setup_common(FwdParams &p, const void *x, esc_dtype dt, int N, int C,
                         const esc_gen_params *gen, void *workspace, const WsLayout &l)
 {
     p = FwdParams{};
-    p.x = x;
+    p.x = p.pool_x = x;
     p.N = N;
-    p.C = C;
+    p.C = p.pool_c = C;
     p.Ca = Ca;
     p.H = H;
     p.W = W;
@@ -352,7 +356,7 @@ esc_status setup_common(FwdParams &p, const void *x, esc_dtype dt, int N, int C,
     p.div_ptiles = make_div((uint32_t)l.ptiles);
     p.div_ptiles_x = make_div((uint32_t)l.ptiles_x);
     // aligned 4-element chunk loads (halo tile, pool tile) need W % 4 == 0 and an aligned base
-    p.conv_ld_vec = (W % 4 == 0) && ((uintptr_t)x % (4 * (size_t)p.elem_bytes) == 0);
+    p.conv_ld_vec = p.pool_ld_vec = (W % 4 == 0) && ((uintptr_t)x % (4 * (size_t)p.elem_bytes) == 0);
     // bf16: 16-byte pieces of 8 elements where the width and the base allow them
     if (p.conv_ld_vec && dt == ESC_BF16 && W % 8 == 0 && (uintptr_t)x % 16 == 0) p.conv_ld_vec = 2;
     p.div_ca = make_div((uint32_t)(Ca > 0 ? Ca : 1));
@@ -427,17 +431,25 @@ esc_status enqueue_dynkernel(const void *x, esc_dtype dt, int N, int C, int H, i
 // The forward on checked arguments: one launch.  `out` holds out_c channels per image, of
 // which the first C_a are written by the conv items; with_copy adds the pass-through copy
 // of channels C_a .. C (then out_c == C).  out_add: a constant per (image, channel) for the
-// conv items to add to their plane's outputs, or NULL.
+// conv items to add to their plane's outputs, or NULL.  pool_x: the tensor the estimator pools, with
+// pool_c channels per image, where that is not x (LK^c lies between the two), or NULL: the call then has pool
+// items of its own for it, beside the conv items, where the estimator as a launch in front cost 7 us at
+// 180 x 320 and 14 at 339 x 511.
 esc_status enqueue_forward(const void *x, esc_dtype dt, int N, int C, int H, int W, int C_a, const float *lk, int Ks,
                            long lk_channel_stride, const esc_gen_params *gen, const float *dk_in, void *out, int out_c,
                            bool with_copy, void *workspace, const WsLayout &l, hipStream_t stream,
-                           const float *out_add = nullptr)
+                           const float *out_add = nullptr, const void *pool_x = nullptr, int pool_c = 0)
 {
     const size_t es = dt == ESC_F32 ? 4 : 2;
     const uintptr_t xa = (uintptr_t)x, oa = (uintptr_t)out;
     FwdParams p;
     esc_status st = setup_common(p, x, dt, N, C, H, W, C_a, gen, workspace, l);
     if (st != ESC_OK) return st;
+    if (pool_x != nullptr) {
+        p.pool_x = pool_x;
+        p.pool_c = pool_c;
+        p.pool_ld_vec = (W % 4 == 0) && ((uintptr_t)pool_x % (4 * es) == 0);
+    }
     p.out = out;
     p.out_c = out_c;
     p.lk = lk;
@@ -460,10 +472,10 @@ esc_status enqueue_forward(const void *x, esc_dtype dt, int N, int C, int H, int
 }
 
 // Workspace of esc_convattn_fused_forward: the forward's own workspace first, then F_res
-// [N,C_a,H,W] in the storage type and, with LK^c, F_att (*) LK^c (same shape) and DK.
+// [N,C_a,H,W] in the storage type and, with LK^c, F_att (*) LK^c (same shape).
 struct FusedLayout {
     WsLayout ws;
-    size_t fres_off, pw_off, dk_off, total;
+    size_t fres_off, pw_off, total;
 };
 
 bool fused_layout(int N, int Ca, int H, int W, esc_dtype dt, bool with_lkc, FusedLayout *f)
@@ -476,12 +488,8 @@ bool fused_layout(int N, int Ca, int H, int W, esc_dtype dt, bool with_lkc, Fuse
     f->fres_off = off;
     off += slice;
     f->pw_off = off;
-    f->dk_off = off;
-    if (with_lkc) {
-        off += slice;
-        f->dk_off = off;
-        off += round_up((size_t)N * Ca * 9 * sizeof(float), kWsAlign);
-    }
+    // (and room for DK, which nothing uses: callers may keep buffers of the size they were told)
+    if (with_lkc) off += slice + round_up((size_t)N * Ca * 9 * sizeof(float), kWsAlign);
     f->total = off;
     return true;
 }
@@ -728,17 +736,9 @@ esc_status esc_convattn_fused_forward(const void *x, esc_dtype dt, int N, int C,
     if (C_a > 0) {
         const void *conv_in = x;
         int conv_c = C;
-        const esc_gen_params *conv_gen = gen;
-        const float *conv_dk = dk_in;
         if (with_lkc) {
-            // Eq. 5: DK from the unfiltered slice first (Eq. 4 line 2), then F_att (*) LK^c,
-            // on which both depth-wise kernels act
-            if (gen != nullptr) {
-                float *dk = (float *)(w + f.dk_off);
-                if ((st = enqueue_dynkernel(x, dt, N, C, H, W, C_a, gen, dk, workspace, f.ws, s)) != ESC_OK) return st;
-                conv_gen = nullptr;
-                conv_dk = dk;
-            }
+            // Eq. 5: F_att (*) LK^c, on which both depth-wise kernels act; DK is estimated from
+            // the unfiltered slice (Eq. 4 line 2)
             PointwiseParams pp{};
             pp.src1 = x;
             pp.src1_img_stride = (size_t)C * plane;
@@ -755,8 +755,8 @@ esc_status esc_convattn_fused_forward(const void *x, esc_dtype dt, int N, int C,
             conv_c = C_a;
         }
         // F_res = F_pw (*) LK^s + F_pw (*) DK into the workspace; no pass-through copy
-        if ((st = enqueue_forward(conv_in, dt, N, conv_c, H, W, C_a, lk, Ks, lk_channel_stride, conv_gen, conv_dk, fres,
-                                  C_a, false, workspace, f.ws, s)) != ESC_OK)
+        if ((st = enqueue_forward(conv_in, dt, N, conv_c, H, W, C_a, lk, Ks, lk_channel_stride, gen, dk_in, fres,
+                                  C_a, false, workspace, f.ws, s, nullptr, with_lkc ? x : nullptr, C)) != ESC_OK)
             return st;
     }
     // Eq. 4 line 4 (and Eq. 3 line 3): Conv_fuse over F_res and the identity channels of x

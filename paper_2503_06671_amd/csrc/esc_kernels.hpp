@@ -147,6 +147,9 @@ constexpr int kPoolBatch = 4;                    // pool tiles per pool item
 struct FwdParams {
     const void *x;
     void *out;
+    const void *pool_x;  // what the pool items read: x, or (LK^c between them) the tensor x was made from,
+    int pool_c;          // with this many channels per image
+    int pool_ld_vec;     // as conv_ld_vec, for pool_x
     const float *lk;
     long lk_cstride;
     const float *dk_in;  // DK given by the caller (no estimator), or NULL
@@ -552,11 +555,11 @@ __device__ __forceinline__ Ctx pool_item(ParamsPtr p, Ctx ctx, unsigned item)
         const unsigned pty = fdiv(t, p->div_ptiles_x.mul, p->div_ptiles_x.shift), ptx = t - pty * (unsigned)p->ptiles_x;
         const unsigned n = fdiv(nc, p->div_ca.mul, p->div_ca.shift);
         const unsigned c = nc - n * (unsigned)p->Ca;
-        const T *plane = (const T *)p->x + ((size_t)n * p->C + c) * (size_t)H * (size_t)W;
+        const T *plane = (const T *)p->pool_x + ((size_t)n * p->pool_c + c) * (size_t)H * (size_t)W;
         const int gx = (int)ptx * kPoolTileW + 4 * tx, gy = (int)pty * kPoolTileH + 2 * ty;
 #pragma unroll
         for (int a = 0; a < 2; ++a) {
-            if (p->conv_ld_vec) {  // W % 4 == 0 and an aligned base: the four pixels are in or out together
+            if (p->pool_ld_vec) {  // W % 4 == 0 and an aligned base: the four pixels are in or out together
                 const int ry = gy + a < H ? gy + a : H - 1, cx = gx < W ? gx : W - 4;
                 load4(plane + (size_t)ry * W + cx, v[b][a]);
                 const bool in = gy + a < H && gx < W;

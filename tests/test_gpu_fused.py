@@ -101,6 +101,21 @@ def test_fused_two_layer_estimator_and_given_dk(oracle):
     gu.assert_att_close(got.astype(np.float64), ref, F32, "given dk")
 
 
+# The call pools x beside convolving F_pw: every arrangement of its items (all resident; batches whose items are dealt
+# from queues; channel means, resident and not; estimators beyond the small ones) gives the bits of DK made beforehand.
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("N,Ca,H,W,hidden", [(1, 16, 64, 64, 8), (1, 16, 33, 67, 0), (24, 16, 64, 64, 8), (20, 20, 63, 65, 24),
+                                             (1, 16, 288, 200, 8), (1, 16, 339, 511, 0), (2, 40, 190, 320, 24)])
+def test_estimator_beside_lkc_equals_dk_made_beforehand(dtype, N, Ca, H, W, hidden):
+    wl = wk.make_random(750 + N + H, N, Ca + 4, H, W, Ca, 13, dtype=dtype, hidden=hidden, bias=True, x_mean=0.5)
+    w_fuse, b_fuse, lkc = pointwise_weights(751, wl.C, wl.Ca)
+    x = gu.to_dev_x(wl.x, wl.dtype)
+    dk = binding.dynkernel_gen(x, Ca, gu.gen_params(wl), binding.new_workspace(N, Ca, H, W)).cpu().numpy()
+    want = run_fused(wl, w_fuse, b_fuse, lkc, use_gen=False, dk_in=dk)
+    got = run_fused(wl, w_fuse, b_fuse, lkc)
+    assert np.array_equal(got.view(np.uint8), want.view(np.uint8))
+
+
 # ------------------------------------------------------------------ exact special cases
 
 @pytest.mark.parametrize("dtype", [F32, BF16])
