@@ -31,6 +31,7 @@
 
 #include "esc_dense.hpp"
 #include "esc_dense_weights.hpp"
+#include "esc_estimator.hpp"
 
 namespace esc {
 namespace {
@@ -41,6 +42,7 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kDnThreads = 256;
 constexpr int kDnTw = 32;  // output tile width; its height TH is 8, or 4 when that is needed to fill the chip
 constexpr unsigned kXcds = 8;
+constexpr unsigned kDkSpinLimit = 1u << 20;  // bounded wait: about a second, far beyond any real one
 
 struct bf16d {
     uint16_t bits;
@@ -413,11 +415,95 @@ inline size_t bf_lds_bytes(int Kse, int th, int nx) { return (size_t)bf_aux_cell
 
 __device__ __forceinline__ void dn_split3(float v, uint16_t (&t)[3]) { dw_split3(v, t); }
 
-// the A-operand table (dense_table_entry), one thread per entry
-__global__ void dense_weights_bf16_kernel(const float *lk, int Ca, int Ks, int Kse, int nw, uint32_t *wa)
+// What the matrix path needs before its first block: the A-operand table (dense_table_entry, one thread per
+// entry) and, where DK comes from the estimator, the pool tiles' sums - four tiles a block, in the forward's pool
+// items' order - and DK's places marked empty.  Nothing here waits for another block: the pooled means and the
+// estimator are the main launch's first blocks' (dense_gen_block), beside the contraction.  The estimator as a launch
+// of its own in front, with its hops from block to block, took 7 us at 180 x 320 fp32 and 13 at 360 x 640 bf16; this
+// one takes 4.8 and 4.9 (the call 34.7 -> 31.6 and 51.8 -> 44.9; 331 x 617 fp32 7 x 7 74 -> 60; 64 x 64 bf16 16.7 -> 14.7).
+template <typename T>
+__global__ __launch_bounds__(kDnThreads) void dense_prep_kernel(const DenseParams p, const float *lk, int Ks, int nw, unsigned n_pool)
 {
-    const int idx = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (idx < dense_table_entries(Kse)) dense_table_entry(lk, Ca, Ks, Kse, nw, wa, idx);
+    const int tid = (int)threadIdx.x;
+    if (blockIdx.x >= n_pool) {
+        const int idx = (int)(blockIdx.x - n_pool) * kDnThreads + tid;
+        if (idx < dense_table_entries(p.Ks)) dense_table_entry(lk, p.Ca, Ks, p.Ks, nw, reinterpret_cast<uint32_t *>(p.wt), idx);
+        return;
+    }
+    __shared__ float s_red[kPoolBatch * (kDnThreads / 64)];
+    const unsigned ndk = (unsigned)(p.N * p.Ca) * 9u;
+    for (unsigned i = blockIdx.x * kDnThreads + tid; i < ndk; i += n_pool * kDnThreads) const_cast<unsigned *>(reinterpret_cast<const unsigned *>(p.dk))[i] = kDkEmpty;
+    const unsigned first = blockIdx.x * kPoolBatch, ntiles = (unsigned)(p.N * p.Ca) * (unsigned)p.ptiles;
+    const int tx = tid & 15, ty = tid >> 4;
+    const T *plane[2 * kPoolBatch];
+    int gy[2 * kPoolBatch], gx[2 * kPoolBatch];
+#pragma unroll
+    for (int b = 0; b < kPoolBatch; ++b) {
+        const unsigned tile = first + b < ntiles ? first + b : ntiles - 1;
+        const unsigned nc = tile / (unsigned)p.ptiles, t = tile - nc * (unsigned)p.ptiles;
+        const unsigned pty = t / (unsigned)p.ptiles_x, ptx = t - pty * (unsigned)p.ptiles_x;
+        const unsigned n = nc / (unsigned)p.Ca, c = nc - n * (unsigned)p.Ca;
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            plane[2 * b + a] = (const T *)p.x + ((size_t)n * p.C + c) * (size_t)p.H * (size_t)p.W;
+            gy[2 * b + a] = (int)pty * kPoolTileH + 2 * ty + a, gx[2 * b + a] = (int)ptx * kPoolTileW + 4 * tx;
+        }
+    }
+    float v[2 * kPoolBatch][4];
+    pool_runs(plane, gy, gx, p.H, p.W, v);
+#pragma unroll
+    for (int b = 0; b < kPoolBatch; ++b) {
+        float s = 0.f;
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) s += v[2 * b + a][q];
+        s = wave_sum(s);
+        if ((tid & 63) == 0) s_red[b * (kDnThreads / 64) + (tid >> 6)] = s;
+    }
+    __syncthreads();
+    if (tid < kPoolBatch && first + tid < ntiles) {
+        float t = s_red[tid * (kDnThreads / 64)];
+#pragma unroll
+        for (int w = 1; w < kDnThreads / 64; ++w) t += s_red[tid * (kDnThreads / 64) + w];
+        p.pool_box[first + tid] = __float_as_uint(t);
+    }
+}
+
+// Eq. 4 line 2 of image n by one block, with the additions and products of the forward's estimator items in their
+// order (the same DK, bit for bit).  Waits for nothing, and sits in front of every block that waits for it.
+__device__ __forceinline__ void dense_gen_block(const DenseParams &p, unsigned n)
+{
+    const int tid = (int)threadIdx.x, Ca = p.Ca, ntile = p.ptiles, hidden = p.hidden, K = hidden > 0 ? hidden : Ca;
+    float *s_g = dn_lds, *s_t = dn_lds + kDenseMaxCa;
+    // few tiles: a row of 16 lanes per channel; many: a wavefront per channel
+    const bool rows = ntile <= 64;
+    const int G = rows ? 16 : 64, r = tid & (G - 1);
+    for (int c = tid / G; c < Ca; c += kDnThreads / G) {
+        const unsigned long long *box = p.pool_box + ((size_t)n * Ca + c) * ntile;
+        float s = 0.f;
+        for (int k0 = r; k0 < ntile; k0 += 8 * G) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = __uint_as_float((unsigned)box[k0 + u * G < ntile ? k0 + u * G : k0]);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s = k0 + u * G < ntile ? s + v[u] : s;
+        }
+        s = rows ? row_sum(s) : wave_sum(s);
+        if (r == G - 1) s_g[c] = s / p.hw;
+    }
+    __syncthreads();
+    if (hidden > 0) {
+        for (int m = tid; m < hidden; m += kDnThreads)
+            s_t[m] = gelu_erf(dot_row(p.w_down + (size_t)m * Ca, s_g, Ca, p.b_down ? p.b_down[m] : 0.f));
+        __syncthreads();
+    }
+    for (int o = tid; o < 9 * Ca; o += kDnThreads) {
+        unsigned bits = __float_as_uint(dot_row(p.w_up + (size_t)o * K, hidden > 0 ? s_t : s_g, K, p.b_up ? p.b_up[o] : 0.f));
+        if (bits == kDkEmpty) bits = 0x7fc00000u;
+        __hip_atomic_store(const_cast<unsigned *>(reinterpret_cast<const unsigned *>(p.dk)) + (size_t)n * 9 * Ca + o, bits,
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
 }
 
 template <typename T, int KS, int TH>
@@ -442,7 +528,9 @@ __global__ __launch_bounds__(kDnThreads, 2) void dense_bf16_kernel(const DensePa
 
     // Blocks go to the chip's eight dies round robin; each die gets a contiguous eighth of the
     // tiles, so that neighbouring tiles (shared halos) meet in one L2.
-    const unsigned nblk = gridDim.x, die = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
+    if (blockIdx.x < (unsigned)p.n_gen) return dense_gen_block(p, blockIdx.x);
+    const unsigned blk = blockIdx.x - (unsigned)p.n_gen;
+    const unsigned nblk = gridDim.x - (unsigned)p.n_gen, die = blk % kXcds, slot = blk / kXcds;
     const unsigned qd = nblk / kXcds, rem = nblk % kXcds;
     const unsigned tile_id = die * qd + (die < rem ? die : rem) + slot;
     const unsigned per_img = (unsigned)(p.tiles_x * p.tiles_y);
@@ -508,10 +596,6 @@ __global__ __launch_bounds__(kDnThreads, 2) void dense_bf16_kernel(const DensePa
             copy_dst = nullptr;
         }
     };
-
-    // DK of this image goes to LDS beside the tile (asked for now, read after the contraction)
-    float dk_v = 0.f;
-    if (p.dk != nullptr && tid < 16 * 9) dk_v = p.dk[(size_t)n * p.Ca * 9 + (tid < p.Ca * 9 ? tid : 0)];
 
     // ---- the zero-extended halo tile, pixel-major ----
     if (kF32 && p.fill_vec) {
@@ -631,8 +715,11 @@ __global__ __launch_bounds__(kDnThreads, 2) void dense_bf16_kernel(const DensePa
             }
         }
     }
-    if (tid < 16 * 9) s_dk[tid] = dk_v;
     __syncthreads();
+
+    // DK of this image: asked for in front of the last walks, looked at behind them
+    const unsigned *dk_at = reinterpret_cast<const unsigned *>(p.dk) + (size_t)n * p.Ca * 9 + (tid < p.Ca * 9 ? tid : 0);
+    unsigned dk_bits = 0;
 
     // ---- the contraction ----
     f32x4 part[NA];
@@ -738,6 +825,7 @@ __global__ __launch_bounds__(kDnThreads, 2) void dense_bf16_kernel(const DensePa
         fetch_a(0, a0);
 #pragma unroll
         for (int jp = 0; jp < NJP; jp += 2) {
+            if (jp + 2 >= NJP && p.dk != nullptr) dk_bits = __hip_atomic_load(dk_at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             walk(jp, a0, a1, cv0, cv1);
             if (jp + 1 < NJP) walk(jp + 1, a1, a0, cv1, cv0);
         }
@@ -750,6 +838,15 @@ __global__ __launch_bounds__(kDnThreads, 2) void dense_bf16_kernel(const DensePa
 #pragma unroll
     for (int m = 0; m < NT; ++m) acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
     if (p.dk != nullptr) {
+        if (p.n_gen > 0) {  // (bounded, as every wait; what never came is NaN, and the workspace's error word says so)
+            for (unsigned spin = 0; dk_bits == kDkEmpty && spin < kDkSpinLimit; ++spin) {
+                __builtin_amdgcn_s_sleep(2);
+                dk_bits = __hip_atomic_load(dk_at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            if (dk_bits == kDkEmpty) __hip_atomic_store(p.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (tid < 16 * 9) s_dk[tid] = __uint_as_float(dk_bits);
+        __syncthreads();
         float d[4][9];
 #pragma unroll
         for (int r = 0; r < 4; ++r)
@@ -878,18 +975,25 @@ hipError_t launch_t(const DenseParams &p, int ct, unsigned grid, size_t lds, hip
 
 }  // namespace
 
-__attribute__((visibility("hidden"))) hipError_t launch_dense_weights(const float *lk, int Ca, int Ks, bool bf16, float *wt, hipStream_t s)
+// rearranges the weights into p.wt; with n_gen also pools (dense_prep_kernel)
+__attribute__((visibility("hidden"))) hipError_t launch_dense_prep(const DenseParams &p_in, const float *lk, bool bf16, hipStream_t s)
 {
-    const int Kse = dense_effective_ks(Ks);
-    if (dense_on_bf16_mfma(Ca, Ks, bf16)) {
-        const int threads = dense_table_entries(Kse);
-        hipLaunchKernelGGL(dense_weights_bf16_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, lk, Ca, Ks, Kse,
-                           bf16 ? 2 : 3, reinterpret_cast<uint32_t *>(wt));
+    DenseParams p = p_in;
+    const int Ks = p.Ks;
+    p.Ks = dense_effective_ks(Ks);
+    if (dense_on_bf16_mfma(p.Ca, Ks, bf16)) {
+        const size_t tiles = p.n_gen > 0 ? (size_t)p.N * p.Ca * p.ptiles : 0;
+        const unsigned table = (unsigned)((dense_table_entries(p.Ks) + kDnThreads - 1) / kDnThreads);
+        const unsigned n_pool = (unsigned)((tiles + kPoolBatch - 1) / kPoolBatch);
+        if (bf16)
+            hipLaunchKernelGGL(dense_prep_kernel<bf16_t>, dim3(n_pool + table), dim3(kDnThreads), 0, s, p, lk, Ks, 2, n_pool);
+        else
+            hipLaunchKernelGGL(dense_prep_kernel<float>, dim3(n_pool + table), dim3(kDnThreads), 0, s, p, lk, Ks, 3, n_pool);
         return hipGetLastError();
     }
-    const size_t total = dense_weight_floats(Ca, Ks);
+    const size_t total = dense_weight_floats(p.Ca, Ks);
     if (total == 0) return hipSuccess;
-    hipLaunchKernelGGL(dense_weights_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, lk, Ca, Ks, Kse, wt, total);
+    hipLaunchKernelGGL(dense_weights_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, lk, p.Ca, Ks, p.Ks, p.wt, total);
     return hipGetLastError();
 }
 
@@ -915,7 +1019,7 @@ __attribute__((visibility("hidden"))) hipError_t launch_dense(const DenseParams 
     p.tiles_y = (p.H + th - 1) / th;
     const size_t per_img = (size_t)p.tiles_x * p.tiles_y;
     const size_t grid = per_img * p.N;
-    if (grid >= ((size_t)1 << 31)) return hipErrorInvalidValue;
+    if (grid + (size_t)p.n_gen >= ((size_t)1 << 31)) return hipErrorInvalidValue;
     if (p.idt_len > 0) {
         // every block of an image moves an equal share, in whole 16 KiB rounds when vector accesses apply
         const size_t grain = p.copy_vec ? (size_t)4 * kDnThreads * 16 : (size_t)p.elem_bytes;
@@ -924,9 +1028,10 @@ __attribute__((visibility("hidden"))) hipError_t launch_dense(const DenseParams 
         p.copy_share = share;
     }
     if (matrix_bf16) {
+        const size_t blocks = grid + (size_t)p.n_gen;
         p.fill_vec = (p.W % 8 == 0) && ((uintptr_t)p.x % 16 == 0);
-        if (!bf16) return launch_bf16<float, 4>(p, (unsigned)grid, s);
-        return th == 8 ? launch_bf16<bf16d, 8>(p, (unsigned)grid, s) : launch_bf16<bf16d, 4>(p, (unsigned)grid, s);
+        if (!bf16) return launch_bf16<float, 4>(p, (unsigned)blocks, s);
+        return th == 8 ? launch_bf16<bf16d, 8>(p, (unsigned)blocks, s) : launch_bf16<bf16d, 4>(p, (unsigned)blocks, s);
     }
     int hr, pitch, plane;
     dense_geom(p.Ks, th, hr, pitch, plane);

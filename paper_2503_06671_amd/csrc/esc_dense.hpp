@@ -12,7 +12,7 @@ constexpr int kDenseMaxKs = 17;   // largest dense kernel (its halo tile and wei
 struct DenseParams {
     const void *x;      // [N,C,H,W] storage type
     void *out;          // [N,C,H,W] storage type
-    const float *wt;    // weights rearranged by launch_dense_weights (workspace)
+    float *wt;          // weights rearranged by launch_dense_prep (workspace)
     const float *dk;    // [N,Ca,3,3] fp32 or nullptr (DK = 0)
     int N, C, Ca, H, W, Ks;
     int tiles_x, tiles_y;
@@ -25,7 +25,18 @@ struct DenseParams {
     unsigned hc_mul, hc_shift, hp_mul, hp_shift;
     // bf16 matrix path: whether the tile is fetched in 16-byte pieces
     int fill_vec;
+    // bf16 matrix path, DK from the estimator: the first n_gen = N blocks finish the GAP from the pool tiles' sums
+    // that launch_dense_prep leaves in pool_box (value in the low word; the high word, where the forward's
+    // mailboxes carry a call's tag, says "empty") and publish DK in dk, which launch_dense_prep fills with kDkEmpty.
+    // n_gen = 0: dk is there already
+    int n_gen, hidden, ptiles_x, ptiles;
+    float hw;
+    const float *w_down, *b_down, *w_up, *b_up;
+    unsigned long long *pool_box;
+    unsigned *err;      // raised when the bounded wait for DK expires
 };
+
+constexpr unsigned kDkEmpty = 0xffffffffu;  // a NaN no arithmetic gives (a DK of these bits is published as another NaN)
 
 // the kernel size the device code walks: a 1 x 1 kernel is embedded in a 3 x 3 one
 inline int dense_effective_ks(int Ks) { return Ks < 3 ? 3 : Ks; }
@@ -43,7 +54,7 @@ inline size_t dense_weight_floats(int Ca, int Ks)
     return ct == 1 ? kse * (kse + 1) * 384 : ct * kse * kse * ct * 256;
 }
 
-hipError_t launch_dense_weights(const float *lk, int Ca, int Ks, bool bf16, float *wt, hipStream_t s);
+hipError_t launch_dense_prep(const DenseParams &p, const float *lk, bool bf16, hipStream_t s);
 hipError_t launch_dense(const DenseParams &p, bool bf16, hipStream_t s);
 
 }  // namespace esc

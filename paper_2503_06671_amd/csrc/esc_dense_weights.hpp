@@ -1,6 +1,5 @@
 // The A-operand table of the dense large kernel's matrix path (esc_dense.hip), entry by entry:
-// shared by the small kernel that builds it and by the estimator launch, which builds it on the
-// side when a dense call has an estimator to run (one launch less).
+// built by the launch in front of the dense kernel, beside the pooling where a call has an estimator to run.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -41,15 +40,23 @@ __device__ __forceinline__ void dense_table_entry(const float *lk, int Ca, int K
 {
     const int q = idx >> 6, l = idx & 63, co = l & 15, kg = l >> 4, off = (Kse - Ks) / 2;
     const int jp = q / Kse, i = q - jp * Kse - off, j = 2 * jp + (kg >> 1) - off;
+    // all eight weights are on their way before the first is looked at (a load behind a condition would be waited for
+    // by itself)
+    float v8[8];
+    bool in8[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const int ci = 8 * (kg & 1) + e;
+        in8[e] = co < Ca && ci < Ca && i >= 0 && i < Ks && j >= 0 && j < Ks;
+        v8[e] = lk[in8[e] ? (((size_t)co * Ca + ci) * Ks + i) * Ks + j : 0];
+    }
     uint32_t term[3][4];
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
         uint16_t t2[2][3];
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-            const int ci = 8 * (kg & 1) + 2 * w + s;
-            const bool in = co < Ca && ci < Ca && i >= 0 && i < Ks && j >= 0 && j < Ks;
-            const float v = in ? lk[(((size_t)co * Ca + ci) * Ks + i) * Ks + j] : 0.f;
+            const float v = in8[2 * w + s] ? v8[2 * w + s] : 0.f;
             if (nw == 3) {
                 dw_split3(v, t2[s]);
             } else {

@@ -73,7 +73,7 @@
 #include <type_traits>
 
 #include "esc_convattn.h"
-#include "esc_dense_weights.hpp"
+#include "esc_estimator.hpp"
 
 namespace esc {
 
@@ -94,9 +94,6 @@ constexpr int kStagePerThread = (kStage + kPollThreads - 1) / kPollThreads;
 constexpr int kGroups = 64;        // block groups with their own call counter and leave counter
 constexpr int kCtlStride = 16;     // 32-bit words between two groups' counters (one 64-byte line each)
 
-struct bf16_t {
-    uint16_t bits;
-};
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned long long u64;
 // Which conv variants move a share of the pass-through copy from inside their tap loops
@@ -141,8 +138,6 @@ enum : int {
 // round by whoever finishes its GAP (a gen item, or each conv item); larger ones go
 // through channel-mean items
 constexpr int kDirectMaxBoxes = 512;
-constexpr int kPoolTileW = 64, kPoolTileH = 32;  // the GAP is cut into 64 x 32 pixel tiles
-constexpr int kPoolBatch = 4;                    // pool tiles per pool item
 
 struct FwdParams {
     const void *x;
@@ -190,12 +185,6 @@ struct FwdParams {
     // mailboxes) come back quickly; measured, a full-rate copy beside them costs more than
     // it saves.
     int copy_gentle;
-    // The variant without conv items only (the estimator launch of a dense call): its copy
-    // entries are not copy items but pieces of 256 entries of the dense kernel's A-operand
-    // table, built from aux_lk beside the pooling (aux_n entries; 0 = none).
-    const float *aux_lk;
-    uint32_t *aux_wa;
-    int aux_n, aux_Ca, aux_Ks, aux_Kse, aux_nw;
     // Carried copy: conv item j of an image (j counts its tiles channel-major) moves bytes
     // [j * carry_g * kGrain, (j + 1) * carry_g * kGrain) of the image's pass-through range
     // (loaded behind its tile, stored behind its tap loop); the copy items cover what lies
@@ -231,9 +220,6 @@ namespace {
 // ---------------------------------------------------------------------------
 // storage helpers
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ float to_f32(float v) { return v; }
-__device__ __forceinline__ float to_f32(bf16_t v) { return __uint_as_float((uint32_t)v.bits << 16); }
-
 // fp32 -> bf16, round to nearest even, NaN kept quiet
 __device__ __forceinline__ uint16_t f32_to_bf16_bits(float f)
 {
@@ -378,43 +364,6 @@ __device__ __forceinline__ void boxes_to_lds(const u64 *boxes, int cnt, float *d
         for (int u = 0; u < PER; ++u)
             if (pend[u]) dst[tid + u * kPollThreads] = __uint_as_float(0x7fc00000u);
     }
-}
-
-// Sum over the 64 lanes of a wavefront, returned in every lane.  Data-parallel-primitive
-// moves inside the vector ALU (a handful of cycles each; the LDS-crossbar shuffles they
-// replace cost over a hundred): an inclusive scan inside each row of 16 lanes, then the
-// row totals are carried over with the two row-broadcast steps; lane 63 ends with the
-// total.  The order of the additions is fixed, which is all the callers rely on.
-__device__ __forceinline__ float wave_sum(float v)
-{
-    constexpr int kRowShr = 0x110, kRowBcast15 = 0x142, kRowBcast31 = 0x143;
-    auto dpp = [](float x, auto ctrl, auto row_mask) {
-        return __builtin_bit_cast(
-            float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value,
-                                               decltype(row_mask)::value, 0xf, false));
-    };
-    v += dpp(v, std::integral_constant<int, kRowShr + 1>{}, std::integral_constant<int, 0xf>{});
-    v += dpp(v, std::integral_constant<int, kRowShr + 2>{}, std::integral_constant<int, 0xf>{});
-    v += dpp(v, std::integral_constant<int, kRowShr + 4>{}, std::integral_constant<int, 0xf>{});
-    v += dpp(v, std::integral_constant<int, kRowShr + 8>{}, std::integral_constant<int, 0xf>{});
-    v += dpp(v, std::integral_constant<int, kRowBcast15>{}, std::integral_constant<int, 0xa>{});
-    v += dpp(v, std::integral_constant<int, kRowBcast31>{}, std::integral_constant<int, 0xc>{});
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
-}
-
-// Running sum along each row of 16 lanes (lane 15 of a row ends with the row's total).
-__device__ __forceinline__ float row_sum(float v)
-{
-    constexpr int kRowShr = 0x110;
-    auto dpp = [](float x, auto ctrl) {
-        return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x),
-                                                                     decltype(ctrl)::value, 0xf, 0xf, false));
-    };
-    v += dpp(v, std::integral_constant<int, kRowShr + 1>{});
-    v += dpp(v, std::integral_constant<int, kRowShr + 2>{});
-    v += dpp(v, std::integral_constant<int, kRowShr + 4>{});
-    v += dpp(v, std::integral_constant<int, kRowShr + 8>{});
-    return v;
 }
 
 // die `die`'s contiguous share of n items: [base, base + cnt)
@@ -602,27 +551,6 @@ __device__ __forceinline__ Ctx pool_item(ParamsPtr p, Ctx ctx, unsigned item)
 // when an image has few pool tiles the conv items skip that hop and derive their
 // own nine values with the same arithmetic.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ float gelu_erf(float v)
-{
-    return 0.5f * v * (1.f + erff(v * 0.70710678118654752440f));
-}
-
-// bias + sum_k w[k] * in[k], accumulated in ascending k.  Weights are fetched eight at
-// a time so their latencies overlap instead of adding up.
-__device__ __forceinline__ float dot_row(const float *w, const float *in, int K, float bias)
-{
-    float s = bias;
-    for (int k0 = 0; k0 < K; k0 += 8) {
-        float wv[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) wv[u] = k0 + u < K ? w[k0 + u] : 0.f;
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (k0 + u < K) s = fmaf(wv[u], in[k0 + u], s);
-    }
-    return s;
-}
-
 // The same for a weight row and an input vector that both sit in LDS.
 typedef const __attribute__((address_space(3))) float *LdsFloats;
 __device__ __forceinline__ float dot_row_lds(const float *w_, const float *in_, int K, float bias)
@@ -1854,14 +1782,7 @@ __global__ __launch_bounds__(kThreads, kBlocksPerCu) void forward_kernel(const F
             if constexpr (KS > 0)
                 ctx = conv_item<KS, RY, T, STAGED>(p, ctx, idx);
         } else {
-            if (KS == 0 && p->aux_n > 0) {
-                if constexpr (KS == 0) {
-                    const int e = (int)idx * kThreads + (int)threadIdx.x;
-                    if (e < p->aux_n) dense_table_entry(p->aux_lk, p->aux_Ca, p->aux_Ks, p->aux_Kse, p->aux_nw, p->aux_wa, e);
-                }
-            } else {
-                ctx = copy_item(p, ctx, idx);
-            }
+            ctx = copy_item(p, ctx, idx);
         }
         if (dynamic) {
             if (threadIdx.x == kThreads - 1) g_next[turn & 1] = k8 + kXcds * (members8 + ctx.claim);

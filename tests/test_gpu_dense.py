@@ -120,6 +120,24 @@ def test_dense_base_pointers_off_the_vector_alignment(oracle, dtype):
         assert all(int(v) == nan_bits for v in edge[:out_shift].tolist() + edge[out_shift + numel:].tolist())
 
 
+# DK of a dense call on the matrix path: pooled by the preparing launch, finished by the main launch's first blocks.
+# The same bits as DK made beforehand, whatever the pool tiles' number and the rows' length, and the workspace
+# serves the other calls afterwards.
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("N,Ca,H,W,hidden", [(1, 16, 32, 64, 0), (1, 3, 33, 65, 8), (5, 16, 20, 3, 8), (9, 16, 31, 1, 0),
+                                             (2, 13, 520, 263, 200), (1, 16, 258, 514, 4), (30, 16, 66, 70, 8)])
+def test_dense_estimator_equals_dk_made_beforehand(dtype, N, Ca, H, W, hidden):
+    wl = wk.make_random(960 + N + H, N, Ca + 2, H, W, Ca, 5, dtype=dtype, hidden=hidden, bias=True, x_mean=0.5)
+    x, gen, lk = gu.to_dev_x(wl.x, wl.dtype), gu.gen_params(wl), gu.dev(dense_kernel(961, Ca, 5))
+    ws = binding.new_dense_workspace(N, Ca, H, W, 5)
+    for _ in range(2):
+        dk = binding.dynkernel_gen(x, Ca, gen, ws)
+        want = binding.convattn_dense_forward(x, Ca, lk, ws, dk_in=dk)
+        got = binding.convattn_dense_forward(x, Ca, lk, ws, gen=gen)
+        assert torch.equal(got, want)
+    assert binding.workspace_errors(ws) == 0
+
+
 @pytest.mark.parametrize("Ks", [1, 3, 5, 7, 9, 11, 15, 17])
 def test_dense_bf16_matrix_path_every_kernel_size_on_eight_row_tiles(oracle, Ks):
     # bf16 storage with 16 channels runs one compiled kernel per kernel size and tile height:
