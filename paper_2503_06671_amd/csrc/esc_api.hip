@@ -17,8 +17,8 @@ namespace esc {
 
 // one pair per kernel size, defined in esc_variants.hip (-DESC_KS=<Ks>)
 #define ESC_DECL_KS(K)                                                                                    \
-    hipError_t launch_ks_##K(int ry, bool bf16, bool staged, unsigned grid, hipStream_t s, const FwdParams &p); \
-    hipError_t occupancy_ks_##K(int ry, bool bf16, bool staged, int *blocks_per_cu);
+    hipError_t launch_ks_##K(int ry, bool bf16, int flavour, unsigned grid, hipStream_t s, const FwdParams &p); \
+    hipError_t occupancy_ks_##K(int ry, bool bf16, int flavour, int *blocks_per_cu);
 #define ESC_FOR_EACH_KS(X) X(0) X(1) X(3) X(5) X(7) X(9) X(11) X(13) X(15) X(17) X(19) X(21) X(23) X(25) X(27) X(29) X(31)
 ESC_FOR_EACH_KS(ESC_DECL_KS)
 #undef ESC_DECL_KS
@@ -189,7 +189,7 @@ Plan plan_items(FwdParams &p, int Ks, int blocks_per_cu, int carry_grains)
     // with what lies beyond.
     p.carry_g = 0;
     p.copy_off = 0;
-    if (carry_grains > 0 && !p.copy_gentle && p.n_conv > 0 && p.idt_len > 0 && p.copy_vec_ok) {
+    if (carry_grains > 0 && !p.copy_gentle && p.n_conv > 0 && p.idt_len > 0) {
         const size_t per_img = p.n_conv / (size_t)p.N;
         const size_t grains = (p.idt_len + kGrain - 1) / kGrain;
         size_t g = (grains + per_img - 1) / per_img;
@@ -272,8 +272,8 @@ Plan plan_items(FwdParams &p, int Ks, int blocks_per_cu, int carry_grains)
 
 // index of a kernel size in the variant tables: 0 for the variant without conv items,
 // (Ks + 1) / 2 for odd Ks
-typedef hipError_t (*LaunchFn)(int, bool, bool, unsigned, hipStream_t, const FwdParams &);
-typedef hipError_t (*OccupancyFn)(int, bool, bool, int *);
+typedef hipError_t (*LaunchFn)(int, bool, int, unsigned, hipStream_t, const FwdParams &);
+typedef hipError_t (*OccupancyFn)(int, bool, int, int *);
 constexpr int kKsSlots = 17;
 #define ESC_LAUNCH_ENTRY(K) launch_ks_##K,
 #define ESC_OCC_ENTRY(K) occupancy_ks_##K,
@@ -285,16 +285,16 @@ const OccupancyFn kOccupancy[kKsSlots] = {ESC_FOR_EACH_KS(ESC_OCC_ENTRY)};
 // Resident blocks per compute unit the grid of a variant may count on: what the runtime's
 // occupancy query grants on the device in hand, asked once per device and variant, capped
 // at what the kernel is compiled for.  0 = the variant cannot run here.
-int resident_blocks_per_cu(int ks_slot, int ry, bool bf16, bool staged)
+int resident_blocks_per_cu(int ks_slot, int ry, bool bf16, int flavour)
 {
     constexpr int kMaxDev = 64;
-    static signed char cache[kMaxDev][kKsSlots][2][2][2];  // 0 = not asked yet, else answer + 1
+    static signed char cache[kMaxDev][kKsSlots][2][2][3];  // 0 = not asked yet, else answer + 1
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDev) return 0;
-    signed char &slot = cache[dev][ks_slot][ry == 4][bf16][staged];
+    signed char &slot = cache[dev][ks_slot][ry == 4][bf16][flavour];
     if (slot == 0) {
         int n = 0;
-        if (kOccupancy[ks_slot](ry, bf16, staged, &n) != hipSuccess) n = 0;
+        if (kOccupancy[ks_slot](ry, bf16, flavour, &n) != hipSuccess) n = 0;
         if (n > kBlocksPerCu) n = kBlocksPerCu;
         if (n < 0) n = 0;
         slot = (signed char)(n + 1);
@@ -324,15 +324,18 @@ esc_status launch_forward(FwdParams &p, int Ks, bool bf16, hipStream_t s)
     }
     const u64 total = (u64)p.n_pool + p.n_gen + p.n_conv + (p.idt_len > 0 ? 1 : 0);
     if (total == 0) return ESC_OK;
+    // whole aligned pieces of 16 bytes everywhere?  (all tensors' planes and images then lie on them too)
+    const uintptr_t bases = (uintptr_t)p.x | (uintptr_t)p.pool_x | (uintptr_t)p.out;
+    if (p.W % (bf16 ? 8 : 4) != 0 || bases % 16 != 0) p.flavour = kAny;
     // the blocks of the grid wait for one another, so all of them must be resident at once:
     // the grid is sized by what the runtime says fits on this device
     const int ks_slot = (Ks + 1) / 2;
-    const int bpc = resident_blocks_per_cu(ks_slot, ry, bf16, p.staged != 0);
+    const int bpc = resident_blocks_per_cu(ks_slot, ry, bf16, p.flavour);
     if (bpc < 1) return ESC_ERR_UNSUPPORTED;
     const Plan plan = plan_items(p, Ks, bpc, Ks > 0 ? conv_carry_grains(Ks, ry, bf16) : 0);
     if ((u64)p.n_pool + p.n_gen + p.n_conv + p.n_copy >= ((u64)1 << 30)) return ESC_ERR_UNSUPPORTED;
     const unsigned grid = plan.per_die * kXcds;
-    return kLaunch[ks_slot](ry, bf16, p.staged != 0, grid, s, p) == hipSuccess ? ESC_OK : ESC_ERR_HIP;
+    return kLaunch[ks_slot](ry, bf16, p.flavour, grid, s, p) == hipSuccess ? ESC_OK : ESC_ERR_HIP;
 }
 
 // fills the parts of FwdParams every entry point shares
@@ -352,10 +355,6 @@ esc_status setup_common(FwdParams &p, const void *x, esc_dtype dt, int N, int C,
     p.elem_bytes = dt == ESC_F32 ? 4 : 2;
     p.div_ptiles = make_div((uint32_t)l.ptiles);
     p.div_ptiles_x = make_div((uint32_t)l.ptiles_x);
-    // aligned 4-element chunk loads (halo tile, pool tile) need W % 4 == 0 and an aligned base
-    p.conv_ld_vec = p.pool_ld_vec = (W % 4 == 0) && ((uintptr_t)x % (4 * (size_t)p.elem_bytes) == 0);
-    // bf16: 16-byte pieces of 8 elements where the width and the base allow them
-    if (p.conv_ld_vec && dt == ESC_BF16 && W % 8 == 0 && (uintptr_t)x % 16 == 0) p.conv_ld_vec = 2;
     p.div_ca = make_div((uint32_t)(Ca > 0 ? Ca : 1));
     p.div_tiles_x = p.div_tiles_y = p.div_chunks = p.div_mix = p.div_mix_a = p.div_mix_b = make_div(1);
     if (gen != nullptr && Ca > 0) {
@@ -376,7 +375,7 @@ esc_status setup_common(FwdParams &p, const void *x, esc_dtype dt, int N, int C,
         // kernel flavour with the staged estimator items.
         const int K = gen->hidden > 0 ? gen->hidden : Ca;
         const bool small_est = K <= 16 && Ca <= 16 && gen->hidden <= kThreads;
-        p.staged = p.dk_mode == kDkFromG || !small_est;
+        p.flavour = p.dk_mode == kDkFromG || !small_est ? kStaged : kPlain;
         if (p.dk_mode == kDkFromG) {
             p.n_gsum = (unsigned)((size_t)N * Ca);
             if (small_est) {  // the conv items run the estimator themselves, from the means
@@ -426,14 +425,12 @@ esc_status enqueue_forward(const void *x, esc_dtype dt, int N, int C, int H, int
                            const float *out_add = nullptr, const void *pool_x = nullptr, int pool_c = 0)
 {
     const size_t es = dt == ESC_F32 ? 4 : 2;
-    const uintptr_t xa = (uintptr_t)x, oa = (uintptr_t)out;
     FwdParams p;
     esc_status st = setup_common(p, x, dt, N, C, H, W, C_a, gen, workspace, l);
     if (st != ESC_OK) return st;
     if (pool_x != nullptr) {
         p.pool_x = pool_x;
         p.pool_c = pool_c;
-        p.pool_ld_vec = (W % 4 == 0) && ((uintptr_t)pool_x % (4 * es) == 0);
     }
     p.out = out;
     p.out_c = out_c;
@@ -442,15 +439,12 @@ esc_status enqueue_forward(const void *x, esc_dtype dt, int N, int C, int H, int
     p.dk_in = (gen == nullptr && C_a > 0) ? dk_in : nullptr;
     if (p.dk_in != nullptr) p.dk_mode = kDkGiven;
     p.out_add = C_a > 0 ? out_add : nullptr;
-    if (p.out_add != nullptr) p.staged = 1;  // the kernel flavour whose conv items know of it
-    // 16-byte (fp32) / 8-byte (bf16) row stores need W % 4 == 0 and an aligned base
-    p.conv_vec_ok = (W % 4 == 0) && (oa % (4 * es) == 0);
+    if (p.out_add != nullptr) p.flavour = kStaged;  // the kernel flavour whose conv items know of it
     if (with_copy && C_a < C) {
         const size_t plane = (size_t)H * W * es;
         p.img_bytes = plane * C;
         p.idt_off = plane * C_a;
         p.idt_len = plane * (C - C_a);
-        p.copy_vec_ok = (xa % 16 == 0) && (oa % 16 == 0) && (p.img_bytes % 16 == 0) && (p.idt_off % 16 == 0);
     }
     const int ks_variant = C_a > 0 ? Ks : 0;
     return launch_forward(p, ks_variant, dt == ESC_BF16, stream);

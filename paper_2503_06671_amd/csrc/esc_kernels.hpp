@@ -111,6 +111,8 @@ typedef __amdgpu_buffer_rsrc_t CarryRsrc;
 constexpr int kRawBufferFlags = 0x00020000;  // raw buffer (no stride, no swizzle), 32-bit data format
 constexpr int kBufferNt = 2;                 // non-temporal
 
+enum : int { kPlain = 0, kStaged = 1, kAny = 2 };
+
 struct FastDiv {
     uint32_t d, mul, shift;
 };
@@ -144,7 +146,6 @@ struct FwdParams {
     void *out;
     const void *pool_x;  // what the pool items read: x, or (LK^c between them) the tensor x was made from,
     int pool_c;          // with this many channels per image
-    int pool_ld_vec;     // as conv_ld_vec, for pool_x
     const float *lk;
     long lk_cstride;
     const float *dk_in;  // DK given by the caller (no estimator), or NULL
@@ -167,7 +168,7 @@ struct FwdParams {
     FastDiv div_ptiles, div_ptiles_x, div_ca, div_tiles_x, div_tiles_y, div_chunks, div_mix, div_mix_a, div_mix_b;
     size_t img_bytes, idt_off, idt_len;      // pass-through range of one image, in bytes
     size_t copy_chunk;                       // bytes per copy item (a multiple of kCopyPiece)
-    int conv_vec_ok, conv_ld_vec, copy_vec_ok, elem_bytes;
+    int elem_bytes;
     u64 *pool_box;       // [N*Ca*ptiles] partial sums
     u64 *dk_box;         // [N*Ca*9]
     u64 *g_box;          // [N*Ca] channel means (calls with gsum items)
@@ -178,7 +179,9 @@ struct FwdParams {
     unsigned *done;      // [kGroups] blocks of the group that have announced their leave
     unsigned *queue;     // [kGroups] entries of the group's list handed out beyond the first per block
     int dynamic;         // blocks take their further entries from the group's queue
-    int staged;          // host only: launch the kernel flavour with the staged estimator items (and out_add)
+    // host only: which kernel.  kPlain: aligned tensors (rows and bases in whole pieces of 16 bytes); kStaged: the same
+    // with the staged estimator items and out_add; kAny: those too, and any width and alignment.
+    int flavour;
     // Every conv item is resident from the start (fused pooling) and the call is so short
     // that the conv items' chain of load, taps, estimator and store is what it lasts: the
     // copy items then keep little in flight, so that the conv items' few accesses (tile,
@@ -242,20 +245,28 @@ __device__ __forceinline__ void store1(float *p, float v) { *p = v; }
 __device__ __forceinline__ void store1(bf16_t *p, float v) { p->bits = f32_to_bf16_bits(v); }
 
 // Output stores are non-temporal: nothing in the call reads them back, and lines that do
-// not linger in the L2 shorten the write-back at the end of the kernel (measured).
+// not linger in the L2 shorten the write-back at the end of the kernel (measured).  Four results
+// are one store wherever they lie.
+typedef float f32x4_16 __attribute__((ext_vector_type(4), aligned(16)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned int u32x2_8 __attribute__((ext_vector_type(2), aligned(8)));
+typedef unsigned int u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
+template <bool ANY>
 __device__ __forceinline__ void store4(float *p, const float *v)
 {
-    typedef float f32x4 __attribute__((ext_vector_type(4)));
-    const f32x4 t = {v[0], v[1], v[2], v[3]};
-    __builtin_nontemporal_store(t, reinterpret_cast<f32x4 *>(p));
+    typedef typename std::conditional<ANY, f32x4_any, f32x4_16>::type V;
+    __builtin_nontemporal_store(V{v[0], v[1], v[2], v[3]}, reinterpret_cast<V *>(p));
 }
+template <bool ANY>
+__device__ __forceinline__ void store4_bits(void *p, uint32_t a, uint32_t b)
+{
+    typedef typename std::conditional<ANY, u32x2_any, u32x2_8>::type V;
+    __builtin_nontemporal_store(V{a, b}, reinterpret_cast<V *>(p));
+}
+template <bool ANY>
 __device__ __forceinline__ void store4(bf16_t *p, const float *v)
 {
-    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-    u32x2 w;
-    w.x = f32_pack2_bf16(v[0], v[1]);
-    w.y = f32_pack2_bf16(v[2], v[3]);
-    __builtin_nontemporal_store(w, reinterpret_cast<u32x2 *>(p));
+    store4_bits<ANY>(p, f32_pack2_bf16(v[0], v[1]), f32_pack2_bf16(v[2], v[3]));
 }
 
 // four consecutive elements from an address aligned to all four
@@ -276,8 +287,15 @@ __device__ __forceinline__ void load4(const bf16_t *p, float *v)
     v[3] = __uint_as_float(w.y & 0xffff0000u);
 }
 
-// the same four bf16 elements, left as they are (two per 32-bit word, lower address low)
-__device__ __forceinline__ uint2 load4_raw(const bf16_t *p) { return *reinterpret_cast<const uint2 *>(p); }
+// the same wherever they lie
+template <typename T>
+__device__ __forceinline__ void load4_any(const T *p, float *v)
+{
+    const Run4<T> r = *reinterpret_cast<const Run4<T> *>(p);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = to_f32(r.e[e]);
+}
+
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
@@ -483,10 +501,9 @@ __device__ __forceinline__ void pool_finish(u64 *pool_box, const float (&s)[NB],
 }
 
 // A pool item covers kPoolBatch consecutive pool tiles: all their loads go out together
-// (no condition around a load - the compiler would wait for each guarded load before the
-// next; addresses are clamped into the plane and what lies outside is zeroed afterwards),
+// (pool_runs; addresses are clamped into the plane and what lies outside is zeroed afterwards),
 // then each tile's sum is formed and published as if it were alone.
-template <typename T>
+template <typename T, bool ANY>
 __device__ __forceinline__ Ctx pool_item(ParamsPtr p, Ctx ctx, unsigned item)
 {
     float *s_red = g_red;
@@ -494,32 +511,46 @@ __device__ __forceinline__ Ctx pool_item(ParamsPtr p, Ctx ctx, unsigned item)
     const int tid = opaque_tid();
     const int tx = tid & 15, ty = tid >> 4;
     const unsigned first = item * kPoolBatch, ntiles = p->n_pool_tiles;
-    float v[kPoolBatch][2][4];
+    float v[2 * kPoolBatch][4];
+    if constexpr (ANY) {
+        const T *plane[2 * kPoolBatch];
+        int gy[2 * kPoolBatch], gx[2 * kPoolBatch];
 #pragma unroll
-    for (int b = 0; b < kPoolBatch; ++b) {
-        const bool have = first + b < ntiles;
-        const unsigned tile = have ? first + b : ntiles - 1;
-        const unsigned nc = fdiv(tile, p->div_ptiles.mul, p->div_ptiles.shift);
-        const unsigned t = tile - nc * (unsigned)p->ptiles;
-        const unsigned pty = fdiv(t, p->div_ptiles_x.mul, p->div_ptiles_x.shift), ptx = t - pty * (unsigned)p->ptiles_x;
-        const unsigned n = fdiv(nc, p->div_ca.mul, p->div_ca.shift);
-        const unsigned c = nc - n * (unsigned)p->Ca;
-        const T *plane = (const T *)p->pool_x + ((size_t)n * p->pool_c + c) * (size_t)H * (size_t)W;
-        const int gx = (int)ptx * kPoolTileW + 4 * tx, gy = (int)pty * kPoolTileH + 2 * ty;
+        for (int b = 0; b < kPoolBatch; ++b) {
+            const bool have = first + b < ntiles;
+            const unsigned tile = have ? first + b : ntiles - 1;
+            const unsigned nc = fdiv(tile, p->div_ptiles.mul, p->div_ptiles.shift);
+            const unsigned t = tile - nc * (unsigned)p->ptiles;
+            const unsigned pty = fdiv(t, p->div_ptiles_x.mul, p->div_ptiles_x.shift), ptx = t - pty * (unsigned)p->ptiles_x;
+            const unsigned n = fdiv(nc, p->div_ca.mul, p->div_ca.shift);
+            const unsigned c = nc - n * (unsigned)p->Ca;
 #pragma unroll
-        for (int a = 0; a < 2; ++a) {
-            if (p->pool_ld_vec) {  // W % 4 == 0 and an aligned base: the four pixels are in or out together
+            for (int a = 0; a < 2; ++a) {
+                plane[2 * b + a] = (const T *)p->pool_x + ((size_t)n * p->pool_c + c) * (size_t)H * (size_t)W;
+                gy[2 * b + a] = (int)pty * kPoolTileH + 2 * ty + a, gx[2 * b + a] = (int)ptx * kPoolTileW + 4 * tx;
+            }
+        }
+        pool_runs(plane, gy, gx, H, W, v);
+    } else {
+#pragma unroll
+        for (int b = 0; b < kPoolBatch; ++b) {
+            const bool have = first + b < ntiles;
+            const unsigned tile = have ? first + b : ntiles - 1;
+            const unsigned nc = fdiv(tile, p->div_ptiles.mul, p->div_ptiles.shift);
+            const unsigned t = tile - nc * (unsigned)p->ptiles;
+            const unsigned pty = fdiv(t, p->div_ptiles_x.mul, p->div_ptiles_x.shift), ptx = t - pty * (unsigned)p->ptiles_x;
+            const unsigned n = fdiv(nc, p->div_ca.mul, p->div_ca.shift);
+            const unsigned c = nc - n * (unsigned)p->Ca;
+            const T *plane = (const T *)p->pool_x + ((size_t)n * p->pool_c + c) * (size_t)H * (size_t)W;
+            const int gx = (int)ptx * kPoolTileW + 4 * tx, gy = (int)pty * kPoolTileH + 2 * ty;
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+                // the four pixels are in or out together
                 const int ry = gy + a < H ? gy + a : H - 1, cx = gx < W ? gx : W - 4;
-                load4(plane + (size_t)ry * W + cx, v[b][a]);
+                load4(plane + (size_t)ry * W + cx, v[2 * b + a]);
                 const bool in = gy + a < H && gx < W;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) v[b][a][q] = in ? v[b][a][q] : 0.f;
-            } else {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    v[b][a][q] = 0.f;
-                    if (gy + a < H && gx + q < W) v[b][a][q] = to_f32(plane[(size_t)(gy + a) * W + gx + q]);
-                }
+                for (int q = 0; q < 4; ++q) v[2 * b + a][q] = in ? v[2 * b + a][q] : 0.f;
             }
         }
     }
@@ -534,7 +565,7 @@ __device__ __forceinline__ Ctx pool_item(ParamsPtr p, Ctx ctx, unsigned item)
 #pragma unroll
         for (int a = 0; a < 2; ++a)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) s += v[b][a][q];
+            for (int q = 0; q < 4; ++q) s += v[2 * b + a][q];
         sums[b] = s;
         box[b] = first + b;
         have[b] = first + b < ntiles;
@@ -891,8 +922,8 @@ struct ConvGeom {
 // lanes that read one B operand's rows at one piece column read 256 consecutive bytes (the
 // LDS delivers 16-byte reads at full rate only then; row-major with any pitch runs at half).
 // HRP is odd: pieces of neighbouring columns start on different banks.  Tile column t is
-// image column x0 - PH - A + t (A pads the halo to 8 columns, so that a piece is 16 aligned
-// bytes of memory where the image's width and base allow 16-byte fetches); all 80
+// image column x0 - PH - A + t (A pads the halo to 8 columns, so that a piece is 16
+// bytes of memory, aligned where the image's width and base are); all 80
 // columns of every row are written for every item, because what lies beyond the halo is
 // multiplied by the zeros of the band and must not be stale.  Lane (m, kg) = (l % 16, l / 16)
 // of an A operand holds T_i[m][8 kg ... 8 kg + 7], which depends on 8 kg - m alone: the 40
@@ -945,7 +976,7 @@ __device__ __forceinline__ ConvWhere conv_where(ParamsPtr p, unsigned item)
     return w;
 }
 
-template <int KS, int RY, typename T, bool ADD>
+template <int KS, int RY, typename T, bool ADD, bool ANY>
 __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
 {
     using G = ConvGeom<KS, RY>;
@@ -993,9 +1024,11 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
     // 360 x 640 and 64 x 64 x 64 against: right behind the tile loads, behind the fill
     // barrier, after the band table, after the loop, before the tile in every other block.)
     // Buffer accesses: the resources end with the share, so grains beyond it read as nothing
-    // and their stores are dropped, without a branch.
+    // and their stores are dropped, without a branch (shares are whole grains of 16 bytes; what is left of a range
+    // that is not, less than one, the item whose share ends there moves element by element).
     constexpr bool kCarry = conv_carries(KS, RY, std::is_same<T, bf16_t>::value);
     constexpr int kCarryN = kCarry ? kCarryGrains : 1;
+    unsigned carry_tail = 0;   // bytes of the range behind this item's share, if they are its to move
     CarryRsrc carry_dst = __builtin_amdgcn_make_buffer_rsrc(nullptr, 0, 0, kRawBufferFlags);
     u32x4 carry_v[kCarryN] = {};
     auto carry_load = [&]() {
@@ -1004,7 +1037,8 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
             const size_t j = (size_t)c * per_plane + (size_t)tyi * p->div_tiles_x.d + (size_t)txi;
             const size_t share = (size_t)p->carry_g * kGrain;
             const size_t begin = j * share;
-            const size_t lim = p->copy_off;  // what the conv items carry ends here
+            const size_t lim = p->copy_off & ~(size_t)15;  // what the conv items carry in grains ends here
+            if (ANY) carry_tail = (begin < lim || (lim == 0 && j == 0)) && begin + share >= lim ? (unsigned)(p->copy_off - lim) : 0u;
             const size_t len = begin < lim ? (lim - begin < share ? lim - begin : share) : 0;
             const size_t base = (size_t)n * p->img_bytes + p->idt_off + begin;
             const CarryRsrc src =
@@ -1022,14 +1056,19 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
 #pragma unroll
             for (int r = 0; r < kCarryN; ++r)
                 __builtin_amdgcn_raw_buffer_store_b128(carry_v[r], carry_dst, voff + r * (int)kGrain, 0, kBufferNt);
+            if (ANY && carry_tail != 0) {
+                const size_t at = (size_t)n * p->img_bytes + p->idt_off + p->copy_off - carry_tail + 2 * (size_t)opaque_tid();
+                if (2 * (unsigned)opaque_tid() < carry_tail)
+                    *reinterpret_cast<uint16_t *>((char *)p->out + at) = *reinterpret_cast<const uint16_t *>((const char *)p->x + at);
+            }
         }
     };
 
     // halo tile -> LDS, zero outside the image
-    if (kMatrix && p->conv_ld_vec == 2) {
-        // bf16, W % 8 == 0 and a 16-byte aligned base: whole pieces of 8 columns (each lies
-        // entirely inside or outside the image), all loads in flight before the first LDS write
-        if constexpr (kMatrix) {
+    if constexpr (kMatrix && !ANY) {
+        // whole aligned pieces of 8 columns (each lies entirely inside or outside the image),
+        // all loads in flight before the first LDS write
+        {
             constexpr int NP8 = MG::COLS / 8;
             constexpr int TOT = HR * NP8;
             constexpr int K = (TOT + kThreads - 1) / kThreads;
@@ -1053,32 +1092,25 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
                 if (q < TOT) *reinterpret_cast<u32x4 *>(tile_d + MG::word(r, 4 * j)) = raw[k];
             }
         }
-    } else if (p->conv_ld_vec) {
-        // W % 4 == 0 and an aligned base: fetch whole 4-element chunks aligned in global
+    } else if constexpr (!ANY) {
+        // fetch whole 4-element chunks aligned in global
         // memory (each lies entirely inside or outside the image), all loads in flight
         // before the first LDS write.  A chunk lands at LDS column 4j - A.
-        constexpr int A = kMatrix ? MG::A : (4 - PH % 4) % 4;
-        constexpr int NCH = kMatrix ? MG::NCH : (HC + A + 3) / 4;
+        constexpr int A = (4 - PH % 4) % 4;
+        constexpr int NCH = (HC + A + 3) / 4;
         constexpr int TOT = HR * NCH;
         constexpr int K = (TOT + kThreads - 1) / kThreads;
         const int g0 = x0 - PH - A;
         float v[K][4];
-        uint2 raw[K];
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             const int q = k * kThreads + tid1;
             const int r = q / NCH, j = q - r * NCH;
             const int gy = y0 - PH + r, gx = g0 + 4 * j;
             const bool in = q < TOT && gy >= 0 && gy < H && gx >= 0 && gx < W;
-            if constexpr (kMatrix) {
-                raw[k] = make_uint2(0u, 0u);
-                if constexpr (std::is_same<T, bf16_t>::value)
-                    if (in) raw[k] = load4_raw(xp + (size_t)gy * W + gx);
-            } else {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[k][e] = 0.f;
-                if (in) load4(xp + (size_t)gy * W + gx, v[k]);
-            }
+            for (int e = 0; e < 4; ++e) v[k][e] = 0.f;
+            if (in) load4(xp + (size_t)gy * W + gx, v[k]);
         }
         load_weights();
         if (p->pool_mode != kPoolNone || ctx.last_item) need_tag(p, ctx);
@@ -1086,9 +1118,100 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
         for (int k = 0; k < K; ++k) {
             const int q = k * kThreads + tid1;
             const int r = q / NCH, j = q - r * NCH;
-            if constexpr (kMatrix) {  // the chunk is words 2j, 2j + 1 of row r
-                if (q < TOT) *reinterpret_cast<uint2 *>(tile_d + MG::word(r, 2 * j)) = raw[k];
-            } else if (q < TOT) {
+            if (q < TOT) {
+                float *dst = tile + r * PITCH + 4 * j - A;
+                if (A == 0) {
+                    *reinterpret_cast<float4 *>(dst) = make_float4(v[k][0], v[k][1], v[k][2], v[k][3]);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int cc = 4 * j - A + e;
+                        if (cc >= 0 && cc < HC) dst[e] = v[k][e];
+                    }
+                }
+            }
+        }
+    } else if (kMatrix && W >= 8) {
+        // Any width and base: the same pieces wherever they lie.  Pieces start a multiple of their length
+        // from column 0, so only a row's last one reaches beyond the image: it is the row's last elements,
+        // moved into place.  (Element by element the fill is a chain of twenty trips to memory: 361 x 639 bf16 26.3 us a
+        // call -> 17.1; aligned shapes have kernels of their own, in which this code would
+        // cost 0.3 - 1 us a short call through nothing but register allocation.)
+        if constexpr (kMatrix) {
+            typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+            constexpr int NP8 = MG::COLS / 8;
+            constexpr int TOT = HR * NP8;
+            constexpr int K = (TOT + kThreads - 1) / kThreads;
+            const int g0 = x0 - PH - MG::A;
+            u32x4 raw[K];
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const int q = k * kThreads + tid1;
+                const int r = q / NP8, j = q - r * NP8;
+                const int gy = y0 - PH + r, gx = g0 + 8 * j;
+                const bool in = q < TOT && gy >= 0 && gy < H && gx >= 0 && gx < W;
+                raw[k] = u32x4{0u, 0u, 0u, 0u};
+                if (in) raw[k] = *reinterpret_cast<const u32x4_any *>(xp + (size_t)gy * W + (gx + 8 <= W ? gx : W - 8));
+            }
+            load_weights();
+            if (p->pool_mode != kPoolNone || ctx.last_item) need_tag(p, ctx);
+            if ((W & 7) != 0) {
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    const int q = k * kThreads + tid1;
+                    const int d = g0 + 8 * (q - q / NP8 * NP8) + 8 - W;   // how many elements too early the piece starts
+                    if (d > 0 && d < 8) {
+                        u32x4 t = raw[k];
+                        if (d & 4) t = u32x4{t.z, t.w, 0u, 0u};
+                        if (d & 2) t = u32x4{t.y, t.z, t.w, 0u};
+                        if (d & 1) t = u32x4{t.x >> 16 | t.y << 16, t.y >> 16 | t.z << 16, t.z >> 16 | t.w << 16, t.w >> 16};
+                        raw[k] = t;
+                    }
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const int q = k * kThreads + tid1;
+                const int r = q / NP8, j = q - r * NP8;
+                if (q < TOT) *reinterpret_cast<u32x4 *>(tile_d + MG::word(r, 4 * j)) = raw[k];
+            }
+        }
+    } else if (!kMatrix && W >= 4) {
+        // (a piece lands at LDS column 4j - A)
+        constexpr int A = (4 - PH % 4) % 4;
+        constexpr int NCH = (HC + A + 3) / 4;
+        constexpr int TOT = HR * NCH;
+        constexpr int K = (TOT + kThreads - 1) / kThreads;
+        const int g0 = x0 - PH - A;
+        float v[K][4];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int q = k * kThreads + tid1;
+            const int r = q / NCH, j = q - r * NCH;
+            const int gy = y0 - PH + r, gx = g0 + 4 * j;
+            const bool in = q < TOT && gy >= 0 && gy < H && gx >= 0 && gx < W;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[k][e] = 0.f;
+            if (in) load4_any(xp + (size_t)gy * W + (gx + 4 <= W ? gx : W - 4), v[k]);
+        }
+        load_weights();
+        if (p->pool_mode != kPoolNone || ctx.last_item) need_tag(p, ctx);
+        if ((W & 3) != 0) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const int q = k * kThreads + tid1;
+                const int d = g0 + 4 * (q - q / NCH * NCH) + 4 - W;
+                if (d > 0 && d < 4) {
+                    if (d & 2) v[k][0] = v[k][2], v[k][1] = v[k][3], v[k][2] = v[k][3] = 0.f;
+                    if (d & 1) v[k][0] = v[k][1], v[k][1] = v[k][2], v[k][2] = v[k][3], v[k][3] = 0.f;
+                }
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int q = k * kThreads + tid1;
+            const int r = q / NCH, j = q - r * NCH;
+            if (q < TOT) {
                 float *dst = tile + r * PITCH + 4 * j - A;
                 if (A == 0) {
                     *reinterpret_cast<float4 *>(dst) = make_float4(v[k][0], v[k][1], v[k][2], v[k][3]);
@@ -1102,7 +1225,7 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
             }
         }
     } else if constexpr (kMatrix) {
-        // element by element, all 80 columns of every row (what lies beyond the halo is
+        // rows shorter than a piece: element by element, all 80 columns of every row (what lies beyond the halo is
         // multiplied by the zeros of the band and must not be stale LDS)
         if constexpr (std::is_same<T, bf16_t>::value) {
             for (int idx = tid1; idx < HR * MG::COLS; idx += kThreads) {
@@ -1551,10 +1674,9 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
             const uint2 w = *reinterpret_cast<const uint2 *>(otile + (ty_d * RY + oy) * MG::OP + 2 * tx_d);
             if (gy >= H) continue;
             uint16_t *dst = reinterpret_cast<uint16_t *>(op) + (size_t)gy * W + gx;
-            if (p->conv_vec_ok && gx + 3 < W) {
-                typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-                __builtin_nontemporal_store(u32x2{w.x, w.y}, reinterpret_cast<u32x2 *>(dst));
-            } else {
+            if (ANY ? gx + 3 < W : gx < W) {
+                store4_bits<ANY>(dst, w.x, w.y);
+            } else if constexpr (ANY) {
                 if (gx + 0 < W) dst[0] = (uint16_t)w.x;
                 if (gx + 1 < W) dst[1] = (uint16_t)(w.x >> 16);
                 if (gx + 2 < W) dst[2] = (uint16_t)w.y;
@@ -1569,9 +1691,9 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
         const int gy = wd.y0 + ty_d * RY + oy;
         if (gy >= H) continue;
         T *dst = op + (size_t)gy * W + gx;
-        if (p->conv_vec_ok && gx + 3 < W) {
-            store4(dst, acc[oy]);
-        } else {
+        if (ANY ? gx + 3 < W : gx < W) {
+            store4<ANY>(dst, acc[oy]);
+        } else if constexpr (ANY) {
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 if (gx + q < W) store1(dst + q, acc[oy][q]);
@@ -1582,9 +1704,10 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
 
 // ---------------------------------------------------------------------------
 // copy item (Eq. 4 lines 1 and 4): copy_chunk bytes of one image's identity
-// channels with 16-byte non-temporal accesses when both sides allow it: 16 KiB pieces,
+// channels with 16-byte non-temporal accesses, at any alignment: 16 KiB pieces,
 // two in flight - or, in the gentle mode, one access per thread at a time.
 // ---------------------------------------------------------------------------
+template <bool ANY>
 __device__ __forceinline__ Ctx copy_item(ParamsPtr p, Ctx ctx, unsigned item)
 {
     const unsigned n = fdiv(item, p->div_chunks.mul, p->div_chunks.shift);
@@ -1596,7 +1719,7 @@ __device__ __forceinline__ Ctx copy_item(ParamsPtr p, Ctx ctx, unsigned item)
     const size_t begin = chunk * p->copy_chunk;
     const size_t end = begin + p->copy_chunk < len ? begin + p->copy_chunk : len;
     const int eb = p->elem_bytes;
-    if (p->copy_vec_ok) {
+    if constexpr (!ANY) {
         // Whole pieces move without a condition per access (a guarded load ends up in a basic
         // block of its own and the compiler then waits for each before the next is issued),
         // the next piece's loads going out before this piece's stores.
@@ -1604,8 +1727,17 @@ __device__ __forceinline__ Ctx copy_item(ParamsPtr p, Ctx ctx, unsigned item)
         const size_t rest = begin + nfull * kCopyPiece;  // start of the partial piece, if any
         const size_t lane_off = (size_t)opaque_tid() * 16;
         if (p->copy_gentle) {
-            // one access per thread in flight
+            // One access per thread in flight - and, where an estimator waits for the conv items' pool sums, none
+            // for the first half microsecond (a whole one where a block has little to copy): the tiles come first.
+            // 64 x 64 fp32 8.9 us without the pauses, 8.45 with them; 120 x 160 fp32 9.7 / 9.1, 180 x 320 fp32 11.1 / 10.8, bf16
+            // 9.5 / 9.0; a microsecond everywhere: 180 x 320 fp32 11.0.  (With DK given nothing waits: a pause costs 16 x 64 x 64's
+            // input gradient 1 us.)
             const size_t nvec = (end - begin) / (kThreads * 16);
+            if (p->pool_mode == kPoolFused) {
+                __builtin_amdgcn_s_sleep(20);                   // of 64 clocks
+                if (nvec <= 2) __builtin_amdgcn_s_sleep(24);
+            }
+            __builtin_amdgcn_s_setprio(1);
             for (size_t i = 0; i < nvec; ++i) {
                 const size_t o = begin + i * kThreads * 16 + lane_off;
                 const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(src + o));
@@ -1619,6 +1751,7 @@ __device__ __forceinline__ Ctx copy_item(ParamsPtr p, Ctx ctx, unsigned item)
                 announce_leave(p, ctx);
                 if (o + 16 <= end) __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(dst + o));
             }
+            __builtin_amdgcn_s_setprio(kPrioHigh);
         } else if (nfull > 0) {
             u32x4 v[kCopyVecPerThread], w[kCopyVecPerThread];
             auto fetch = [&](u32x4 *r, size_t i) {
@@ -1677,8 +1810,27 @@ __device__ __forceinline__ Ctx copy_item(ParamsPtr p, Ctx ctx, unsigned item)
             }
         }
     } else {
-        announce_leave(p, ctx);
-        for (size_t o = begin + (size_t)threadIdx.x * eb; o < end; o += (size_t)kThreads * eb) {
+        // ranges off the 16-byte alignment: the same accesses wherever they lie, a piece at a time
+        typedef unsigned int Grain __attribute__((ext_vector_type(4), aligned(2)));
+        if (end - begin >= 16) {
+            for (size_t o0 = begin; o0 < end; o0 += kCopyPiece) {
+                const size_t lane_o = o0 + (size_t)opaque_tid() * 16;
+                Grain v[kCopyVecPerThread];
+#pragma unroll
+                for (int k = 0; k < kCopyVecPerThread; ++k) {
+                    const size_t o = lane_o + (size_t)k * kThreads * 16;
+                    v[k] = __builtin_nontemporal_load(reinterpret_cast<const Grain *>(src + (o + 16 <= end ? o : begin)));
+                }
+                if (o0 + kCopyPiece >= end) announce_leave(p, ctx);
+#pragma unroll
+                for (int k = 0; k < kCopyVecPerThread; ++k) {
+                    const size_t o = lane_o + (size_t)k * kThreads * 16;
+                    if (o + 16 <= end) __builtin_nontemporal_store(v[k], reinterpret_cast<Grain *>(dst + o));
+                }
+            }
+        }
+        const size_t tail = len & ~(size_t)15, o = tail + (size_t)threadIdx.x * eb;
+        if (end == len && o < len) {
             if (eb == 4)
                 *reinterpret_cast<uint32_t *>(dst + o) = *reinterpret_cast<const uint32_t *>(src + o);
             else
@@ -1692,12 +1844,11 @@ __device__ __forceinline__ Ctx copy_item(ParamsPtr p, Ctx ctx, unsigned item)
 // the one kernel.  KS == 0 builds the variant without conv items (used by
 // esc_dynkernel_gen and for C_a == 0).
 // ---------------------------------------------------------------------------
-template <int KS, int RY, typename T, bool STAGED = false>
-__global__ __launch_bounds__(kThreads, kBlocksPerCu) void forward_kernel(const FwdParams params)
+template <int KS, int RY, typename T, bool STAGED, bool ANY>
+__device__ __forceinline__ void forward_body()
 {
     // the item functions (all inlined here) read the parameters from the kernel argument
-    // segment, which starts with `params`, where they need them
-    (void)params;
+    // segment, which starts with the FwdParams, where they need them
     ParamsPtr p = (ParamsPtr)__builtin_amdgcn_kernarg_segment_ptr();
     __builtin_amdgcn_s_setprio(kPrioHigh);
 
@@ -1766,7 +1917,7 @@ __global__ __launch_bounds__(kThreads, kBlocksPerCu) void forward_kernel(const F
         ctx.last_item = !dynamic && li + S >= total;
         if (kind == 0 || kind == 3) claim_next(p, ctx);
         if (kind == 0) {
-            ctx = pool_item<T>(p, ctx, idx);
+            ctx = pool_item<T, ANY>(p, ctx, idx);
         } else if (kind == 1) {
             if constexpr (STAGED) {
                 // the gsum items of every (image, channel), then one gen item per image
@@ -1780,9 +1931,9 @@ __global__ __launch_bounds__(kThreads, kBlocksPerCu) void forward_kernel(const F
             }
         } else if (kind == 2) {
             if constexpr (KS > 0)
-                ctx = conv_item<KS, RY, T, STAGED>(p, ctx, idx);
+                ctx = conv_item<KS, RY, T, STAGED, ANY>(p, ctx, idx);
         } else {
-            ctx = copy_item(p, ctx, idx);
+            ctx = copy_item<ANY>(p, ctx, idx);
         }
         if (dynamic) {
             if (threadIdx.x == kThreads - 1) g_next[turn & 1] = k8 + kXcds * (members8 + ctx.claim);
@@ -1808,6 +1959,19 @@ __global__ __launch_bounds__(kThreads, kBlocksPerCu) void forward_kernel(const F
                                __HIP_MEMORY_SCOPE_AGENT);
         }
     }
+}
+
+template <int KS, int RY, typename T, bool STAGED = false>
+__global__ __launch_bounds__(kThreads, kBlocksPerCu) void forward_kernel(const FwdParams)
+{
+    forward_body<KS, RY, T, STAGED, false>();
+}
+
+// the same at any width and alignment
+template <int KS, int RY, typename T>
+__global__ __launch_bounds__(kThreads, kBlocksPerCu) void forward_any_kernel(const FwdParams)
+{
+    forward_body<KS, RY, T, true, true>();
 }
 
 

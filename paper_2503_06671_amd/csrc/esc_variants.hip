@@ -16,9 +16,11 @@ namespace esc {
 namespace {
 
 template <int KS, int RY, typename T>
-hipError_t launch_flavour(bool staged, unsigned grid, hipStream_t s, const FwdParams &p)
+hipError_t launch_flavour(int flavour, unsigned grid, hipStream_t s, const FwdParams &p)
 {
-    if (staged)
+    if (flavour == kAny)
+        hipLaunchKernelGGL((forward_any_kernel<KS, RY, T>), dim3(grid), dim3(kThreads), 0, s, p);
+    else if (flavour == kStaged)
         hipLaunchKernelGGL((forward_kernel<KS, RY, T, true>), dim3(grid), dim3(kThreads), 0, s, p);
     else
         hipLaunchKernelGGL((forward_kernel<KS, RY, T, false>), dim3(grid), dim3(kThreads), 0, s, p);
@@ -26,9 +28,11 @@ hipError_t launch_flavour(bool staged, unsigned grid, hipStream_t s, const FwdPa
 }
 
 template <int KS, int RY, typename T>
-hipError_t occupancy_flavour(bool staged, int *blocks_per_cu)
+hipError_t occupancy_flavour(int flavour, int *blocks_per_cu)
 {
-    if (staged)
+    if (flavour == kAny)
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, forward_any_kernel<KS, RY, T>, kThreads, 0);
+    if (flavour == kStaged)
         return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, forward_kernel<KS, RY, T, true>, kThreads, 0);
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, forward_kernel<KS, RY, T, false>, kThreads, 0);
 }
@@ -36,31 +40,31 @@ hipError_t occupancy_flavour(bool staged, int *blocks_per_cu)
 }  // namespace
 
 // ry: 2 or 4 (4 exists for Ks <= 17 only; Ks == 0 ignores it)
-__attribute__((visibility("hidden"))) hipError_t ESC_CAT(launch_ks_, ESC_KS)(int ry, bool bf16, bool staged,
+__attribute__((visibility("hidden"))) hipError_t ESC_CAT(launch_ks_, ESC_KS)(int ry, bool bf16, int flavour,
                                                                              unsigned grid, hipStream_t s,
                                                                              const FwdParams &p)
 {
     constexpr int KS = ESC_KS;
     if constexpr (KS > 0 && KS <= 17) {
         if (ry == 4)
-            return bf16 ? launch_flavour<KS, 4, bf16_t>(staged, grid, s, p)
-                        : launch_flavour<KS, 4, float>(staged, grid, s, p);
+            return bf16 ? launch_flavour<KS, 4, bf16_t>(flavour, grid, s, p)
+                        : launch_flavour<KS, 4, float>(flavour, grid, s, p);
     }
-    return bf16 ? launch_flavour<KS, 2, bf16_t>(staged, grid, s, p) : launch_flavour<KS, 2, float>(staged, grid, s, p);
+    return bf16 ? launch_flavour<KS, 2, bf16_t>(flavour, grid, s, p) : launch_flavour<KS, 2, float>(flavour, grid, s, p);
 }
 
 // resident blocks per compute unit the runtime grants this variant on the current device
-__attribute__((visibility("hidden"))) hipError_t ESC_CAT(occupancy_ks_, ESC_KS)(int ry, bool bf16, bool staged,
+__attribute__((visibility("hidden"))) hipError_t ESC_CAT(occupancy_ks_, ESC_KS)(int ry, bool bf16, int flavour,
                                                                                 int *blocks_per_cu)
 {
     constexpr int KS = ESC_KS;
     if constexpr (KS > 0 && KS <= 17) {
         if (ry == 4)
-            return bf16 ? occupancy_flavour<KS, 4, bf16_t>(staged, blocks_per_cu)
-                        : occupancy_flavour<KS, 4, float>(staged, blocks_per_cu);
+            return bf16 ? occupancy_flavour<KS, 4, bf16_t>(flavour, blocks_per_cu)
+                        : occupancy_flavour<KS, 4, float>(flavour, blocks_per_cu);
     }
-    return bf16 ? occupancy_flavour<KS, 2, bf16_t>(staged, blocks_per_cu)
-                : occupancy_flavour<KS, 2, float>(staged, blocks_per_cu);
+    return bf16 ? occupancy_flavour<KS, 2, bf16_t>(flavour, blocks_per_cu)
+                : occupancy_flavour<KS, 2, float>(flavour, blocks_per_cu);
 }
 
 }  // namespace esc

@@ -350,6 +350,14 @@ def test_kernel_variants_fit_four_blocks_per_cu_without_scratch(lib):
             assert scratch <= 64, (ks, ry, t, st, scratch)
 
 
+def test_forward_any_kernels_fit_four_blocks_per_cu(lib):
+    # the forward at any width and alignment: the same grid sizing, next to no private segment
+    meta = [(n, s, v, l) for n, s, v, l in kernel_notes() if "forward_any_kernel" in n]
+    assert len(meta) == 2 * len(VARIANT_SHAPES)
+    for name, scratch, vgprs, lds in meta:
+        assert vgprs <= 128 and 4 * lds <= LDS_PER_CU and scratch <= 64, (name, scratch, vgprs, lds)
+
+
 def test_dense_bf16_kernels_fit_two_blocks_per_cu_without_scratch(lib):
     # dense_bf16_kernel<T, Ks, TH>: bf16 storage one instantiation per odd kernel size 3 ... 17 and
     # tile height, fp32 storage (three tiles in LDS) per odd kernel size 3 ... 13 at four rows; two

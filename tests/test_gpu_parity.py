@@ -74,6 +74,17 @@ def test_no_attention_channels_is_a_pure_copy(oracle):
     assert np.array_equal(out.view(np.uint8), wl.x.view(np.uint8))
 
 
+# Rows fetched, pooled and stored in pieces wherever they end: widths round the pieces' and the tiles' lengths, identity
+# ranges of any number of bytes (carried by conv items, too: the last case fills every block slot with them).
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("N,H,W,Ks", [(2, 5, 1, 3), (1, 7, 3, 7), (3, 7, 4, 13), (1, 5, 5, 1), (2, 33, 7, 13), (2, 33, 8, 13),
+                                      (1, 9, 9, 31), (3, 37, 15, 13), (1, 67, 59, 17), (2, 33, 63, 13), (1, 40, 65, 7),
+                                      (1, 33, 71, 31), (1, 70, 127, 13), (2, 31, 129, 17), (1, 257, 259, 13), (61, 63, 63, 13)])
+def test_widths_round_the_pieces(oracle, dtype, N, H, W, Ks):
+    wl = wk.make_random(350 + W, N, 19, H, W, 16, Ks, dtype=dtype, x_mean=0.3)
+    check_forward(wl, oracle, f"{N}x{H}x{W} ks{Ks}")
+
+
 @pytest.mark.parametrize("dtype", [F32, BF16])
 @pytest.mark.parametrize("Ks", list(range(1, 18, 2)))
 def test_tall_register_block_variant_ragged(oracle, Ks, dtype):
