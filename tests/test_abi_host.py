@@ -391,6 +391,14 @@ def test_convffn_kernels_use_no_scratch(lib):
             assert scratch == 0 and vgprs <= 256, (name, scratch, vgprs)
 
 
+def test_pointwise_runs_kernels_use_no_scratch(lib):
+    # row blocks x (what becomes of the sums, how many stages): bf16 one and two pixels a lane, fp32 one, two for one stage
+    meta = [(n, s, v) for n, s, v, _ in kernel_notes() if "pointwise_runs_kernelI" in n]
+    assert len(meta) == 2 * (7 * 2 + 7 + 1)
+    for name, scratch, vgprs in meta:
+        assert scratch == 0 and vgprs <= 256, (name, scratch, vgprs)
+
+
 def test_three_bf16_terms_hold_an_fp32_value_exactly():
     # The backward's correlation feeds fp32 values to the bf16 matrix instructions as three terms
     # taken by truncation (top 16 bits of the value, of the remainder, of what is left).  The

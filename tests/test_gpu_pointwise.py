@@ -30,6 +30,18 @@ def test_tile_edges(oracle, dtype, N, C, H, W, Ca):
     check_fused(wl, oracle, w_fuse, b_fuse, lkc, residual_for(wl, 902), what=f"{N}x{C}x{H}x{W} Ca={Ca}")
 
 
+# Channels in whole runs of sixteen: one to eight stages, the last one half full or full, both tensors' border inside a stage
+# and between two, with and without the residual that takes an input buffer over.
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("N,C,Ca", [(1, 16, 16), (1, 32, 16), (2, 48, 16), (1, 64, 32), (1, 80, 48), (2, 96, 32), (1, 112, 16),
+                                    (1, 128, 64), (1, 240, 48), (400, 32, 16), (300, 48, 32), (300, 64, 16), (200, 80, 16)])
+def test_stages_of_whole_runs(oracle, dtype, N, C, Ca):
+    wl = wk.make_random(960 + C, N, C, 3, 45, Ca, 3, dtype=dtype, x_mean=0.3)
+    w_fuse, b_fuse, lkc = pointwise_weights(961 + C, C, Ca)
+    check_fused(wl, oracle, w_fuse, b_fuse, lkc, residual_for(wl, 962), what=f"{N}x{C} Ca={Ca} residual")
+    check_fused(wl, oracle, w_fuse, None, lkc, what=f"{N}x{C} Ca={Ca}")
+
+
 @pytest.mark.parametrize("N,C", [(1, 20), (1, 40), (1, 64), (1, 96), (600, 24), (600, 32), (600, 64), (600, 70)])  # one to three stages of channels, one and two row blocks and pixels per lane
 def test_residual_is_rounded_once(N, C):
     # fp32 storage: the residual is added to the finished sums, so that one far larger than they are costs them no
