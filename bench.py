@@ -500,7 +500,7 @@ def main():
                    if fused is None and not args.dense and not args.backward else
                    "corr_mfma_kernel (grad_out x correlation on the matrix cores), sums, estimator kernels, forward_kernel on grad_out with flipped kernels and the GAP term"
                    if args.backward else
-                   "dense_bf16_kernel / dense_kernel (implicit GEMM on the matrix cores, DK taps, pass-through share) after the estimator launch and the weight rearrangement"
+                   "dense_bf16_kernel / dense_kernel (implicit GEMM on the matrix cores, DK taps, pass-through share) after one launch that pools and rearranges the weights"
                    if args.dense else
                    "forward_kernel (F_res into the workspace) + pointwise_kernel (Conv_fuse on the matrix cores)"
                    + ("; with LK^c also a second pointwise_kernel" if args.lkc else "")),

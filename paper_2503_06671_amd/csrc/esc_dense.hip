@@ -1000,7 +1000,7 @@ __attribute__((visibility("hidden"))) hipError_t launch_dense_prep(const DensePa
 __attribute__((visibility("hidden"))) hipError_t launch_dense(const DenseParams &p_in, bool bf16, hipStream_t s)
 {
     DenseParams p = p_in;
-    p.Ks = dense_effective_ks(p.Ks);  // the kernel walks the embedding kernel (launch_dense_weights)
+    p.Ks = dense_effective_ks(p.Ks);  // the kernel walks the embedding kernel (launch_dense_prep)
     if (p.Ca < 1 || p.Ca > kDenseMaxCa || p.Ks < 1 || p.Ks > kDenseMaxKs) return hipErrorInvalidValue;
     const int ct = (p.Ca + 15) / 16;
     // 8-row tiles, or 4-row ones while those are needed to give every compute unit two blocks

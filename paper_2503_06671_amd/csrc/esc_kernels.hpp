@@ -13,7 +13,8 @@
 //
 //   pool items   GAP partial sums of the attention slice, four 64 x 32 pixel tiles each;
 //                left out when every conv item is resident at once - then each conv
-//                item publishes the sums of its own tile from LDS ("fused pooling")
+//                item publishes the sums of its own tile from LDS ("fused pooling").  They
+//                may pool another tensor than the one convolved (LK^c lies between the two)
 //   gen items    one per image with few pool tiles: finish the GAP, run the kernel
 //                estimator, publish DK (esc_dynkernel_gen: also write it out)
 //   gsum items   for images with many pool tiles: one per (image, channel), publish the

@@ -1,7 +1,7 @@
 // One translation unit per large-kernel size: compiled with -DESC_KS=<Ks> (0 builds the
 // variant without conv items that esc_dynkernel_gen and pure copies use).  Instantiates
 // forward_kernel<Ks, RY, T, STAGED> for both register blockings, both storage types and
-// both estimator flavours, and exports one host function that launches the one asked for.
+// both estimator flavours, and forward_any_kernel<Ks, RY, T> for tensors off the 16-byte alignment, and exports one host function that launches the one asked for.
 #include "esc_kernels.hpp"
 
 #ifndef ESC_KS
