@@ -1729,14 +1729,14 @@ __device__ __forceinline__ Ctx copy_item(ParamsPtr p, Ctx ctx, unsigned item)
         const size_t lane_off = (size_t)opaque_tid() * 16;
         if (p->copy_gentle) {
             // One access per thread in flight - and, where an estimator waits for the conv items' pool sums, none
-            // for the first half microsecond (a whole one where a block has little to copy): the tiles come first.
-            // 64 x 64 fp32 8.9 us without the pauses, 8.45 with them; 120 x 160 fp32 9.7 / 9.1, 180 x 320 fp32 11.1 / 10.8, bf16
+            // for the first three quarters of a microsecond (a whole one where a block has little to copy): the tiles come first.
+            // 64 x 64 fp32 8.9 us without the pauses, 8.45 with them; 120 x 160 fp32 9.7 / 9.1, 180 x 320 fp32 11.1 / 10.7, bf16
             // 9.5 / 9.0; a microsecond everywhere: 180 x 320 fp32 11.0.  (With DK given nothing waits: a pause costs 16 x 64 x 64's
             // input gradient 1 us.)
             const size_t nvec = (end - begin) / (kThreads * 16);
             if (p->pool_mode == kPoolFused) {
-                __builtin_amdgcn_s_sleep(20);                   // of 64 clocks
-                if (nvec <= 2) __builtin_amdgcn_s_sleep(24);
+                __builtin_amdgcn_s_sleep(28);                   // of 64 clocks
+                if (nvec <= 2) __builtin_amdgcn_s_sleep(16);
             }
             __builtin_amdgcn_s_setprio(1);
             for (size_t i = 0; i < nvec; ++i) {
