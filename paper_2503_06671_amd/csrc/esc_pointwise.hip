@@ -757,33 +757,36 @@ hipError_t launch_typed(const PointwiseParams &p, int mt, int nt, unsigned grid,
                        : launch_one<pointwise_bf16_kernel<2, GELU>>(p, grid, pw_lds_bytes<T, 2>(), s);
 }
 
-template <typename T, int MODE, int LIE>
-hipError_t launch_runs(const PointwiseParams &p, int mt, int nt, unsigned grid, hipStream_t s)
+template <typename T, int NT, int MODE, int LIE>
+hipError_t launch_runs(const PointwiseParams &p, int mt, unsigned grid, hipStream_t s)
 {
-    if (nt == 1)
-        return mt == 1 ? launch_one<pointwise_runs_kernel<T, 1, 1, MODE, LIE>>(p, grid, pw_lds_bytes<T, 1>(), s)
-                       : launch_one<pointwise_runs_kernel<T, 2, 1, MODE, LIE>>(p, grid, pw_lds_bytes<T, 2>(), s);
-    if constexpr (sizeof(T) == 4 && LIE != kPwOne)
-        return hipErrorInvalidValue;   // (launch_mode sends none here)
-    else
-        return mt == 1 ? launch_one<pointwise_runs_kernel<T, 1, 2, MODE, LIE>>(p, grid, pw_lds_bytes<T, 1>(), s)
-                       : launch_one<pointwise_runs_kernel<T, 2, 2, MODE, LIE>>(p, grid, pw_lds_bytes<T, 2>(), s);
+    return mt == 1 ? launch_one<pointwise_runs_kernel<T, 1, NT, MODE, LIE>>(p, grid, pw_lds_bytes<T, 1>(), s)
+                   : launch_one<pointwise_runs_kernel<T, 2, NT, MODE, LIE>>(p, grid, pw_lds_bytes<T, 2>(), s);
+}
+
+// Every way through here ends in a kernel: a variant that is not compiled is not named.
+template <typename T, int NT, int MODE>
+hipError_t launch_mode(const PointwiseParams &p, int mt, unsigned grid, hipStream_t s)
+{
+    const int K = p.K1 + p.K2;
+    // Fetching ahead pays where latency counts: few pixels (192-channel residual step 64 x 64 fp32 77 us -> 64, 64 channels
+    // of 25 images of 63 x 63 120 -> 111), bf16 storage (Conv_fuse 360 x 640 21 -> 19) and LK^c's single stage.  Large calls of
+    // fp32 are bound by memory: waiting for everything, 40 images of 72 x 72 of 64 channels take 196 us, fetched ahead 207, 180
+    // x 320 of 192 channels 244 and 249 (on another box 239 and 234).
+    if (p.K1 % 16 == 0 && p.K2 % 16 == 0) {
+        if constexpr (MODE == kPwPlain)
+            if (K <= kPwStage) return launch_runs<T, NT, MODE, kPwOne>(p, mt, grid, s);
+        if constexpr (sizeof(T) == 2 || NT == 1)
+            return K > kPwStage && K <= 2 * kPwStage ? launch_runs<T, NT, MODE, kPwTwo>(p, mt, grid, s)
+                                                     : launch_runs<T, NT, MODE, kPwRuns>(p, mt, grid, s);
+    }
+    return launch_typed<T, MODE == kPwGelu>(p, mt, NT, grid, s);
 }
 
 template <typename T, int MODE>
-hipError_t launch_mode(const PointwiseParams &p, int mt, int nt, unsigned grid, hipStream_t s)
+hipError_t launch_pixels(const PointwiseParams &p, int mt, int nt, unsigned grid, hipStream_t s)
 {
-    const int K = p.K1 + p.K2;
-    const bool two = K > kPwStage && K <= 2 * kPwStage;
-    // Fetching ahead pays where latency counts: few pixels (192-channel residual step 64 x 64 fp32 77 us -> 64, 64 channels
-    // of 25 images of 63 x 63 120 -> 111), bf16 storage (Conv_fuse 360 x 640 21 -> 19) and a single stage.  Large calls of
-    // fp32 are bound by memory: waiting for everything, 40 images of 72 x 72 of 64 channels take 196 us, fetched ahead 207, 180
-    // x 320 of 192 channels 244 and 249 (on another box 239 and 234).
-    if (p.K1 % 16 != 0 || p.K2 % 16 != 0 || (sizeof(T) == 4 && nt == 2 && K > kPwStage)) return launch_typed<T, MODE == kPwGelu>(p, mt, nt, grid, s);
-    if (two) return launch_runs<T, MODE, kPwTwo>(p, mt, nt, grid, s);
-    if constexpr (MODE == kPwPlain)
-        if (K <= kPwStage) return launch_runs<T, MODE, kPwOne>(p, mt, nt, grid, s);
-    return launch_runs<T, MODE, kPwRuns>(p, mt, nt, grid, s);
+    return nt == 1 ? launch_mode<T, 1, MODE>(p, mt, grid, s) : launch_mode<T, 2, MODE>(p, mt, grid, s);
 }
 
 }  // namespace
@@ -812,9 +815,9 @@ __attribute__((visibility("hidden"))) hipError_t launch_pointwise(const Pointwis
     const int nt = (p.P >= 2 && blocks(mt, 2) >= 2L * cus) ? 2 : 1;
     const long grid = blocks(mt, nt);
     if (grid >= (1L << 31)) return hipErrorInvalidValue;
-    if (p.gelu) return bf16 ? launch_mode<bf16s, kPwGelu>(p, mt, nt, (unsigned)grid, s) : launch_mode<float, kPwGelu>(p, mt, nt, (unsigned)grid, s);
-    if (p.res != nullptr) return bf16 ? launch_mode<bf16s, kPwRes>(p, mt, nt, (unsigned)grid, s) : launch_mode<float, kPwRes>(p, mt, nt, (unsigned)grid, s);
-    return bf16 ? launch_mode<bf16s, kPwPlain>(p, mt, nt, (unsigned)grid, s) : launch_mode<float, kPwPlain>(p, mt, nt, (unsigned)grid, s);
+    if (p.gelu) return bf16 ? launch_pixels<bf16s, kPwGelu>(p, mt, nt, (unsigned)grid, s) : launch_pixels<float, kPwGelu>(p, mt, nt, (unsigned)grid, s);
+    if (p.res != nullptr) return bf16 ? launch_pixels<bf16s, kPwRes>(p, mt, nt, (unsigned)grid, s) : launch_pixels<float, kPwRes>(p, mt, nt, (unsigned)grid, s);
+    return bf16 ? launch_pixels<bf16s, kPwPlain>(p, mt, nt, (unsigned)grid, s) : launch_pixels<float, kPwPlain>(p, mt, nt, (unsigned)grid, s);
 }
 
 }  // namespace esc

@@ -5,6 +5,7 @@ import pytest
 import torch
 
 from paper_2503_06671_amd import binding, workloads as wk
+from tests.test_gpu_ffn import check_ffn
 from tests.test_gpu_fused import check_fused, pointwise_weights, residual_for, run_fused
 
 pytestmark = pytest.mark.gpu
@@ -40,6 +41,19 @@ def test_stages_of_whole_runs(oracle, dtype, N, C, Ca):
     w_fuse, b_fuse, lkc = pointwise_weights(961 + C, C, Ca)
     check_fused(wl, oracle, w_fuse, b_fuse, lkc, residual_for(wl, 962), what=f"{N}x{C} Ca={Ca} residual")
     check_fused(wl, oracle, w_fuse, None, lkc, what=f"{N}x{C} Ca={Ca}")
+
+
+# The same widths on maps large enough for two pixels per lane (planes of one tile: two images to a compute unit), whatever
+# becomes of the sums: nothing, a residual, a GELU (a hidden layer beyond 128 channels takes the layers' own launches).
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("C,Ca", [(16, 0), (16, 16), (32, 0), (32, 16), (32, 32), (48, 16), (64, 32), (80, 16)])
+def test_whole_runs_two_pixels_per_lane(oracle, dtype, C, Ca):
+    N = 2 * torch.cuda.get_device_properties(0).multi_processor_count
+    wl = wk.make_random(970 + C, N, C, 3, 15, Ca, 3, dtype=dtype, x_mean=0.3)
+    w_fuse, b_fuse, lkc = pointwise_weights(971 + C, C, Ca)
+    for residual in (None, residual_for(wl, 972)):
+        check_fused(wl, oracle, w_fuse, b_fuse, lkc if Ca else None, residual, what=f"{N}x{C} Ca={Ca}")
+    check_ffn(oracle, 973, N, C, 3, 15, 160, dtype)
 
 
 @pytest.mark.parametrize("N,C", [(1, 20), (1, 40), (1, 64), (1, 96), (600, 24), (600, 32), (600, 64), (600, 70)])  # one to three stages of channels, one and two row blocks and pixels per lane
