@@ -246,7 +246,7 @@ esc_status esc_residual_step_forward(const void *f_in, esc_dtype dt, int N, int 
  * C_a <= 64, Ks odd <= 17.
  * The workspace is esc_dense_workspace_bytes large (the forward's workspace, DK and the
  * rearranged weights), prepared with esc_workspace_init.  Two launches on `stream`; with an
- * estimator on the fp32 instructions three.
+ * estimator on the fp32 instructions, or for tens of millions of planes or tiles, three.
  */
 size_t esc_dense_workspace_bytes(int N, int C_a, int H, int W, int Ks);
 esc_status esc_convattn_dense_forward(const void *x, esc_dtype dt, int N, int C, int H, int W, int C_a,

@@ -973,10 +973,9 @@ esc_status esc_convattn_dense_forward(const void *x, esc_dtype dt, int N, int C,
     }
     if (gen != nullptr) {
         p.dk = (float *)(w + d.dk_off);
-        if (dense_on_bf16_mfma(C_a, Ks, dt == ESC_BF16)) {
+        if (dense_on_bf16_mfma(C_a, Ks, dt == ESC_BF16) && dense_prep_pools(N, C_a, H, W, d.ws.ptiles)) {
             // Eq. 4 line 2: the preparing launch pools beside rearranging the weights, a block per image of the
             // main one turns the sums into DK while the others multiply
-            if ((size_t)N * C_a * d.ws.ptiles >= ((size_t)1 << 30)) return ESC_ERR_UNSUPPORTED;
             p.n_gen = N;
             p.hidden = gen->hidden;
             p.w_down = gen->w_down, p.b_down = gen->b_down, p.w_up = gen->w_up, p.b_up = gen->b_up;
@@ -986,7 +985,7 @@ esc_status esc_convattn_dense_forward(const void *x, esc_dtype dt, int N, int C,
             p.ptiles = d.ws.ptiles;
             p.hw = (float)((double)H * (double)W);
         } else if ((st = enqueue_dynkernel(x, dt, N, C, H, W, C_a, gen, (float *)(w + d.dk_off), workspace, d.ws, s)) != ESC_OK) {
-            return st;  // (otherwise one launch of the variant without conv items)
+            return st;  // (otherwise one launch of the variant without conv items, which takes any number of images)
         }
     }
     if (launch_dense_prep(p, lk_dense, dt == ESC_BF16, s) != hipSuccess) return ESC_ERR_HIP;

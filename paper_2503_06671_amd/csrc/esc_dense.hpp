@@ -38,6 +38,17 @@ struct DenseParams {
 
 constexpr unsigned kDkEmpty = 0xffffffffu;  // a NaN no arithmetic gives (a DK of these bits is published as another NaN)
 
+// Does the preparing launch pool (and the main one estimate)?  The one has a block to four pool tiles, the other one more
+// to an image, and a launch holds less than 2^32 threads of these kernels' 256 to a block.  Up to 2^25 tiles the first has
+// at most 2^31, and its index and stride over DK stay in 32 bits together; the second is counted in its smaller tiles.
+// Beyond that (2^21 images of one tile and 16 channels) DK comes from the estimator's own, resident grid, in a launch more;
+// 65536 images of 8 x 8 fp32, 2^20 tiles: 2541 us so, 2902 with the estimator in front.
+inline bool dense_prep_pools(int N, int Ca, int H, int W, int ptiles)
+{
+    const size_t tiles = (size_t)N * Ca * ptiles, blocks = (size_t)N * (1 + (size_t)((W + 31) / 32) * ((H + 3) / 4));
+    return tiles < ((size_t)1 << 25) && blocks < ((size_t)1 << 24);
+}
+
 // the kernel size the device code walks: a 1 x 1 kernel is embedded in a 3 x 3 one
 inline int dense_effective_ks(int Ks) { return Ks < 3 ? 3 : Ks; }
 

@@ -138,6 +138,21 @@ def test_dense_estimator_equals_dk_made_beforehand(dtype, N, Ca, H, W, hidden):
     assert binding.workspace_errors(ws) == 0
 
 
+# Images beyond the number whose tiles the preparing launch pools: one short of the line, on it, and so many that a block
+# to four tiles, or one more to an image, would be more threads than a launch holds.
+@pytest.mark.parametrize("N,Ca,dtype", [((1 << 21) - 1, 16, BF16), (1 << 21, 16, BF16), (1 << 22, 16, F32), ((1 << 23) + 3, 1, F32)])
+def test_dense_estimator_of_very_many_images(N, Ca, dtype):
+    print(f"[case] dense estimator N={N} Ca={Ca} {dtype}", flush=True)
+    x = torch.randn(N, Ca, 1, 1, device="cuda").to(torch.float32 if dtype == F32 else torch.bfloat16)
+    rng = np.random.default_rng(970)
+    gen = binding.GenParams(gu.dev(rng.standard_normal((9 * Ca, Ca))))
+    lk, ws = gu.dev(dense_kernel(971, Ca, 3)), binding.new_dense_workspace(N, Ca, 1, 1, 3)
+    got = binding.convattn_dense_forward(x, Ca, lk, ws, gen=gen)
+    dk = binding.dynkernel_gen(x, Ca, gen, ws)
+    assert torch.equal(got, binding.convattn_dense_forward(x, Ca, lk, ws, dk_in=dk))
+    assert binding.workspace_errors(ws) == 0
+
+
 @pytest.mark.parametrize("Ks", [1, 3, 5, 7, 9, 11, 15, 17])
 def test_dense_bf16_matrix_path_every_kernel_size_on_eight_row_tiles(oracle, Ks):
     # bf16 storage with 16 channels runs one compiled kernel per kernel size and tile height:
