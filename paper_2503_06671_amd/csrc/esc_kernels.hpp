@@ -1705,12 +1705,15 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
 
 // ---------------------------------------------------------------------------
 // copy item (Eq. 4 lines 1 and 4): copy_chunk bytes of one image's identity
-// channels with 16-byte non-temporal accesses, at any alignment: 16 KiB pieces,
-// two in flight - or, in the gentle mode, one access per thread at a time.
+// channels with 16-byte non-temporal accesses, wherever they lie (ANY): 16 KiB pieces,
+// two in flight (64 x 540 x 961 fp32 without attention channels: 52.6 us, one in flight 56.8) - or, in the
+// gentle mode, one access per thread at a time.
 // ---------------------------------------------------------------------------
 template <bool ANY>
 __device__ __forceinline__ Ctx copy_item(ParamsPtr p, Ctx ctx, unsigned item)
 {
+    typedef unsigned int AnyGrain __attribute__((ext_vector_type(4), aligned(2)));
+    typedef typename std::conditional<ANY, AnyGrain, u32x4>::type Grain;
     const unsigned n = fdiv(item, p->div_chunks.mul, p->div_chunks.shift);
     const size_t chunk = (size_t)(item - n * p->div_chunks.d);
     // (what the conv items carry inside their tap loops comes first in the range)
@@ -1719,117 +1722,85 @@ __device__ __forceinline__ Ctx copy_item(ParamsPtr p, Ctx ctx, unsigned item)
     const size_t len = p->idt_len - p->copy_off;
     const size_t begin = chunk * p->copy_chunk;
     const size_t end = begin + p->copy_chunk < len ? begin + p->copy_chunk : len;
-    const int eb = p->elem_bytes;
-    if constexpr (!ANY) {
-        // Whole pieces move without a condition per access (a guarded load ends up in a basic
-        // block of its own and the compiler then waits for each before the next is issued),
-        // the next piece's loads going out before this piece's stores.
-        const size_t nfull = (end - begin) / kCopyPiece;
-        const size_t rest = begin + nfull * kCopyPiece;  // start of the partial piece, if any
-        const size_t lane_off = (size_t)opaque_tid() * 16;
-        if (p->copy_gentle) {
-            // One access per thread in flight - and, where an estimator waits for the conv items' pool sums, none
-            // for the first three quarters of a microsecond (a whole one where a block has little to copy): the tiles come first.
-            // 64 x 64 fp32 8.9 us without the pauses, 8.45 with them; 120 x 160 fp32 9.7 / 9.1, 180 x 320 fp32 11.1 / 10.7, bf16
-            // 9.5 / 9.0; a microsecond everywhere: 180 x 320 fp32 11.0.  (With DK given nothing waits: a pause costs 16 x 64 x 64's
-            // input gradient 1 us.)
-            const size_t nvec = (end - begin) / (kThreads * 16);
-            if (p->pool_mode == kPoolFused) {
-                __builtin_amdgcn_s_sleep(28);                   // of 64 clocks
-                if (nvec <= 2) __builtin_amdgcn_s_sleep(16);
-            }
-            __builtin_amdgcn_s_setprio(1);
-            for (size_t i = 0; i < nvec; ++i) {
-                const size_t o = begin + i * kThreads * 16 + lane_off;
-                const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(src + o));
-                if (i + 1 == nvec && begin + nvec * kThreads * 16 >= end) announce_leave(p, ctx);
-                __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(dst + o));
-            }
-            const size_t o = begin + nvec * kThreads * 16 + lane_off;
-            if (begin + nvec * kThreads * 16 < end) {
-                u32x4 v = {};
-                if (o + 16 <= end) v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(src + o));
-                announce_leave(p, ctx);
-                if (o + 16 <= end) __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(dst + o));
-            }
-            __builtin_amdgcn_s_setprio(kPrioHigh);
-        } else if (nfull > 0) {
-            u32x4 v[kCopyVecPerThread], w[kCopyVecPerThread];
-            auto fetch = [&](u32x4 *r, size_t i) {
-#pragma unroll
-                for (int k = 0; k < kCopyVecPerThread; ++k)
-                    r[k] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(
-                        src + begin + i * kCopyPiece + (size_t)k * kThreads * 16 + lane_off));
-            };
-            auto put = [&](const u32x4 *r, size_t i) {
-#pragma unroll
-                for (int k = 0; k < kCopyVecPerThread; ++k)
-                    __builtin_nontemporal_store(r[k], reinterpret_cast<u32x4 *>(
-                        dst + begin + i * kCopyPiece + (size_t)k * kThreads * 16 + lane_off));
-            };
-            // two pieces per trip, the register sets swapping roles (copying one set into the
-            // other would wait for its loads on the spot)
-            fetch(v, 0);
-            for (size_t i = 0;; i += 2) {
-                if (i + 1 < nfull)
-                    fetch(w, i + 1);
-                else if (rest >= end)
-                    announce_leave(p, ctx);  // the item's last loads are out
-                put(v, i);
-                if (i + 1 >= nfull) break;
-                if (i + 2 < nfull)
-                    fetch(v, i + 2);
-                else if (rest >= end)
-                    announce_leave(p, ctx);
-                put(w, i + 1);
-                if (i + 2 >= nfull) break;
-            }
+    auto get = [&](size_t o) -> u32x4 { return __builtin_nontemporal_load(reinterpret_cast<const Grain *>(src + o)); };
+    auto set = [&](size_t o, u32x4 v) { __builtin_nontemporal_store((Grain)v, reinterpret_cast<Grain *>(dst + o)); };
+    // Whole pieces move without a condition per access (a guarded load ends up in a basic
+    // block of its own and the compiler then waits for each before the next is issued),
+    // the next piece's loads going out before this piece's stores.
+    const size_t nfull = (end - begin) / kCopyPiece;
+    const size_t rest = begin + nfull * kCopyPiece;  // start of the partial piece, if any
+    const size_t lane_off = (size_t)opaque_tid() * 16;
+    if (p->copy_gentle) {
+        // One access per thread in flight - and, where an estimator waits for the conv items' pool sums, none
+        // for the first three quarters of a microsecond (a whole one where a block has little to copy): the tiles come first.
+        // 64 x 64 fp32 8.9 us without the pauses, 8.45 with them; 120 x 160 fp32 9.7 / 9.1, 180 x 320 fp32 11.1 / 10.7, bf16
+        // 9.5 / 9.0; a microsecond everywhere: 180 x 320 fp32 11.0.  (With DK given nothing waits: a pause costs 16 x 64 x 64's
+        // input gradient 1 us.)
+        const size_t nvec = (end - begin) / (kThreads * 16);
+        if (p->pool_mode == kPoolFused) {
+            __builtin_amdgcn_s_sleep(28);                   // of 64 clocks
+            if (nvec <= 2) __builtin_amdgcn_s_sleep(16);
         }
-        if (!p->copy_gentle && rest < end) {  // at most one partial piece per call and image
-            u32x4 v[kCopyVecPerThread];
-#pragma unroll
-            for (int k = 0; k < kCopyVecPerThread; ++k) {
-                const size_t o = rest + (size_t)k * kThreads * 16 + lane_off;
-                if (o + 16 <= end) v[k] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(src + o));
-            }
+        __builtin_amdgcn_s_setprio(1);
+        for (size_t i = 0; i < nvec; ++i) {
+            const size_t o = begin + i * kThreads * 16 + lane_off;
+            const u32x4 v = get(o);
+            if (i + 1 == nvec && begin + nvec * kThreads * 16 >= end) announce_leave(p, ctx);
+            set(o, v);
+        }
+        const size_t o = begin + nvec * kThreads * 16 + lane_off;
+        if (begin + nvec * kThreads * 16 < end) {
+            u32x4 v = {};
+            if (o + 16 <= end) v = get(o);
             announce_leave(p, ctx);
-#pragma unroll
-            for (int k = 0; k < kCopyVecPerThread; ++k) {
-                const size_t o = rest + (size_t)k * kThreads * 16 + lane_off;
-                if (o + 16 <= end) __builtin_nontemporal_store(v[k], reinterpret_cast<u32x4 *>(dst + o));
-            }
+            if (o + 16 <= end) set(o, v);
         }
+        __builtin_amdgcn_s_setprio(kPrioHigh);
+    } else if (nfull > 0) {
+        u32x4 v[kCopyVecPerThread], w[kCopyVecPerThread];
+        auto fetch = [&](u32x4 *r, size_t i) {
+#pragma unroll
+            for (int k = 0; k < kCopyVecPerThread; ++k) r[k] = get(begin + i * kCopyPiece + (size_t)k * kThreads * 16 + lane_off);
+        };
+        auto put = [&](const u32x4 *r, size_t i) {
+#pragma unroll
+            for (int k = 0; k < kCopyVecPerThread; ++k) set(begin + i * kCopyPiece + (size_t)k * kThreads * 16 + lane_off, r[k]);
+        };
+        // two pieces per trip, the register sets swapping roles (copying one set into the
+        // other would wait for its loads on the spot)
+        fetch(v, 0);
+        for (size_t i = 0;; i += 2) {
+            if (i + 1 < nfull)
+                fetch(w, i + 1);
+            else if (rest >= end)
+                announce_leave(p, ctx);  // the item's last loads are out
+            put(v, i);
+            if (i + 1 >= nfull) break;
+            if (i + 2 < nfull)
+                fetch(v, i + 2);
+            else if (rest >= end)
+                announce_leave(p, ctx);
+            put(w, i + 1);
+            if (i + 2 >= nfull) break;
+        }
+    }
+    if (!p->copy_gentle && rest < end) {  // at most one partial piece per call and image
+        u32x4 v[kCopyVecPerThread];
+#pragma unroll
+        for (int k = 0; k < kCopyVecPerThread; ++k) {
+            const size_t o = rest + (size_t)k * kThreads * 16 + lane_off;
+            if (o + 16 <= end) v[k] = get(o);
+        }
+        announce_leave(p, ctx);
+#pragma unroll
+        for (int k = 0; k < kCopyVecPerThread; ++k) {
+            const size_t o = rest + (size_t)k * kThreads * 16 + lane_off;
+            if (o + 16 <= end) set(o, v[k]);
+        }
+    }
+    if constexpr (ANY) {
         // a range that is not a multiple of 16 bytes ends with whole elements
-        const size_t tail = len & ~(size_t)15;
-        if (end == len && tail < len) {
-            const size_t o = tail + (size_t)threadIdx.x * eb;
-            if (o < len) {
-                if (eb == 4)
-                    *reinterpret_cast<uint32_t *>(dst + o) = *reinterpret_cast<const uint32_t *>(src + o);
-                else
-                    *reinterpret_cast<uint16_t *>(dst + o) = *reinterpret_cast<const uint16_t *>(src + o);
-            }
-        }
-    } else {
-        // ranges off the 16-byte alignment: the same accesses wherever they lie, a piece at a time
-        typedef unsigned int Grain __attribute__((ext_vector_type(4), aligned(2)));
-        if (end - begin >= 16) {
-            for (size_t o0 = begin; o0 < end; o0 += kCopyPiece) {
-                const size_t lane_o = o0 + (size_t)opaque_tid() * 16;
-                Grain v[kCopyVecPerThread];
-#pragma unroll
-                for (int k = 0; k < kCopyVecPerThread; ++k) {
-                    const size_t o = lane_o + (size_t)k * kThreads * 16;
-                    v[k] = __builtin_nontemporal_load(reinterpret_cast<const Grain *>(src + (o + 16 <= end ? o : begin)));
-                }
-                if (o0 + kCopyPiece >= end) announce_leave(p, ctx);
-#pragma unroll
-                for (int k = 0; k < kCopyVecPerThread; ++k) {
-                    const size_t o = lane_o + (size_t)k * kThreads * 16;
-                    if (o + 16 <= end) __builtin_nontemporal_store(v[k], reinterpret_cast<Grain *>(dst + o));
-                }
-            }
-        }
+        const int eb = p->elem_bytes;
         const size_t tail = len & ~(size_t)15, o = tail + (size_t)threadIdx.x * eb;
         if (end == len && o < len) {
             if (eb == 4)

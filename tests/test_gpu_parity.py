@@ -74,6 +74,19 @@ def test_no_attention_channels_is_a_pure_copy(oracle):
     assert np.array_equal(out.view(np.uint8), wl.x.view(np.uint8))
 
 
+# Copies of odd widths (no attention channels): less than one 16-byte access, one, less than one 16 KiB piece, several of
+# them with a rest and a ragged end; and short calls beside conv items, whose copy items make one access at a time.
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("N,C,Ca,H,W", [(1, 1, 0, 1, 3), (3, 1, 0, 1, 7), (2, 1, 0, 1, 9), (1, 3, 0, 33, 31), (2, 5, 0, 91, 61),
+                                        (1, 16, 0, 1001, 1003), (1, 17, 1, 65, 63), (2, 21, 2, 47, 97), (1, 5, 4, 7, 3)])
+def test_copies_of_odd_widths(oracle, dtype, N, C, Ca, H, W):
+    wl = wk.make_random(370 + W, N, C, H, W, Ca, 5, dtype=dtype, x_mean=0.3)
+    if Ca:
+        check_forward(wl, oracle, f"{N}x{C}x{H}x{W} Ca={Ca}")
+    else:
+        assert np.array_equal(gu.run_forward(wl, use_gen=False).view(np.uint8), wl.x.view(np.uint8))
+
+
 # Rows fetched, pooled and stored in pieces wherever they end: widths round the pieces' and the tiles' lengths, identity
 # ranges of any number of bytes (carried by conv items, too: the last case fills every block slot with them).
 @pytest.mark.parametrize("dtype", [F32, BF16])
