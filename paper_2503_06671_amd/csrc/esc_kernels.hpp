@@ -69,6 +69,7 @@
 //     and held through every item: each phase takes the thread index afresh (opaque_tid).
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include <type_traits>
@@ -142,11 +143,13 @@ enum : int {
 // through channel-mean items
 constexpr int kDirectMaxBoxes = 512;
 
+// The order matters: every launch's parameters are new memory, fetched a 64-byte line at a time by the scalar cache, and a
+// conv item waits for the lines it reads in front of its tile.  Sizes and modes are one of them; what only some items
+// read stands at the end.  (With pool_x and pool_c behind `out`, N ... W lay across two lines: 64 x 64 fp32 with DK given
+// 8.7 us, so 8.35; 160 x 256 fp32 7 x 7 the same way 8.2 and 7.7.)
 struct FwdParams {
     const void *x;
     void *out;
-    const void *pool_x;  // what the pool items read: x, or (LK^c between them) the tensor x was made from,
-    int pool_c;          // with this many channels per image
     const float *lk;
     long lk_cstride;
     const float *dk_in;  // DK given by the caller (no estimator), or NULL
@@ -195,7 +198,10 @@ struct FwdParams {
     // beyond copy_off (bytes from the start of the range).  0 = nothing is carried.
     unsigned carry_g;
     size_t copy_off;
+    const void *pool_x;  // what the pool items read: x, or (LK^c between them) the tensor x was made from,
+    int pool_c;          // with this many channels per image
 };
+static_assert(offsetof(FwdParams, pool_mode) / 64 == offsetof(FwdParams, W) / 64, "sizes and modes are one line of parameters");
 
 // The kernel's parameter block as the item functions see it: a pointer into the kernel
 // argument segment (constant address space), read with scalar loads where needed instead
