@@ -1264,6 +1264,10 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
     }
     // (the call tag, asked for behind the tile, has arrived in this wavefront too)
     asm volatile("" ::"v"(ctx.tag));
+    // Nothing is under way any more: said here, because otherwise the compiler may, for a register of the tile loads,
+    // wait for it behind the barrier - and then for the announcement's round trip too, in front of the pool sums every
+    // estimator waits for (180 x 320 bf16 9.2 us a call, so 8.75; 120 x 160 fp32 8.8 and 8.45)
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0), the other counters at their maxima
     __syncthreads();
     // The leave is announced here: every wavefront of the block has its tile and its copy of
     // the call tag (the barrier above), and the announcing wavefront's atomic is then in

@@ -275,18 +275,16 @@ def test_binding_refuses_cpu_tensors(lib):
 
 # ---------------------------------------------------------------- compiled kernel variants
 
-def kernel_notes():
-    """(mangled name, private segment bytes, VGPRs, static LDS bytes) of every kernel in the built
-    library, read from the code objects' notes.  The library holds one offload bundle per
-    translation unit."""
+def code_objects(tool, holding=b""):
+    """What the LLVM tool `tool` (name, options) prints of each of the built library's gfx950 code objects that hold the
+    name `holding`: the library has one offload bundle per translation unit."""
     import subprocess
     import tempfile
     tools = "/opt/rocm/llvm/bin"
-    need = [os.path.join(tools, t) for t in ("llvm-objcopy", "clang-offload-bundler", "llvm-readelf")]
+    need = [os.path.join(tools, t) for t in ("llvm-objcopy", "clang-offload-bundler", tool[0])]
     if not all(os.path.exists(t) for t in need):
         pytest.skip("LLVM binary tools not found")
     magic = b"__CLANG_OFFLOAD_BUNDLE__"
-    out = []
     with tempfile.TemporaryDirectory() as tmp:
         fat = os.path.join(tmp, "fat.bin")
         subprocess.run([need[0], f"--dump-section=.hip_fatbin={fat}", binding.LIB_PATH, os.path.join(tmp, "copy.so")],
@@ -299,16 +297,26 @@ def kernel_notes():
             i = data.find(magic, i + 1)
         for k, s in enumerate(starts):
             one, dev = os.path.join(tmp, f"b{k}.bin"), os.path.join(tmp, f"d{k}.co")
-            open(one, "wb").write(data[s:starts[k + 1] if k + 1 < len(starts) else len(data)])
+            bundle = data[s:starts[k + 1] if k + 1 < len(starts) else len(data)]
+            if holding not in bundle:
+                continue
+            open(one, "wb").write(bundle)
             subprocess.run([need[1], "--unbundle", "--type=o", f"--input={one}",
                             "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", f"--output={dev}"], check=True)
-            notes = subprocess.run([need[2], "--notes", dev], check=True, capture_output=True, text=True).stdout
-            for block in notes.split("- .agpr_count:")[1:]:
-                name = re.search(r"\.name:\s*(\S+)", block).group(1)
-                scratch = int(re.search(r"\.private_segment_fixed_size:\s*(\d+)", block).group(1))
-                vgprs = int(re.search(r"\.vgpr_count:\s*(\d+)", block).group(1))
-                lds = int(re.search(r"\.group_segment_fixed_size:\s*(\d+)", block).group(1))
-                out.append((name, scratch, vgprs, lds))
+            yield subprocess.run([need[2], *tool[1:], dev], check=True, capture_output=True, text=True).stdout
+
+
+def kernel_notes():
+    """(mangled name, private segment bytes, VGPRs, static LDS bytes) of every kernel in the built
+    library, read from the code objects' notes."""
+    out = []
+    for notes in code_objects(("llvm-readelf", "--notes")):
+        for block in notes.split("- .agpr_count:")[1:]:
+            name = re.search(r"\.name:\s*(\S+)", block).group(1)
+            scratch = int(re.search(r"\.private_segment_fixed_size:\s*(\d+)", block).group(1))
+            vgprs = int(re.search(r"\.vgpr_count:\s*(\d+)", block).group(1))
+            lds = int(re.search(r"\.group_segment_fixed_size:\s*(\d+)", block).group(1))
+            out.append((name, scratch, vgprs, lds))
     return out
 
 
@@ -356,6 +364,26 @@ def test_forward_any_kernels_fit_four_blocks_per_cu(lib):
     assert len(meta) == 2 * len(VARIANT_SHAPES)
     for name, scratch, vgprs, lds in meta:
         assert vgprs <= 128 and 4 * lds <= LDS_PER_CU and scratch <= 64, (name, scratch, vgprs, lds)
+
+
+@pytest.mark.parametrize("Ks", [1, 7, 13, 17])
+def test_conv_items_do_not_wait_for_their_announcement(Ks):
+    # A conv item announces its leave with an atomic whose answer is wanted at the block's end.  Between it and the pool
+    # sums, which every estimator waits for, no instruction may wait for memory: results return in order, so that would be
+    # a wait for the atomic's round trip.  The place: behind a barrier, in front of the comparison with kPoolFused (2).
+    kernels = 0
+    for text in code_objects(("llvm-objdump", "-d", "--no-show-raw-insn", "--no-leading-addr"), b"forward_kernelILi%dE" % Ks):
+        for name, body in re.findall(r"<(_Z\S*forward_(?:any_)?kernelILi%dE\S*)>:\n(.*?)(?=\n\n|\Z)" % Ks, text, re.S):
+            code = [line.split("//")[0].strip() for line in body.splitlines()]
+            places = [i for i, c in enumerate(code) if c.startswith("global_atomic_add")
+                      and any(c.startswith("s_barrier") for c in code[max(0, i - 20):i])
+                      and any(re.match(r"s_cmp_(lg|eq)_u32 s\d+, 2$", c) for c in code[i + 1:i + 26])]
+            assert len(places) == 1, (name, places)
+            behind = code[places[0] + 1:]
+            sums = next(i for i, c in enumerate(behind) if c.startswith("ds_read"))
+            assert not any("vmcnt(" in c for c in behind[:sums]), (name, behind[:sums])
+            kernels += 1
+    assert kernels == 2 * 2 * 3  # register blockings, storage types, flavours
 
 
 def test_dense_bf16_kernels_fit_two_blocks_per_cu_without_scratch(lib):
