@@ -1741,17 +1741,17 @@ __device__ __forceinline__ Ctx copy_item(ParamsPtr p, Ctx ctx, unsigned item)
     const size_t rest = begin + nfull * kCopyPiece;  // start of the partial piece, if any
     const size_t lane_off = (size_t)opaque_tid() * 16;
     if (p->copy_gentle) {
-        // One access per thread in flight - and, where an estimator waits for the conv items' pool sums, none
-        // for the first three quarters of a microsecond (a whole one where a block has little to copy): the tiles come first.
-        // 64 x 64 fp32 8.9 us without the pauses, 8.45 with them; 120 x 160 fp32 9.7 / 9.1, 180 x 320 fp32 11.1 / 10.7, bf16
-        // 9.5 / 9.0; a microsecond everywhere: 180 x 320 fp32 11.0.  (With DK given nothing waits: a pause costs 16 x 64 x 64's
-        // input gradient 1 us.)
+        // One access per thread in flight.  Where an estimator waits for the conv items' pool sums, blocks with little
+        // to copy - up to four accesses a thread - leave the tiles half a microsecond's start, one with a single access
+        // twice that: it is done in time all the same.  Without, with: 64 x 64 fp32 8.4 us, 8.05; 120 x 160 fp32 8.8,
+        // 8.35, bf16 8.55, 7.75; 180 x 256 fp32 9.7, 9.45.  With more to copy the copy is what a call lasts: 180 x 320
+        // fp32, six accesses, 10.0 and 10.1, 7 x 7 9.55 and 10.15, 14 images of 64 x 64 fp32 9.9 and 10.6.  (Where nothing
+        // waits, with DK given, a pause costs 160 x 256 fp32 7 x 7 half a microsecond.)
         const size_t nvec = (end - begin) / (kThreads * 16);
-        if (p->pool_mode == kPoolFused) {
-            __builtin_amdgcn_s_sleep(28);                   // of 64 clocks
-            if (nvec <= 2) __builtin_amdgcn_s_sleep(16);
+        if (p->pool_mode == kPoolFused && nvec <= 4) {
+            __builtin_amdgcn_s_sleep(16);                   // of 64 clocks
+            if (nvec <= 1) __builtin_amdgcn_s_sleep(16);
         }
-        __builtin_amdgcn_s_setprio(1);
         for (size_t i = 0; i < nvec; ++i) {
             const size_t o = begin + i * kThreads * 16 + lane_off;
             const u32x4 v = get(o);
@@ -1765,7 +1765,6 @@ __device__ __forceinline__ Ctx copy_item(ParamsPtr p, Ctx ctx, unsigned item)
             announce_leave(p, ctx);
             if (o + 16 <= end) set(o, v);
         }
-        __builtin_amdgcn_s_setprio(kPrioHigh);
     } else if (nfull > 0) {
         u32x4 v[kCopyVecPerThread], w[kCopyVecPerThread];
         auto fetch = [&](u32x4 *r, size_t i) {
