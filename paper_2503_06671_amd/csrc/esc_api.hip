@@ -324,9 +324,10 @@ esc_status launch_forward(FwdParams &p, int Ks, bool bf16, hipStream_t s)
     }
     const u64 total = (u64)p.n_pool + p.n_gen + p.n_conv + (p.idt_len > 0 ? 1 : 0);
     if (total == 0) return ESC_OK;
-    // whole aligned pieces of 16 bytes everywhere?  (all tensors' planes and images then lie on them too)
+    // Planes of whole aligned pieces of 16 bytes everywhere, and rows of whole runs of four elements (fp32: such pieces
+    // as well; bf16: halves of them)?
     const uintptr_t bases = (uintptr_t)p.x | (uintptr_t)p.pool_x | (uintptr_t)p.out;
-    if (p.W % (bf16 ? 8 : 4) != 0 || bases % 16 != 0) p.flavour = kAny;
+    if (p.W % 4 != 0 || bases % 16 != 0 || (size_t)p.H * p.W * p.elem_bytes % 16 != 0) p.flavour = kAny;
     // the blocks of the grid wait for one another, so all of them must be resident at once:
     // the grid is sized by what the runtime says fits on this device
     const int ks_slot = (Ks + 1) / 2;

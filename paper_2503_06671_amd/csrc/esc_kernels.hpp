@@ -183,8 +183,9 @@ struct FwdParams {
     unsigned *done;      // [kGroups] blocks of the group that have announced their leave
     unsigned *queue;     // [kGroups] entries of the group's list handed out beyond the first per block
     int dynamic;         // blocks take their further entries from the group's queue
-    // host only: which kernel.  kPlain: aligned tensors (rows and bases in whole pieces of 16 bytes); kStaged: the same
-    // with the staged estimator items and out_add; kAny: those too, and any width and alignment.
+    // host only: which kernel.  kPlain: aligned tensors (planes and bases in whole pieces of 16 bytes, rows in whole runs of
+    // four elements); kStaged: the same with the staged estimator items and out_add; kAny: those too, and any width and
+    // alignment.
     int flavour;
     // Every conv item is resident from the start (fused pooling) and the call is so short
     // that the conv items' chain of load, taps, estimator and store is what it lasts: the
@@ -1075,7 +1076,7 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
     if constexpr (kMatrix && !ANY) {
         // whole aligned pieces of 8 columns (each lies entirely inside or outside the image),
         // all loads in flight before the first LDS write
-        {
+        if ((W & 7) == 0) {
             constexpr int NP8 = MG::COLS / 8;
             constexpr int TOT = HR * NP8;
             constexpr int K = (TOT + kThreads - 1) / kThreads;
@@ -1091,12 +1092,38 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
                 if (in) raw[k] = *reinterpret_cast<const u32x4 *>(xp + (size_t)gy * W + gx);
             }
             load_weights();
-        if (p->pool_mode != kPoolNone || ctx.last_item) need_tag(p, ctx);
+            if (p->pool_mode != kPoolNone || ctx.last_item) need_tag(p, ctx);
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 const int q = k * kThreads + tid1;
                 const int r = q / NP8, j = q - r * NP8;
                 if (q < TOT) *reinterpret_cast<u32x4 *>(tile_d + MG::word(r, 4 * j)) = raw[k];
+            }
+        } else {
+            // rows that are whole pieces of 4 columns alone (180 x 324, 17 x 17: 12.15 us a call, by the kernel for
+            // any width 12.75; 16 x 60 x 60 9.1 and 10.0; 540 x 956 alone is faster there, 34.6 and 35.3).  Written out, not shared with the pieces of 8: a function of
+            // both has the compiler wait for each load before the next.
+            constexpr int NP4 = MG::COLS / 4;
+            constexpr int TOT = HR * NP4;
+            constexpr int K = (TOT + kThreads - 1) / kThreads;
+            const int g0 = x0 - PH - MG::A;
+            uint2 raw[K];
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const int q = k * kThreads + tid1;
+                const int r = q / NP4, j = q - r * NP4;
+                const int gy = y0 - PH + r, gx = g0 + 4 * j;
+                const bool in = q < TOT && gy >= 0 && gy < H && gx >= 0 && gx < W;
+                raw[k] = make_uint2(0u, 0u);
+                if (in) raw[k] = *reinterpret_cast<const uint2 *>(xp + (size_t)gy * W + gx);
+            }
+            load_weights();
+            if (p->pool_mode != kPoolNone || ctx.last_item) need_tag(p, ctx);
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const int q = k * kThreads + tid1;
+                const int r = q / NP4, j = q - r * NP4;
+                if (q < TOT) *reinterpret_cast<uint2 *>(tile_d + MG::word(r, 2 * j)) = raw[k];
             }
         }
     } else if constexpr (!ANY) {

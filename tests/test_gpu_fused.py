@@ -105,7 +105,8 @@ def test_fused_two_layer_estimator_and_given_dk(oracle):
 # from queues; channel means, resident and not; estimators beyond the small ones) gives the bits of DK made beforehand.
 @pytest.mark.parametrize("dtype", [F32, BF16])
 @pytest.mark.parametrize("N,Ca,H,W,hidden", [(1, 16, 64, 64, 8), (1, 16, 33, 67, 0), (24, 16, 64, 64, 8), (20, 20, 63, 65, 24),
-                                             (1, 16, 288, 200, 8), (1, 16, 339, 511, 0), (2, 40, 190, 320, 24)])
+                                             (1, 16, 288, 200, 8), (1, 16, 339, 511, 0), (2, 40, 190, 320, 24),
+                                             (1, 16, 62, 60, 8), (2, 20, 130, 140, 24)])
 def test_estimator_beside_lkc_equals_dk_made_beforehand(dtype, N, Ca, H, W, hidden):
     wl = wk.make_random(750 + N + H, N, Ca + 4, H, W, Ca, 13, dtype=dtype, hidden=hidden, bias=True, x_mean=0.5)
     w_fuse, b_fuse, lkc = pointwise_weights(751, wl.C, wl.Ca)

@@ -74,6 +74,16 @@ def test_no_attention_channels_is_a_pure_copy(oracle):
     assert np.array_equal(out.view(np.uint8), wl.x.view(np.uint8))
 
 
+# Rows of whole runs of four elements, in bf16 half a 16-byte piece: planes that are whole pieces and planes that are not
+# (odd heights), matrix and other kernel sizes, short and long calls, pool items and carried copies among them.
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("N,H,W,Ks", [(2, 6, 4, 3), (2, 7, 4, 13), (1, 34, 12, 17), (1, 40, 60, 1), (3, 33, 68, 13), (1, 66, 76, 31),
+                                      (1, 180, 324, 7), (1, 290, 324, 13), (40, 64, 60, 13), (61, 62, 60, 17), (1, 530, 260, 13)])
+def test_rows_of_runs_of_four(oracle, dtype, N, H, W, Ks):
+    wl = wk.make_random(380 + W + H, N, 19, H, W, 16, Ks, dtype=dtype, x_mean=0.3)
+    check_forward(wl, oracle, f"{N}x{H}x{W} ks{Ks}")
+
+
 # Copies of odd widths (no attention channels): less than one 16-byte access, one, less than one 16 KiB piece, several of
 # them with a rest and a ragged end; and short calls beside conv items, whose copy items make one access at a time.
 @pytest.mark.parametrize("dtype", [F32, BF16])
