@@ -23,8 +23,9 @@
 // Layout.  A wavefront owns 32 NT pixels and 32 MT output channels; a lane of the matrix
 // instruction's B operand wants eight consecutive channels of one pixel, which is what eight
 // loads of one channel row each bring it (32 lanes on a run of 32 NT pixels: whole cache
-// lines), so the inputs go from memory into the operand's registers without passing LDS,
-// two stages of 32 channels ahead.  Only the weights pass LDS, split into their terms there by
+// lines), so the inputs go from memory into the operand's registers without passing LDS, asked
+// for two stages of 32 channels ahead (runs_body has them under way until they are wanted; in
+// pointwise_body the compiler waits for all of them at every stage: see there).  Only the weights pass LDS, split into their terms there by
 // the block, a stage at a time in two buffers and one barrier a stage.  The residual's first row
 // block is on its way with them, its second takes an input buffer as that falls free; it is added to
 // the finished sums: one rounding at its size, where sums started from it are rounded there by every
@@ -107,7 +108,7 @@ __device__ __forceinline__ void pw_finish(const PointwiseParams &p, const f32x16
     const unsigned P = (unsigned)p.P, pb = P * (unsigned)sizeof(T);
     auto row_of = [](int mt, int i) { return (unsigned)(32 * mt + 8 * (i >> 2) + (i & 3)); };
     // ConvFFN's hidden layer is read back by the next launch; the other results are not, or lie better in memory
-    constexpr int kStoreAux = GELU ? 0 : kNt;   // (192 -> 384 channels, 180 x 320 fp32: 7 us between the two for the next launch)
+    constexpr int kStoreAux = GELU ? 0 : kNt;   // (step of 192 channels fp32, past the L2 and through it: 169 x 341 259 and 254.6 us, 180 x 320 246.0 and 246.3)
     // (taken afresh: kept from the residual's loads, the offsets would fill registers)
     unsigned st_off = out_off;
     asm volatile("" : "+v"(st_off));
@@ -447,7 +448,9 @@ __device__ __forceinline__ void pointwise_body(const PointwiseParams &p)
 // what becomes of the sums
 enum : int { kPwPlain = 0, kPwGelu = 1, kPwRes = 2 };
 
-// any number of stages; all channels in one (LK^c: 339 x 511 fp32 8.9 us -> 7.8); in two
+// any number of stages; all channels in one (LK^c: 339 x 511 fp32 8.9 us -> 7.8); in two, written out (as a loop: the fused
+// call with a residual 64 x 64 x 64 bf16 39.0 us, so 36.7, 360 x 640 bf16 36.7 and 34.6, 180 x 320 fp32 22.2 and 21.4;
+// without one at 360 x 640 bf16 31 - 33 either way)
 enum : int { kPwRuns = 0, kPwOne = 1, kPwTwo = 2 };
 
 template <typename T, int MT, int NT, int MODE, int LIE>
@@ -500,8 +503,8 @@ __device__ __forceinline__ void runs_body(const PointwiseParams &p)
     // Sixteen loads on every way through here and through the loop: at a point that could be reached without them, or
     // behind a wait for some of them, the compiler waits for all that are under way, and nothing is fetched ahead.  A
     // chunk beyond the channels is asked for beyond the tensor: zeros, and no traffic.  (With the fetches behind
-    // conditions: residual step of the 192-channel model 169 x 341 fp32 256 us, so 240; 64 x 64 72 -> 60; 64 channels of 25
-    // images of 63 x 63 119 -> 111; Conv_fuse 360 x 640 bf16 21.1 -> 19.1.)
+    // conditions: residual step of the 192-channel model 64 x 64 fp32 72 us, so 60; 64 channels of 25 images of 63 x 63
+    // 119 and 111; Conv_fuse 360 x 640 bf16 21.1 and 19.1.)
     auto fetch = [&](int st, Raw (&r)[16]) {
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
@@ -516,7 +519,6 @@ __device__ __forceinline__ void runs_body(const PointwiseParams &p)
     };
 
     // ---- weights of a stage: unit u = eight weights of one row ----
-    const bool k8 = (K & 7) == 0;   // a run of eight is inside or outside as a whole
     struct __attribute__((packed, aligned(4))) W4 {
         float v[4];
     };
@@ -526,15 +528,10 @@ __device__ __forceinline__ void runs_body(const PointwiseParams &p)
             const int u = tid + i * kPwThreads;
             const int m = m0 + (u >> 2), k = st * kPwStage + 8 * (u & 3);
             const bool row_in = m < M;
-            if (k8) {
-                const float *s = p.w + ((row_in && k < K) ? (size_t)m * p.w_ld + k : 0);
-                const W4 a = *reinterpret_cast<const W4 *>(s), b = *reinterpret_cast<const W4 *>(s + 4);
+            const float *s = p.w + ((row_in && k < K) ? (size_t)m * p.w_ld + k : 0);   // (a run of eight is inside or outside as a whole)
+            const W4 a = *reinterpret_cast<const W4 *>(s), b = *reinterpret_cast<const W4 *>(s + 4);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) w[i][e] = a.v[e], w[i][4 + e] = b.v[e];
-            } else {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) w[i][e] = p.w[(row_in && k + e < K) ? (size_t)m * p.w_ld + k + e : 0];
-            }
+            for (int e = 0; e < 4; ++e) w[i][e] = a.v[e], w[i][4 + e] = b.v[e];
         }
     };
     auto wput = [&](int st, const float (&w)[kUnits][8]) {
