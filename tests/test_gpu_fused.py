@@ -117,6 +117,23 @@ def test_estimator_beside_lkc_equals_dk_made_beforehand(dtype, N, Ca, H, W, hidd
     assert np.array_equal(got.view(np.uint8), want.view(np.uint8))
 
 
+# x off the 16-byte alignment while what is convolved, F_pw in the workspace, lies on it: the pool items go by both.
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("shift", [1, 4])
+@pytest.mark.parametrize("N,H,W", [(1, 64, 64), (9, 40, 72), (1, 290, 320)])
+def test_lkc_of_an_unaligned_tensor(dtype, shift, N, H, W):
+    wl = wk.make_random(760 + N + H, N, 20, H, W, 16, 13, dtype=dtype, hidden=8, bias=True, x_mean=0.5)
+    w_fuse, b_fuse, lkc = pointwise_weights(761, wl.C, wl.Ca)
+    x = gu.to_dev_x(wl.x, wl.dtype)
+    off = torch.empty(x.numel() + 8, dtype=x.dtype, device="cuda")[shift:shift + x.numel()].view_as(x).copy_(x)
+    assert off.data_ptr() % 16 == shift * x.element_size() % 16
+    ws = binding.new_fused_workspace(N, 16, H, W, x.dtype, True)
+    a, b = (binding.convattn_fused_forward(t, 16, gu.dev(wl.lk), gu.dev(w_fuse), ws, b_fuse=gu.dev(b_fuse), lk_c=gu.dev(lkc),
+                                           residual=t, gen=gu.gen_params(wl)) for t in (x, off))
+    assert torch.equal(a, b)
+    assert binding.workspace_errors(ws) == 0
+
+
 # ------------------------------------------------------------------ exact special cases
 
 @pytest.mark.parametrize("dtype", [F32, BF16])

@@ -32,10 +32,11 @@ def test_tile_edges(oracle, dtype, N, C, H, W, Ca):
 
 
 # Channels in whole runs of sixteen: one to eight stages, the last one half full or full, both tensors' border inside a stage
-# and between two, with and without the residual that takes an input buffer over.
+# and between two, with and without the residual that takes an input buffer over; many images: two pixels per lane (from
+# 512 groups of up to 64 output channels of an image on).
 @pytest.mark.parametrize("dtype", [F32, BF16])
 @pytest.mark.parametrize("N,C,Ca", [(1, 16, 16), (1, 32, 16), (2, 48, 16), (1, 64, 32), (1, 80, 48), (2, 96, 32), (1, 112, 16),
-                                    (1, 128, 64), (1, 240, 48), (400, 32, 16), (300, 48, 32), (300, 64, 16), (200, 80, 16)])
+                                    (1, 128, 64), (1, 240, 48), (600, 32, 16), (600, 48, 32), (600, 64, 16), (300, 80, 16)])
 def test_stages_of_whole_runs(oracle, dtype, N, C, Ca):
     wl = wk.make_random(960 + C, N, C, 3, 45, Ca, 3, dtype=dtype, x_mean=0.3)
     w_fuse, b_fuse, lkc = pointwise_weights(961 + C, C, Ca)
@@ -57,10 +58,11 @@ def test_whole_runs_two_pixels_per_lane(oracle, dtype, C, Ca):
 
 
 @pytest.mark.parametrize("N,C", [(1, 20), (1, 40), (1, 64), (1, 96), (600, 24), (600, 32), (600, 64), (600, 70)])  # one to three stages of channels, one and two row blocks and pixels per lane
-def test_residual_is_rounded_once(N, C):
+@pytest.mark.parametrize("Ca", [8, 16])   # 16: the kernels for whole runs, where C is one too
+def test_residual_is_rounded_once(N, C, Ca):
     # fp32 storage: the residual is added to the finished sums, so that one far larger than they are costs them no
     # more than the one rounding of that addition
-    H, W, Ca = 3, 15, 8
+    H, W = 3, 15
     wl = wk.make_random(930 + C, N, C, H, W, Ca, 3, dtype=F32, x_mean=0.3)
     w_fuse, b_fuse, _ = pointwise_weights(931, C, Ca)
     res = 100 * residual_for(wl, 932)
