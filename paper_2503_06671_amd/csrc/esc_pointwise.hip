@@ -443,7 +443,8 @@ __device__ __forceinline__ void pointwise_body(const PointwiseParams &p)
 
 // ---- the same with everything fetched ahead, where src1's channels, and all of them, are whole runs of sixteen (a chunk
 // lies in one tensor, or beyond both): pointwise_body's loads stand behind conditions, which make the compiler wait for
-// all that are under way at every stage ----
+// all that are under way at every stage.  (Its steps are written out a second time: as functions of both bodies they leave
+// pointwise_kernel<2, false>, which fills its registers, with 36 to 44 bytes in the private segment.) ----
 
 // what becomes of the sums
 enum : int { kPwPlain = 0, kPwGelu = 1, kPwRes = 2 };
