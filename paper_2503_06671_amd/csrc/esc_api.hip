@@ -334,7 +334,9 @@ esc_status launch_forward(FwdParams &p, int Ks, bool bf16, hipStream_t s)
     const int bpc = resident_blocks_per_cu(ks_slot, ry, bf16, p.flavour);
     if (bpc < 1) return ESC_ERR_UNSUPPORTED;
     const Plan plan = plan_items(p, Ks, bpc, Ks > 0 ? conv_carry_grains(Ks, ry, bf16) : 0);
-    if ((u64)p.n_pool + p.n_gen + p.n_conv + p.n_copy >= ((u64)1 << 30)) return ESC_ERR_UNSUPPORTED;
+    // (with a tensor of their own to pool, the estimator's items are counted by themselves, as in a launch of their own)
+    const u64 estimate = (u64)p.n_pool + p.n_gen, rest = (u64)p.n_conv + p.n_copy, most = (u64)1 << 30;
+    if (p.pool_x == p.x ? estimate + rest >= most : estimate >= most || rest >= most) return ESC_ERR_UNSUPPORTED;
     const unsigned grid = plan.per_die * kXcds;
     return kLaunch[ks_slot](ry, bf16, p.flavour, grid, s, p) == hipSuccess ? ESC_OK : ESC_ERR_HIP;
 }
