@@ -90,6 +90,8 @@ def test_backward_bf16_rows_of_whole_pieces(oracle, Ks):
     (1, 5, 1, 1, 2, 3, 0, True, F32),          # a single pixel
     (40, 6, 12, 12, 4, 3, 0, False, F32),      # many small images: sums over the batch
     (1, 4, 70, 200, 4, 9, 0, False, BF16),     # no identity channels, several tiles
+    (9, 20, 62, 60, 16, 13, 8, True, BF16),    # rows of whole runs of four, planes of whole pieces
+    (2, 6, 61, 60, 4, 7, 0, True, BF16),       # the same rows, planes that are not
 ])
 def test_backward_shapes_and_estimators(oracle, N, C, H, W, Ca, Ks, hidden, bias, dtype):
     wl = wk.make_random(1200 + H + Ca, N, C, H, W, Ca, Ks, dtype=dtype, hidden=hidden, bias=bias, x_mean=0.4)
