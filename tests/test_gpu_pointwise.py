@@ -132,3 +132,31 @@ def test_nan_costs_no_more_than_a_few_ordinary_calls(what):
     print(f"{what}: {ordinary:.1f} us, with NaN {with_nan:.1f} us", flush=True)
     assert torch.isnan(out).all()
     assert with_nan <= 5 * ordinary
+
+
+@pytest.mark.parametrize("N,C", [(1, 32), (1, 64), (600, 64), (1, 96), (600, 80), (2, 192), (130, 112)])
+def test_values_and_weights_of_any_size(N, C):
+    # fp32 storage: a common factor of the values, of a row of weights, or of the channels of one stage beside another's
+    # (2^12 here: a later stage's values a thousand times the first's, the other way round, and pixels without any) leaves
+    # the error against float64 where fp32 sums have it.  K products and sums, each within 2^-24 of terms whose squares add
+    # up: sqrt(2 K) 2^-24 of the result, and the weights' terms and the dropped product within 2^-23.
+    H, W = 3, 45
+    rng = np.random.default_rng(940 + C)
+    w0, x0 = rng.standard_normal((C, C)) / np.sqrt(C), rng.standard_normal((N, C, H, W)) + 0.3
+    bound = (np.sqrt(2 * C) / 2 + 1) * 2.0 ** -23
+    first, second = np.ones((C, 1, 1)), np.ones((C, 1, 1))
+    first[:C // 2], second[C // 2:] = 2.0 ** -12, 2.0 ** -12
+    some = np.ones((1, H, W))
+    some[:, :, W // 2:] = 0.0
+    rows = 2.0 ** rng.integers(-60, 60, (C, 1))
+    for what, xs, ws in (("2^-30", 2.0 ** -30, 1.0), ("2^30", 2.0 ** 30, 1.0), ("2^-100 x 2^60", 2.0 ** -100, 2.0 ** 60), ("rows", 1.0, rows),
+                         ("small first", first, 1.0), ("small last", second, 1.0), ("both", first * 2.0 ** -20, rows), ("zeros", some * 2.0 ** 14, 1.0)):
+        x, w = (x0 * xs).astype(np.float32), (w0 * ws).astype(np.float32)
+        wl = wk.make_random(941, N, C, H, W, 0, 3, dtype=F32)
+        wl.x[...] = x
+        print(f"[case] {what} N={N} C={C}", flush=True)
+        got = run_fused(wl, w).astype(np.float64)
+        want = np.einsum("mk,nkp->nmp", w.astype(np.float64), x.reshape(N, C, -1).astype(np.float64), optimize=True).reshape(got.shape)
+        scale = np.sqrt((want ** 2).mean(axis=(0, 2, 3), keepdims=True))   # rows of W differ in size, and so do their results
+        err = np.sqrt((((got - want) / scale) ** 2).mean())
+        assert err <= bound, (what, err, bound)
