@@ -402,8 +402,13 @@ __device__ __forceinline__ void die_share(unsigned n, unsigned die, unsigned &ba
 
 // LDS of a block, shared by all item kinds: the conv tile and weights are sized for the
 // largest variant (Ks = 17 with 4-row register blocks; Ks = 31 with 2-row blocks).
+#if defined(ESC_KS) && ESC_KS >= 15   // (the terms' tiles of SplitGeom and their weights)
+constexpr int kLdsTileFloats = 6480;
+constexpr int kLdsWeightFloats = ESC_KS > 17 ? 2048 : 31 * 32;
+#else
 constexpr int kLdsTileFloats = 6400;
 constexpr int kLdsWeightFloats = 31 * 32;
+#endif
 __shared__ __align__(16) float g_tile[kLdsTileFloats];
 __shared__ __align__(16) float g_wl[kLdsWeightFloats];
 __shared__ float g_part[kStage];
@@ -962,6 +967,48 @@ struct MatrixGeom {
     __device__ static __forceinline__ int word(int r, int wi) { return ((wi >> 2) * HRP + r) * 4 + (wi & 3); }
 };
 
+// fp32 storage from Ks = 15 on (and bf16 storage from 19 on): the same Toeplitz products on fp16
+// instructions, where the vector loop was bound by its multiply-adds.  A tile's values, brought to
+// at most 2^15 by a power of two, are taken apart into two fp16 terms, v = h + l, h the nearest fp16
+// to v and l the nearest to what is left: to a unit of fp32's last place at most (a quarter of the values), from
+// 2^15 down to 1, and to 2^-25 below.  So are the weights, and three of the four products of terms
+// are accumulated in fp32 (the fourth is below 2^-22 of a product), the two with a low term in sums
+// of their own; bf16 values are a term each.  K of an instruction is sixteen columns of two
+// neighbouring tile rows, i.e. two kernel rows at once: sixteen outputs need NQ = 2 or 3 runs of
+// sixteen columns, and a B operand serves every block of outputs that needs its run.
+// Error against float64: 540 x 960, Ks = 31 4.3e-7 -> 1.6e-7, Ks = 17 2.7e-7 -> 1.6e-7.
+//
+// Bound by LDS reads (per pair of kernel rows 60 clocks for the A operands, 8 for a B operand's term, against 16 a
+// product).  540 x 960 fp32 Ks = 31 193 -> 97 us a call, Ks = 17 78.6 -> 63.5 (the copy alone takes 52), bf16
+// Ks = 31 176 -> 72, 64 x 64 fp32 Ks = 31 24.0 -> 12.3, Ks = 17 9.5 -> 8.6.  Smaller kernels keep the
+// vector loop: with Ks = 13 this one takes 8.3 us at 64 x 64, so 8.1, 10.8 and 10.35 at 180 x 320, 30.6 and 25.7 at 339 x 511.
+//
+// LDS: the terms' tiles, each laid out as in MatrixGeom, and the weights as rows of fp16 terms with
+// zeros round them (element e of a row is tap e - 15 - S0), from which a lane takes the eight
+// neighbouring ones that its A operand wants, wherever they start.
+template <int KS, int RY, int TX>
+struct SplitGeom {
+    using G = ConvGeom<KS, RY>;
+    static constexpr int A = (8 - G::PH % 8) % 8;
+    static constexpr int S0 = A + G::OFF;
+    static constexpr int NQ = (15 + KS - 1 + S0) / 16 + 1;
+    static constexpr int COLS = kTileW + 16 * (NQ - 1);
+    static constexpr int HRP = G::HR + 1;        // odd, and a row more for the last kernel row's partner
+    static constexpr int TERM_WORDS = (COLS / 8) * HRP * 4;
+    static constexpr int WROW = 8 * NQ + 8;      // words of a weight row's term
+    static constexpr int WTERM = (KS + 1) * WROW;
+    static constexpr int PAIRS = (KS + 1) / 2;
+    // Two-row blocking, three runs: two wavefronts share sixteen rows by pairs of kernel rows, not by columns, so that a B
+    // operand serves three blocks and an A operand four (otherwise two; the loop is bound by LDS reads), and add up through LDS.
+    static constexpr bool HALVES = RY == 2 && NQ == 3;
+    static constexpr int NT = HALVES ? 4 : RY;   // blocks of 16 x 16 outputs a wavefront works on
+    static_assert(KS < 3 || (G::HR % 2 == 0 && G::HC + A <= COLS), "the halo does not fit");
+    static_assert(KS < 15 || (TX * TERM_WORDS <= kLdsTileFloats && 2 * WTERM <= kLdsWeightFloats && (!HALVES || kLdsWeightFloats >= 2048)), "LDS pool too small");
+};
+// which variants take it
+template <int KS, typename T>
+constexpr bool conv_splits = KS >= 15 && !(std::is_same<T, bf16_t>::value && KS <= 17);
+
 // where a conv item lies
 struct ConvWhere {
     unsigned n, nc;
@@ -982,6 +1029,16 @@ __device__ __forceinline__ ConvWhere conv_where(ParamsPtr p, unsigned item)
     w.x0 = w.txi * kTileW;
     w.y0 = w.tyi * TH;
     return w;
+}
+
+// v = h + l (SplitGeom), two values at a time
+__device__ __forceinline__ void split_f16(float v0, float v1, uint32_t &h, uint32_t &l)
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+    const f16x2 a = __builtin_convertvector(f32x2{v0, v1}, f16x2);
+    h = __builtin_bit_cast(uint32_t, a);
+    l = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{v0 - (float)a.x, v1 - (float)a.y}, f16x2));
 }
 
 template <int KS, int RY, typename T, bool ADD, bool ANY>
@@ -1340,6 +1397,79 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
         }
         pool_finish<NPT>(p->pool_box, sums, box, have, ctx.tag, g_red);
     }
+    // fp32 on the matrix cores (SplitGeom).  Tiles and kernels with infinities or NaN keep the vector loop, which
+    // gives special values where the definition does and nowhere else.
+    constexpr bool kSplit = conv_splits<KS, T>;
+    constexpr int TX = std::is_same<T, float>::value ? 2 : 1;
+    using SG = SplitGeom<KS, RY, TX>;
+    bool split = false;   // block-uniform
+    int wback = 0, xback = 0;   // the powers of two that bring the weights and the tile's values back to their size
+    if constexpr (kSplit) {
+        // a thread takes two columns of every fourth row, and two elements of every eighth weight row
+        constexpr int KU = (SG::HRP + 3) / 4, KWU = (KS + 1 + 7) / 8;
+        const int tc = tid2 & 63, tr = tid2 >> 6, wc = tid2 & 31, wr = tid2 >> 5;
+        const int cc = 2 * tc - SG::A, jj = 2 * wc - 15 - SG::S0;
+        float v[KU][2], w[KWU][2];
+        unsigned mx = 0, mw = 0;
+        {
+            const bool in0 = cc >= 0 && cc < HC, in1 = cc + 1 >= 0 && cc + 1 < HC;
+            const float *src0 = tile + tr * PITCH + (in0 ? cc : 0), *src1 = tile + tr * PITCH + (in1 ? cc + 1 : 0);
+#pragma unroll
+            for (int k = 0; k < KU; ++k) {
+                const bool row = 4 * k + 3 < HR || 4 * k + tr < HR;
+                v[k][0] = row ? src0[4 * k * PITCH] : 0.f;
+                v[k][1] = row ? src1[4 * k * PITCH] : 0.f;
+                v[k][0] = in0 ? v[k][0] : 0.f;
+                v[k][1] = in1 ? v[k][1] : 0.f;
+                mx = max(mx, max(__float_as_uint(v[k][0]) & 0x7fffffffu, __float_as_uint(v[k][1]) & 0x7fffffffu));
+            }
+        }
+        {
+            const bool in0 = jj >= 0 && jj < KS, in1 = jj + 1 >= 0 && jj + 1 < KS;
+            const float *src0 = wl + wr * WP + (in0 ? jj : 0), *src1 = wl + wr * WP + (in1 ? jj + 1 : 0);
+#pragma unroll
+            for (int k = 0; k < KWU; ++k) {
+                const bool row = 8 * k + 7 < KS || 8 * k + wr < KS;
+                w[k][0] = row ? src0[8 * k * WP] : 0.f;
+                w[k][1] = row ? src1[8 * k * WP] : 0.f;
+                w[k][0] = in0 ? w[k][0] : 0.f;
+                w[k][1] = in1 ? w[k][1] : 0.f;
+                mw = max(mw, max(__float_as_uint(w[k][0]) & 0x7fffffffu, __float_as_uint(w[k][1]) & 0x7fffffffu));
+            }
+        }
+        unsigned *s_max = reinterpret_cast<unsigned *>(g_small);
+        mx = wave_max(mx);
+        mw = wave_max(mw);
+        if ((tid2 & 63) == 63) s_max[tid2 >> 6] = mx, s_max[4 + (tid2 >> 6)] = mw;
+        __syncthreads();  // also: everyone has read what is now written over
+        mx = max(max(s_max[0], s_max[1]), max(s_max[2], s_max[3]));
+        mw = max(max(s_max[4], s_max[5]), max(s_max[6], s_max[7]));
+        split = mx < 0x7f800000u && mw < 0x72000000u;   // (weights below 2^101: values stay 2^15 large until the end)
+        if (split) {
+            // powers of two that bring the largest to 2^14 ... 2^15 (as far as fp32 reaches)
+            const int ex = min(14 + 127 - (int)(mx >> 23), 126), ew = min(14 + 127 - (int)(mw >> 23), 126);
+            const float fx = __uint_as_float((unsigned)(127 + ex) << 23), fw = __uint_as_float((unsigned)(127 + ew) << 23);
+            wback = -ew, xback = -ex;
+            uint32_t *dst = tile_d + ((tc >> 2) * SG::HRP + tr) * 4 + (tc & 3);
+            uint32_t *sw = reinterpret_cast<uint32_t *>(g_wl) + wr * SG::WROW + wc;
+#pragma unroll
+            for (int k = 0; k < KU; ++k) {
+                uint32_t h, l;
+                split_f16(v[k][0] * fx, v[k][1] * fx, h, l);
+                if (tc < SG::COLS / 2 && (4 * k + 3 < SG::HRP || 4 * k + tr < SG::HRP)) {
+                    dst[16 * k] = h;
+                    if (TX > 1) dst[SG::TERM_WORDS + 16 * k] = l;
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < KWU; ++k) {
+                uint32_t h, l;
+                split_f16(w[k][0] * fw, w[k][1] * fw, h, l);
+                if (wc < SG::WROW && 8 * k + wr < KS + 1) sw[8 * k * SG::WROW] = h, sw[8 * k * SG::WROW + SG::WTERM] = l;
+            }
+            __syncthreads();
+        }
+    }
     carry_load();
     if constexpr (kMatrix) {
         // The band table (MatrixGeom), made from the weights in LDS once the pool sums are
@@ -1558,7 +1688,103 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
         for (int t = 0; t < RY; ++t)
 #pragma unroll
             for (int q = 0; q < 4; ++q) acc[t][q] = macc[t][q];
-    } else if (G::UNROLL) {
+    } else if (kSplit && split) {
+        if constexpr (kSplit) {
+            // Blocks of 16 x 16 outputs and the result's layout as on the bf16 matrix path.  Per pair of kernel rows: the
+            // NQ A operands' terms from the weight rows (lane (m, kg): kernel row 2 ip + kg / 2, eight taps from
+            // 16 o + 8 (kg % 2) - m on), and per run q of sixteen columns a B operand's terms, for the blocks that need it.
+            typedef float f32x4 __attribute__((ext_vector_type(4)));
+            typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+            const int lane = tid2 & 63, b0 = (tid2 >> 6) * RY;
+            const int m = lane & 15, kg = lane >> 4;
+            const int e0 = 8 * (kg & 1) - m + 15;
+            const int first = SG::HALVES ? (tid2 >> 6) & 1 : 0;   // the wavefront's first pair of kernel rows
+            constexpr int STEP = SG::HALVES ? 2 : 1, NT = SG::NT;
+            const uint32_t *a_src = reinterpret_cast<const uint32_t *>(g_wl) + ((kg >> 1) + 2 * first) * SG::WROW + (e0 >> 1);
+            const unsigned sh = 16 * (e0 & 1);
+            const uint32_t *b_src = tile_d + ((SG::HALVES ? kg & 1 : 2 * (b0 & 3) + (kg & 1)) * SG::HRP +
+                                              16 * (b0 >> 2) + OFF + (kg >> 1) + m + 2 * first) * 4;
+            f32x4 hi[NT], lo[NT];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) hi[t] = lo[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+            // the next pair's weights and the next run's values travel while this one's are multiplied
+            constexpr int NB = NT + SG::NQ - 1;
+            uint32_t aw[SG::NQ][5];
+            f16x8 a[SG::NQ][2];
+            u32x4 bv[TX];
+            auto load_aw = [&](const uint32_t *src) {
+#pragma unroll
+                for (int o = 0; o < SG::NQ; ++o)
+#pragma unroll
+                    for (int k = 0; k < 5; ++k) aw[o][k] = src[8 * o + k];
+            };
+            auto take_aw = [&](int term) {
+#pragma unroll
+                for (int o = 0; o < SG::NQ; ++o) {
+                    u32x4 u;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) u[k] = __builtin_amdgcn_alignbit(aw[o][k + 1], aw[o][k], sh);
+                    a[o][term] = __builtin_bit_cast(f16x8, u);
+                }
+            };
+            auto load_bv = [&](const uint32_t *src, int q, u32x4 (&b)[TX]) {
+#pragma unroll
+                for (int x = 0; x < TX; ++x) b[x] = *reinterpret_cast<const u32x4 *>(src + x * SG::TERM_WORDS + 2 * q * SG::HRP * 4);
+            };
+            auto multiply = [&](bool more) {
+                take_aw(0);
+                load_aw(a_src + SG::WTERM);
+                take_aw(1);
+                if (more) load_aw(a_src += 2 * STEP * SG::WROW);
+#pragma unroll
+                for (int q = 0; q < NB; ++q) {
+                    u32x4 next[TX];
+                    if (q + 1 < NB)
+                        load_bv(b_src, q + 1, next);
+                    else if (more)
+                        load_bv(b_src += 8 * STEP, 0, next);
+#pragma unroll
+                    for (int o = 0; o < SG::NQ; ++o) {
+                        const int t = q - o;
+                        if (t < 0 || t >= NT) continue;
+                        const f16x8 b0 = __builtin_bit_cast(f16x8, bv[0]);
+                        lo[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[o][1], b0, lo[t], 0, 0, 0);
+                        if (TX > 1) lo[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[o][0], __builtin_bit_cast(f16x8, bv[TX - 1]), lo[t], 0, 0, 0);
+                        hi[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[o][0], b0, hi[t], 0, 0, 0);
+                    }
+                    if (q + 1 < NB || more) {
+#pragma unroll
+                        for (int x = 0; x < TX; ++x) bv[x] = next[x];
+                    }
+                }
+            };
+            load_aw(a_src);
+            load_bv(b_src, 0, bv);
+#pragma unroll 1
+            for (int ip = first + STEP; ip < SG::PAIRS; ip += STEP) multiply(true);
+            if (G::UNROLL) ask_again();
+            multiply(false);
+            if constexpr (SG::HALVES) {
+                // the wavefront keeps blocks 2 (wave % 2), + 1 and hands the other two over
+                __syncthreads();  // the weights have been read
+                f32x4 *x = reinterpret_cast<f32x4 *>(g_wl) + (tid2 >> 6) * 128 + lane;
+                f32x4 *y = reinterpret_cast<f32x4 *>(g_wl) + ((tid2 >> 6) ^ 1) * 128 + lane;
+#pragma unroll
+                for (int t = 0; t < 2; ++t) x[64 * t] = first ? hi[t] + lo[t] : hi[NT - 2 + t] + lo[NT - 2 + t];
+                __syncthreads();
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const f32x4 other = y[64 * t];
+                    hi[t] = first ? hi[NT - 2 + t] + lo[NT - 2 + t] : hi[t] + lo[t];
+                    lo[t] = other;
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < RY; ++t)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) acc[t][q] = __builtin_amdgcn_ldexpf(hi[t][q] + lo[t][q], wback);
+        }
+    } else if (G::UNROLL && !kSplit) {
 #pragma unroll
         for (int r0 = 0; r0 < G::ROWS; r0 += RY)
 #pragma unroll
@@ -1570,7 +1796,7 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
     } else {
         // Large kernels: a loop, two rows per trip; the kernel rows are re-read from LDS for
         // every output row instead of being held (they would not fit in the registers).
-#pragma unroll 2
+#pragma unroll 1
         for (int r = 0; r < G::ROWS; ++r) {
             XT xr[NX];
             load_x(r, xr);
@@ -1585,6 +1811,7 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
             }
             __builtin_amdgcn_sched_barrier(0);  // one row's loads at a time: the registers are few
         }
+        if (G::UNROLL) ask_again();
     }
     __builtin_amdgcn_s_setprio(kPrioHigh);
 
@@ -1660,8 +1887,38 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
                 }
             }
         }
+        if constexpr (kSplit) {
+            if (split) {
+                // as on the bf16 matrix path, from the terms
+                typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+                for (int t = 0; t < RY; ++t) {
+                    const int wi = (16 * ((mb0 & 3) + t) + 4 * mg4 + PH + SG::A) / 2;
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) {
+                        const int row = 16 * (mb0 >> 2) + mrow + PH - 1 + i;
+                        float v[8];
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            const int w = wi - 1 + k, at = ((w >> 2) * SG::HRP + row) * 4 + (w & 3);
+                            const f16x2 h = __builtin_bit_cast(f16x2, tile_d[at]);
+                            v[2 * k] = (float)h.x, v[2 * k + 1] = (float)h.y;
+                            if constexpr (TX > 1) {
+                                const f16x2 l = __builtin_bit_cast(f16x2, tile_d[SG::TERM_WORDS + at]);
+                                v[2 * k] += (float)l.x, v[2 * k + 1] += (float)l.y;
+                            }
+                        }
+#pragma unroll
+                        for (int j = 0; j < 3; ++j)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) acc[t][q] = fmaf(d[i * 3 + j], v[1 + j + q], acc[t][q]);
+                    }
+                }
+            }
+        }
 #pragma unroll
         for (int r = 0; r < (kMatrix ? 0 : RY + 2); ++r) {
+            if (kSplit && split) break;
             float v[6];
             {
                 const float *src = trow_d + (r + PH - 1) * PITCH + (PH - 1);
@@ -1682,6 +1939,12 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
         }
     }
 
+    if (kSplit && split) {
+#pragma unroll
+        for (int t = 0; t < RY; ++t)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[t][q] = __builtin_amdgcn_ldexpf(acc[t][q], xback);
+    }
     if (p->dk_mode == kDkNone) claim_next(p, ctx);
     // (only in the kernel flavour that calls with such a constant are sent to: the flavour
     // the short forward calls use stays free of it)
@@ -1725,8 +1988,9 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
     }
 #pragma unroll
     for (int oy = 0; oy < RY; ++oy) {
-        const int gx = wd.x0 + 4 * tx_d;
-        const int gy = wd.y0 + ty_d * RY + oy;
+        const bool blocks = kSplit && split;   // sums of 16 x 16 blocks: a row of each, four columns
+        const int gx = wd.x0 + (blocks ? 16 * ((mb0 & 3) + oy) + 4 * mg4 : 4 * tx_d);
+        const int gy = wd.y0 + (blocks ? 16 * (mb0 >> 2) + mrow : ty_d * RY + oy);
         if (gy >= H) continue;
         T *dst = op + (size_t)gy * W + gx;
         if (ANY ? gx + 3 < W : gx < W) {

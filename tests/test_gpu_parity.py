@@ -432,6 +432,38 @@ def test_non_finite_pixels_in_the_attention_slice(oracle, dtype, Ks):
     assert (d <= tol * (np.abs(ref_att[ok]) + rms)).all()
 
 
+@pytest.mark.parametrize("dtype,Ks,N,H,W", [(F32, 15, 1, 33, 66), (F32, 17, 1, 65, 129), (F32, 17, 24, 64, 65), (F32, 19, 1, 31, 64),
+                                            (F32, 31, 2, 40, 80), (BF16, 19, 1, 32, 72), (BF16, 31, 1, 33, 64)])
+def test_large_kernels_at_any_scale(oracle, dtype, Ks, N, H, W):
+    # values and weights of every size, a plane of zeros, planes whose sizes lie 2^40 apart, weights too large for
+    # the terms and a NaN (both: the vector loop).  fp32 storage, in the 2-norm: fp32 products and sums stay within sqrt(2 taps) 2^-24 of
+    # terms whose squares add up to the result's, and two terms are within 2^-23 of each factor.
+    base = wk.make_random(920 + Ks, N, 6, H, W, 4, Ks, dtype=dtype)
+    dk0 = np.random.default_rng(921).standard_normal((N, 4, 3, 3)).astype(np.float32)
+    planes = np.array([1.0, 0.0, 2.0 ** 20, 2.0 ** -20]).reshape(1, 4, 1, 1)
+    for what, fx, fw in (("ordinary", 1.0, 1.0), ("small", 2.0 ** -90, 2.0 ** -20), ("large", 2.0 ** 90, 2.0 ** -30),
+                         ("small x large", 2.0 ** -100, 2.0 ** 100), ("beyond", 2.0 ** -60, 2.0 ** 110), ("planes", planes, 1.0), ("nan", 1.0, 1.0)):
+        print(f"[case] {what} {dtype} Ks={Ks}", flush=True)
+        xf = base.x_as_f32().copy()
+        xf[:, :4] = (xf[:, :4] * fx).astype(np.float32)
+        if what == "nan":
+            xf[0, 1, H // 2, W // 2] = np.nan
+        x = wk.f32_to_bf16_bits(xf) if dtype == BF16 else xf
+        wl = wk.make_random(920 + Ks, N, 6, H, W, 4, Ks, dtype=dtype)
+        wl.x, wl.lk = x, (base.lk * fw).astype(np.float32)
+        dk = (dk0 * fw).astype(np.float32)
+        ref, _, _ = oracle.convattn_forward(x, 4, wl.lk, dtype, dk_in=dk, want_out=False)
+        got = gu.att_as_f64(gu.run_forward(wl, use_gen=False, dk_in=dk), wl)
+        assert np.array_equal(np.isnan(ref), np.isnan(got)), what
+        for c in range(4):
+            r, g = ref[:, c], got[:, c]
+            ok = ~np.isnan(r)
+            rms = np.sqrt((r[ok] ** 2).mean())
+            err = np.sqrt(((g - r)[ok] ** 2).mean())
+            bound = (np.sqrt(2 * Ks * Ks) + 4) * 2.0 ** -24 if dtype == F32 else 2.0 ** -8
+            assert err <= bound * rms, (what, c, err / rms, bound)
+
+
 def test_bf16_large_kernel_weight_rounding_error_bound(oracle):
     # With bf16 storage and Ks <= 17 the fp32 large-kernel weights are rounded to bf16 on
     # the device (operands of the bf16 matrix instructions).  Bound asserted here: the normwise error
