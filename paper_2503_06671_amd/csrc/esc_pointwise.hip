@@ -7,11 +7,12 @@
 // per image, with P = H*W pixels contiguous in memory for every channel of B and D, so
 // it runs on the matrix cores, on v_mfma_f32_32x32x16_bf16 for both storage types:
 //
-//  fp32 storage, channels in whole runs of sixteen and more than 32 of them: every value as three fp16 terms (exact:
-//    split_pair_f16), every weight, its row brought to a common size first, as two (to 2^-24 of it), and the four of the six
-//    products of terms that matter, the three with a low term in sums of their own, accumulated in fp32.  64 channels come out
-//    to 7.1e-8 of float64, 192 to 8.8e-8, 240 to 9.3e-8 (with the six bf16 products below 8.4e-8, 1.5e-7, 1.7e-7: half as
-//    many roundings of the large sums), whatever the size of values and weights.
+//  fp32 storage, channels in whole runs of sixteen and more than 32 of them: every value and every weight (its row brought
+//    to a common size first) as two fp16 terms (split_pair_f16), and three of the four products of terms, the two with a low
+//    term in sums of their own, accumulated in fp32.  Error against float64, whatever the size of values and weights:
+//    64 channels 9.8e-8, 192 1.2e-7, 240 1.3e-7 (with the six bf16 products below 1.1e-7, 2.0e-7, 2.3e-7, by twice as many
+//    roundings of the large sums; with a third term of the values, which is one bit, 8.8e-8, 1.1e-7, 1.2e-7 and the
+//    192-channel step 212 us, so 198).
 //  fp32 storage otherwise: every value and every weight as three bf16 terms (v = t0 + t1 + t2, each the
 //    nearest bf16 to what the terms before it left: exact, down to magnitudes of 2^-110, where t2
 //    runs out of bits: 64 channels of standard deviation 2^-114 come out to 5.6e-7, of 2^-118 to
@@ -94,22 +95,17 @@ __device__ __forceinline__ void split_pair(float v0, float v1, unsigned (&t)[N])
     }
 }
 
-// fp32 storage, fp16 terms: v = h + l / 4096 + t / 4096, h the nearest fp16 to v, l the nearest to 4096 times what is left,
-// t what l leaves of that.  h has 11 of the 24 bits and l with its sign 12, so t is the one bit that may remain: the three are
-// exact for magnitudes from 2^-13 to 65504, below that to 2^-37.
+// fp32 storage, fp16 terms: v = h + l / 4096, h the nearest fp16 to v, l the nearest to 4096 times what is left.  h has 11 of
+// the 24 bits and l with its sign 12: a bit is missing in a quarter of the values, from 2^-13 to 65504; below that all beyond 2^-37.
 typedef _Float16 pw_f16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 constexpr float kLowScale = 4096.f;
-template <int N>
-__device__ __forceinline__ void split_pair_f16(float v0, float v1, unsigned (&t)[N])
+__device__ __forceinline__ void split_pair_f16(float v0, float v1, unsigned (&t)[2])
 {
     const pw_f16x2 h = __builtin_convertvector(pw_f32x2{v0, v1}, pw_f16x2);
     const float r0 = __builtin_fmaf(-kLowScale, (float)h.x, v0 * kLowScale), r1 = __builtin_fmaf(-kLowScale, (float)h.y, v1 * kLowScale);
-    const pw_f16x2 l = __builtin_convertvector(pw_f32x2{r0, r1}, pw_f16x2);
     t[0] = __builtin_bit_cast(unsigned, h);
-    t[1] = __builtin_bit_cast(unsigned, l);
-    if constexpr (N > 2)
-        t[2] = __builtin_bit_cast(unsigned, pw_f16x2{(_Float16)__builtin_fmaf(-1.f, (float)l.x, r0), (_Float16)__builtin_fmaf(-1.f, (float)l.y, r1)});
+    t[1] = __builtin_bit_cast(unsigned, __builtin_convertvector(pw_f32x2{r0, r1}, pw_f16x2));
 }
 
 extern __shared__ __align__(16) u32x4 pw_lds[];
@@ -506,7 +502,7 @@ __device__ __forceinline__ void runs_body(const PointwiseParams &p)
     // fp32 storage on fp16 terms; on bf16 ones up to one stage, whose few sums these keep nearer (16 -> 16 channels, error
     // against float64: 3.6e-8, on fp16 terms 6.2e-8; 32 -> 32 5.6e-8 and 6.7e-8; 48 -> 48 7.2e-8 and 6.8e-8)
     constexpr bool H = F && !ONE;
-    constexpr int TX = F ? 3 : 1, TW = F && !H ? 3 : 2;   // terms of a value, of a weight
+    constexpr int TX = F ? (H ? 2 : 3) : 1, TW = F && !H ? 3 : 2;   // terms of a value, of a weight
     constexpr int RW = (NT * (int)sizeof(T) + 3) / 4;     // words a load brings
     constexpr int kUnits = (MT * 128 + kPwThreads - 1) / kPwThreads;  // runs of eight weights a thread stages
     typedef typename std::conditional<RW == 2, u32x2, unsigned>::type Raw;
@@ -586,9 +582,8 @@ __device__ __forceinline__ void runs_body(const PointwiseParams &p)
             for (int e = 0; e < 4; ++e) w[i][e] = a.v[e], w[i][4 + e] = b.v[e];
         }
     };
-    // fp16 terms: a row is multiplied by the power of two that brings the largest of its first 32 weights to 1 ... 2, and its
-    // finished sums by the inverse (s_back), so that its terms have their bits whatever its size
-    float wscale[kUnits];
+    // fp16 terms: a row is multiplied by the power of two that brings the largest weight of its first stage that has any to
+    // 1 ... 2, and its finished sums by the inverse (s_back), so that its terms have their bits whatever its size
     auto wput = [&](int st, const float (&w)[kUnits][8]) {
 #pragma unroll
         for (int i = 0; i < kUnits; ++i) {
@@ -597,19 +592,21 @@ __device__ __forceinline__ void runs_body(const PointwiseParams &p)
             const int in = m0 + row < M ? K - (st * kPwStage + 8 * kq) : 0;   // how many of the eight lie in W
             unsigned t[4][TW];
             if constexpr (H) {
-                if (st == 0) {
+                const bool own = MT * 128 % kPwThreads == 0 || u < MT * 128;
+                float back = st == 0 || !own ? 0.f : s_back[row];
+                if (back == 0.f) {   // (the first stage, or a row without weights so far)
                     float m = 0.f;
 #pragma unroll
                     for (int e = 0; e < 8; ++e) m = __builtin_fmaxf(m, e < in ? __builtin_fabsf(w[i][e]) : 0.f);
                     m = __builtin_fmaxf(m, quad_swap<0xb1>(m));   // the other three of the row's four threads
                     m = __builtin_fmaxf(m, quad_swap<0x4e>(m));
-                    wscale[i] = to_unit(m);
-                    if (MT * 128 % kPwThreads == 0 || u < MT * 128)
-                        if (kq == 0) s_back[row] = 1.f / wscale[i];
+                    back = m == 0.f ? 0.f : 1.f / to_unit(m);
+                    if (own && kq == 0) s_back[row] = back;
                 }
+                const float wscale = back == 0.f ? 1.f : to_unit(back);
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    split_pair_f16<TW>((2 * e < in ? w[i][2 * e] : 0.f) * wscale[i], (2 * e + 1 < in ? w[i][2 * e + 1] : 0.f) * wscale[i], t[e]);
+                    split_pair_f16((2 * e < in ? w[i][2 * e] : 0.f) * wscale, (2 * e + 1 < in ? w[i][2 * e + 1] : 0.f) * wscale, t[e]);
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) split_pair<TW>(2 * e < in ? w[i][2 * e] : 0.f, 2 * e + 1 < in ? w[i][2 * e + 1] : 0.f, t[e]);
@@ -699,15 +696,15 @@ __device__ __forceinline__ void runs_body(const PointwiseParams &p)
     };
     if constexpr (H) {
         const float m = largest(ra);
-        scaled = __builtin_amdgcn_ballot_w64(m > 64.f) != 0 ||
-                 (__builtin_amdgcn_ballot_w64(m >= 1.f / 64.f) == 0 && __builtin_amdgcn_ballot_w64(m > 0.f) != 0);
+        scaled = __builtin_amdgcn_ballot_w64(m > 64.f) != 0 || __builtin_amdgcn_ballot_w64(m >= 1.f / 64.f) == 0;
     }
     auto rescale = [&](Raw (&raw)[16]) {
         float m = largest(raw);
         if (xscale == 0.f || __builtin_amdgcn_ballot_w64(m * xscale > 32768.f) != 0) {
 #pragma unroll
             for (int d = 1; d < 64; d *= 2) m = __builtin_fmaxf(m, __shfl_xor(m, d));
-            const float s = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(to_unit(m)))), f = xscale == 0.f ? 1.f : s / xscale;
+            m = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(m)));
+            const float s = m == 0.f ? 0.f : to_unit(m), f = xscale == 0.f ? 1.f : s / xscale;   // (nothing but zeros: no size yet)
             xscale = s;
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
@@ -724,7 +721,7 @@ __device__ __forceinline__ void runs_body(const PointwiseParams &p)
     };
     auto split = [](float v0, float v1, unsigned (&t)[TX]) {
         if constexpr (H)
-            split_pair_f16<TX>(v0, v1, t);
+            split_pair_f16(v0, v1, t);
         else
             split_pair<TX>(v0, v1, t);
     };
@@ -827,7 +824,7 @@ __device__ __forceinline__ void runs_body(const PointwiseParams &p)
         if (LATE) rfetch(1, rb);
     }
     if constexpr (H) {
-        const float back = scaled ? 1.f / xscale : 1.f;
+        const float back = scaled && xscale != 0.f ? 1.f / xscale : 1.f;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -922,7 +919,7 @@ hipError_t launch_mode(const PointwiseParams &p, int mt, unsigned grid, hipStrea
 {
     const int K = p.K1 + p.K2;
     // Whole runs of sixteen channels: everything fetched ahead, and fp32 storage on half as many matrix instructions (192-channel
-    // residual step 180 x 320 fp32 233 us, by the body for any channels, -> 201; 64 x 64 61 -> 56)
+    // residual step 180 x 320 fp32 234 us, by the body for any channels, -> 190; 64 x 64 58 -> 51)
     if (p.K1 % 16 == 0 && p.K2 % 16 == 0) {
         if constexpr (MODE == kPwPlain || sizeof(T) == 4)
             if (K <= kPwStage) return launch_runs<T, NT, MODE, kPwOne>(p, mt, grid, s);

@@ -149,8 +149,10 @@ def test_values_and_weights_of_any_size(N, C):
     some = np.ones((1, H, W))
     some[:, :, W // 2:] = 0.0
     rows = 2.0 ** rng.integers(-60, 60, (C, 1))
+    late = (np.arange(C) >= (32 if C > 32 else 0)).astype(float)[:, None]   # no weight and no value in the first stage
     for what, xs, ws in (("2^-30", 2.0 ** -30, 1.0), ("2^30", 2.0 ** 30, 1.0), ("2^-100 x 2^60", 2.0 ** -100, 2.0 ** 60), ("rows", 1.0, rows),
-                         ("small first", first, 1.0), ("small last", second, 1.0), ("both", first * 2.0 ** -20, rows), ("zeros", some * 2.0 ** 14, 1.0)):
+                         ("small first", first, 1.0), ("small last", second, 1.0), ("both", first * 2.0 ** -20, rows), ("zeros", some * 2.0 ** 14, 1.0),
+                         ("late", late[:, :, None] * 2.0 ** -24, late.T * 2.0 ** -20)):
         x, w = (x0 * xs).astype(np.float32), (w0 * ws).astype(np.float32)
         wl = wk.make_random(941, N, C, H, W, 0, 3, dtype=F32)
         wl.x[...] = x
