@@ -6,8 +6,8 @@
 // A full C_a -> C_a convolution is a dense contraction over K = C_a * Ks * Ks (2704 for the
 // paper's 13 x 13 x 16 x 16), sixteen times the depth-wise form's arithmetic on the same
 // bytes: it is bound by the matrix cores, so it runs as an implicit GEMM - with up to 16
-// channels on the bf16 instructions (dense_bf16_kernel, further down: bf16 storage, and fp32
-// storage up to 13 x 13 with values and weights as exact bf16 terms), else on
+// channels on the 16-bit instructions (dense_bf16_kernel, further down: bf16 storage, and fp32
+// storage up to 13 x 13 with values and weights as fp16 terms), else on
 // v_mfma_f32_16x16x4_f32 (fp32 products and accumulation; bf16 storage is widened exactly
 // when a tile is staged and rounded once at the store).  That kernel: per block an 8 x 32 (small calls:
 // 4 x 32) pixel output tile of one image, all output channels.  Sixteen input channels at a time, their
@@ -372,16 +372,20 @@ __global__ __launch_bounds__(kDnThreads, CT <= 2 ? 2 : 1) void dense_kernel(cons
 }
 
 // ---------------------------------------------------------------------------------------
-// Up to 16 channels: the contraction on v_mfma_f32_16x16x32_bf16.
+// Up to 16 channels: the contraction on v_mfma_f32_16x16x32_bf16 and, fp32 storage, v_mfma_f32_16x16x32_f16.
 //
 // K of one instruction = two neighbouring taps of a kernel row x 16 input channels.  bf16
 // storage: the stored values are the operands; each fp32 weight enters as two bf16 terms,
 // w = hi + lo to 16 mantissa bits, so two instructions per operand pair, products exact,
-// accumulation fp32.  fp32 storage (kernels up to 13 x 13): the bf16 instructions are sixteen
-// times as fast as the fp32 ones, so every value and every weight is split exactly into three
-// bf16 terms (dn_split3; one tile in LDS per term, three terms in the table) and the six
-// products of terms whose orders add up to at most two are accumulated - what is left out
-// lies below 2^-24 of a product, the size of fp32's own rounding.  The halo tile sits in LDS pixel-major, as cells of 16 bytes = eight
+// accumulation fp32.  fp32 storage (kernels up to 13 x 13): the 16-bit instructions are sixteen
+// times as fast as the fp32 ones, so values and weights enter as fp16 terms (dn_split_f16), the values of a
+// tile behind a power of two that brings its largest to 2^14 ... 2^15, the weights of an output channel behind
+// another (the largest of each is found by the preparing launch, a power a tile or channel at a time): a value
+// as three terms, exact, a weight as two, and four of the six products of terms are accumulated - what is
+// left out lies below 2^-22 of a product and a weight's second term ends within a unit of fp32's last place.
+// (Before: three bf16 terms each and six products.  180 x 320, 13 x 13 35.4 -> 31.1 us a call, 360 x 640 105.5 -> 93.8,
+// error against float64 2.0e-7 -> 1.5e-7.  Values as two terms, three products: 27.8 us at the same error, but then
+// a kernel of a single one no longer moves the values as they are.)  The halo tile sits in LDS pixel-major, as cells of 16 bytes = eight
 // channels of one pixel, in two half planes (channels 0-7, 8-15): the sixteen lanes that read
 // one B operand's pixels read 256 consecutive bytes, the only pattern in which 16-byte LDS
 // reads run at full rate.  The tile's columns start at x0 - 8, so that (W % 8 == 0, 16-byte
@@ -413,7 +417,24 @@ __host__ __device__ constexpr int bf_aux_cell(int Kse, int th, int nx)
 }
 inline size_t bf_lds_bytes(int Kse, int th, int nx) { return (size_t)bf_aux_cell(Kse, th, nx) * 16 + 16 * 9 * sizeof(float); }
 
-__device__ __forceinline__ void dn_split3(float v, uint16_t (&t)[3]) { dw_split3(v, t); }
+// fp32 storage: fp16 terms, each the nearest to what the ones before it left, two values at a time.  Two are within a unit of
+// fp32's last place (and miss it in a quarter of the values), three are exact, for magnitudes from 2^15 down to 1;
+// below that all beyond 2^-25 is lost.
+template <int N>
+__device__ __forceinline__ void dn_split_f16(float v0, float v1, uint32_t (&t)[N])
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+        const f16x2 h = __builtin_convertvector(f32x2{v0, v1}, f16x2);
+        t[q] = __builtin_bit_cast(uint32_t, h);
+        v0 -= (float)h.x, v1 -= (float)h.y;
+    }
+}
+// the power of two that brings a magnitude of these bits to 2^14 ... 2^15, as far as fp32 reaches
+__device__ __forceinline__ int dn_exponent(unsigned bits) { return min(14 + 127 - (int)(bits >> 23), 126); }
+__device__ __forceinline__ float dn_power(int e) { return __uint_as_float((unsigned)(127 + e) << 23); }
 
 // What the matrix path needs before its first block: the A-operand table (dense_table_entry, one thread per
 // entry) and, where DK comes from the estimator, the pool tiles' sums - four tiles a block, in the forward's pool
@@ -422,12 +443,22 @@ __device__ __forceinline__ void dn_split3(float v, uint16_t (&t)[3]) { dw_split3
 // of its own in front, with its hops from block to block, took 7 us at 180 x 320 fp32 and 13 at 360 x 640 bf16; this
 // one takes 4.8 and 4.9 (the call 34.7 -> 31.6 and 51.8 -> 44.9; 331 x 617 fp32 7 x 7 74 -> 60; 64 x 64 bf16 16.7 -> 14.7).
 template <typename T>
-__global__ __launch_bounds__(kDnThreads) void dense_prep_kernel(const DenseParams p, const float *lk, int Ks, int nw, unsigned n_pool)
+__global__ __launch_bounds__(kDnThreads) void dense_prep_kernel(const DenseParams p, const float *lk, int Ks, unsigned n_pool)
 {
     const int tid = (int)threadIdx.x;
     if (blockIdx.x >= n_pool) {
-        const int idx = (int)(blockIdx.x - n_pool) * kDnThreads + tid;
-        if (idx < dense_table_entries(p.Ks)) dense_table_entry(lk, p.Ca, Ks, p.Ks, nw, reinterpret_cast<uint32_t *>(p.wt), idx);
+        constexpr bool terms = !std::is_same<T, float>::value;
+        const int part = (int)(blockIdx.x - n_pool), idx = part * kDnThreads + tid;
+        uint32_t *wa = reinterpret_cast<uint32_t *>(p.wt);
+        unsigned m = idx < dense_table_entries(p.Ks) ? dense_table_entry(lk, p.Ca, Ks, p.Ks, terms, wa, idx) : 0u;
+        if constexpr (!terms) {
+            __shared__ unsigned s_max[kDnThreads / 64][16];
+            m = max(m, (unsigned)__shfl_xor((int)m, 16));
+            m = max(m, (unsigned)__shfl_xor((int)m, 32));
+            if ((tid & 63) < 16) s_max[tid >> 6][tid & 15] = m;
+            __syncthreads();
+            if (tid < 16) wa[dense_table_words(p.Ks) + part * 16 + tid] = max(max(s_max[0][tid], s_max[1][tid]), max(s_max[2][tid], s_max[3][tid]));
+        }
         return;
     }
     __shared__ float s_red[kPoolBatch * (kDnThreads / 64)];
@@ -510,10 +541,12 @@ template <typename T, int KS, int TH>
 __global__ __launch_bounds__(kDnThreads, 2) void dense_bf16_kernel(const DenseParams p)
 {
     typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+    typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
     typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
     constexpr bool kF32 = std::is_same<T, float>::value;
-    constexpr int NX = kF32 ? 3 : 1;  // bf16 terms of a stored value (one tile in LDS per term)
-    constexpr int NW = kF32 ? 3 : 2;  // bf16 terms of a weight
+    constexpr int NX = kF32 ? 3 : 1;  // terms of a stored value (one tile in LDS per term; fp32 storage: fp16 terms)
+    constexpr int NW = 2;             // terms of a weight
     constexpr int NA = 2 * TH;  // runs of 16 pixels in the tile: run nt = row nt / 2, columns 16 (nt % 2) ..
     constexpr int NT = TH / 2;  // runs whose results a wavefront ends up with
     constexpr int pad = (KS - 1) / 2, HR = TH + 2 * pad, HP = HR * kBfPitch;
@@ -597,51 +630,78 @@ __global__ __launch_bounds__(kDnThreads, 2) void dense_bf16_kernel(const DensePa
         }
     };
 
+    // fp32 storage: the largest weight of this lane's output channel, from what the preparing launch's blocks found
+    // (asked for in front of the tile, looked at behind it)
+    constexpr int kParts = kF32 ? ((KS + 1) / 2 * KS * 64 + 255) / 256 : 0, kMine = (kParts + 3) / 4;
+    unsigned wmax[kMine > 0 ? kMine : 1];
+    if constexpr (kF32) {
+        const unsigned *found = reinterpret_cast<const unsigned *>(p.wt) + dense_table_words(KS) + l16;
+#pragma unroll
+        for (int k = 0; k < kMine; ++k) wmax[k] = found[(4 * k + kq < kParts ? 4 * k + kq : kParts - 1) * 16];
+    }
+
     // ---- the zero-extended halo tile, pixel-major ----
+    // fp32 storage: the tile's largest finite magnitude, which every wavefront looks its own values through for
+    // and all meet at a barrier for; a value that is not finite is not in it and comes out as inf and NaN terms.
+    int xexp = 0;
+    auto tile_exponent = [&](auto each) {
+        unsigned *s_max = reinterpret_cast<unsigned *>(s_dk);   // (DK comes there later)
+        unsigned m = 0;
+        each([&](float v) { m = max(m, __float_as_uint(v) & 0x7fffffffu); });
+        if (__builtin_amdgcn_ballot_w64(m >= 0x7f800000u) != 0) {
+            m = 0;
+            each([&](float v) { const unsigned b = __float_as_uint(v) & 0x7fffffffu; m = max(m, b < 0x7f800000u ? b : 0u); });
+        }
+        m = wave_max(m);
+        if (lane == 63) s_max[wave] = m;
+        __syncthreads();
+        xexp = dn_exponent(max(max(s_max[0], s_max[1]), max(s_max[2], s_max[3])));
+    };
     if (kF32 && p.fill_vec) {
-        // fp32 storage: the same tasks, 32 bytes (eight pixels) of each of eight channels per task,
-        // every value split into its three terms on the way to the three tiles
+        // fp32 storage: the same tasks, 32 bytes (eight pixels) of each of eight channels per task, at most one per thread,
+        // every value split into its terms on the way to the tiles
         if constexpr (kF32) {
-            constexpr int tasks = 2 * (kBfCols / 8) * HR, KT = (tasks + kDnThreads - 1) / kDnThreads;
-            u32x4 v[KT][8][2];
-            bool in[KT];
+            constexpr int tasks = 2 * (kBfCols / 8) * HR;
+            static_assert(tasks <= kDnThreads, "one task per thread");
+            u32x4 v[8][2];
+            const int r = tid % HR, rest = tid / HR, pc = rest % (kBfCols / 8), h2 = rest / (kBfCols / 8);
+            const int gy = y0 - pad + r, gx = x0 - 8 + 8 * pc;
+            const bool in = tid < tasks && gy >= 0 && gy < H && gx >= 0 && gx < W;
+            const size_t o = in ? (size_t)gy * W + gx : 0;
 #pragma unroll
-            for (int k = 0; k < KT; ++k) {
-                const int task = k * kDnThreads + tid;
-                const int r = task % HR, rest = task / HR, pc = rest % (kBfCols / 8), h2 = rest / (kBfCols / 8);
-                const int gy = y0 - pad + r, gx = x0 - 8 + 8 * pc;
-                in[k] = task < tasks && gy >= 0 && gy < H && gx >= 0 && gx < W;
-                const size_t o = in[k] ? (size_t)gy * W + gx : 0;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int ch = 8 * h2 + e;
-                    const float *src = xn + (ch < p.Ca ? (size_t)ch * plane_px : 0) + o;
-                    v[k][e][0] = *reinterpret_cast<const u32x4 *>(src);
-                    v[k][e][1] = *reinterpret_cast<const u32x4 *>(src + 4);
-                }
+            for (int e = 0; e < 8; ++e) {
+                const int ch = 8 * h2 + e;
+                const float *src = xn + (ch < p.Ca ? (size_t)ch * plane_px : 0) + o;
+                v[e][0] = *reinterpret_cast<const u32x4 *>(src);
+                v[e][1] = *reinterpret_cast<const u32x4 *>(src + 4);
             }
             copy_last_store();
 #pragma unroll
-            for (int k = 0; k < KT; ++k) {
-                const int task = k * kDnThreads + tid;
-                const int r = task % HR, rest = task / HR, pc = rest % (kBfCols / 8), h2 = rest / (kBfCols / 8);
-                u32x4 *dst = s_cells + h2 * HP + r * kBfPitch + 8 * pc;
+            for (int e = 0; e < 8; ++e)
 #pragma unroll
-                for (int d = 0; d < 8; ++d) {
-                    u32x4 cell[3];  // pixel d of the piece, one cell per term
+                for (int h = 0; h < 2; ++h)
+                    if (!in || 8 * h2 + e >= p.Ca) v[e][h] = u32x4{0u, 0u, 0u, 0u};
+            tile_exponent([&](auto look) {
 #pragma unroll
-                    for (int w = 0; w < 4; ++w) {
-                        uint16_t ta[3], tb[3];
-                        const bool a_in = in[k] && 8 * h2 + 2 * w < p.Ca, b_in = in[k] && 8 * h2 + 2 * w + 1 < p.Ca;
-                        dn_split3(a_in ? __uint_as_float(v[k][2 * w][d >> 2][d & 3]) : 0.f, ta);
-                        dn_split3(b_in ? __uint_as_float(v[k][2 * w + 1][d >> 2][d & 3]) : 0.f, tb);
+                for (int e = 0; e < 8; ++e)
 #pragma unroll
-                        for (int t = 0; t < 3; ++t) cell[t][w] = (uint32_t)ta[t] | ((uint32_t)tb[t] << 16);
-                    }
-                    if (task < tasks) {
+                    for (int d = 0; d < 8; ++d) look(__uint_as_float(v[e][d >> 2][d & 3]));
+            });
+            const float f = dn_power(xexp);
+            u32x4 *dst = s_cells + h2 * HP + r * kBfPitch + 8 * pc;
 #pragma unroll
-                        for (int t = 0; t < 3; ++t) dst[t * TILE + d] = cell[t];
-                    }
+            for (int d = 0; d < 8; ++d) {
+                u32x4 cell[NX];  // pixel d of the piece, one cell per term
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    uint32_t t[NX];
+                    dn_split_f16(__uint_as_float(v[2 * w][d >> 2][d & 3]) * f, __uint_as_float(v[2 * w + 1][d >> 2][d & 3]) * f, t);
+#pragma unroll
+                    for (int q = 0; q < NX; ++q) cell[q][w] = t[q];
+                }
+                if (tid < tasks) {
+#pragma unroll
+                    for (int q = 0; q < NX; ++q) dst[q * TILE + d] = cell[q];
                 }
             }
         }
@@ -687,30 +747,55 @@ __global__ __launch_bounds__(kDnThreads, 2) void dense_bf16_kernel(const DensePa
             }
         }
     } else {
-        // any width and alignment: element by element
+        // any width and alignment: element by element (fp32 storage: all of a thread's, in pairs of channels, before the first
+        // is taken apart)
         copy_last_store();
-        constexpr int total = 16 * HR * kBfCols;
-        for (int i0 = 0; i0 < total; i0 += 8 * kDnThreads) {
-            float v[8];
+        constexpr int total = (kF32 ? 8 : 16) * HR * kBfCols, E = kF32 ? 2 : 1, U = kF32 ? total / kDnThreads : 8;
+        static_assert(!kF32 || total % kDnThreads == 0, "whole rounds");
+        for (int i0 = 0; i0 < total; i0 += U * kDnThreads) {
+            float v[U][E];
+            int t0 = i0 + tid;
+            asm volatile("" : "+v"(t0));  // (nothing of this is to be computed ahead and kept)
+            auto where = [&](int u, int &ci, int &r, int &c) {
+                const int idx = t0 + u * kDnThreads;
+                ci = idx / (HR * kBfCols);
+                const int r2 = idx - ci * (HR * kBfCols);
+                r = r2 / kBfCols, c = r2 - r * kBfCols, ci *= E;
+                return idx < total;
+            };
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int idx = i0 + u * kDnThreads + tid;
-                const int ci = idx / (HR * kBfCols), r2 = idx - ci * (HR * kBfCols), r = r2 / kBfCols, c = r2 - r * kBfCols;
+            for (int u = 0; u < U; ++u) {
+                int ci, r, c;
+                const bool some = where(u, ci, r, c);
                 const int gy = y0 - pad + r, gx = x0 - 8 + c;
-                const bool ok = idx < total && ci < p.Ca && gy >= 0 && gy < H && gx >= 0 && gx < W;
-                const float raw = dn_load(xn + (ok ? (size_t)ci * plane_px + (size_t)gy * W + gx : 0));
-                v[u] = ok ? raw : 0.f;
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    const bool ok = some && ci + e < p.Ca && gy >= 0 && gy < H && gx >= 0 && gx < W;
+                    const float raw = dn_load(xn + (ok ? (size_t)(ci + e) * plane_px + (size_t)gy * W + gx : 0));
+                    v[u][e] = ok ? raw : 0.f;
+                }
             }
+            if constexpr (kF32) {
+                tile_exponent([&](auto look) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int idx = i0 + u * kDnThreads + tid;
-                const int ci = idx / (HR * kBfCols), r2 = idx - ci * (HR * kBfCols), r = r2 / kBfCols, c = r2 - r * kBfCols;
-                uint16_t t3[3];
-                dn_split3(v[u], t3);  // (bf16 storage: the value is its own first term)
-                if (idx < total) {
+                    for (int u = 0; u < U; ++u)
 #pragma unroll
-                    for (int t = 0; t < NX; ++t)
-                        *reinterpret_cast<uint16_t *>(s_bytes + (size_t)(t * TILE + (ci >> 3) * HP + r * kBfPitch + c) * 16 + (ci & 7) * 2) = t3[t];
+                        for (int e = 0; e < E; ++e) look(v[u][e]);
+                });
+            }
+            const float f = dn_power(xexp);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                int ci, r, c;
+                const bool some = where(u, ci, r, c);
+                char *at = s_bytes + (size_t)((ci >> 3) * HP + r * kBfPitch + c) * 16 + (ci & 7) * 2;
+                if constexpr (kF32) {
+                    uint32_t t[NX];
+                    dn_split_f16(v[u][0] * f, v[u][E - 1] * f, t);
+#pragma unroll
+                    for (int q = 0; q < NX; ++q) *reinterpret_cast<uint32_t *>(at + (size_t)q * TILE * 16) = t[q];
+                } else if (some) {
+                    *reinterpret_cast<uint16_t *>(at) = (uint16_t)(__float_as_uint(v[u][0]) >> 16);   // (the stored value)
                 }
             }
         }
@@ -722,6 +807,15 @@ __global__ __launch_bounds__(kDnThreads, 2) void dense_bf16_kernel(const DensePa
     unsigned dk_bits = 0;
 
     // ---- the contraction ----
+    int wexp = 0;   // of output channel l16
+    if constexpr (kF32) {
+        unsigned m = wmax[0];
+#pragma unroll
+        for (int k = 1; k < kMine; ++k) m = max(m, wmax[k]);
+        m = max(m, (unsigned)__shfl_xor((int)m, 16));
+        wexp = dn_exponent(max(m, (unsigned)__shfl_xor((int)m, 32)));
+    }
+    const float wscale = dn_power(wexp);
     f32x4 part[NA];
 #pragma unroll
     for (int nt = 0; nt < NA; ++nt) part[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -749,14 +843,32 @@ __global__ __launch_bounds__(kDnThreads, 2) void dense_bf16_kernel(const DensePa
             }
         };
         // the products of a value's and a weight's terms that are accumulated, small ones first:
-        // bf16 storage (value, lo) and (value, hi); fp32 storage the six products of terms whose
-        // orders add up to at most two - the three left out lie below 2^-24 of the product
-        constexpr int NP = kF32 ? 6 : 2;
-        constexpr int kPx[6] = {2, 0, 1, 1, 0, 0}, kPw[6] = {0, 2, 1, 0, 1, 0};
-        auto px = [&](int q) { return kF32 ? kPx[q] : 0; };
-        auto pw = [&](int q) { return kF32 ? kPw[q] : 1 - q; };
+        // bf16 storage (value, lo) and (value, hi); fp32 storage the value's three terms with the weight's first (weights
+        // of eleven bits give exact products) and its first with the weight's second: what is left out lies below 2^-22 of the product
+        constexpr int NP = kF32 ? 4 : 2;
+        auto px = [&](int q) { return q == 0 ? 0 : NP - 1 - q; };
+        auto pw = [&](int q) { return q == 0 ? 1 : 0; };
         auto mma = [&](const u32x4 &a, const u32x4 &b, f32x4 &c) {
-            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+            if constexpr (kF32)
+                c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+            else
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+        };
+        // fp32 storage: the table's weights as two fp16 terms
+        auto take = [&](u32x4 (&a)[MB][NW]) {
+            if constexpr (kF32) {
+#pragma unroll
+                for (int m = 0; m < MB; ++m) {
+                    const u32x4 w0 = a[m][0], w1 = a[m][1];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        uint32_t t[2];
+                        const u32x4 &w = k < 2 ? w0 : w1;
+                        dn_split_f16(__uint_as_float(w[2 * (k & 1)]) * wscale, __uint_as_float(w[2 * (k & 1) + 1]) * wscale, t);
+                        a[m][0][k] = t[0], a[m][1][k] = t[1];
+                    }
+                }
+            }
         };
         // a walk's piece of the pass-through copy: asked for at its start, behind the next
         // pair's A operands (which are waited for first), stored at the end of the NEXT walk -
@@ -775,10 +887,11 @@ __global__ __launch_bounds__(kDnThreads, 2) void dense_bf16_kernel(const DensePa
                 if (jp >= 0 && o + 16 <= walk_len) __builtin_nontemporal_store(cv[g], reinterpret_cast<u32x4 *>(walk_dst + o));
             }
         };
-        auto walk = [&](int jp, const u32x4 (&a)[MB][NW], u32x4 (&a_next)[MB][NW], u32x4 (&cv)[kWalkGrains],
+        auto walk = [&](int jp, u32x4 (&a)[MB][NW], u32x4 (&a_next)[MB][NW], u32x4 (&cv)[kWalkGrains],
                         const u32x4 (&cv_before)[kWalkGrains]) {
             int i0, cnt;
             rows_of(jp, i0, cnt);
+            take(a);
             fetch_a(jp + 1 < NJP ? jp + 1 : jp, a_next);
             copy_ask(jp, cv);
             const bool full = cnt == MB;  // wavefront-uniform
@@ -860,19 +973,38 @@ __global__ __launch_bounds__(kDnThreads, 2) void dense_bf16_kernel(const DensePa
             for (int di = 0; di < 3; ++di)
 #pragma unroll
                 for (int dj = 0; dj < 3; ++dj) {
-                    float xv[4] = {0.f, 0.f, 0.f, 0.f};  // the stored value: the sum of its terms, smallest first (exact)
+                    float xv[4];  // the value: fp32 storage the sum of its terms
+                    const u32x2 v = *reinterpret_cast<const u32x2 *>(src + (di * kBfPitch + dj) * 16);
+                    if constexpr (kF32) {
+                        const u32x2 low = *reinterpret_cast<const u32x2 *>(src + (TILE + di * kBfPitch + dj) * 16);
+                        const u32x2 last = *reinterpret_cast<const u32x2 *>(src + (2 * TILE + di * kBfPitch + dj) * 16);
 #pragma unroll
-                    for (int t = NX - 1; t >= 0; --t) {
-                        const u32x2 v = *reinterpret_cast<const u32x2 *>(src + (t * TILE + di * kBfPitch + dj) * 16);
-                        xv[0] += __uint_as_float(v[0] << 16);
-                        xv[1] += __uint_as_float(v[0] & 0xffff0000u);
-                        xv[2] += __uint_as_float(v[1] << 16);
-                        xv[3] += __uint_as_float(v[1] & 0xffff0000u);
+                        for (int u = 0; u < 2; ++u) {
+                            const uint32_t hb = v[u], lb = low[u], tb = last[u];
+                            const f16x2 h = __builtin_bit_cast(f16x2, hb), l = __builtin_bit_cast(f16x2, lb), e = __builtin_bit_cast(f16x2, tb);
+                            xv[2 * u] = (float)h.x + ((float)l.x + (float)e.x), xv[2 * u + 1] = (float)h.y + ((float)l.y + (float)e.y);
+                        }
+                    } else {
+                        xv[0] = __uint_as_float(v[0] << 16);
+                        xv[1] = __uint_as_float(v[0] & 0xffff0000u);
+                        xv[2] = __uint_as_float(v[1] << 16);
+                        xv[3] = __uint_as_float(v[1] & 0xffff0000u);
                     }
 #pragma unroll
                     for (int r = 0; r < 4; ++r) acc[m][r] = fmaf(d[r][di * 3 + dj], xv[r], acc[m][r]);
                 }
         }
+    }
+
+    // fp32 storage: the powers of two that bring the sums of this lane's channels 4 kq + r back
+    int back[4] = {0, 0, 0, 0};
+    if constexpr (kF32) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) back[r] = __shfl(wexp, 4 * kq + r);
+#pragma unroll
+        for (int m = 0; m < NT; ++m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[m][r] = __builtin_amdgcn_ldexpf(acc[m][r], -xexp);
     }
 
     // ---- the four wavefronts' partial results: run nt goes to wavefront nt / NT ----
@@ -892,6 +1024,10 @@ __global__ __launch_bounds__(kDnThreads, 2) void dense_bf16_kernel(const DensePa
                     f32x4 sum = s_red[(u * 4 + 0) * 64 + lane];
 #pragma unroll
                     for (int w = 1; w < 4; ++w) sum += s_red[(u * 4 + w) * 64 + lane];
+                    if constexpr (kF32) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) sum[r] = __builtin_amdgcn_ldexpf(sum[r], -xexp - back[r]);
+                    }
 #pragma unroll
                     for (int m = 0; m < NT; ++m)  // (a constant index: the accumulators stay in registers)
                         if (m == nt % NT) acc[m] += sum;
@@ -983,12 +1119,12 @@ __attribute__((visibility("hidden"))) hipError_t launch_dense_prep(const DensePa
     p.Ks = dense_effective_ks(Ks);
     if (dense_on_bf16_mfma(p.Ca, Ks, bf16)) {
         const size_t tiles = p.n_gen > 0 ? (size_t)p.N * p.Ca * p.ptiles : 0;
-        const unsigned table = (unsigned)((dense_table_entries(p.Ks) + kDnThreads - 1) / kDnThreads);
+        const unsigned table = (unsigned)dense_table_blocks(p.Ks);
         const unsigned n_pool = (unsigned)((tiles + kPoolBatch - 1) / kPoolBatch);
         if (bf16)
-            hipLaunchKernelGGL(dense_prep_kernel<bf16_t>, dim3(n_pool + table), dim3(kDnThreads), 0, s, p, lk, Ks, 2, n_pool);
+            hipLaunchKernelGGL(dense_prep_kernel<bf16_t>, dim3(n_pool + table), dim3(kDnThreads), 0, s, p, lk, Ks, n_pool);
         else
-            hipLaunchKernelGGL(dense_prep_kernel<float>, dim3(n_pool + table), dim3(kDnThreads), 0, s, p, lk, Ks, 3, n_pool);
+            hipLaunchKernelGGL(dense_prep_kernel<float>, dim3(n_pool + table), dim3(kDnThreads), 0, s, p, lk, Ks, n_pool);
         return hipGetLastError();
     }
     const size_t total = dense_weight_floats(p.Ca, Ks);
@@ -1014,7 +1150,7 @@ __attribute__((visibility("hidden"))) hipError_t launch_dense(const DenseParams 
     p.tiles_x = (p.W + kDnTw - 1) / kDnTw;
     const size_t blocks8 = (size_t)p.tiles_x * ((p.H + 7) / 8) * p.N;
     const bool matrix_bf16 = dense_on_bf16_mfma(p.Ca, p.Ks, bf16);
-    // (fp32 storage on the bf16 instructions keeps three tiles in LDS: 4-row tiles, two blocks per compute unit)
+    // (fp32 storage on the fp16 instructions keeps three tiles in LDS: 4-row tiles, two blocks per compute unit)
     const int th = (blocks8 >= 2 * (size_t)cus && !(matrix_bf16 && !bf16)) ? 8 : 4;
     p.tiles_y = (p.H + th - 1) / th;
     const size_t per_img = (size_t)p.tiles_x * p.tiles_y;

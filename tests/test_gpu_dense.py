@@ -173,6 +173,36 @@ def test_dense_fp32_on_bf16_terms_every_kernel_size(oracle, Ks, W):
     assert rel <= 2e-6, rel  # (six of the nine products of terms: fp32 accuracy, far inside the 1e-5 bar)
 
 
+@pytest.mark.parametrize("N,H,W,Ca,Ks", [(1, 9, 40, 16, 13), (2, 5, 45, 13, 7), (1, 33, 32, 16, 3), (1, 4, 33, 5, 1)])
+def test_dense_fp32_at_any_scale(oracle, N, H, W, Ca, Ks):
+    # values and output channels of every size, a channel without weights, a NaN.  In the 2-norm of an output
+    # channel: sums of K fp32 products within sqrt(2 K) 2^-24 of terms whose squares add up, factors within 2^-23 each.
+    base = wk.make_random(960 + Ks, N, Ca + 2, H, W, Ca, Ks, dtype=F32)
+    lk0 = dense_kernel(961, Ca, Ks)
+    dk = np.random.default_rng(962).standard_normal((N, Ca, 3, 3)).astype(np.float32)
+    rows = (2.0 ** np.random.default_rng(963).integers(-40, 40, Ca))
+    rows[1] = 0.0
+    for what, fx, fw in (("ordinary", 1.0, np.ones(Ca)), ("small", 2.0 ** -80, np.full(Ca, 2.0 ** -30)), ("large", 2.0 ** 80, np.full(Ca, 2.0 ** -60)),
+                         ("small x large", 2.0 ** -110, np.full(Ca, 2.0 ** 100)), ("rows", 1.0, rows), ("nan", 1.0, np.ones(Ca))):
+        print(f"[case] {what} Ca={Ca} Ks={Ks}", flush=True)
+        if what == "nan" and Ks == 1:
+            continue   # (embedded in a 3 x 3 kernel, whose zeros touch the NaN too)
+        wl = wk.make_random(960 + Ks, N, Ca + 2, H, W, Ca, Ks, dtype=F32)
+        wl.x = (base.x * np.float32(fx)).astype(np.float32)
+        if what == "nan":
+            wl.x[0, Ca - 1, H // 2, W // 2] = np.nan
+        lk = (lk0 * fw[:, None, None, None]).astype(np.float32)
+        d = (dk * fw[None, :, None, None]).astype(np.float32)
+        ref = oracle.convattn_dense_forward(wl.x, Ca, lk, F32, dk_in=d, want_out=False)[0]
+        got = run_dense(wl, lk, use_gen=False, dk_in=d)[:, :Ca].astype(np.float64)
+        assert np.array_equal(np.isnan(ref), np.isnan(got)), what
+        bound = (np.sqrt(2 * Ca * Ks * Ks) + 6) * 2.0 ** -24
+        for c in range(Ca):
+            ok = ~np.isnan(ref[:, c])
+            rms = np.sqrt((ref[:, c][ok] ** 2).mean())
+            assert np.sqrt(((got - ref)[:, c][ok] ** 2).mean()) <= bound * rms, (what, c)
+
+
 @pytest.mark.parametrize("idx", [0, 1, 2, 3])
 def test_dense_benchmark_shapes_full_size(oracle, idx):
     wl = wk.make_config(idx)
