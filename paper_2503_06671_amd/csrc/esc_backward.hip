@@ -9,10 +9,8 @@
 //   dx[n,c]     = go[n,c] (*) flip(LK[c] + ZP(DK[n,c])) + dg[n,c] / (H W)     (c < C_a; dx = go elsewhere)
 //
 // The input gradient's convolution is the forward kernel itself, run on grad_out with the
-// flipped kernels (esc_api.hip); this file holds what is new: the correlation S - windows up
-// to 15 x 15 as Toeplitz products on the matrix cores (corr_mfma_kernel), larger ones with
-// the forward's vector tap loop turned round (corr_kernel: 2 Ks^2 flops per pixel into Ks^2
-// sums) - and the small estimator kernels; the GAP term of dx is a constant per plane that the
+// flipped kernels (esc_api.hip); this file holds what is new: the correlation S,
+// as Toeplitz products on the matrix cores (corr_mfma_kernel), and the small estimator kernels; the GAP term of dx is a constant per plane that the
 // input gradient's launch adds at its stores.  Every sum has a fixed order
 // (per-tile partial sums in the workspace, then one thread per result), so results do not
 // depend on scheduling.
@@ -22,6 +20,7 @@
 #include <type_traits>
 
 #include "esc_backward.hpp"
+#include "esc_estimator.hpp"
 
 namespace esc {
 namespace {
@@ -33,14 +32,6 @@ struct bf16b {
 };
 __device__ __forceinline__ float bw_load(const float *p) { return *p; }
 __device__ __forceinline__ float bw_load(const bf16b *p) { return __uint_as_float((uint32_t)p->bits << 16); }
-__device__ __forceinline__ uint16_t bw_f32_to_bf16(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x0040u);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
-
 // running sum along each row of 16 lanes (data-parallel moves inside the vector unit):
 // lane 15 of a row ends with the row's total, in a fixed order
 __device__ __forceinline__ float row16_sum(float v)
@@ -59,174 +50,47 @@ __device__ __forceinline__ float row16_sum(float v)
 extern __shared__ __align__(16) float bw_lds[];
 
 // ---------------------------------------------------------------------------
-// S per tile.  A block takes a 64 x 32 pixel tile of one (image, channel) plane: grad_out's
-// tile and x's zero-extended halo tile go to LDS.  Thread (tx, tg) = (t & 15, t >> 4) owns the
-// 4-pixel column strip tx and two rows (2*ip, 2*ip + 1) of the correlation window; with at
-// most eight row pairs the sixteen groups also split the tile's rows in two halves.  Walking
-// down its rows it reads one grad_out segment and one new x segment per row (the x segment
-// of window row 2*ip + 1 at tile row y is that of window row 2*ip at y + 1) and applies
-// 2 * KC * 4 multiply-adds to its 2 * KC sums - the forward tap loop's ratio of arithmetic
-// to LDS traffic.  The strip sums are added along each row of 16 lanes, then over the row
-// halves, and written as the tile's partial sums; the last entry is the tile's sum of x
-// (for the GAP).
-// ---------------------------------------------------------------------------
-template <typename T, int KC>
-__global__ __launch_bounds__(kBwThreads) void corr_kernel(const BackwardParams p)
-{
-    constexpr int P = (KC - 1) / 2;
-    constexpr int NP = (KC + 1) / 2;             // row pairs of the window
-    constexpr int YS = NP <= 8 ? 2 : 1;           // halves the tile's rows are split in
-    constexpr int ROWS = kCorrTileH / YS;
-    constexpr int NXV = (KC + 3 + 3) & ~3;        // x values a thread reads per row
-    constexpr int HC = kCorrTileW + KC - 1;
-    constexpr int PITCH = ((60 + NXV > HC ? 60 + NXV : HC) + 3) & ~3;
-    constexpr int HR = kCorrTileH + KC - 1 + 1;   // one spare row of zeros (an odd window's last pair reads it)
-    float *xs = bw_lds;                            // [HR][PITCH]
-    float *gs = xs + HR * PITCH;                   // [32][64]
-    float *red = gs + kCorrTileH * kCorrTileW;     // [16][2*KC + 1]
-
-    const int tid = (int)threadIdx.x;
-    const int H = p.H, W = p.W;
-    const int tiles_x = (W + kCorrTileW - 1) / kCorrTileW;
-    const int tiles = corr_tiles(H, W);
-    const unsigned nc = blockIdx.x / (unsigned)tiles, tile = blockIdx.x - nc * (unsigned)tiles;
-    const unsigned n = nc / (unsigned)p.Ca, c = nc - n * (unsigned)p.Ca;
-    const int ty0 = (int)(tile / (unsigned)tiles_x) * kCorrTileH, tx0 = (int)(tile % (unsigned)tiles_x) * kCorrTileW;
-    const size_t plane = ((size_t)n * p.C + c) * (size_t)H * W;
-    const T *xp = (const T *)p.x + plane, *gp = (const T *)p.go + plane;
-
-    // ---- tiles to LDS (all of a batch's loads before their uses) ----
-    for (int i0 = 0; i0 < HR * PITCH; i0 += 8 * kBwThreads) {
-        float v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int idx = i0 + u * kBwThreads + tid;
-            const int r = idx / PITCH, cc = idx - r * PITCH;
-            const int gy = ty0 - P + r, gx = tx0 - P + cc;
-            const bool in = idx < HR * PITCH && gy >= 0 && gy < H && gx >= 0 && gx < W;
-            v[u] = bw_load(xp + (in ? (size_t)gy * W + gx : 0));
-            v[u] = in ? v[u] : 0.f;
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int idx = i0 + u * kBwThreads + tid;
-            if (idx < HR * PITCH) xs[idx] = v[u];
-        }
-    }
-    {
-        float v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int idx = u * kBwThreads + tid;
-            const int r = idx >> 6, cc = idx & 63;
-            const int gy = ty0 + r, gx = tx0 + cc;
-            const bool in = gy < H && gx < W;
-            v[u] = bw_load(gp + (in ? (size_t)gy * W + gx : 0));
-            v[u] = in ? v[u] : 0.f;
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) gs[u * kBwThreads + tid] = v[u];
-    }
-    __syncthreads();
-
-    const int tx = tid & 15, tg = tid >> 4;
-    const int ip = YS == 2 ? (tg & 7) : tg, yh = YS == 2 ? (tg >> 3) : 0;
-    const int i_first = 2 * ip;
-    float acc0[KC], acc1[KC];
-#pragma unroll
-    for (int j = 0; j < KC; ++j) acc0[j] = acc1[j] = 0.f;
-    float sx = 0.f;
-    if (i_first < KC) {  // (uniform per row of 16 lanes)
-        const int ya = yh * ROWS;
-        float xa[NXV], xb[NXV];
-        {
-            const float4 *src = reinterpret_cast<const float4 *>(xs + (ya + i_first) * PITCH + 4 * tx);
-#pragma unroll
-            for (int k = 0; k < NXV / 4; ++k) {
-                const float4 f = src[k];
-                xa[4 * k] = f.x, xa[4 * k + 1] = f.y, xa[4 * k + 2] = f.z, xa[4 * k + 3] = f.w;
-            }
-        }
-        for (int y = ya; y < ya + ROWS; ++y) {
-            const float4 g4 = *reinterpret_cast<const float4 *>(gs + y * kCorrTileW + 4 * tx);
-            const float4 *src = reinterpret_cast<const float4 *>(xs + (y + i_first + 1) * PITCH + 4 * tx);
-#pragma unroll
-            for (int k = 0; k < NXV / 4; ++k) {
-                const float4 f = src[k];
-                xb[4 * k] = f.x, xb[4 * k + 1] = f.y, xb[4 * k + 2] = f.z, xb[4 * k + 3] = f.w;
-            }
-            const float g[4] = {g4.x, g4.y, g4.z, g4.w};
-#pragma unroll
-            for (int j = 0; j < KC; ++j)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    acc0[j] = fmaf(g[q], xa[q + j], acc0[j]);
-                    acc1[j] = fmaf(g[q], xb[q + j], acc1[j]);
-                }
-            if (ip == 0) {  // the tile's own pixels, for the GAP: the window's centre row of this tile row
-                const float *ctr = xs + (y + P) * PITCH + 4 * tx + P;
-                sx += (ctr[0] + ctr[1]) + (ctr[2] + ctr[3]);
-            }
-#pragma unroll
-            for (int k = 0; k < NXV; ++k) xa[k] = xb[k];
-        }
-    }
-    // ---- strips -> rows of 16 lanes -> row halves -> the tile's partial sums ----
-#pragma unroll
-    for (int j = 0; j < KC; ++j) {
-        const float a = row16_sum(acc0[j]), b = row16_sum(acc1[j]);
-        if (tx == 15) {
-            red[tg * (2 * KC + 1) + j] = a;
-            red[tg * (2 * KC + 1) + KC + j] = b;
-        }
-    }
-    {
-        const float a = row16_sum(sx);
-        if (tx == 15) red[tg * (2 * KC + 1) + 2 * KC] = a;
-    }
-    __syncthreads();
-    float *dst = p.partial + ((size_t)nc * tiles + tile) * (KC * KC + 1);
-    for (int o = tid; o < KC * KC + 1; o += kBwThreads) {
-        float s;
-        if (o == KC * KC) {
-            s = red[2 * KC];
-            if (YS == 2) s += red[8 * (2 * KC + 1) + 2 * KC];
-        } else {
-            const int i = o / KC, j = o - i * KC;
-            const int g0 = i >> 1, off = (i & 1) * KC + j;
-            s = red[g0 * (2 * KC + 1) + off];
-            if (YS == 2) s += red[(g0 + 8) * (2 * KC + 1) + off];
-        }
-        dst[o] = s;
-    }
-}
-
-// ---------------------------------------------------------------------------
-// S per tile for windows up to 15 x 15, on the matrix cores.  For one row y of grad_out's
-// tile the sums over x are a product of two 16 x K matrices:
+// S per tile.  A block takes a 64 x 32 pixel tile of one (image, channel) plane; the window's sums over
+// it run on the matrix cores.  For one row y of grad_out's tile the sums over x are a product of two matrices:
 //   S[i][j] += sum_c  X_y[i][c] * G_y[c][j],   X_y[i][c] = xz[y + i][c]  (rows of x's halo tile),
 //                                              G_y[c][j] = go[y][c - j]  (a Toeplitz matrix of the row)
-// with K = the halo tile's columns, 32 per v_mfma_f32_16x16x32_bf16: 3 instructions per tile
-// row, 96 per tile, against 5400 vector multiply-adds per thread in corr_kernel.  With bf16
-// storage the stored values are the operands (products exact, fp32 accumulation).  fp32 values
-// are split into three bf16 terms each (8 + 8 + 8 mantissa bits, by truncation: exact but for
-// values within 2^24 of the smallest normal number, whose third term loses denormal bits), kept
-// as three tiles, and all nine products of terms are accumulated - every product is still
-// exact, and nine times 96 instructions are still a fifth of the vector loop's time.
+// with K = the halo tile's columns, 32 per v_mfma_f32_16x16x32: one 16 x 16 block of sums up to 15 x 15, 3
+// instructions per tile row; two by two blocks beyond, 12.  With bf16 storage the stored values are the operands
+// (products exact, fp32 accumulation).  fp32 values are taken apart into two fp16 terms behind a power of two that brings the
+// tile's largest to 2^14 ... 2^15 (within a unit of fp32's last place), kept as two tiles, and three of the four
+// products of terms are accumulated (the fourth is below 2^-22 of a product).
 // A operand: lane (i, kg) reads 16 bytes of halo row y + i - the halo tile is laid out from the
-// aligned column x0 - 8, so every read is aligned.  B operand: lane (j, kg) wants eight
+// aligned column x0 - 8 (x0 - 16), so every read is aligned.  B operand: lane (j, kg) wants eight
 // consecutive values of the row starting j elements to the left - a start that is odd for
 // every other lane.  grad_out's rows are therefore kept twice, zero-extended: as they are and
 // moved by one element; a lane reads four whole words from the copy of its parity.  The four
 // wavefronts take eight rows each (neighbouring rows share their A operands, see there) and add
-// their results through LDS; the sum of x (for the
-// GAP) comes from the halo tile's loads.  Same partial sums, same layout as corr_kernel.
+// their results through LDS; the sum of x (for the GAP) comes from the halo tile's loads.  The partial sums of a
+// tile end with it.  Bound by LDS reads.
+// 64 x 64 x 64, the whole backward: 17 x 17 bf16 79 us -> 43, fp32 98 -> 80 (31 x 31 196 -> 71 and 223 -> 101), by a vector kernel
+// with the window's rows in registers until then; 13 x 13 fp32 71 -> 61 and 16 x 64 x 64 28.6 -> 26.8, with three bf16 terms and nine
+// products until then, error against float64 5.0e-7 -> 1.7e-7 (products with a low term summed apart; together 5.0e-7).  Widths off the pieces, all loads of a thread
+// at once instead of one after the other: 8 x 63 x 63 fp32 29 -> 25 us, 64 x 63 x 63 bf16 47 -> 39.
 // ---------------------------------------------------------------------------
 constexpr int kCmXP = 104;  // halo tile: elements per row (96 columns are read; 13 x 16 bytes: rows fall on different banks)
-constexpr int kCmXR = 48;   // halo tile rows (rows up to 31 + 15 are read; those beyond the window feed discarded results)
-constexpr int kCmGP = 112;  // elements per zero-extended row of grad_out
-constexpr size_t kCmG0 = (size_t)kCmXR * kCmXP * 2, kCmG1 = kCmG0 + (size_t)kCorrTileH * kCmGP * 2 + 64;
-constexpr size_t kCmLds = kCmG1 + (size_t)kCorrTileH * kCmGP * 2;  // per term
+// the tiles of a window: one 16 x 16 block of sums up to 15 x 15, two by two beyond
+template <int KC, bool F32>
+struct CorrGeom {
+    static constexpr int NB = KC <= 15 ? 1 : 2;
+    static constexpr int BASE = 8 * NB;                // the halo tile starts this many columns left of the tile
+    static constexpr int PIECES = 8 + 2 * NB;          // pieces of eight columns of a halo row
+    // neighbouring rows of grad_out that share their A operands: a block's sixteen rows serve 16 NB - KC + 1, at most four;
+    // two where four rows' sums would leave a block alone on its compute unit
+    static constexpr int SH = NB == 1 && 16 - KC + 1 >= 4 ? 4 : 2;
+    static constexpr int BLOCKS = F32 ? 4 - NB : NB == 1 ? 6 : 3;   // resident blocks per compute unit the registers are cut for
+    static constexpr int XR = NB == 1 ? 48 : 64;       // halo tile rows (those read beyond the window feed discarded results)
+    static constexpr int GP = NB == 1 ? 112 : 128;     // elements per zero-extended row of grad_out
+    static constexpr size_t G0 = (size_t)XR * kCmXP * 2, G1 = G0 + (size_t)kCorrTileH * GP * 2 + 64;
+    static constexpr size_t TERM = G1 + (size_t)kCorrTileH * GP * 2;  // bytes per term
+    static constexpr size_t RED = NB == 1 ? (size_t)4 * SH * 256 * 4 + 64 : (size_t)4 * 1024 * 4 + 64;
+    static constexpr size_t tiles(int terms) { return terms * TERM > RED ? terms * TERM : RED; }
+    static constexpr size_t lds() { return tiles(F32 ? 2 : 1) + 8 * sizeof(unsigned); }
+};
 
 // eight consecutive bf16 values to row[q ...]: whole words where the parity of q allows
 template <bool EVEN>
@@ -244,23 +108,26 @@ __device__ __forceinline__ void cm_put8(uint16_t *row, int q, const uint16_t (&v
 }
 
 template <typename T, int KC>
-__global__ __launch_bounds__(kBwThreads) void corr_mfma_kernel(const BackwardParams p)
+__global__ __launch_bounds__(kBwThreads, (CorrGeom<KC, std::is_same<T, float>::value>::BLOCKS)) void corr_mfma_kernel(const BackwardParams p)
 {
     typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+    typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-    static_assert(KC % 2 == 1 && KC >= 3 && KC <= 15, "one 16 x 16 block of sums");
+    static_assert(KC % 2 == 1 && KC >= 3 && KC <= 31, "at most two by two blocks of sums");
     constexpr bool kF32 = std::is_same<T, float>::value;
-    constexpr int NT = kF32 ? 3 : 1;          // bf16 terms per value
-    constexpr int P = (KC - 1) / 2;
+    using CG = CorrGeom<KC, kF32>;
+    constexpr int NT = kF32 ? 2 : 1;          // terms per value (fp32 storage: fp16 terms)
+    constexpr int NB = CG::NB, P = (KC - 1) / 2, PC = CG::PIECES;
     constexpr int HRU = kCorrTileH + KC - 1;  // halo rows the window reaches
-    constexpr int GOFF = P + 8;               // element of a zero-extended row that holds the tile's column 0
+    constexpr int GOFF = P + CG::BASE;        // element of a zero-extended row that holds the tile's column 0
     char *lds = reinterpret_cast<char *>(bw_lds);
-    // term t: halo tile [kCmXR][kCmXP] (column c = image column x0 - 8 + c), then grad_out's rows
-    // [32][kCmGP] (element q = column q - GOFF) and the same moved by one (element q = column q + 1 - GOFF)
-    auto xs = [&](int t) { return reinterpret_cast<uint16_t *>(lds + t * kCmLds); };
-    auto g0 = [&](int t) { return reinterpret_cast<uint16_t *>(lds + t * kCmLds + kCmG0); };
-    auto g1 = [&](int t) { return reinterpret_cast<uint16_t *>(lds + t * kCmLds + kCmG1); };
+    // term t: halo tile [XR][kCmXP] (column c = image column x0 - BASE + c), then grad_out's rows
+    // [32][GP] (element q = column q - GOFF) and the same moved by one (element q = column q + 1 - GOFF)
+    auto xs = [&](int t) { return reinterpret_cast<uint16_t *>(lds + t * CG::TERM); };
+    auto g0 = [&](int t) { return reinterpret_cast<uint16_t *>(lds + t * CG::TERM + CG::G0); };
+    auto g1 = [&](int t) { return reinterpret_cast<uint16_t *>(lds + t * CG::TERM + CG::G1); };
+    unsigned *s_max = reinterpret_cast<unsigned *>(lds + CG::tiles(NT));   // [wavefront][x, grad_out]
 
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int H = p.H, W = p.W;
@@ -272,13 +139,38 @@ __global__ __launch_bounds__(kBwThreads) void corr_mfma_kernel(const BackwardPar
     const size_t plane = ((size_t)n * p.C + c) * (size_t)H * W;
     const T *xp = (const T *)p.x + plane, *gp = (const T *)p.go + plane;
 
-    // a value as NT bf16 terms (fp32: the top eight mantissa bits, the next eight, the rest - exact)
-    auto split = [](float v, uint16_t (&t)[3]) {
-        const uint32_t hb = __float_as_uint(v) & 0xffff0000u;
-        const float r1 = v - __uint_as_float(hb);
-        const uint32_t mb = __float_as_uint(r1) & 0xffff0000u;
-        const float r2 = r1 - __uint_as_float(mb);
-        t[0] = (uint16_t)(hb >> 16), t[1] = (uint16_t)(mb >> 16), t[2] = (uint16_t)(__float_as_uint(r2) >> 16);
+    // Up to 15 x 15 in bf16 storage a value that is not finite makes what its instructions touch NaN.  Otherwise the largest
+    // magnitudes of the two tiles are looked for: finite ones give fp32 storage its powers of two, and larger windows
+    // with others among them are summed plainly.
+    constexpr bool kLook = kF32 || NB == 2;
+    unsigned mx = 0, mg = 0;
+    auto magnitude = [](float v) {
+        const unsigned b = __float_as_uint(v) & 0x7fffffffu;
+        return NB == 1 && b >= 0x7f800000u ? 0u : b;
+    };
+    auto agree = [&](bool barrier) {
+        if constexpr (kLook) {
+            mx = wave_max(mx), mg = wave_max(mg);
+            if (lane == 63) s_max[2 * wave] = mx, s_max[2 * wave + 1] = mg;
+        }
+        if (kLook || barrier) __syncthreads();
+        if constexpr (kLook) {
+            mx = max(max(s_max[0], s_max[2]), max(s_max[4], s_max[6]));
+            mg = max(max(s_max[1], s_max[3]), max(s_max[5], s_max[7]));
+        }
+    };
+    // the power of two that brings the largest to 2^14 ... 2^15, as far as fp32 reaches
+    auto exponent = [](unsigned m) { return min(14 + 127 - (int)(m >> 23), 126); };
+    auto power = [](int e) { return __uint_as_float((unsigned)(127 + e) << 23); };
+    // a value as NT terms: bf16 storage itself; fp32 the nearest fp16 and the nearest to what is left, within a unit
+    // of fp32's last place from the largest down to 2^-15 of it
+    auto split = [](float v, uint16_t (&t)[NT]) {
+        if constexpr (kF32) {
+            const _Float16 h = (_Float16)v, l = (_Float16)(v - (float)h);
+            t[0] = __builtin_bit_cast(uint16_t, h), t[NT - 1] = __builtin_bit_cast(uint16_t, l);
+        } else {
+            t[0] = (uint16_t)(__float_as_uint(v) >> 16);
+        }
     };
     // eight neighbouring values (16 or 32 bytes of memory) at e, or zeros; their sum for the GAP
     auto fetch8 = [](const T *e, bool in, u32x4 (&raw)[kF32 ? 2 : 1]) {
@@ -287,21 +179,22 @@ __global__ __launch_bounds__(kBwThreads) void corr_mfma_kernel(const BackwardPar
         if (!in)
             for (int k = 0; k < (kF32 ? 2 : 1); ++k) raw[k] = u32x4{0u, 0u, 0u, 0u};
     };
-    auto terms8 = [&](const u32x4 (&raw)[kF32 ? 2 : 1], uint16_t (&v)[NT][8], float &sum) {
+    auto value8 = [](const u32x4 (&raw)[kF32 ? 2 : 1], int e) {
+        if constexpr (kF32)
+            return __uint_as_float(raw[e >> 2][e & 3]);
+        else
+            return __uint_as_float(e & 1 ? raw[0][e >> 1] & 0xffff0000u : raw[0][e >> 1] << 16);
+    };
+    auto terms8 = [&](const u32x4 (&raw)[kF32 ? 2 : 1], float f, uint16_t (&v)[NT][8], float &sum) {
         sum = 0.f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            if (kF32) {
-                uint16_t t3[3];
-                const float f = __uint_as_float(raw[kF32 ? e >> 2 : 0][e & 3]);
-                split(f, t3);
+            const float a = value8(raw, e);
+            uint16_t t[NT];
+            split(kF32 ? a * f : a, t);
 #pragma unroll
-                for (int t = 0; t < NT; ++t) v[t][e] = t3[t];
-                sum += f;
-            } else {
-                v[0][e] = (uint16_t)(raw[0][e >> 1] >> (16 * (e & 1)));
-                sum += __uint_as_float((uint32_t)v[0][e] << 16);
-            }
+            for (int q = 0; q < NT; ++q) v[q][e] = t[q];
+            sum += a;
         }
     };
 
@@ -309,12 +202,12 @@ __global__ __launch_bounds__(kBwThreads) void corr_mfma_kernel(const BackwardPar
     if (p.corr_vec) {
         // whole pieces of eight columns, each entirely inside or outside the image; the loads
         // travel while the LDS is cleared
-        constexpr int XT = HRU * 10, XK = (XT + kBwThreads - 1) / kBwThreads;
+        constexpr int XT = HRU * PC, XK = (XT + kBwThreads - 1) / kBwThreads;
         u32x4 xv[XK][kF32 ? 2 : 1], gv[kF32 ? 2 : 1];
 #pragma unroll
         for (int k = 0; k < XK; ++k) {
-            const int t = k * kBwThreads + tid, r = t / 10, pc = t - r * 10;
-            const int gy = ty0 - P + r, gx = tx0 - 8 + 8 * pc;
+            const int t = k * kBwThreads + tid, r = t / PC, pc = t - r * PC;
+            const int gy = ty0 - P + r, gx = tx0 - CG::BASE + 8 * pc;
             const bool in = t < XT && gy >= 0 && gy < H && gx >= 0 && gx < W;
             fetch8(xp + (in ? (size_t)gy * W + gx : 0), in, xv[k]);
         }
@@ -324,60 +217,101 @@ __global__ __launch_bounds__(kBwThreads) void corr_mfma_kernel(const BackwardPar
             const bool in = gy < H && gx < W;
             fetch8(gp + (in ? (size_t)gy * W + gx : 0), in, gv);
         }
-        for (int o = tid; o < (int)(NT * kCmLds / 16); o += kBwThreads) reinterpret_cast<u32x4 *>(lds)[o] = u32x4{0u, 0u, 0u, 0u};
-        __syncthreads();
+        for (int o = tid; o < (int)(NT * CG::TERM / 16); o += kBwThreads) reinterpret_cast<u32x4 *>(lds)[o] = u32x4{0u, 0u, 0u, 0u};
+        if constexpr (kLook) {
+#pragma unroll
+            for (int k = 0; k < XK; ++k)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) mx = max(mx, magnitude(value8(xv[k], e)));
+#pragma unroll
+            for (int e = 0; e < 8; ++e) mg = max(mg, magnitude(value8(gv, e)));
+        }
+        agree(true);
+        const float fx = kF32 ? power(exponent(mx)) : 1.f, fg = kF32 ? power(exponent(mg)) : 1.f;
 #pragma unroll
         for (int k = 0; k < XK; ++k) {
-            const int t = k * kBwThreads + tid, r = t / 10, pc = t - r * 10;
+            const int t = k * kBwThreads + tid, r = t / PC, pc = t - r * PC;
             uint16_t v[NT][8];
             float sum;
-            terms8(xv[k], v, sum);
+            terms8(xv[k], fx, v, sum);
             if (t < XT) {
 #pragma unroll
                 for (int tt = 0; tt < NT; ++tt) cm_put8<true>(xs(tt) + r * kCmXP, 8 * pc, v[tt]);
                 // the tile's own pixels, for the GAP
-                if (r >= P && r < P + kCorrTileH && pc >= 1 && pc <= 8) sx += sum;
+                if (r >= P && r < P + kCorrTileH && pc >= NB && pc < NB + 8) sx += sum;
             }
         }
         {
             const int r = tid >> 3, pc = tid & 7;
             uint16_t v[NT][8];
             float sum;
-            terms8(gv, v, sum);
+            terms8(gv, fg, v, sum);
 #pragma unroll
             for (int tt = 0; tt < NT; ++tt) {
-                cm_put8<GOFF % 2 == 0>(g0(tt) + r * kCmGP, GOFF + 8 * pc, v[tt]);
-                cm_put8<GOFF % 2 != 0>(g1(tt) + r * kCmGP, GOFF + 8 * pc - 1, v[tt]);
+                cm_put8<GOFF % 2 == 0>(g0(tt) + r * CG::GP, GOFF + 8 * pc, v[tt]);
+                cm_put8<GOFF % 2 != 0>(g1(tt) + r * CG::GP, GOFF + 8 * pc - 1, v[tt]);
             }
         }
     } else {
-        for (int o = tid; o < (int)(NT * kCmLds / 16); o += kBwThreads) reinterpret_cast<u32x4 *>(lds)[o] = u32x4{0u, 0u, 0u, 0u};
-        __syncthreads();
-        for (int t = tid; t < HRU * 80; t += kBwThreads) {
-            const int r = t / 80, cc = t - r * 80;
-            const int gy = ty0 - P + r, gx = tx0 - 8 + cc;
-            if (gy >= 0 && gy < H && gx >= 0 && gx < W) {
-                const float f = bw_load(xp + (size_t)gy * W + gx);
-                uint16_t t3[3];
-                split(f, t3);
+        for (int o = tid; o < (int)(NT * CG::TERM / 16); o += kBwThreads) reinterpret_cast<u32x4 *>(lds)[o] = u32x4{0u, 0u, 0u, 0u};
+        // element by element: eight of a thread's on their way at once, or all of them where the largest is looked for first
+        constexpr int XT = HRU * 8 * PC, XK = (XT + kBwThreads - 1) / kBwThreads, GK = kCorrTileH * kCorrTileW / kBwThreads;
+        constexpr int STEP = kLook ? XK : 8;
+        int t0 = tid;
+        asm volatile("" : "+v"(t0));  // (nothing of this is to be computed ahead and kept)
+        float xv[STEP], gv[GK];
+        auto get_x = [&](int k0) {
 #pragma unroll
-                for (int tt = 0; tt < NT; ++tt) xs(tt)[r * kCmXP + cc] = t3[tt];
-                if (r >= P && r < P + kCorrTileH && cc >= 8 && cc < 8 + kCorrTileW) sx += f;
+            for (int k = 0; k < STEP; ++k) {
+                const int t = (k0 + k) * kBwThreads + t0, r = t / (8 * PC), cc = t - r * (8 * PC);
+                const int gy = ty0 - P + r, gx = tx0 - CG::BASE + cc;
+                const bool in = t < XT && gy >= 0 && gy < H && gx >= 0 && gx < W;
+                const float f = bw_load(xp + (in ? (size_t)gy * W + gx : 0));
+                xv[k] = in ? f : 0.f;
             }
-        }
-        for (int t = tid; t < kCorrTileH * kCorrTileW; t += kBwThreads) {
-            const int r = t >> 6, cc = t & 63;
-            const int gy = ty0 + r, gx = tx0 + cc;
-            if (gy < H && gx < W) {
-                uint16_t t3[3];
-                split(bw_load(gp + (size_t)gy * W + gx), t3);
+        };
+        auto put_x = [&](int k0, float f) {
 #pragma unroll
-                for (int tt = 0; tt < NT; ++tt) {
-                    g0(tt)[r * kCmGP + GOFF + cc] = t3[tt];
-                    g1(tt)[r * kCmGP + GOFF + cc - 1] = t3[tt];
+            for (int k = 0; k < STEP; ++k) {
+                const int t = (k0 + k) * kBwThreads + t0, r = t / (8 * PC), cc = t - r * (8 * PC);
+                uint16_t v[NT];
+                split(kF32 ? xv[k] * f : xv[k], v);
+                if (t < XT) {
+#pragma unroll
+                    for (int tt = 0; tt < NT; ++tt) xs(tt)[r * kCmXP + cc] = v[tt];
+                    if (r >= P && r < P + kCorrTileH && cc >= CG::BASE && cc < CG::BASE + kCorrTileW) sx += xv[k];
                 }
             }
+        };
+        get_x(0);
+#pragma unroll
+        for (int k = 0; k < GK; ++k) {
+            const int t = k * kBwThreads + t0, gy = ty0 + (t >> 6), gx = tx0 + (t & 63);
+            const bool in = gy < H && gx < W;
+            const float f = bw_load(gp + (in ? (size_t)gy * W + gx : 0));
+            gv[k] = in ? f : 0.f;
         }
+        if constexpr (kLook) {
+#pragma unroll
+            for (int k = 0; k < STEP; ++k) mx = max(mx, magnitude(xv[k]));
+#pragma unroll
+            for (int k = 0; k < GK; ++k) mg = max(mg, magnitude(gv[k]));
+        }
+        agree(true);
+        const float fx = kF32 ? power(exponent(mx)) : 1.f, fg = kF32 ? power(exponent(mg)) : 1.f;
+        put_x(0, fx);
+#pragma unroll
+        for (int k = 0; k < GK; ++k) {
+            const int t = k * kBwThreads + t0, r = t >> 6, cc = t & 63;
+            uint16_t v[NT];
+            split(kF32 ? gv[k] * fg : gv[k], v);
+#pragma unroll
+            for (int tt = 0; tt < NT; ++tt) {
+                g0(tt)[r * CG::GP + GOFF + cc] = v[tt];
+                g1(tt)[r * CG::GP + GOFF + cc - 1] = v[tt];
+            }
+        }
+        for (int k0 = STEP; k0 < XK; k0 += STEP) get_x(k0), put_x(k0, fx);
     }
     __syncthreads();
 
@@ -385,58 +319,119 @@ __global__ __launch_bounds__(kBwThreads) void corr_mfma_kernel(const BackwardPar
     // share their A operands: the halo rows R .. R + 15 serve tile row R + s as window rows
     // i = i' - s (i' the row of the product), s < SH = 16 - KC + 1 (at most 4); every shift has
     // accumulators of its own, and the shifted results are put together at the end ----
-    constexpr int SH = KC <= 13 ? 4 : 2;
+    constexpr int SH = CG::SH;
     const int l16 = lane & 15, kg = lane >> 4;
-    const int jc = l16 < KC ? l16 : KC - 1;  // (columns beyond the window repeat its last one; their sums are dropped)
-    const size_t gsel = (jc & 1) ? kCmG1 : kCmG0;
-    const int o0 = 8 * kg - jc + 2 * P - (jc & 1);  // even: the lane's first element in its copy, for block 0
-    f32x4 acc[SH][3];
+    // block jb of the window's columns: column 16 jb + l16 (those beyond the window repeat its last one; their sums are
+    // dropped), in the copy of its parity, from an even element on
+    size_t gsel[NB];
+    int o0[NB];
+#pragma unroll
+    for (int jb = 0; jb < NB; ++jb) {
+        const int jc = min(16 * jb + l16, KC - 1);
+        gsel[jb] = (jc & 1) ? CG::G1 : CG::G0;
+        o0[jb] = 8 * kg - jc + 2 * P - (jc & 1);
+    }
+    constexpr int NC = NB == 1 ? 3 : 1;   // one 16 x 16 block: the three column blocks' sums apart, so that their chains take turns
+    f32x4 acc[SH][NB][NB][NC], low[kF32 ? SH : 1][NB][NB][NC];   // (fp32 storage: products with a low term apart)
 #pragma unroll
     for (int sft = 0; sft < SH; ++sft)
 #pragma unroll
-        for (int b = 0; b < 3; ++b) acc[sft][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int ib = 0; ib < NB; ++ib)
+#pragma unroll
+            for (int jb = 0; jb < NB; ++jb)
+#pragma unroll
+                for (int b = 0; b < NC; ++b) acc[sft][ib][jb][b] = low[kF32 ? sft : 0][ib][jb][b] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int u = 0; u < 8 / SH; ++u) {
         const int R = 8 * wave + SH * u;
-        u32x4 a[NT][3];
+        u32x4 a[NT][NB][3];
 #pragma unroll
         for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
-            for (int b = 0; b < 3; ++b) a[tt][b] = *reinterpret_cast<const u32x4 *>(xs(tt) + (R + l16) * kCmXP + 32 * b + 8 * kg);
+            for (int ib = 0; ib < NB; ++ib)
+#pragma unroll
+                for (int b = 0; b < 3; ++b) a[tt][ib][b] = *reinterpret_cast<const u32x4 *>(xs(tt) + (R + 16 * ib + l16) * kCmXP + 32 * b + 8 * kg);
 #pragma unroll
         for (int sft = 0; sft < SH; ++sft) {
-            u32x4 bv[NT][3];
+            u32x4 bv[NT][NB][3];
 #pragma unroll
             for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
-                for (int b = 0; b < 3; ++b)
-                    __builtin_memcpy(&bv[tt][b],
-                                     reinterpret_cast<const uint32_t *>(reinterpret_cast<const uint16_t *>(lds + tt * kCmLds + gsel) +
-                                                                        (R + sft) * kCmGP + o0 + 32 * b),
-                                     16);
-            // (small terms first; the three column blocks' chains take turns)
+                for (int jb = 0; jb < NB; ++jb)
+#pragma unroll
+                    for (int b = 0; b < 3; ++b)
+                        __builtin_memcpy(&bv[tt][jb][b],
+                                         reinterpret_cast<const uint32_t *>(reinterpret_cast<const uint16_t *>(lds + tt * CG::TERM + gsel[jb]) +
+                                                                            (R + sft) * CG::GP + o0[jb] + 32 * b),
+                                         16);
+            // (small terms first; neighbouring products belong to different sums)
 #pragma unroll
             for (int ta = NT - 1; ta >= 0; --ta)
 #pragma unroll
-                for (int tb = NT - 1; tb >= 0; --tb)
+                for (int tb = NT - 1; tb >= 0; --tb) {
+                    if (ta + tb > 1) continue;   // (below 2^-22 of a product)
 #pragma unroll
                     for (int b = 0; b < 3; ++b)
-                        acc[sft][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[ta][b]),
-                                                                              __builtin_bit_cast(bf16x8, bv[tb][b]), acc[sft][b], 0, 0, 0);
+#pragma unroll
+                        for (int ib = 0; ib < NB; ++ib)
+#pragma unroll
+                            for (int jb = 0; jb < NB; ++jb) {
+                                f32x4 &d = (ta + tb > 0 ? low[kF32 ? sft : 0] : acc[sft])[ib][jb][NC == 3 ? b : 0];
+                                if constexpr (kF32)
+                                    d = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a[ta][ib][b]),
+                                                                               __builtin_bit_cast(f16x8, bv[tb][jb][b]), d, 0, 0, 0);
+                                else
+                                    d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[ta][ib][b]),
+                                                                                __builtin_bit_cast(bf16x8, bv[tb][jb][b]), d, 0, 0, 0);
+                            }
+                }
         }
+    }
+    if constexpr (kF32) {
+#pragma unroll
+        for (int sft = 0; sft < SH; ++sft)
+#pragma unroll
+            for (int ib = 0; ib < NB; ++ib)
+#pragma unroll
+                for (int jb = 0; jb < NB; ++jb)
+#pragma unroll
+                    for (int b = 0; b < NC; ++b) acc[sft][ib][jb][b] += low[sft][ib][jb][b];
     }
     const float sxr = row16_sum(sx);
     __syncthreads();  // the tiles are no longer read: their LDS takes the wavefronts' results
-    float *red = bw_lds;                   // [4 wavefronts][SH shifts][16 i'][16 j]
-    float *sxs = bw_lds + 4 * SH * 256;    // [16 rows of lanes]
+    // one block: [4 wavefronts][SH shifts][16 i'][16 j]; two by two: [4 wavefronts][32 i][32 j], a shift at a time
+    float *red = bw_lds, *sxs = bw_lds + (NB == 1 ? 4 * SH * 256 : 4096);    // [16 rows of lanes]
+    if constexpr (NB == 1) {
 #pragma unroll
-    for (int sft = 0; sft < SH; ++sft) {
-        const f32x4 tot = (acc[sft][0] + acc[sft][1]) + acc[sft][2];
+        for (int sft = 0; sft < SH; ++sft) {
+            const f32x4 tot = (acc[sft][0][0][0] + acc[sft][0][0][1 % NC]) + acc[sft][0][0][2 % NC];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) red[(wave * SH + sft) * 256 + (4 * kg + r) * 16 + l16] = tot[r];
+            for (int r = 0; r < 4; ++r) red[(wave * SH + sft) * 256 + (4 * kg + r) * 16 + l16] = tot[r];
+        }
+    } else {
+#pragma unroll
+        for (int sft = 0; sft < SH; ++sft) {
+#pragma unroll
+            for (int ib = 0; ib < NB; ++ib)
+#pragma unroll
+                for (int jb = 0; jb < NB; ++jb)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int i = 16 * ib + 4 * kg + r - sft;   // the window row that row i' of the product is for this shift
+                        float *d = red + wave * 1024 + i * 32 + 16 * jb + l16;
+                        if (sft == 0)
+                            *d = acc[sft][ib][jb][0][r];
+                        else if (i >= 0)
+                            *d += acc[sft][ib][jb][0][r];
+                    }
+            __syncthreads();  // (the next shift's rows lie in other lanes)
+        }
     }
     if (l16 == 15) sxs[tid >> 4] = sxr;
     __syncthreads();
+    const int back = kF32 ? -exponent(mx) - exponent(mg) : 0;
+    // values that are not finite, in a window beyond 15 x 15: every sum plainly, so that those they do not reach stay finite
+    const bool plain = NB == 2 && (mx >= 0x7f800000u || mg >= 0x7f800000u);
     float *dst = p.partial + ((size_t)nc * tiles + tile) * (KC * KC + 1);
     for (int o = tid; o < KC * KC + 1; o += kBwThreads) {
         float s2 = 0.f;
@@ -445,10 +440,25 @@ __global__ __launch_bounds__(kBwThreads) void corr_mfma_kernel(const BackwardPar
             for (int k = 0; k < 16; ++k) s2 += sxs[k];
         } else {
             const int i = o / KC, j = o - i * KC;
+            if (NB == 2 && plain) {
+                for (int y = ty0; y < min(ty0 + kCorrTileH, H); ++y)
+                    for (int x = tx0; x < min(tx0 + kCorrTileW, W); ++x) {
+                        const int sy = y + i - P, sx2 = x + j - P;
+                        const bool in = sy >= 0 && sy < H && sx2 >= 0 && sx2 < W;
+                        s2 = fmaf(bw_load(gp + (size_t)y * W + x), in ? bw_load(xp + (size_t)sy * W + sx2) : 0.f, s2);
+                    }
+            } else {
 #pragma unroll
-            for (int w = 0; w < 4; ++w)
+                for (int w = 0; w < 4; ++w) {
+                    if constexpr (NB == 2) {
+                        s2 += red[w * 1024 + i * 32 + j];
+                    } else {
 #pragma unroll
-                for (int sft = 0; sft < SH; ++sft) s2 += red[(w * SH + sft) * 256 + (i + sft) * 16 + j];
+                        for (int sft = 0; sft < SH; ++sft) s2 += red[(w * SH + sft) * 256 + (i + sft) * 16 + j];
+                    }
+                }
+                if (kF32) s2 = __builtin_amdgcn_ldexpf(s2, back);
+            }
         }
         dst[o] = s2;
     }
@@ -457,7 +467,7 @@ __global__ __launch_bounds__(kBwThreads) void corr_mfma_kernel(const BackwardPar
 template <typename T, int KC>
 hipError_t launch_corr_mfma(const BackwardParams &p, unsigned grid, hipStream_t s)
 {
-    constexpr size_t lds = (std::is_same<T, float>::value ? 3 : 1) * kCmLds;
+    constexpr size_t lds = CorrGeom<KC, std::is_same<T, float>::value>::lds();
     static bool granted = false;
     if (lds > 48 * 1024 && !granted) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&corr_mfma_kernel<T, KC>),
@@ -474,7 +484,8 @@ hipError_t launch_corr_mfma_kc(const BackwardParams &p, int kc, unsigned grid, h
 {
     switch (kc) {
 #define ESC_KC(K) case K: return launch_corr_mfma<T, K>(p, grid, s);
-        ESC_KC(3) ESC_KC(5) ESC_KC(7) ESC_KC(9) ESC_KC(11) ESC_KC(13) ESC_KC(15)
+        ESC_KC(3) ESC_KC(5) ESC_KC(7) ESC_KC(9) ESC_KC(11) ESC_KC(13) ESC_KC(15) ESC_KC(17)
+        ESC_KC(19) ESC_KC(21) ESC_KC(23) ESC_KC(25) ESC_KC(27) ESC_KC(29) ESC_KC(31)
 #undef ESC_KC
     }
     return hipErrorInvalidValue;
@@ -681,29 +692,6 @@ __global__ __launch_bounds__(256) void batch_sums_kernel(const BackwardParams p,
 }
 
 
-template <typename T, int KC>
-hipError_t launch_corr(const BackwardParams &p, unsigned grid, hipStream_t s)
-{
-    constexpr int NXV = (KC + 3 + 3) & ~3, HC = kCorrTileW + KC - 1;
-    constexpr int PITCH = ((60 + NXV > HC ? 60 + NXV : HC) + 3) & ~3, HR = kCorrTileH + KC;
-    constexpr size_t lds = ((size_t)HR * PITCH + kCorrTileH * kCorrTileW + 16 * (2 * KC + 1)) * sizeof(float);
-    static_assert(lds <= 64 * 1024, "the correlation kernel's tiles must fit the default LDS limit");
-    hipLaunchKernelGGL((corr_kernel<T, KC>), dim3(grid), dim3(kBwThreads), lds, s, p);
-    return hipGetLastError();
-}
-
-template <typename T>
-hipError_t launch_corr_kc(const BackwardParams &p, int kc, unsigned grid, hipStream_t s)
-{
-    switch (kc) {
-#define ESC_KC(K) case K: return launch_corr<T, K>(p, grid, s);
-        ESC_KC(3) ESC_KC(5) ESC_KC(7) ESC_KC(9) ESC_KC(11) ESC_KC(13) ESC_KC(15) ESC_KC(17)
-        ESC_KC(19) ESC_KC(21) ESC_KC(23) ESC_KC(25) ESC_KC(27) ESC_KC(29) ESC_KC(31)
-#undef ESC_KC
-    }
-    return hipErrorInvalidValue;
-}
-
 }  // namespace
 
 // the correlation of grad_out with x, tile by tile
@@ -713,12 +701,9 @@ __attribute__((visibility("hidden"))) hipError_t launch_backward_sums(const Back
     const int kc = corr_window(p.Ks), tiles = corr_tiles(p.H, p.W);
     const size_t grid = (size_t)p.N * p.Ca * tiles;
     if (grid >= ((size_t)1 << 31)) return hipErrorInvalidValue;
-    if (kc <= 15) {  // one 16 x 16 block of sums: the matrix cores
-        BackwardParams q = p;
-        q.corr_vec = (p.W % 8 == 0) && ((uintptr_t)p.x % 16 == 0) && ((uintptr_t)p.go % 16 == 0);
-        return bf16 ? launch_corr_mfma_kc<bf16b>(q, kc, (unsigned)grid, s) : launch_corr_mfma_kc<float>(q, kc, (unsigned)grid, s);
-    }
-    return bf16 ? launch_corr_kc<bf16b>(p, kc, (unsigned)grid, s) : launch_corr_kc<float>(p, kc, (unsigned)grid, s);
+    BackwardParams q = p;
+    q.corr_vec = (p.W % 8 == 0) && ((uintptr_t)p.x % 16 == 0) && ((uintptr_t)p.go % 16 == 0);
+    return bf16 ? launch_corr_mfma_kc<bf16b>(q, kc, (unsigned)grid, s) : launch_corr_mfma_kc<float>(q, kc, (unsigned)grid, s);
 }
 
 // per image: dDK and g from the tiles' sums, the estimator forwards and backwards, the

@@ -428,9 +428,9 @@ def test_pointwise_runs_kernels_use_no_scratch(lib):
 
 
 def test_three_bf16_terms_hold_an_fp32_value_exactly():
-    # The backward's correlation feeds fp32 values to the bf16 matrix instructions as three terms
-    # taken by truncation (top 16 bits of the value, of the remainder, of what is left).  The
-    # claim the kernel rests on, checked here in numpy: every term is a bf16 value and the three
+    # fp32 values enter the bf16 matrix instructions as three terms, the first of ConvFFN's V
+    # taken by truncation (here all three: top 16 bits of the value, of the remainder, of what is left).  The
+    # claim such kernels rest on, checked here in numpy: every term is a bf16 value and the three
     # add up to the fp32 value exactly, so that all nine products of two values' terms are exact
     # (values within 2^24 of the smallest normal number lose denormal bits of the third term:
     # an error below 2^-133, checked last).

@@ -201,3 +201,29 @@ def test_backward_and_dense_calls_replay_from_a_captured_graph(dtype):
         with torch.cuda.stream(stream):  # plain work on the same workspaces between replays
             enqueue(scratch, scratch_d)
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("dtype,Ks,N,H,W", [(F32, 13, 1, 33, 72), (F32, 15, 2, 20, 37), (F32, 17, 1, 32, 64), (F32, 29, 1, 40, 67), (F32, 31, 1, 33, 72),
+                                            (BF16, 17, 2, 33, 64), (BF16, 31, 1, 31, 65)])
+def test_sums_at_any_scale_and_of_special_values(oracle, dtype, Ks, N, H, W):
+    # grad_lk of values and gradients of every size: sums of H W products, each within 2^-23 of either factor and
+    # added up with sqrt(2 H W) roundings of 2^-24 at most.  Windows beyond 15 x 15: infinities and NaN of x where the
+    # definition has them and nowhere else.
+    base = wk.make_random(1500 + Ks, N, 5, H, W, 3, Ks, dtype=dtype)
+    go = grad_out_for(base, 1501)
+    cases = [("ordinary", 1.0, 1.0), ("small", 2.0 ** -60, 2.0 ** -50), ("apart", 2.0 ** -90, 2.0 ** 80), ("large", 2.0 ** 40, 2.0 ** 60)]
+    for what, fx, fg in cases + ([("inf", 1.0, 1.0), ("nan", 1.0, 1.0)] if Ks > 15 else []):
+        print(f"[case] {what} {dtype} Ks={Ks}", flush=True)
+        xf = (base.x_as_f32() * np.float32(fx)).astype(np.float32)
+        gf = (wk.bf16_bits_to_f32(go) if dtype == BF16 else go).astype(np.float32) * np.float32(fg)
+        if what in ("inf", "nan"):
+            xf[0, 1, 0, W - 1] = np.inf if what == "inf" else np.nan   # a corner: a quarter of the window reaches it
+        wl = wk.make_random(1500 + Ks, N, 5, H, W, 3, Ks, dtype=dtype)
+        wl.x, g = (wk.f32_to_bf16_bits(xf), wk.f32_to_bf16_bits(gf)) if dtype == BF16 else (xf, gf)
+        with np.errstate(invalid="ignore"):
+            ref = oracle.convattn_backward(wl.x, g, 3, wl.lk, dtype)["dlk"]
+        got = run_backward(wl, g, use_gen=False)["grad_lk"].cpu().numpy().astype(np.float64)
+        assert np.array_equal(np.isfinite(ref), np.isfinite(got)), what
+        ok = np.isfinite(ref)
+        bound = (np.sqrt(2 * H * W * N) + 8) * 2.0 ** -24
+        assert np.linalg.norm(got[ok] - ref[ok]) <= bound * np.linalg.norm(ref[ok]), what
