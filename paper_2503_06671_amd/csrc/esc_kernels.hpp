@@ -1988,9 +1988,11 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
     }
 #pragma unroll
     for (int oy = 0; oy < RY; ++oy) {
-        const bool blocks = kSplit && split;   // sums of 16 x 16 blocks: a row of each, four columns
-        const int gx = wd.x0 + (blocks ? 16 * ((mb0 & 3) + oy) + 4 * mg4 : 4 * tx_d);
-        const int gy = wd.y0 + (blocks ? 16 * (mb0 >> 2) + mrow : ty_d * RY + oy);
+        int gx = wd.x0 + 4 * tx_d;
+        int gy = wd.y0 + ty_d * RY + oy;
+        if constexpr (kSplit) {
+            if (split) gx = wd.x0 + 16 * ((mb0 & 3) + oy) + 4 * mg4, gy = wd.y0 + 16 * (mb0 >> 2) + mrow;   // (blocks of 16 x 16)
+        }
         if (gy >= H) continue;
         T *dst = op + (size_t)gy * W + gx;
         if (ANY ? gx + 3 < W : gx < W) {
