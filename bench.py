@@ -141,14 +141,14 @@ BF16_MFMA_PEAK_TFLOPS = 2500.0        # dense bf16 matrix-core peak
 
 
 def taps_on_matrix_cores(wl) -> bool:
-    """bf16 storage with Ks <= 17: the library runs the depth-wise taps as bf16 matrix
-    instructions (fp32 accumulation), so their roof is the bf16 matrix peak."""
-    return wl.elem_bytes == 2 and wl.Ks <= 17
+    """bf16 storage, and fp32 storage with Ks >= 15: the library runs the depth-wise taps as 16-bit matrix
+    instructions (fp32 accumulation), so their roof is the bf16 (and fp16) matrix peak."""
+    return wl.elem_bytes == 2 or wl.Ks >= 15
 
 
 def roofline_of(wl, sec):
     """Which roof bounds this workload (HBM at 8 TB/s, or the units the taps run on: the fp32
-    vector units at 157.3 TFLOP/s, for bf16 storage with Ks <= 17 the bf16 matrix cores at
+    vector units at 157.3 TFLOP/s, where they are matrix products the matrix cores at
     2.5 PFLOP/s) and the fraction of it reached; the fractions against the other ceilings ride along."""
     b_alg = 2.0 * wl.N * wl.C * wl.H * wl.W * wl.elem_bytes   # read x once, write out once
     f_alg = 2.0 * wl.Ks * wl.Ks * wl.N * wl.Ca * wl.H * wl.W  # merged-kernel tap count
@@ -178,14 +178,15 @@ FP32_MFMA_PEAK_TFLOPS = 157.3         # dense fp32 matrix-core peak
 
 
 def terms_per_product(wl) -> float:
-    """bf16 matrix instructions the point-wise layers issue per block of products: fp32 storage has every
-    value and weight in three bf16 terms and multiplies six of the nine pairs, bf16 storage has every weight in two."""
-    return 2.0 if wl.elem_bytes == 2 else 6.0
+    """Matrix instructions the point-wise layers issue per block of products: fp32 storage has every
+    value and weight in two fp16 terms and multiplies three of the four pairs (ConvFFN in one launch and channels
+    that are not whole runs of sixteen: six of nine of bf16 terms), bf16 storage has every weight in two."""
+    return 2.0 if wl.elem_bytes == 2 else 3.0
 
 
 def fused_roofline_of(wl, sec, lkc, residual):
     """The fused call: x read once (plus the residual), out written once; the depth-wise taps on
-    the vector units (bf16 storage with Ks <= 17: the bf16 matrix cores), Conv_fuse (and LK^c) on the
+    the vector units (or the matrix cores, taps_on_matrix_cores), Conv_fuse (and LK^c) on the
     bf16 matrix cores: `achieved` counts the instructions issued (`terms_per_product` times the
     algorithmic flops, which hold each product once)."""
     P = wl.N * wl.H * wl.W
@@ -209,7 +210,7 @@ def dense_roofline_of(wl, sec):
     """The dense-LK call: same bytes as the depth-wise forward; the C_a x C_a x Ks x Ks contraction on the
     matrix cores, DK's nine taps on the vector units.  With up to 16 channels the contraction runs on the
     bf16 instructions: bf16 storage with every weight as two bf16 terms (two instructions per product
-    block), fp32 storage (Ks <= 13) with every value and weight as three exact bf16 terms (six
+    block), fp32 storage (Ks <= 13) with every value as three fp16 terms and every weight as two (four
     instructions per product block).  What bounds such a kernel is the instructions it issues at the
     bf16 peak: `achieved` counts those (`terms_per_product` times the algorithmic flops, which hold
     each product once and are reported beside it, also against the fp32 matrix peak).  Otherwise
@@ -219,7 +220,7 @@ def dense_roofline_of(wl, sec):
     f_mat = 2.0 * wl.Ks * wl.Ks * wl.Ca * wl.Ca * P
     on_bf16 = wl.Ca <= 16 and (wl.elem_bytes == 2 or wl.Ks <= 13)
     mat_peak = BF16_MFMA_PEAK_TFLOPS if on_bf16 else FP32_MFMA_PEAK_TFLOPS
-    issued = (2.0 if wl.elem_bytes == 2 else 6.0) if on_bf16 else 1.0
+    issued = (2.0 if wl.elem_bytes == 2 else 4.0) if on_bf16 else 1.0
     t_hbm, t_mat = b_alg / (HBM_PEAK_GBS * 1e9), issued * f_mat / (mat_peak * 1e12)
     if t_hbm >= t_mat:
         r = {"bound": "hbm", "achieved": b_alg / sec / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s"}
@@ -227,7 +228,7 @@ def dense_roofline_of(wl, sec):
         r = {"bound": "mfma", "achieved": issued * f_mat / sec / 1e12, "peak": mat_peak, "unit": "TFLOP/s"}
     r["frac"] = r["achieved"] / r["peak"]
     r.update({"algorithmic_bytes": b_alg, "algorithmic_flops_matrix": f_mat, "terms_per_product": issued,
-              "matrix_instructions": "bf16" if on_bf16 else "fp32", "hbm_gbps": b_alg / sec / 1e9,
+              "matrix_instructions": ("bf16" if wl.elem_bytes == 2 else "fp16") if on_bf16 else "fp32", "hbm_gbps": b_alg / sec / 1e9,
               "mfma_tflops": f_mat / sec / 1e12, "mfma_issued_tflops": issued * f_mat / sec / 1e12,
               "algorithmic_frac_of_fp32_mfma_peak": f_mat / sec / 1e12 / FP32_MFMA_PEAK_TFLOPS,
               "algorithmic_frac_of_bf16_mfma_peak": f_mat / sec / 1e12 / BF16_MFMA_PEAK_TFLOPS, "alu_tflops": 0.0})
@@ -236,14 +237,14 @@ def dense_roofline_of(wl, sec):
 
 def backward_roofline_of(wl, sec):
     """The backward call: x and grad_out read once, grad_x written once (3 tensors); two passes of
-    2 Ks^2 flops per attention pixel: the correlation (on the bf16 matrix cores for Ks <= 15 - fp32
-    values as three exact bf16 terms each, nine instructions per product block, which the algorithmic
-    count does not include - else on the vector units) and the input gradient (the forward kernel: the
+    2 Ks^2 flops per attention pixel: the correlation (on the matrix cores - fp32
+    values as two fp16 terms each, three instructions per product block, which the algorithmic
+    count does not include) and the input gradient (the forward kernel: the
     vector units, or the bf16 matrix cores where the forward's taps run there)."""
     P = wl.N * wl.H * wl.W
     b_alg = 3.0 * P * wl.C * wl.elem_bytes
     f_alg = 4.0 * wl.Ks * wl.Ks * P * wl.Ca
-    f_vec = (0.0 if wl.Ks <= 15 else f_alg / 2.0) + (0.0 if taps_on_matrix_cores(wl) else f_alg / 2.0)
+    f_vec = 0.0 if taps_on_matrix_cores(wl) else f_alg / 2.0
     f_mat = f_alg - f_vec
     t = {"hbm": b_alg / (HBM_PEAK_GBS * 1e9), "alu": f_vec / (FP32_VECTOR_PEAK_TFLOPS * 1e12),
          "mfma": f_mat / (BF16_MFMA_PEAK_TFLOPS * 1e12)}
@@ -257,8 +258,8 @@ def backward_roofline_of(wl, sec):
 
 def ffn_roofline_of(wl, sec, with_module):
     """ConvFFN (hidden width 2 C): x read once, out written once; the two point-wise layers on the
-    bf16 matrix cores (`achieved` counts the instructions issued, `terms_per_product` per block of products),
-    the 3 x 3 branch and the two GELUs per hidden element on the vector units.  with_module: the whole residual step, the fused module's work and bytes added
+    bf16 matrix cores (`achieved` counts the instructions issued: fp32 storage six of the nine products of three bf16
+    terms each, bf16 storage two), the 3 x 3 branch and the two GELUs per hidden element on the vector units.  with_module: the whole residual step, the fused module's work and bytes added
     (the tensor between the two calls is written and read once more: it is an output and an input)."""
     P = wl.N * wl.H * wl.W
     Ch = 2 * wl.C
@@ -274,7 +275,7 @@ def ffn_roofline_of(wl, sec, with_module):
         f_taps = 2.0 * wl.Ks * wl.Ks * P * wl.Ca
     else:
         f_taps = 0.0
-    issued = terms_per_product(wl)
+    issued = 2.0 if wl.elem_bytes == 2 else 6.0   # (ConvFFN in one launch; Conv_fuse is priced as its layers are)
     taps_peak = BF16_MFMA_PEAK_TFLOPS if taps_on_matrix_cores(wl) else FP32_VECTOR_PEAK_TFLOPS
     t = {"hbm": b_alg / (HBM_PEAK_GBS * 1e9), "mfma": issued * f_mat / (BF16_MFMA_PEAK_TFLOPS * 1e12),
          "alu": f_vec / (FP32_VECTOR_PEAK_TFLOPS * 1e12) + f_taps / (taps_peak * 1e12)}
