@@ -7,13 +7,7 @@
 // per image, with P = H*W pixels contiguous in memory for every channel of B and D, so
 // it runs on the matrix cores, on v_mfma_f32_32x32x16_bf16 for both storage types:
 //
-//  fp32 storage, channels in whole runs of sixteen and more than 32 of them: every value and every weight (its row brought
-//    to a common size first) as two fp16 terms (split_pair_f16), and three of the four products of terms, the two with a low
-//    term in sums of their own, accumulated in fp32.  Error against float64, whatever the size of values and weights:
-//    64 channels 9.8e-8, 192 1.2e-7, 240 1.3e-7 (with the six bf16 products below 1.1e-7, 2.0e-7, 2.3e-7, by twice as many
-//    roundings of the large sums; with a third term of the values, which is one bit, 8.8e-8, 1.1e-7, 1.2e-7 and the
-//    192-channel step 212 us, so 198).
-//  fp32 storage otherwise: every value and every weight as three bf16 terms (v = t0 + t1 + t2, each the
+//  fp32 storage: every value and every weight as three bf16 terms (v = t0 + t1 + t2, each the
 //    nearest bf16 to what the terms before it left: exact, down to magnitudes of 2^-110, where t2
 //    runs out of bits: 64 channels of standard deviation 2^-114 come out to 5.6e-7, of 2^-118 to
 //    8.8e-6, ordinary ones to 1.1e-7), and the six of the nine products of
@@ -95,28 +89,7 @@ __device__ __forceinline__ void split_pair(float v0, float v1, unsigned (&t)[N])
     }
 }
 
-// fp32 storage, fp16 terms: v = h + l / 4096, h the nearest fp16 to v, l the nearest to 4096 times what is left.  h has 11 of
-// the 24 bits and l with its sign 12: a bit is missing in a quarter of the values, from 2^-13 to 65504; below that all beyond 2^-37.
-typedef _Float16 pw_f16x2 __attribute__((ext_vector_type(2)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-constexpr float kLowScale = 4096.f;
-__device__ __forceinline__ void split_pair_f16(float v0, float v1, unsigned (&t)[2])
-{
-    const pw_f16x2 h = __builtin_convertvector(pw_f32x2{v0, v1}, pw_f16x2);
-    const float r0 = __builtin_fmaf(-kLowScale, (float)h.x, v0 * kLowScale), r1 = __builtin_fmaf(-kLowScale, (float)h.y, v1 * kLowScale);
-    t[0] = __builtin_bit_cast(unsigned, h);
-    t[1] = __builtin_bit_cast(unsigned, __builtin_convertvector(pw_f32x2{r0, r1}, pw_f16x2));
-}
-
 extern __shared__ __align__(16) u32x4 pw_lds[];
-
-// bytes of LDS of runs_body: the weights of two stages, [2 buffers][2 chunks][MT][terms][64 lanes] operands, the biases and
-// the rows' scales
-template <int MT>
-constexpr size_t runs_lds_bytes(int terms)
-{
-    return (size_t)2 * 2 * MT * terms * 64 * 16 + 2 * MT * 32 * sizeof(float);
-}
 
 // bytes of LDS: the weights of two stages, [2 buffers][2 chunks][MT][terms][64 lanes] operands, and the biases
 template <typename T, int MT>
@@ -481,33 +454,15 @@ enum : int { kPwPlain = 0, kPwGelu = 1, kPwRes = 2 };
 // without one at 360 x 640 bf16 31 - 33 either way)
 enum : int { kPwRuns = 0, kPwOne = 1, kPwTwo = 2 };
 
-// the power of two that brings m to 1 ... 2 (1 for zero and for what is not finite)
-__device__ __forceinline__ float to_unit(float m)
-{
-    const unsigned e = __float_as_uint(m) >> 23;
-    return e == 0 || e >= 255 ? 1.f : __uint_as_float((e >= 253 ? 1u : 254u - e) << 23);
-}
-// the value another lane of the same four holds
-template <int PERM>
-__device__ __forceinline__ float quad_swap(float v)
-{
-    return __uint_as_float((unsigned)__builtin_amdgcn_mov_dpp((int)__float_as_uint(v), PERM, 0xf, 0xf, true));
-}
-
 template <typename T, int MT, int NT, int MODE, int LIE>
 __device__ __forceinline__ void runs_body(const PointwiseParams &p)
 {
     constexpr bool GELU = MODE == kPwGelu, has_res = MODE == kPwRes, ONE = LIE == kPwOne, TWO = LIE == kPwTwo;
     constexpr bool F = sizeof(T) == 4;
-    // fp32 storage on fp16 terms; on bf16 ones up to one stage, whose few sums these keep nearer (16 -> 16 channels, error
-    // against float64: 3.6e-8, on fp16 terms 6.2e-8; 32 -> 32 5.6e-8 and 6.7e-8; 48 -> 48 7.2e-8 and 6.8e-8)
-    constexpr bool H = F && !ONE;
-    constexpr int TX = F ? (H ? 2 : 3) : 1, TW = F && !H ? 3 : 2;   // terms of a value, of a weight
+    constexpr int TX = F ? 3 : 1, TW = F ? 3 : 2;         // bf16 terms of a value, of a weight
     constexpr int RW = (NT * (int)sizeof(T) + 3) / 4;     // words a load brings
     constexpr int kUnits = (MT * 128 + kPwThreads - 1) / kPwThreads;  // runs of eight weights a thread stages
     typedef typename std::conditional<RW == 2, u32x2, unsigned>::type Raw;
-    // no registers for the residual beside two stages of values and two sets of sums: both row blocks take an input buffer
-    constexpr bool LATE = F && has_res && MT == 2 && NT == 2 && LIE == kPwRuns;
     // what is asked for stays in the order it is written in
     auto order = [] { __builtin_amdgcn_sched_barrier(kSchedNoVmem); };
     const int tid = (int)threadIdx.x;
@@ -564,8 +519,6 @@ __device__ __forceinline__ void runs_body(const PointwiseParams &p)
         }
     };
 
-    float *s_bias = reinterpret_cast<float *>(pw_lds + 2 * 2 * MT * TW * 64), *s_back = s_bias + 32 * MT;
-
     // ---- weights of a stage: unit u = eight weights of one row ----
     struct __attribute__((packed, aligned(4))) W4 {
         float v[4];
@@ -582,8 +535,6 @@ __device__ __forceinline__ void runs_body(const PointwiseParams &p)
             for (int e = 0; e < 4; ++e) w[i][e] = a.v[e], w[i][4 + e] = b.v[e];
         }
     };
-    // fp16 terms: a row is multiplied by the power of two that brings the largest weight of its first stage that has any to
-    // 1 ... 2, and its finished sums by the inverse (s_back), so that its terms have their bits whatever its size
     auto wput = [&](int st, const float (&w)[kUnits][8]) {
 #pragma unroll
         for (int i = 0; i < kUnits; ++i) {
@@ -591,26 +542,8 @@ __device__ __forceinline__ void runs_body(const PointwiseParams &p)
             const int row = u >> 2, kq = u & 3;
             const int in = m0 + row < M ? K - (st * kPwStage + 8 * kq) : 0;   // how many of the eight lie in W
             unsigned t[4][TW];
-            if constexpr (H) {
-                const bool own = MT * 128 % kPwThreads == 0 || u < MT * 128;
-                float back = st == 0 || !own ? 0.f : s_back[row];
-                if (back == 0.f) {   // (the first stage, or a row without weights so far)
-                    float m = 0.f;
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) m = __builtin_fmaxf(m, e < in ? __builtin_fabsf(w[i][e]) : 0.f);
-                    m = __builtin_fmaxf(m, quad_swap<0xb1>(m));   // the other three of the row's four threads
-                    m = __builtin_fmaxf(m, quad_swap<0x4e>(m));
-                    back = m == 0.f ? 0.f : 1.f / to_unit(m);
-                    if (own && kq == 0) s_back[row] = back;
-                }
-                const float wscale = back == 0.f ? 1.f : to_unit(back);
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    split_pair_f16((2 * e < in ? w[i][2 * e] : 0.f) * wscale, (2 * e + 1 < in ? w[i][2 * e + 1] : 0.f) * wscale, t[e]);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) split_pair<TW>(2 * e < in ? w[i][2 * e] : 0.f, 2 * e + 1 < in ? w[i][2 * e + 1] : 0.f, t[e]);
-            }
+            for (int e = 0; e < 4; ++e) split_pair<TW>(2 * e < in ? w[i][2 * e] : 0.f, 2 * e + 1 < in ? w[i][2 * e + 1] : 0.f, t[e]);
             if (MT * 128 % kPwThreads == 0 || u < MT * 128) {
                 u32x4 *d = pw_lds + ((((st & 1) * 2 + (kq >> 1)) * MT + (row >> 5)) * TW) * 64 + 32 * (kq & 1) + (row & 31);
 #pragma unroll
@@ -648,25 +581,19 @@ __device__ __forceinline__ void runs_body(const PointwiseParams &p)
         }
     };
     Raw rv[16];
+    float *s_bias = reinterpret_cast<float *>(pw_lds + 2 * 2 * MT * TW * 64);
     {
         if (tid < 32 * MT) s_bias[tid] = m0 + tid < M ? bias : 0.f;
         wput(0, wr);
         order();
         if constexpr (!ONE) wfetch(1, wr);
         order();
-        if (has_res && !LATE) rfetch(0, rv);
+        if (has_res) rfetch(0, rv);
         order();
     }
 
-    // fp16 terms: the products with a low term have sums of their own, 4096 times too large
-    f32x16 acc[MT][NT], low[H ? MT : 1][H ? NT : 1];
+    f32x16 acc[MT][NT];
     __syncthreads();  // the first stage's weights are in LDS
-    if constexpr (H) {
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int t = 0; t < NT; ++t) acc[mt][t] = f32x16{0.f}, low[mt][t] = f32x16{0.f};
-    } else {
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -677,58 +604,8 @@ __device__ __forceinline__ void runs_body(const PointwiseParams &p)
 #pragma unroll
                     for (int t = 0; t < NT; ++t) acc[mt][t][4 * g + e] = b[e];
             }
-    }
-    // fp16 terms: values within 2^6 of 1 in the first stage, on either side, are taken as they are.  Others are multiplied
-    // by the power of two (the same for all of the wavefront's values) that brings the largest to 1 ... 2, which a later stage
-    // corrects where its values would then be beyond the largest fp16.
-    float xscale = 0.f;   // 0: none, yet or at all
-    bool scaled = false;
-    auto largest = [&](const Raw (&raw)[16]) {
-        float m = 0.f;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            if constexpr (F && NT == 2)
-                m = __builtin_fmaxf(m, __builtin_fmaxf(__builtin_fabsf(__uint_as_float(raw[j].x)), __builtin_fabsf(__uint_as_float(raw[j].y))));
-            else if constexpr (F)
-                m = __builtin_fmaxf(m, __builtin_fabsf(__uint_as_float(raw[j])));
-        }
-        return m;
-    };
-    if constexpr (H) {
-        const float m = largest(ra);
-        scaled = __builtin_amdgcn_ballot_w64(m > 64.f) != 0 || __builtin_amdgcn_ballot_w64(m >= 1.f / 64.f) == 0;
-    }
-    auto rescale = [&](Raw (&raw)[16]) {
-        float m = largest(raw);
-        if (xscale == 0.f || __builtin_amdgcn_ballot_w64(m * xscale > 32768.f) != 0) {
-#pragma unroll
-            for (int d = 1; d < 64; d *= 2) m = __builtin_fmaxf(m, __shfl_xor(m, d));
-            m = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(m)));
-            const float s = m == 0.f ? 0.f : to_unit(m), f = xscale == 0.f ? 1.f : s / xscale;   // (nothing but zeros: no size yet)
-            xscale = s;
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int t = 0; t < NT; ++t) acc[mt][t] *= f, low[mt][t] *= f;
-        }
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            if constexpr (F && NT == 2)
-                raw[j] = u32x2{__float_as_uint(__uint_as_float(raw[j].x) * xscale), __float_as_uint(__uint_as_float(raw[j].y) * xscale)};
-            else if constexpr (F)
-                raw[j] = __float_as_uint(__uint_as_float(raw[j]) * xscale);
-        }
-    };
-    auto split = [](float v0, float v1, unsigned (&t)[TX]) {
-        if constexpr (H)
-            split_pair_f16(v0, v1, t);
-        else
-            split_pair<TX>(v0, v1, t);
-    };
     // one stage's products; `next` fetches into the registers it has done with
     auto multiply = [&](int st, Raw (&raw)[16], auto next, bool full = false) {
-        if constexpr (H)
-            if (scaled) rescale(raw);
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
             if (c == 1 && !full && st * kPwStage + 16 >= K) break;   // wavefront-uniform: nothing left in the second chunk
@@ -740,14 +617,14 @@ __device__ __forceinline__ void runs_body(const PointwiseParams &p)
                 if constexpr (F) {
                     unsigned t[TX];
                     if constexpr (NT == 2) {
-                        split(__uint_as_float(x0.x), __uint_as_float(x1.x), t);
+                        split_pair<TX>(__uint_as_float(x0.x), __uint_as_float(x1.x), t);
 #pragma unroll
                         for (int q = 0; q < TX; ++q) b[0][q][e] = t[q];
-                        split(__uint_as_float(x0.y), __uint_as_float(x1.y), t);
+                        split_pair<TX>(__uint_as_float(x0.y), __uint_as_float(x1.y), t);
 #pragma unroll
                         for (int q = 0; q < TX; ++q) b[NT - 1][q][e] = t[q];
                     } else {
-                        split(__uint_as_float(x0), __uint_as_float(x1), t);
+                        split_pair<TX>(__uint_as_float(x0), __uint_as_float(x1), t);
 #pragma unroll
                         for (int q = 0; q < TX; ++q) b[0][q][e] = t[q];
                     }
@@ -767,19 +644,13 @@ __device__ __forceinline__ void runs_body(const PointwiseParams &p)
             for (int qw = TW - 1; qw >= 0; --qw)
 #pragma unroll
                 for (int qx = TX - 1; qx >= 0; --qx) {
-                    if (H ? qw > 0 && qx > 0 : qw + qx > 2) continue;
+                    if (F && qw + qx > 2) continue;
 #pragma unroll
                     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-                        for (int t = 0; t < NT; ++t) {
-                            if constexpr (H) {
-                                f32x16 &d = qw + qx > 0 ? low[mt][t] : acc[mt][t];
-                                d = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a[mt][qw]), __builtin_bit_cast(f16x8, b[t][qx]), d, 0, 0, 0);
-                            } else {
-                                acc[mt][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[mt][qw]),
-                                                                                     __builtin_bit_cast(bf16x8, b[t][qx]), acc[mt][t], 0, 0, 0);
-                            }
-                        }
+                        for (int t = 0; t < NT; ++t)
+                            acc[mt][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[mt][qw]),
+                                                                                 __builtin_bit_cast(bf16x8, b[t][qx]), acc[mt][t], 0, 0, 0);
                 }
         }
         order();
@@ -813,37 +684,20 @@ __device__ __forceinline__ void runs_body(const PointwiseParams &p)
             __syncthreads();
         }
         multiply(st, ra, [&] {
-            if (has_res && LATE) rfetch(0, ra);
-            if (has_res && !LATE && MT > 1) rfetch(1, ra);
+            if (has_res && MT > 1) rfetch(1, ra);
         });
         if (st + 1 < stages) {
             wput(st + 1, wr);
             __syncthreads();
             multiply(st + 1, rb, [] {});
         }
-        if (LATE) rfetch(1, rb);
-    }
-    if constexpr (H) {
-        const float back = scaled && xscale != 0.f ? 1.f / xscale : 1.f;
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const f32x4 b = *reinterpret_cast<const f32x4 *>(s_bias + 32 * mt + 8 * g + 4 * half);
-                const f32x4 r = *reinterpret_cast<const f32x4 *>(s_back + 32 * mt + 8 * g + 4 * half);
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-#pragma unroll
-                    for (int t = 0; t < NT; ++t)
-                        acc[mt][t][4 * g + e] = __builtin_fmaf(__builtin_fmaf(low[mt][t][4 * g + e], 1.f / kLowScale, acc[mt][t][4 * g + e]), r[e] * back, b[e]);
-            }
     }
     if (has_res) {
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                const Raw r = LATE ? (mt == 0 ? ra[i] : rb[i]) : mt == 0 ? rv[i] : ra[i];
+                const Raw r = mt == 0 ? rv[i] : ra[i];
                 if constexpr (F && NT == 2) {
                     acc[mt][0][i] += __uint_as_float(r.x);
                     acc[mt][NT - 1][i] += __uint_as_float(r.y);
@@ -908,9 +762,8 @@ hipError_t launch_typed(const PointwiseParams &p, int mt, int nt, unsigned grid,
 template <typename T, int NT, int MODE, int LIE>
 hipError_t launch_runs(const PointwiseParams &p, int mt, unsigned grid, hipStream_t s)
 {
-    constexpr int terms = sizeof(T) == 4 && LIE == kPwOne ? 3 : 2;
-    return mt == 1 ? launch_one<pointwise_runs_kernel<T, 1, NT, MODE, LIE>>(p, grid, runs_lds_bytes<1>(terms), s)
-                   : launch_one<pointwise_runs_kernel<T, 2, NT, MODE, LIE>>(p, grid, runs_lds_bytes<2>(terms), s);
+    return mt == 1 ? launch_one<pointwise_runs_kernel<T, 1, NT, MODE, LIE>>(p, grid, pw_lds_bytes<T, 1>(), s)
+                   : launch_one<pointwise_runs_kernel<T, 2, NT, MODE, LIE>>(p, grid, pw_lds_bytes<T, 2>(), s);
 }
 
 // Every way through here ends in a kernel: a variant that is not compiled is not named.
@@ -918,13 +771,17 @@ template <typename T, int NT, int MODE>
 hipError_t launch_mode(const PointwiseParams &p, int mt, unsigned grid, hipStream_t s)
 {
     const int K = p.K1 + p.K2;
-    // Whole runs of sixteen channels: everything fetched ahead, and fp32 storage on half as many matrix instructions (192-channel
-    // residual step 180 x 320 fp32 234 us, by the body for any channels, -> 190; 64 x 64 58 -> 51)
+    // Fetching ahead pays where latency counts: few pixels (192-channel residual step 64 x 64 fp32 77 us -> 64, 64 channels
+    // of 25 images of 63 x 63 120 -> 111), bf16 storage (Conv_fuse 360 x 640 21 -> 19), LK^c's single stage, and more than two
+    // stages (192-channel residual step 180 x 320 fp32 240 -> 211, 64 x 64 58 -> 54).  Large calls of fp32 with two are
+    // bound by memory: waiting for everything, the residual step of 40 images of 72 x 72 of 64 channels takes 187 us, fetched
+    // ahead 206; the fused call 339 x 511 63.0 and 66.2, 360 x 640 49.8 and 52.0.
     if (p.K1 % 16 == 0 && p.K2 % 16 == 0) {
-        if constexpr (MODE == kPwPlain || sizeof(T) == 4)
+        if constexpr (MODE == kPwPlain)
             if (K <= kPwStage) return launch_runs<T, NT, MODE, kPwOne>(p, mt, grid, s);
-        return K > kPwStage && K <= 2 * kPwStage ? launch_runs<T, NT, MODE, kPwTwo>(p, mt, grid, s)
-                                                 : launch_runs<T, NT, MODE, kPwRuns>(p, mt, grid, s);
+        if (K > 2 * kPwStage) return launch_runs<T, NT, MODE, kPwRuns>(p, mt, grid, s);
+        if constexpr (sizeof(T) == 2 || NT == 1)
+            return K > kPwStage ? launch_runs<T, NT, MODE, kPwTwo>(p, mt, grid, s) : launch_runs<T, NT, MODE, kPwRuns>(p, mt, grid, s);
     }
     return launch_typed<T, MODE == kPwGelu>(p, mt, NT, grid, s);
 }

@@ -162,3 +162,60 @@ def test_values_and_weights_of_any_size(N, C):
         scale = np.sqrt((want ** 2).mean(axis=(0, 2, 3), keepdims=True))   # rows of W differ in size, and so do their results
         err = np.sqrt((((got - want) / scale) ** 2).mean())
         assert err <= bound, (what, err, bound)
+
+
+def sum_bound(w, x):
+    # |error| of sums of K fp32 products, each product and each addition rounded at most twice: K + 4 units of 2^-23 of the
+    # sum of magnitudes, whatever their order
+    return (w.shape[1] + 4) * 2.0 ** -23 * np.einsum("mk,nkp->nmp", np.abs(w).astype(np.float64), np.abs(x).astype(np.float64), optimize=True)
+
+
+@pytest.mark.parametrize("N,C", [(1, 12), (1, 64), (1, 96), (600, 64), (2, 192), (130, 112)])   # one and two pixels a lane, two to seven stages
+def test_a_pixel_depends_on_itself_alone(N, C):
+    # fp32 storage: finite values of any size, in any channel, cost their own pixel's sums no more than fp32 arithmetic
+    # does, and the other pixels nothing; infinities likewise.  (32784 and 40016 are values whose rest behind the
+    # nearest fp16 is 16.)
+    H, W = 3, 45
+    w, _, _ = pointwise_weights(981 + C, C, 0)
+    wl = wk.make_random(980 + C, N, C, H, W, 0, 3, dtype=F32, x_mean=0.3)
+    clean = run_fused(wl, w)
+    planted = [(C - 1, 0, 0, 32784.0), (C // 2 + 4, 0, 7, -40016.0), (C - 2, 0, 40, 1e5), (0, 1, 3, 1e8), (C - 1, 1, 30, -1e10), (C // 2, 2, 2, 1e12),
+               (1, 2, 20, 1e30), (C - 3, 2, 33, np.inf)]
+    touched = np.zeros((N, H, W), bool)
+    for i, (c, y, xx, v) in enumerate(planted):
+        wl.x[i % N, c, y, xx] = v
+        touched[i % N, y, xx] = True
+    print(f"[case] large pixels N={N} C={C}", flush=True)
+    got = run_fused(wl, w)
+    other = np.broadcast_to(~touched[:, None], got.shape)
+    assert np.array_equal(got[other], clean[other])
+    x = wl.x.reshape(N, C, -1)
+    with np.errstate(invalid="ignore"):
+        want = np.einsum("mk,nkp->nmp", w.astype(np.float64), x.astype(np.float64), optimize=True).reshape(got.shape)
+        bound = sum_bound(w, x).reshape(got.shape)
+    assert np.array_equal(np.isfinite(got), np.isfinite(want))
+    fin = np.isfinite(want)
+    assert (np.abs(got[fin].astype(np.float64) - want[fin]) <= bound[fin]).all()
+
+
+@pytest.mark.parametrize("N,C", [(1, 64), (1, 96), (600, 64), (2, 192), (130, 112)])
+def test_rows_and_pixels_of_any_range(N, C):
+    # fp32 storage: weights behind the first 32 far larger or smaller than those, channels likewise, each sum within fp32's own
+    # bound of magnitudes; a weight of one alone moves the values as they are.
+    H, W = 3, 45
+    wl = wk.make_random(990 + C, N, C, H, W, 0, 3, dtype=F32, x_mean=0.3)
+    x0 = wl.x.copy()
+    w0, _, _ = pointwise_weights(991 + C, C, 0)
+    late = np.where(np.arange(C) < 32, 1.0, 0.0)
+    for what, xs, ws in (("late weights 2^15", 1.0, 2.0 ** -15 * late + (1 - late)), ("late weights 2^20", 1.0, 2.0 ** -20 * late + (1 - late)),
+                         ("late weights 2^-40", 1.0, late + 2.0 ** -40 * (1 - late)), ("late channels 2^40", 2.0 ** -40 * late + (1 - late), 1.0),
+                         ("late channels 2^-40", late + 2.0 ** -40 * (1 - late), late * 2.0 ** -40 + (1 - late))):
+        print(f"[case] {what} N={N} C={C}", flush=True)
+        w = (w0 * np.asarray(ws)).astype(np.float32)
+        wl.x[...] = (x0 * np.asarray(xs).reshape(-1, *([1, 1] if np.ndim(xs) else []))).astype(np.float32)
+        got = run_fused(wl, w).astype(np.float64)
+        x = wl.x.reshape(N, C, -1)
+        want = np.einsum("mk,nkp->nmp", w.astype(np.float64), x.astype(np.float64), optimize=True).reshape(got.shape)
+        assert (np.abs(got - want) <= sum_bound(w, x).reshape(got.shape)).all(), what
+    wl.x[...] = x0 * 2.0 ** np.random.default_rng(992).integers(-60, 60, x0.shape)
+    assert np.array_equal(run_fused(wl, np.eye(C, dtype=np.float32)), wl.x)
