@@ -415,6 +415,7 @@ __shared__ float g_part[kStage];
 __shared__ __align__(16) float g_g[kMaxCa];
 __shared__ __align__(16) float g_t[kMaxHidden];
 __shared__ float g_small[16];
+__shared__ unsigned g_range[16];         // SplitGeom: each wavefront's largest magnitudes (words of their own: no barrier need part their reads from DK's writes)
 __shared__ float g_red[4 * kPoolBatch];  // wavefront totals of the pool tiles being finished
 __shared__ unsigned g_next[2];
 
@@ -1437,7 +1438,7 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
                 mw = max(mw, max(__float_as_uint(w[k][0]) & 0x7fffffffu, __float_as_uint(w[k][1]) & 0x7fffffffu));
             }
         }
-        unsigned *s_max = reinterpret_cast<unsigned *>(g_small);
+        unsigned *s_max = g_range;
         mx = wave_max(mx);
         mw = wave_max(mw);
         if ((tid2 & 63) == 63) s_max[tid2 >> 6] = mx, s_max[4 + (tid2 >> 6)] = mw;
