@@ -415,7 +415,7 @@ __shared__ float g_part[kStage];
 __shared__ __align__(16) float g_g[kMaxCa];
 __shared__ __align__(16) float g_t[kMaxHidden];
 __shared__ float g_small[16];
-__shared__ unsigned g_range[16];         // SplitGeom: each wavefront's largest magnitudes (words of their own: no barrier need part their reads from DK's writes)
+__shared__ u32x4 g_range[4];             // SplitGeom: each wavefront's ranges (words of their own: no barrier need part their reads from DK's writes)
 __shared__ float g_red[4 * kPoolBatch];  // wavefront totals of the pool tiles being finished
 __shared__ unsigned g_next[2];
 
@@ -970,9 +970,9 @@ struct MatrixGeom {
 
 // fp32 storage from Ks = 15 on (and bf16 storage from 19 on): the same Toeplitz products on fp16
 // instructions, where the vector loop was bound by its multiply-adds.  A tile's values, brought to
-// at most 2^15 by a power of two, are taken apart into two fp16 terms, v = h + l, h the nearest fp16
-// to v and l the nearest to what is left: to a unit of fp32's last place at most (a quarter of the values), from
-// 2^15 down to 1, and to 2^-25 below.  So are the weights, and three of the four products of terms
+// at most 2^15 by a power of two, are taken apart into two fp16 terms, v = h + l / 4096, h the nearest fp16
+// to v and l the nearest to 4096 times what is left: to a unit of fp32's last place at most (a quarter of the values), from
+// 2^15 down to 2^-14 (Range; a tile with magnitudes further apart keeps the vector loop).  So are the weights, and three of the four products of terms
 // are accumulated in fp32 (the fourth is below 2^-22 of a product), the two with a low term in sums
 // of their own; bf16 values are a term each.  K of an instruction is sixteen columns of two
 // neighbouring tile rows, i.e. two kernel rows at once: sixteen outputs need NQ = 2 or 3 runs of
@@ -1032,15 +1032,36 @@ __device__ __forceinline__ ConvWhere conv_where(ParamsPtr p, unsigned item)
     return w;
 }
 
-// v = h + l (SplitGeom), two values at a time
+// v = h + l / 4096 (SplitGeom), two values at a time
+constexpr float kLowTerm = 4096.f;
 __device__ __forceinline__ void split_f16(float v0, float v1, uint32_t &h, uint32_t &l)
 {
     typedef float f32x2 __attribute__((ext_vector_type(2)));
     typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
     const f16x2 a = __builtin_convertvector(f32x2{v0, v1}, f16x2);
     h = __builtin_bit_cast(uint32_t, a);
-    l = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{v0 - (float)a.x, v1 - (float)a.y}, f16x2));
+    l = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{(v0 - (float)a.x) * kLowTerm, (v1 - (float)a.y) * kLowTerm}, f16x2));
 }
+// The range of some values: their largest magnitude (NaN if there is one) and the smallest apart from zeros, its sign shifted
+// out and one subtracted, so that a zero is beyond all.  Two instructions a value.
+struct Range {
+    float large = 0.f;
+    unsigned small = 0xffffffffu;
+    __device__ __forceinline__ void look(float a, float b)
+    {
+        large = __builtin_elementwise_maximum(__builtin_elementwise_maximum(large, __builtin_fabsf(a)), __builtin_fabsf(b));
+        small = min(min(small, (__float_as_uint(a) << 1) - 1u), (__float_as_uint(b) << 1) - 1u);
+    }
+};
+// the same of a block's values: bits of the largest, and 2^32 - 1 less what Range keeps of the smallest, as maxima
+struct BlockRange {
+    unsigned large, small;
+    __device__ __forceinline__ bool finite() const { return large < 0x7f800000u; }
+    __device__ __forceinline__ int exponent() const { return (int)(large >> 23); }
+    // Brought to 2^14 ... 2^15 at the largest, the smallest is still 2^-14 at least (or all are zeros): two terms hold every
+    // value to a unit of fp32's last place.  (Values below fp32's smallest normal one have fewer bits than that.)
+    __device__ __forceinline__ bool narrow() const { return (int)(large >> 23) - (int)((0u - small) >> 24) <= 28; }
+};
 
 template <int KS, int RY, typename T, bool ADD, bool ANY>
 __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
@@ -1399,7 +1420,8 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
         pool_finish<NPT>(p->pool_box, sums, box, have, ctx.tag, g_red);
     }
     // fp32 on the matrix cores (SplitGeom).  Tiles and kernels with infinities or NaN keep the vector loop, which
-    // gives special values where the definition does and nowhere else.
+    // gives special values where the definition does and nowhere else; so do those whose magnitudes reach further
+    // than two terms do.
     constexpr bool kSplit = conv_splits<KS, T>;
     constexpr int TX = std::is_same<T, float>::value ? 2 : 1;
     using SG = SplitGeom<KS, RY, TX>;
@@ -1411,7 +1433,7 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
         const int tc = tid2 & 63, tr = tid2 >> 6, wc = tid2 & 31, wr = tid2 >> 5;
         const int cc = 2 * tc - SG::A, jj = 2 * wc - 15 - SG::S0;
         float v[KU][2], w[KWU][2];
-        unsigned mx = 0, mw = 0;
+        Range rx, rw;
         {
             const bool in0 = cc >= 0 && cc < HC, in1 = cc + 1 >= 0 && cc + 1 < HC;
             const float *src0 = tile + tr * PITCH + (in0 ? cc : 0), *src1 = tile + tr * PITCH + (in1 ? cc + 1 : 0);
@@ -1422,7 +1444,7 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
                 v[k][1] = row ? src1[4 * k * PITCH] : 0.f;
                 v[k][0] = in0 ? v[k][0] : 0.f;
                 v[k][1] = in1 ? v[k][1] : 0.f;
-                mx = max(mx, max(__float_as_uint(v[k][0]) & 0x7fffffffu, __float_as_uint(v[k][1]) & 0x7fffffffu));
+                rx.look(v[k][0], v[k][1]);
             }
         }
         {
@@ -1435,20 +1457,24 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
                 w[k][1] = row ? src1[8 * k * WP] : 0.f;
                 w[k][0] = in0 ? w[k][0] : 0.f;
                 w[k][1] = in1 ? w[k][1] : 0.f;
-                mw = max(mw, max(__float_as_uint(w[k][0]) & 0x7fffffffu, __float_as_uint(w[k][1]) & 0x7fffffffu));
+                rw.look(w[k][0], w[k][1]);
             }
         }
-        unsigned *s_max = g_range;
-        mx = wave_max(mx);
-        mw = wave_max(mw);
-        if ((tid2 & 63) == 63) s_max[tid2 >> 6] = mx, s_max[4 + (tid2 >> 6)] = mw;
+        const u32x4 mine{wave_max(__float_as_uint(rx.large) & 0x7fffffffu), wave_max(~rx.small),
+                         wave_max(__float_as_uint(rw.large) & 0x7fffffffu), wave_max(~rw.small)};
+        if ((tid2 & 63) == 63) g_range[tid2 >> 6] = mine;
         __syncthreads();  // also: everyone has read what is now written over
-        mx = max(max(s_max[0], s_max[1]), max(s_max[2], s_max[3]));
-        mw = max(max(s_max[4], s_max[5]), max(s_max[6], s_max[7]));
-        split = mx < 0x7f800000u && mw < 0x72000000u;   // (weights below 2^101: values stay 2^15 large until the end)
+        const u32x4 wave0 = g_range[0], wave1 = g_range[1], wave2 = g_range[2], wave3 = g_range[3];
+        auto all = [&](int k) {
+            unsigned m = wave0[k];
+            for (const unsigned o : {wave1[k], wave2[k], wave3[k]}) m = o > m ? o : m;
+            return m;
+        };
+        const BlockRange mx{all(0), all(1)}, mw{all(2), all(3)};
+        split = mx.finite() && mw.large < 0x72000000u && mx.narrow() && mw.narrow();   // (weights below 2^101: values stay 2^15 large until the end)
         if (split) {
             // powers of two that bring the largest to 2^14 ... 2^15 (as far as fp32 reaches)
-            const int ex = min(14 + 127 - (int)(mx >> 23), 126), ew = min(14 + 127 - (int)(mw >> 23), 126);
+            const int ex = min(14 + 127 - mx.exponent(), 126), ew = min(14 + 127 - mw.exponent(), 126);
             const float fx = __uint_as_float((unsigned)(127 + ex) << 23), fw = __uint_as_float((unsigned)(127 + ew) << 23);
             wback = -ew, xback = -ex;
             uint32_t *dst = tile_d + ((tc >> 2) * SG::HRP + tr) * 4 + (tc & 3);
@@ -1768,22 +1794,28 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
             if constexpr (SG::HALVES) {
                 // the wavefront keeps blocks 2 (wave % 2), + 1 and hands the other two over
                 __syncthreads();  // the weights have been read
+                auto sum = [&](int t) {
+                    f32x4 s4;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) s4[q] = fmaf(lo[t][q], 1.f / kLowTerm, hi[t][q]);
+                    return s4;
+                };
                 f32x4 *x = reinterpret_cast<f32x4 *>(g_wl) + (tid2 >> 6) * 128 + lane;
                 f32x4 *y = reinterpret_cast<f32x4 *>(g_wl) + ((tid2 >> 6) ^ 1) * 128 + lane;
 #pragma unroll
-                for (int t = 0; t < 2; ++t) x[64 * t] = first ? hi[t] + lo[t] : hi[NT - 2 + t] + lo[NT - 2 + t];
+                for (int t = 0; t < 2; ++t) x[64 * t] = first ? sum(t) : sum(NT - 2 + t);
                 __syncthreads();
 #pragma unroll
                 for (int t = 0; t < 2; ++t) {
                     const f32x4 other = y[64 * t];
-                    hi[t] = first ? hi[NT - 2 + t] + lo[NT - 2 + t] : hi[t] + lo[t];
-                    lo[t] = other;
+                    hi[t] = (first ? sum(NT - 2 + t) : sum(t)) + other;
+                    lo[t] = f32x4{0.f, 0.f, 0.f, 0.f};
                 }
             }
 #pragma unroll
             for (int t = 0; t < RY; ++t)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) acc[t][q] = __builtin_amdgcn_ldexpf(hi[t][q] + lo[t][q], wback);
+                for (int q = 0; q < 4; ++q) acc[t][q] = __builtin_amdgcn_ldexpf(fmaf(lo[t][q], 1.f / kLowTerm, hi[t][q]), wback);
         }
     } else if (G::UNROLL && !kSplit) {
 #pragma unroll
@@ -1906,7 +1938,7 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
                             v[2 * k] = (float)h.x, v[2 * k + 1] = (float)h.y;
                             if constexpr (TX > 1) {
                                 const f16x2 l = __builtin_bit_cast(f16x2, tile_d[SG::TERM_WORDS + at]);
-                                v[2 * k] += (float)l.x, v[2 * k + 1] += (float)l.y;
+                                v[2 * k] = fmaf((float)l.x, 1.f / kLowTerm, v[2 * k]), v[2 * k + 1] = fmaf((float)l.y, 1.f / kLowTerm, v[2 * k + 1]);
                             }
                         }
 #pragma unroll

@@ -464,6 +464,38 @@ def test_large_kernels_at_any_scale(oracle, dtype, Ks, N, H, W):
             assert err <= bound * rms, (what, c, err / rms, bound)
 
 
+@pytest.mark.parametrize("dtype,Ks,N,H,W", [(F32, 15, 1, 33, 66), (F32, 17, 1, 65, 129), (F32, 17, 24, 64, 65), (F32, 19, 1, 31, 64),
+                                            (F32, 31, 2, 40, 80), (BF16, 19, 1, 32, 72), (BF16, 31, 1, 33, 64)])
+def test_large_kernels_of_wide_range(oracle, dtype, Ks, N, H, W):
+    # magnitudes far apart inside a tile or a kernel.  Every output lies within its own terms' bound - Ks^2 + 9 products and
+    # additions, each within 2^-23 of the magnitudes summed, and eight more for the terms of both factors - and those
+    # whose window does not reach the large values are as near as without them.
+    base = wk.make_random(925 + Ks, N, 4, H, W, 4, Ks, dtype=dtype)
+    dk = np.random.default_rng(926).standard_normal((N, 4, 3, 3)).astype(np.float32)
+    rng = np.random.default_rng(927)
+    centre = np.zeros((Ks, Ks))
+    centre[Ks // 2, Ks // 2] = 1.0
+    sparse = np.where(rng.random(base.x.shape) < 0.01, 1.0, 0.0)
+    for what, large, fx, fw in (("1e8", 1e8, 1.0, 1.0), ("1e12", 1e12, 1.0, 1.0), ("1e30", 1e30, 1.0, 1.0), ("2^28 apart", 2.0 ** 27, 1.0, 1.0),
+                                ("any size", 1.0, 2.0 ** rng.integers(-60, 60, base.x.shape), 1.0),
+                                ("weights 2^-45", 1.0, sparse, centre + 2.0 ** -45 * (1 - centre)),
+                                ("weights 2^-30", 1.0, sparse, centre + 2.0 ** -30 * (1 - centre))):
+        print(f"[case] {what} {dtype} Ks={Ks}", flush=True)
+        xf = (base.x_as_f32() * fx).astype(np.float32)
+        if large != 1.0:
+            xf[0, 1, 2, 3] = large
+            xf[N - 1, 2, H - 1, W - 1] = -large
+        wl = wk.make_random(925 + Ks, N, 4, H, W, 4, Ks, dtype=dtype)
+        wl.x, wl.lk = (wk.f32_to_bf16_bits(xf) if dtype == BF16 else xf), (base.lk * fw).astype(np.float32)
+        d = (dk * (2.0 ** -45 if "weights" in what else 1.0)).astype(np.float32)
+        ref, _, _ = oracle.convattn_forward(wl.x, 4, wl.lk, dtype, dk_in=d, want_out=False)
+        ax = wl.x & 0x7fff if dtype == BF16 else np.abs(wl.x)
+        mags, _, _ = oracle.convattn_forward(ax, 4, np.abs(wl.lk), dtype, dk_in=np.abs(d), want_out=False)
+        got = gu.att_as_f64(gu.run_forward(wl, use_gen=False, dk_in=d), wl)
+        bound = (Ks * Ks + 17) * 2.0 ** -23 * mags + (2.0 ** -8 * np.abs(ref) if dtype == BF16 else 0.0)
+        assert (np.abs(got - ref) <= bound).all(), (what, (np.abs(got - ref) / bound).max())
+
+
 def test_bf16_large_kernel_weight_rounding_error_bound(oracle):
     # With bf16 storage and Ks <= 17 the fp32 large-kernel weights are rounded to bf16 on
     # the device (operands of the bf16 matrix instructions).  Bound asserted here: the normwise error
