@@ -1426,7 +1426,8 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
     constexpr int TX = std::is_same<T, float>::value ? 2 : 1;
     using SG = SplitGeom<KS, RY, TX>;
     bool split = false;   // block-uniform
-    int wback = 0, xback = 0;   // the powers of two that bring the weights and the tile's values back to their size
+    int back = 0;        // the power of two that brings the products back to their size
+    float xback = 1.f;   // and the one that brings the values
     if constexpr (kSplit) {
         // a thread takes two columns of every fourth row, and two elements of every eighth weight row
         constexpr int KU = (SG::HRP + 3) / 4, KWU = (KS + 1 + 7) / 8;
@@ -1471,12 +1472,12 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
             return m;
         };
         const BlockRange mx{all(0), all(1)}, mw{all(2), all(3)};
-        split = mx.finite() && mw.large < 0x72000000u && mx.narrow() && mw.narrow();   // (weights below 2^101: values stay 2^15 large until the end)
+        split = mx.finite() && mw.finite() && mx.narrow() && mw.narrow();
         if (split) {
             // powers of two that bring the largest to 2^14 ... 2^15 (as far as fp32 reaches)
             const int ex = min(14 + 127 - mx.exponent(), 126), ew = min(14 + 127 - mw.exponent(), 126);
             const float fx = __uint_as_float((unsigned)(127 + ex) << 23), fw = __uint_as_float((unsigned)(127 + ew) << 23);
-            wback = -ew, xback = -ex;
+            back = -ex - ew, xback = __uint_as_float((unsigned)(127 - ex) << 23);
             uint32_t *dst = tile_d + ((tc >> 2) * SG::HRP + tr) * 4 + (tc & 3);
             uint32_t *sw = reinterpret_cast<uint32_t *>(g_wl) + wr * SG::WROW + wc;
 #pragma unroll
@@ -1815,7 +1816,7 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
 #pragma unroll
             for (int t = 0; t < RY; ++t)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) acc[t][q] = __builtin_amdgcn_ldexpf(fmaf(lo[t][q], 1.f / kLowTerm, hi[t][q]), wback);
+                for (int q = 0; q < 4; ++q) acc[t][q] = __builtin_amdgcn_ldexpf(fmaf(lo[t][q], 1.f / kLowTerm, hi[t][q]), back);
         }
     } else if (G::UNROLL && !kSplit) {
 #pragma unroll
@@ -1922,7 +1923,7 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
         }
         if constexpr (kSplit) {
             if (split) {
-                // as on the bf16 matrix path, from the terms
+                // as on the bf16 matrix path, from the terms, at the values' own size: DK may be of any
                 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 #pragma unroll
                 for (int t = 0; t < RY; ++t) {
@@ -1935,10 +1936,10 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
                         for (int k = 0; k < 4; ++k) {
                             const int w = wi - 1 + k, at = ((w >> 2) * SG::HRP + row) * 4 + (w & 3);
                             const f16x2 h = __builtin_bit_cast(f16x2, tile_d[at]);
-                            v[2 * k] = (float)h.x, v[2 * k + 1] = (float)h.y;
+                            v[2 * k] = (float)h.x * xback, v[2 * k + 1] = (float)h.y * xback;
                             if constexpr (TX > 1) {
                                 const f16x2 l = __builtin_bit_cast(f16x2, tile_d[SG::TERM_WORDS + at]);
-                                v[2 * k] = fmaf((float)l.x, 1.f / kLowTerm, v[2 * k]), v[2 * k + 1] = fmaf((float)l.y, 1.f / kLowTerm, v[2 * k + 1]);
+                                v[2 * k] = fmaf((float)l.x, xback / kLowTerm, v[2 * k]), v[2 * k + 1] = fmaf((float)l.y, xback / kLowTerm, v[2 * k + 1]);
                             }
                         }
 #pragma unroll
@@ -1972,12 +1973,6 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
         }
     }
 
-    if (kSplit && split) {
-#pragma unroll
-        for (int t = 0; t < RY; ++t)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) acc[t][q] = __builtin_amdgcn_ldexpf(acc[t][q], xback);
-    }
     if (p->dk_mode == kDkNone) claim_next(p, ctx);
     // (only in the kernel flavour that calls with such a constant are sent to: the flavour
     // the short forward calls use stays free of it)

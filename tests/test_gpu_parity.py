@@ -496,6 +496,20 @@ def test_large_kernels_of_wide_range(oracle, dtype, Ks, N, H, W):
         assert (np.abs(got - ref) <= bound).all(), (what, (np.abs(got - ref) / bound).max())
 
 
+@pytest.mark.parametrize("dtype,Ks", [(F32, 15), (F32, 17), (F32, 31), (BF16, 19), (BF16, 31)])
+def test_large_kernels_with_dk_of_any_size(oracle, dtype, Ks):
+    # DK of up to 2^120 and weights of up to 2^125 on values whose products are ordinary numbers
+    wl = wk.make_random(935 + Ks, 1, 4, 33, 70, 4, Ks, dtype=dtype)
+    dk = np.random.default_rng(936).standard_normal((1, 4, 3, 3)).astype(np.float32)
+    x0, lk0 = wl.x_as_f32(), wl.lk.copy()
+    for what, fx, fw, fd in (("dk", 2.0 ** -100, 1.0, 2.0 ** 120), ("weights", 2.0 ** -100, 2.0 ** 125, 2.0 ** 100), ("large x", 2.0 ** 100, 2.0 ** -120, 2.0 ** -110)):
+        print(f"[case] {what} {dtype} Ks={Ks}", flush=True)
+        xf = (x0 * fx).astype(np.float32)
+        wl.x, wl.lk, d = (wk.f32_to_bf16_bits(xf) if dtype == BF16 else xf), (lk0 * fw).astype(np.float32), (dk * fd).astype(np.float32)
+        ref, _, _ = oracle.convattn_forward(wl.x, 4, wl.lk, dtype, dk_in=d, want_out=False)
+        gu.assert_att_close(gu.att_as_f64(gu.run_forward(wl, use_gen=False, dk_in=d), wl), ref, dtype, what)
+
+
 def test_bf16_large_kernel_weight_rounding_error_bound(oracle):
     # With bf16 storage and Ks <= 17 the fp32 large-kernel weights are rounded to bf16 on
     # the device (operands of the bf16 matrix instructions).  Bound asserted here: the normwise error
