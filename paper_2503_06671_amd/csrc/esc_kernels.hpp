@@ -1818,7 +1818,9 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) acc[t][q] = __builtin_amdgcn_ldexpf(fmaf(lo[t][q], 1.f / kLowTerm, hi[t][q]), back);
         }
-    } else if (G::UNROLL && !kSplit) {
+    } else if (G::UNROLL) {
+        // (with the kernel rows re-read instead, as below, tiles that SplitGeom leaves to this loop take longer: 540 x 960
+        // fp32, each with a value of 1e10, Ks = 17 83.7 us a call, so 77.4, Ks = 15 73.6 and 68.5; ordinary ones alike)
 #pragma unroll
         for (int r0 = 0; r0 < G::ROWS; r0 += RY)
 #pragma unroll
@@ -1828,7 +1830,7 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
                     step(r0 + u, u);
                 }
     } else {
-        // Large kernels: a loop, two rows per trip; the kernel rows are re-read from LDS for
+        // Large kernels: a loop, one tile row per trip; the kernel rows are re-read from LDS for
         // every output row instead of being held (they would not fit in the registers).
 #pragma unroll 1
         for (int r = 0; r < G::ROWS; ++r) {
@@ -1845,7 +1847,6 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
             }
             __builtin_amdgcn_sched_barrier(0);  // one row's loads at a time: the registers are few
         }
-        if (G::UNROLL) ask_again();
     }
     __builtin_amdgcn_s_setprio(kPrioHigh);
 
