@@ -21,6 +21,7 @@
 
 #include "esc_backward.hpp"
 #include "esc_estimator.hpp"
+#include "esc_terms.hpp"
 
 namespace esc {
 namespace {

@@ -378,13 +378,15 @@ __global__ __launch_bounds__(kDnThreads, CT <= 2 ? 2 : 1) void dense_kernel(cons
 // storage: the stored values are the operands; each fp32 weight enters as two bf16 terms,
 // w = hi + lo to 16 mantissa bits, so two instructions per operand pair, products exact,
 // accumulation fp32.  fp32 storage (kernels up to 13 x 13): the 16-bit instructions are sixteen
-// times as fast as the fp32 ones, so values and weights enter as fp16 terms (dn_split_f16), the values of a
+// times as fast as the fp32 ones, so values and weights enter as fp16 terms (split_f16), the values of a
 // tile behind a power of two that brings its largest to 2^14 ... 2^15, the weights of an output channel behind
-// another (the largest of each is found by the preparing launch, a power a tile or channel at a time): a value
-// as three terms, exact, a weight as two, and four of the six products of terms are accumulated - what is
-// left out lies below 2^-22 of a product and a weight's second term ends within a unit of fp32's last place.
-// (Before: three bf16 terms each and six products.  180 x 320, 13 x 13 35.4 -> 31.1 us a call, 360 x 640 105.5 -> 93.8,
-// error against float64 2.0e-7 -> 1.5e-7.  Values as two terms, three products: 27.8 us at the same error, but then
+// another (their range is found by the preparing launch): a value as three terms, exact, a weight as two, and four of the
+// six products of terms are accumulated, those with a low term apart - what is left out lies below 2^-22 of a product and a weight's
+// second term ends within a unit of fp32's last place.  A tile, or a kernel, whose magnitudes lie further apart than fp16 terms
+// reach (BlockRange) or that has infinities or NaN in it takes the terms that have fp32's exponents, three bf16 ones of values and
+// weights, and six products.
+// (180 x 320, 13 x 13: three bf16 terms for all 36.4 us a call, so 31.2, such tiles alone 39; 360 x 640 108.4 and 99.1, 64 x 64 21.0
+// and 20.2; error against float64 2.0e-7 and 1.0e-7.  Values as two fp16 terms, three products: 3 us less, but then
 // a kernel of a single one no longer moves the values as they are.)  The halo tile sits in LDS pixel-major, as cells of 16 bytes = eight
 // channels of one pixel, in two half planes (channels 0-7, 8-15): the sixteen lanes that read
 // one B operand's pixels read 256 consecutive bytes, the only pattern in which 16-byte LDS
@@ -417,25 +419,6 @@ __host__ __device__ constexpr int bf_aux_cell(int Kse, int th, int nx)
 }
 inline size_t bf_lds_bytes(int Kse, int th, int nx) { return (size_t)bf_aux_cell(Kse, th, nx) * 16 + 16 * 9 * sizeof(float); }
 
-// fp32 storage: fp16 terms, each the nearest to what the ones before it left, two values at a time.  Two are within a unit of
-// fp32's last place (and miss it in a quarter of the values), three are exact, for magnitudes from 2^15 down to 1;
-// below that all beyond 2^-25 is lost.
-template <int N>
-__device__ __forceinline__ void dn_split_f16(float v0, float v1, uint32_t (&t)[N])
-{
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-#pragma unroll
-    for (int q = 0; q < N; ++q) {
-        const f16x2 h = __builtin_convertvector(f32x2{v0, v1}, f16x2);
-        t[q] = __builtin_bit_cast(uint32_t, h);
-        v0 -= (float)h.x, v1 -= (float)h.y;
-    }
-}
-// the power of two that brings a magnitude of these bits to 2^14 ... 2^15, as far as fp32 reaches
-__device__ __forceinline__ int dn_exponent(unsigned bits) { return min(14 + 127 - (int)(bits >> 23), 126); }
-__device__ __forceinline__ float dn_power(int e) { return __uint_as_float((unsigned)(127 + e) << 23); }
-
 // What the matrix path needs before its first block: the A-operand table (dense_table_entry, one thread per
 // entry) and, where DK comes from the estimator, the pool tiles' sums - four tiles a block, in the forward's pool
 // items' order - and DK's places marked empty.  Nothing here waits for another block: the pooled means and the
@@ -450,14 +433,20 @@ __global__ __launch_bounds__(kDnThreads) void dense_prep_kernel(const DenseParam
         constexpr bool terms = !std::is_same<T, float>::value;
         const int part = (int)(blockIdx.x - n_pool), idx = part * kDnThreads + tid;
         uint32_t *wa = reinterpret_cast<uint32_t *>(p.wt);
-        unsigned m = idx < dense_table_entries(p.Ks) ? dense_table_entry(lk, p.Ca, Ks, p.Ks, terms, wa, idx) : 0u;
+        BlockRange m;
+        if (idx < dense_table_entries(p.Ks)) m = BlockRange(dense_table_entry(lk, p.Ca, Ks, p.Ks, terms, wa, idx));
         if constexpr (!terms) {
-            __shared__ unsigned s_max[kDnThreads / 64][16];
-            m = max(m, (unsigned)__shfl_xor((int)m, 16));
-            m = max(m, (unsigned)__shfl_xor((int)m, 32));
-            if ((tid & 63) < 16) s_max[tid >> 6][tid & 15] = m;
+            __shared__ uint2 s_range[kDnThreads / 64][16];
+#pragma unroll
+            for (int d = 16; d < 64; d *= 2) m.merge((unsigned)__shfl_xor((int)m.large, d), (unsigned)__shfl_xor((int)m.small, d));
+            if ((tid & 63) < 16) s_range[tid >> 6][tid & 15] = make_uint2(m.large, m.small);
             __syncthreads();
-            if (tid < 16) wa[dense_table_words(p.Ks) + part * 16 + tid] = max(max(s_max[0][tid], s_max[1][tid]), max(s_max[2][tid], s_max[3][tid]));
+            if (tid < 16) {
+                m = BlockRange();
+#pragma unroll
+                for (int w = 0; w < kDnThreads / 64; ++w) m.merge(s_range[w][tid].x, s_range[w][tid].y);
+                reinterpret_cast<uint2 *>(wa + dense_table_words(p.Ks))[part * 16 + tid] = make_uint2(m.large, m.small);
+            }
         }
         return;
     }
@@ -545,8 +534,7 @@ __global__ __launch_bounds__(kDnThreads, 2) void dense_bf16_kernel(const DensePa
     typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
     typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
     constexpr bool kF32 = std::is_same<T, float>::value;
-    constexpr int NX = kF32 ? 3 : 1;  // terms of a stored value (one tile in LDS per term; fp32 storage: fp16 terms)
-    constexpr int NW = 2;             // terms of a weight
+    constexpr int NX = kF32 ? 3 : 1;  // terms of a stored value (one tile in LDS per term)
     constexpr int NA = 2 * TH;  // runs of 16 pixels in the tile: run nt = row nt / 2, columns 16 (nt % 2) ..
     constexpr int NT = TH / 2;  // runs whose results a wavefront ends up with
     constexpr int pad = (KS - 1) / 2, HR = TH + 2 * pad, HP = HR * kBfPitch;
@@ -630,32 +618,56 @@ __global__ __launch_bounds__(kDnThreads, 2) void dense_bf16_kernel(const DensePa
         }
     };
 
-    // fp32 storage: the largest weight of this lane's output channel, from what the preparing launch's blocks found
-    // (asked for in front of the tile, looked at behind it)
+    // fp32 storage: the range of this lane's output channel's weights, from what the preparing launch's blocks found
+    // (asked for in front of the tile, looked at with it)
     constexpr int kParts = kF32 ? ((KS + 1) / 2 * KS * 64 + 255) / 256 : 0, kMine = (kParts + 3) / 4;
-    unsigned wmax[kMine > 0 ? kMine : 1];
+    uint2 found[kMine > 0 ? kMine : 1];
     if constexpr (kF32) {
-        const unsigned *found = reinterpret_cast<const unsigned *>(p.wt) + dense_table_words(KS) + l16;
+        const uint2 *src = reinterpret_cast<const uint2 *>(reinterpret_cast<const unsigned *>(p.wt) + dense_table_words(KS)) + l16;
 #pragma unroll
-        for (int k = 0; k < kMine; ++k) wmax[k] = found[(4 * k + kq < kParts ? 4 * k + kq : kParts - 1) * 16];
+        for (int k = 0; k < kMine; ++k) found[k] = src[(4 * k + kq < kParts ? 4 * k + kq : kParts - 1) * 16];
     }
 
     // ---- the zero-extended halo tile, pixel-major ----
-    // fp32 storage: the tile's largest finite magnitude, which every wavefront looks its own values through for
-    // and all meet at a barrier for; a value that is not finite is not in it and comes out as inf and NaN terms.
-    int xexp = 0;
-    auto tile_exponent = [&](auto each) {
-        unsigned *s_max = reinterpret_cast<unsigned *>(s_dk);   // (DK comes there later)
-        unsigned m = 0;
-        each([&](float v) { m = max(m, __float_as_uint(v) & 0x7fffffffu); });
-        if (__builtin_amdgcn_ballot_w64(m >= 0x7f800000u) != 0) {
-            m = 0;
-            each([&](float v) { const unsigned b = __float_as_uint(v) & 0x7fffffffu; m = max(m, b < 0x7f800000u ? b : 0u); });
+    // fp32 storage: whether fp16 terms hold all of the tile's values and all weights, and the powers of two they take for it (of
+    // the tile; of output channel l16).  Every wavefront looks its own values through and all meet at a barrier.
+    bool wide = false;   // block-uniform
+    int xexp = 0, wexp = 0;
+    auto take_range = [&](auto each) {
+        if constexpr (kF32) {
+            uint2 *s_range = reinterpret_cast<uint2 *>(s_dk);   // (DK comes there later)
+            Range r;
+            each(r);
+            const BlockRange mine(r);
+            const unsigned large = wave_max(mine.large), small = wave_max(mine.small);
+            if (lane == 63) s_range[wave] = make_uint2(large, small);
+            BlockRange wr;
+#pragma unroll
+            for (int k = 0; k < kMine; ++k) wr.merge(found[k].x, found[k].y);
+#pragma unroll
+            for (int d = 16; d < 64; d *= 2) wr.merge((unsigned)__shfl_xor((int)wr.large, d), (unsigned)__shfl_xor((int)wr.small, d));
+            __syncthreads();
+            BlockRange xr;
+#pragma unroll
+            for (int w = 0; w < kDnThreads / 64; ++w) xr.merge(s_range[w].x, s_range[w].y);
+            wide = !xr.finite() || !xr.narrow() || __builtin_amdgcn_ballot_w64(!wr.finite() || !wr.narrow()) != 0;
+            if (!wide) xexp = xr.up(), wexp = wr.up();
         }
-        m = wave_max(m);
-        if (lane == 63) s_max[wave] = m;
-        __syncthreads();
-        xexp = dn_exponent(max(max(s_max[0], s_max[1]), max(s_max[2], s_max[3])));
+    };
+    // a step for either kind of terms, `wide` known when it is compiled (as a branch inside, it would be one per value)
+    auto either = [&](auto step) {
+        if (wide)
+            step(std::true_type{});
+        else
+            step(std::false_type{});
+    };
+    auto split_x = [&](auto w, float v0, float v1, uint32_t (&t)[3]) {
+        if constexpr (decltype(w)::value) {
+            split_bf16(v0, v1, t);
+        } else {
+            const float f = power_of_two(xexp);
+            split_f16(v0 * f, v1 * f, t);
+        }
     };
     if (kF32 && p.fill_vec) {
         // fp32 storage: the same tasks, 32 bytes (eight pixels) of each of eight channels per task, at most one per thread,
@@ -681,29 +693,30 @@ __global__ __launch_bounds__(kDnThreads, 2) void dense_bf16_kernel(const DensePa
 #pragma unroll
                 for (int h = 0; h < 2; ++h)
                     if (!in || 8 * h2 + e >= p.Ca) v[e][h] = u32x4{0u, 0u, 0u, 0u};
-            tile_exponent([&](auto look) {
+            take_range([&](Range &range) {
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
 #pragma unroll
-                    for (int d = 0; d < 8; ++d) look(__uint_as_float(v[e][d >> 2][d & 3]));
+                    for (int d = 0; d < 8; d += 2) range.look(__uint_as_float(v[e][d >> 2][d & 3]), __uint_as_float(v[e][d >> 2][(d & 3) + 1]));
             });
-            const float f = dn_power(xexp);
             u32x4 *dst = s_cells + h2 * HP + r * kBfPitch + 8 * pc;
+            either([&](auto kind) {
 #pragma unroll
-            for (int d = 0; d < 8; ++d) {
-                u32x4 cell[NX];  // pixel d of the piece, one cell per term
+                for (int d = 0; d < 8; ++d) {
+                    u32x4 cell[NX];  // pixel d of the piece, one cell per term
 #pragma unroll
-                for (int w = 0; w < 4; ++w) {
-                    uint32_t t[NX];
-                    dn_split_f16(__uint_as_float(v[2 * w][d >> 2][d & 3]) * f, __uint_as_float(v[2 * w + 1][d >> 2][d & 3]) * f, t);
+                    for (int w = 0; w < 4; ++w) {
+                        uint32_t t[NX];
+                        split_x(kind, __uint_as_float(v[2 * w][d >> 2][d & 3]), __uint_as_float(v[2 * w + 1][d >> 2][d & 3]), t);
 #pragma unroll
-                    for (int q = 0; q < NX; ++q) cell[q][w] = t[q];
+                        for (int q = 0; q < NX; ++q) cell[q][w] = t[q];
+                    }
+                    if (tid < tasks) {
+#pragma unroll
+                        for (int q = 0; q < NX; ++q) dst[q * TILE + d] = cell[q];
+                    }
                 }
-                if (tid < tasks) {
-#pragma unroll
-                    for (int q = 0; q < NX; ++q) dst[q * TILE + d] = cell[q];
-                }
-            }
+            });
         }
     } else if (p.fill_vec) {
         // task = (half, piece of eight columns, row), lanes on consecutive rows; at most two per thread
@@ -776,28 +789,27 @@ __global__ __launch_bounds__(kDnThreads, 2) void dense_bf16_kernel(const DensePa
                 }
             }
             if constexpr (kF32) {
-                tile_exponent([&](auto look) {
+                take_range([&](Range &range) {
 #pragma unroll
-                    for (int u = 0; u < U; ++u)
-#pragma unroll
-                        for (int e = 0; e < E; ++e) look(v[u][e]);
+                    for (int u = 0; u < U; ++u) range.look(v[u][0], v[u][E - 1]);
                 });
             }
-            const float f = dn_power(xexp);
+            either([&](auto kind) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                int ci, r, c;
-                const bool some = where(u, ci, r, c);
-                char *at = s_bytes + (size_t)((ci >> 3) * HP + r * kBfPitch + c) * 16 + (ci & 7) * 2;
-                if constexpr (kF32) {
-                    uint32_t t[NX];
-                    dn_split_f16(v[u][0] * f, v[u][E - 1] * f, t);
+                for (int u = 0; u < U; ++u) {
+                    int ci, r, c;
+                    const bool some = where(u, ci, r, c);
+                    char *at = s_bytes + (size_t)((ci >> 3) * HP + r * kBfPitch + c) * 16 + (ci & 7) * 2;
+                    if constexpr (kF32) {
+                        uint32_t t[NX];
+                        split_x(kind, v[u][0], v[u][E - 1], t);
 #pragma unroll
-                    for (int q = 0; q < NX; ++q) *reinterpret_cast<uint32_t *>(at + (size_t)q * TILE * 16) = t[q];
-                } else if (some) {
-                    *reinterpret_cast<uint16_t *>(at) = (uint16_t)(__float_as_uint(v[u][0]) >> 16);   // (the stored value)
+                        for (int q = 0; q < NX; ++q) *reinterpret_cast<uint32_t *>(at + (size_t)q * TILE * 16) = t[q];
+                    } else if (some) {
+                        *reinterpret_cast<uint16_t *>(at) = (uint16_t)(__float_as_uint(v[u][0]) >> 16);   // (the stored value)
+                    }
                 }
-            }
+            });
         }
     }
     __syncthreads();
@@ -807,18 +819,9 @@ __global__ __launch_bounds__(kDnThreads, 2) void dense_bf16_kernel(const DensePa
     unsigned dk_bits = 0;
 
     // ---- the contraction ----
-    int wexp = 0;   // of output channel l16
-    if constexpr (kF32) {
-        unsigned m = wmax[0];
+    f32x4 part[NA], low[kF32 ? NA : 1];   // (fp32 storage on fp16 terms: products with a low term apart, 4096 times too large)
 #pragma unroll
-        for (int k = 1; k < kMine; ++k) m = max(m, wmax[k]);
-        m = max(m, (unsigned)__shfl_xor((int)m, 16));
-        wexp = dn_exponent(max(m, (unsigned)__shfl_xor((int)m, 32)));
-    }
-    const float wscale = dn_power(wexp);
-    f32x4 part[NA];
-#pragma unroll
-    for (int nt = 0; nt < NA; ++nt) part[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int nt = 0; nt < NA; ++nt) part[nt] = low[kF32 ? nt : 0] = f32x4{0.f, 0.f, 0.f, 0.f};
     {
         constexpr int NJP = (KS + 1) / 2;                // pairs of tap columns
         constexpr int kBase = KS / 4, kExtra = KS % 4;   // kernel rows per wavefront: kBase, one more for kExtra of the four
@@ -831,7 +834,7 @@ __global__ __launch_bounds__(kDnThreads, 2) void dense_bf16_kernel(const DensePa
             i0 = pos * kBase + (pos < kExtra ? pos : kExtra);
             cnt = kBase + (pos < kExtra ? 1 : 0);
         };
-        auto fetch_a = [&](int jp, u32x4 (&a)[MB][NW]) {
+        auto fetch_a = [&](int jp, u32x4 (&a)[MB][2]) {
             int i0, cnt;
             rows_of(jp, i0, cnt);
 #pragma unroll
@@ -839,36 +842,36 @@ __global__ __launch_bounds__(kDnThreads, 2) void dense_bf16_kernel(const DensePa
                 int i = i0 + (m < cnt ? m : 0);
                 i = i < KS ? i : KS - 1;
 #pragma unroll
-                for (int t = 0; t < NW; ++t) a[m][t] = wa[((size_t)(jp * KS + i) * NW + t) * 64];
+                for (int t = 0; t < 2; ++t) a[m][t] = wa[((size_t)(jp * KS + i) * 2 + t) * 64];
             }
         };
-        // the products of a value's and a weight's terms that are accumulated, small ones first:
-        // bf16 storage (value, lo) and (value, hi); fp32 storage the value's three terms with the weight's first (weights
-        // of eleven bits give exact products) and its first with the weight's second: what is left out lies below 2^-22 of the product
-        constexpr int NP = kF32 ? 4 : 2;
-        auto px = [&](int q) { return q == 0 ? 0 : NP - 1 - q; };
-        auto pw = [&](int q) { return q == 0 ? 1 : 0; };
-        auto mma = [&](const u32x4 &a, const u32x4 &b, f32x4 &c) {
-            if constexpr (kF32)
-                c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
-            else
-                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-        };
-        // fp32 storage: the table's weights as two fp16 terms
-        auto take = [&](u32x4 (&a)[MB][NW]) {
+        // fp32 storage: the table's weights as two fp16 terms, or as three bf16 ones
+        auto weight = [](const u32x4 (&a)[2], int k) { return __uint_as_float(a[k >> 2][k & 3]); };
+        auto take = [&](u32x4 (&a)[MB][2]) {
             if constexpr (kF32) {
+                const float f = power_of_two(wexp);
 #pragma unroll
                 for (int m = 0; m < MB; ++m) {
-                    const u32x4 w0 = a[m][0], w1 = a[m][1];
+                    const u32x4 w[2] = {a[m][0], a[m][1]};
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
                         uint32_t t[2];
-                        const u32x4 &w = k < 2 ? w0 : w1;
-                        dn_split_f16(__uint_as_float(w[2 * (k & 1)]) * wscale, __uint_as_float(w[2 * (k & 1) + 1]) * wscale, t);
+                        split_f16(weight(w, 2 * k) * f, weight(w, 2 * k + 1) * f, t);
                         a[m][0][k] = t[0], a[m][1][k] = t[1];
                     }
                 }
             }
+        };
+        auto take_wide = [&](const u32x4 (&w)[MB][2], u32x4 (&a)[MB][3]) {
+#pragma unroll
+            for (int m = 0; m < MB; ++m)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    uint32_t t[3];
+                    split_bf16(weight(w[m], 2 * k), weight(w[m], 2 * k + 1), t);
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) a[m][q][k] = t[q];
+                }
         };
         // a walk's piece of the pass-through copy: asked for at its start, behind the next
         // pair's A operands (which are waited for first), stored at the end of the NEXT walk -
@@ -887,13 +890,12 @@ __global__ __launch_bounds__(kDnThreads, 2) void dense_bf16_kernel(const DensePa
                 if (jp >= 0 && o + 16 <= walk_len) __builtin_nontemporal_store(cv[g], reinterpret_cast<u32x4 *>(walk_dst + o));
             }
         };
-        auto walk = [&](int jp, u32x4 (&a)[MB][NW], u32x4 (&a_next)[MB][NW], u32x4 (&cv)[kWalkGrains],
-                        const u32x4 (&cv_before)[kWalkGrains]) {
+        // one pair of tap columns, a weight as `terms` terms; `ahead` asks for what comes next
+        auto walk = [&](auto terms, int jp, const u32x4 (&a)[MB][decltype(terms)::value], auto ahead) {
+            constexpr int NW = decltype(terms)::value;
             int i0, cnt;
             rows_of(jp, i0, cnt);
-            take(a);
-            fetch_a(jp + 1 < NJP ? jp + 1 : jp, a_next);
-            copy_ask(jp, cv);
+            ahead();
             const bool full = cnt == MB;  // wavefront-uniform
             // this lane's B operand for tile row i0, half 0: its tap column's shift (the empty
             // column reads the one before it), its half plane, its pixel
@@ -908,6 +910,20 @@ __global__ __launch_bounds__(kDnThreads, 2) void dense_bf16_kernel(const DensePa
                     bb[1][t] = *reinterpret_cast<const u32x4 *>(bp + (t * TILE + R * kBfPitch) * 16 + 256);
                 }
             };
+            // the products of a value's and a weight's terms that are accumulated, small ones first: bf16 storage (value, lo) and
+            // (value, hi); fp16 terms the value's three with the weight's first (weights of eleven bits give exact products) and its
+            // first with the weight's second, what is left out lies below 2^-22 of the product; three bf16 terms each the six
+            // whose orders add up to at most two, what is left out lies below 2^-24
+            constexpr int NP = !kF32 ? 2 : NW == 2 ? 4 : 6;
+            auto mma = [&](int q, int m, const u32x4 (&bb)[NX], int nt) {
+                constexpr int kPx[6] = {2, 0, 1, 1, 0, 0}, kPw[6] = {0, 2, 1, 0, 1, 0};
+                const int qx = NP == 6 ? kPx[q] : q == 0 ? 0 : NP - 1 - q, qw = NP == 6 ? kPw[q] : q == 0 ? 1 : 0;
+                f32x4 &c = NP == 4 && qx + qw > 0 ? low[kF32 ? nt : 0] : part[nt];
+                if constexpr (NP == 4)
+                    c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a[m][qw]), __builtin_bit_cast(f16x8, bb[qx]), c, 0, 0, 0);
+                else
+                    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[m][qw]), __builtin_bit_cast(bf16x8, bb[qx]), c, 0, 0, 0);
+            };
             read_b(0, b[0]);
 #pragma unroll
             for (int R = 0; R < NR; ++R) {
@@ -920,29 +936,50 @@ __global__ __launch_bounds__(kDnThreads, 2) void dense_bf16_kernel(const DensePa
 #pragma unroll
                     for (int m = 0; m < MB - 1; ++m)
                         if (R - m >= 0 && R - m < TH) {
-                            mma(a[m][pw(q)], b[R & 1][0][px(q)], part[2 * (R - m)]);
-                            mma(a[m][pw(q)], b[R & 1][1][px(q)], part[2 * (R - m) + 1]);
+                            mma(q, m, b[R & 1][0], 2 * (R - m));
+                            mma(q, m, b[R & 1][1], 2 * (R - m) + 1);
                         }
                 if (R - (MB - 1) >= 0 && R - (MB - 1) < TH && full) {
 #pragma unroll
                     for (int q = 0; q < NP; ++q) {
-                        mma(a[MB - 1][pw(q)], b[R & 1][0][px(q)], part[2 * (R - (MB - 1))]);
-                        mma(a[MB - 1][pw(q)], b[R & 1][1][px(q)], part[2 * (R - (MB - 1)) + 1]);
+                        mma(q, MB - 1, b[R & 1][0], 2 * (R - (MB - 1)));
+                        mma(q, MB - 1, b[R & 1][1], 2 * (R - (MB - 1)) + 1);
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
+        };
+        u32x4 a0[MB][2], a1[MB][2], cv0[kWalkGrains] = {}, cv1[kWalkGrains] = {};
+        auto pair = [&](int jp, u32x4 (&a)[MB][2], u32x4 (&a_next)[MB][2], u32x4 (&cv)[kWalkGrains], const u32x4 (&cv_before)[kWalkGrains]) {
+            take(a);
+            walk(std::integral_constant<int, 2>{}, jp, a, [&] {
+                fetch_a(jp + 1 < NJP ? jp + 1 : jp, a_next);
+                copy_ask(jp, cv);
+            });
             copy_put(jp - 1, cv_before);
         };
-        u32x4 a0[MB][NW], a1[MB][NW], cv0[kWalkGrains] = {}, cv1[kWalkGrains] = {};
-        fetch_a(0, a0);
+        if (kF32 && wide) {
+            if constexpr (kF32) {
+#pragma unroll 1
+                for (int jp = 0; jp < NJP; ++jp) {   // (nothing is asked for ahead: there are no registers for it)
+                    u32x4 a[MB][3];
+                    fetch_a(jp, a0);
+                    take_wide(a0, a);
+                    walk(std::integral_constant<int, 3>{}, jp, a, [&] { copy_ask(jp, cv0); });
+                    copy_put(jp, cv0);
+                }
+                if (p.dk != nullptr) dk_bits = __hip_atomic_load(dk_at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        } else {
+            fetch_a(0, a0);
 #pragma unroll
-        for (int jp = 0; jp < NJP; jp += 2) {
-            if (jp + 2 >= NJP && p.dk != nullptr) dk_bits = __hip_atomic_load(dk_at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            walk(jp, a0, a1, cv0, cv1);
-            if (jp + 1 < NJP) walk(jp + 1, a1, a0, cv1, cv0);
+            for (int jp = 0; jp < NJP; jp += 2) {
+                if (jp + 2 >= NJP && p.dk != nullptr) dk_bits = __hip_atomic_load(dk_at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                pair(jp, a0, a1, cv0, cv1);
+                if (jp + 1 < NJP) pair(jp + 1, a1, a0, cv1, cv0);
+            }
+            copy_put(NJP - 1, (NJP - 1) % 2 == 0 ? cv0 : cv1);
         }
-        copy_put(NJP - 1, (NJP - 1) % 2 == 0 ? cv0 : cv1);
     }
 
     // ---- DK's nine depth-wise taps for the runs this wavefront ends up with, from the same
@@ -965,35 +1002,43 @@ __global__ __launch_bounds__(kDnThreads, 2) void dense_bf16_kernel(const DensePa
         for (int r = 0; r < 4; ++r)
 #pragma unroll
             for (int k = 0; k < 9; ++k) d[r][k] = s_dk[(4 * kq + r) * 9 + k];
+        either([&](auto kind) {
 #pragma unroll
-        for (int m = 0; m < NT; ++m) {
-            const int nt = wave * NT + m, rr = nt >> 1, c = 16 * (nt & 1);
-            const char *src = s_bytes + (size_t)((kq >> 1) * HP + (rr + pad - 1) * kBfPitch + c + l16 + 7) * 16 + 8 * (kq & 1);
+            for (int m = 0; m < NT; ++m) {
+                const int nt = wave * NT + m, rr = nt >> 1, c = 16 * (nt & 1);
+                const char *src = s_bytes + (size_t)((kq >> 1) * HP + (rr + pad - 1) * kBfPitch + c + l16 + 7) * 16 + 8 * (kq & 1);
 #pragma unroll
-            for (int di = 0; di < 3; ++di)
+                for (int di = 0; di < 3; ++di)
 #pragma unroll
-                for (int dj = 0; dj < 3; ++dj) {
-                    float xv[4];  // the value: fp32 storage the sum of its terms
-                    const u32x2 v = *reinterpret_cast<const u32x2 *>(src + (di * kBfPitch + dj) * 16);
-                    if constexpr (kF32) {
-                        const u32x2 low = *reinterpret_cast<const u32x2 *>(src + (TILE + di * kBfPitch + dj) * 16);
-                        const u32x2 last = *reinterpret_cast<const u32x2 *>(src + (2 * TILE + di * kBfPitch + dj) * 16);
+                    for (int dj = 0; dj < 3; ++dj) {
+                        float xv[4];  // the value: fp32 storage the sum of its terms
+                        const u32x2 v = *reinterpret_cast<const u32x2 *>(src + (di * kBfPitch + dj) * 16);
+                        if constexpr (kF32) {
+                            const u32x2 second = *reinterpret_cast<const u32x2 *>(src + (TILE + di * kBfPitch + dj) * 16);
+                            const u32x2 last = *reinterpret_cast<const u32x2 *>(src + (2 * TILE + di * kBfPitch + dj) * 16);
 #pragma unroll
-                        for (int u = 0; u < 2; ++u) {
-                            const uint32_t hb = v[u], lb = low[u], tb = last[u];
-                            const f16x2 h = __builtin_bit_cast(f16x2, hb), l = __builtin_bit_cast(f16x2, lb), e = __builtin_bit_cast(f16x2, tb);
-                            xv[2 * u] = (float)h.x + ((float)l.x + (float)e.x), xv[2 * u + 1] = (float)h.y + ((float)l.y + (float)e.y);
+                            for (int u = 0; u < 2; ++u) {
+                                const uint32_t hb = v[u], lb = second[u], tb = last[u];
+                                if constexpr (decltype(kind)::value) {
+                                    xv[2 * u] = __uint_as_float(hb << 16) + (__uint_as_float(lb << 16) + __uint_as_float(tb << 16));
+                                    xv[2 * u + 1] = __uint_as_float(hb & 0xffff0000u) + (__uint_as_float(lb & 0xffff0000u) + __uint_as_float(tb & 0xffff0000u));
+                                } else {   // (exact: the terms' bits do not overlap)
+                                    const f16x2 h = __builtin_bit_cast(f16x2, hb), l = __builtin_bit_cast(f16x2, lb), e = __builtin_bit_cast(f16x2, tb);
+                                    xv[2 * u] = fmaf((float)l.x + (float)e.x, 1.f / kLowTerm, (float)h.x);
+                                    xv[2 * u + 1] = fmaf((float)l.y + (float)e.y, 1.f / kLowTerm, (float)h.y);
+                                }
+                            }
+                        } else {
+                            xv[0] = __uint_as_float(v[0] << 16);
+                            xv[1] = __uint_as_float(v[0] & 0xffff0000u);
+                            xv[2] = __uint_as_float(v[1] << 16);
+                            xv[3] = __uint_as_float(v[1] & 0xffff0000u);
                         }
-                    } else {
-                        xv[0] = __uint_as_float(v[0] << 16);
-                        xv[1] = __uint_as_float(v[0] & 0xffff0000u);
-                        xv[2] = __uint_as_float(v[1] << 16);
-                        xv[3] = __uint_as_float(v[1] & 0xffff0000u);
-                    }
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) acc[m][r] = fmaf(d[r][di * 3 + dj], xv[r], acc[m][r]);
-                }
-        }
+                        for (int r = 0; r < 4; ++r) acc[m][r] = fmaf(d[r][di * 3 + dj], xv[r], acc[m][r]);
+                    }
+            }
+        });
     }
 
     // fp32 storage: the powers of two that bring the sums of this lane's channels 4 kq + r back
@@ -1015,7 +1060,14 @@ __global__ __launch_bounds__(kDnThreads, 2) void dense_bf16_kernel(const DensePa
         for (int p0 = 0; p0 < NA; p0 += kPass) {
             __syncthreads();  // the tile (DK's taps) or the previous pass is no longer read
 #pragma unroll
-            for (int u = 0; u < kPass; ++u) s_red[((u * 4) + wave) * 64 + lane] = part[p0 + u];
+            for (int u = 0; u < kPass; ++u) {
+                f32x4 sum = part[p0 + u];
+                if constexpr (kF32) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) sum[r] = fmaf(low[p0 + u][r], 1.f / kLowTerm, sum[r]);
+                }
+                s_red[((u * 4) + wave) * 64 + lane] = sum;
+            }
             __syncthreads();
 #pragma unroll
             for (int u = 0; u < kPass; ++u) {

@@ -53,12 +53,12 @@ inline bool dense_prep_pools(int N, int Ca, int H, int W, int ptiles)
 inline int dense_effective_ks(int Ks) { return Ks < 3 ? 3 : Ks; }
 
 // up to 16 channels run on the 16-bit matrix instructions: bf16 storage for every kernel size,
-// fp32 storage (a value as three fp16 terms, a weight as two; three tiles in LDS) up to 13 x 13
+// fp32 storage (a value as three terms, three tiles in LDS) up to 13 x 13
 inline bool dense_on_bf16_mfma(int Ca, int Ks, bool bf16) { return Ca <= 16 && (bf16 || dense_effective_ks(Ks) <= 13); }
 
 // floats the rearranged weights take: [CT chunks][Kse rows][Kse taps][CT][16 ci][16 co], or, for
 // the 16-bit matrix path, [(Kse + 1) / 2 pairs of tap columns][Kse rows][64 lanes] entries of 32 bytes and, behind them, the
-// largest weights (room for entries of 48 bytes: callers keep buffers of the size they were told)
+// weights' ranges (room for entries of 48 bytes: callers keep buffers of the size they were told)
 inline size_t dense_weight_floats(int Ca, int Ks)
 {
     const size_t ct = (size_t)(Ca + 15) / 16, kse = (size_t)dense_effective_ks(Ks);

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "esc_terms.hpp"
+
 namespace esc {
 
 typedef unsigned dw_u32x4 __attribute__((ext_vector_type(4)));
@@ -24,9 +26,9 @@ __host__ __device__ inline int dense_table_entries(int Kse) { return (Kse + 1) /
 // tap (i, 2 jp + l / 32), input channels 8 ((l / 16) % 2) .. + 7 - the A operand of the
 // instruction; zero beyond the kernel (the last pair's second column) and beyond C_a.  bf16 storage: two
 // operands of terms, hi = bf16(w), lo = bf16(w - hi); fp32 storage: the eight weights as they are, four and four (the
-// dense kernel takes them apart behind the power of two that belongs to its output channel's largest).
-// Entry idx = (jp * Kse + i) * 64 + l.  Returns the largest finite magnitude among the eight (its bits).
-__device__ __forceinline__ unsigned dense_table_entry(const float *lk, int Ca, int Ks, int Kse, bool terms, uint32_t *wa, int idx)
+// dense kernel takes them apart).
+// Entry idx = (jp * Kse + i) * 64 + l.  Returns the eight weights' range.
+__device__ __forceinline__ Range dense_table_entry(const float *lk, int Ca, int Ks, int Kse, bool terms, uint32_t *wa, int idx)
 {
     const int q = idx >> 6, l = idx & 63, co = l & 15, kg = l >> 4, off = (Kse - Ks) / 2;
     const int jp = q / Kse, i = q - jp * Kse - off, j = 2 * jp + (kg >> 1) - off;
@@ -40,13 +42,12 @@ __device__ __forceinline__ unsigned dense_table_entry(const float *lk, int Ca, i
         in8[e] = co < Ca && ci < Ca && i >= 0 && i < Ks && j >= 0 && j < Ks;
         v8[e] = lk[in8[e] ? (((size_t)co * Ca + ci) * Ks + i) * Ks + j : 0];
     }
-    unsigned largest = 0;
+    Range range;
     uint32_t part[2][4];
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
         const float a = in8[2 * w] ? v8[2 * w] : 0.f, b = in8[2 * w + 1] ? v8[2 * w + 1] : 0.f;
-        const unsigned ma = __float_as_uint(a) & 0x7fffffffu, mb = __float_as_uint(b) & 0x7fffffffu;
-        largest = max(largest, max(ma < 0x7f800000u ? ma : 0u, mb < 0x7f800000u ? mb : 0u));
+        range.look(a, b);
         if (terms) {
             const uint16_t ha = dw_f32_to_bf16(a), hb = dw_f32_to_bf16(b);
             part[0][w] = (uint32_t)ha | ((uint32_t)hb << 16);
@@ -59,10 +60,10 @@ __device__ __forceinline__ unsigned dense_table_entry(const float *lk, int Ca, i
     dw_u32x4 *dst = reinterpret_cast<dw_u32x4 *>(wa) + (size_t)q * 128 + l;
 #pragma unroll
     for (int t = 0; t < 2; ++t) dst[t * 64] = dw_u32x4{part[t][0], part[t][1], part[t][2], part[t][3]};
-    return largest;
+    return range;
 }
 
-// fp32 storage: behind the table, a block of the preparing launch leaves each output channel's largest among its 256 entries
+// fp32 storage: behind the table, a block of the preparing launch leaves the ranges of its 256 entries per output channel (BlockRange)
 __host__ __device__ inline int dense_table_blocks(int Kse) { return (dense_table_entries(Kse) + 255) / 256; }
 __host__ __device__ inline size_t dense_table_words(int Kse) { return (size_t)dense_table_entries(Kse) * 8; }
 

@@ -88,21 +88,6 @@ __device__ __forceinline__ float wave_sum(float v)
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
 
-// Largest of the 64 values of a wavefront, in lane 63.
-__device__ __forceinline__ unsigned wave_max(unsigned v)
-{
-    constexpr int kRowShr = 0x110, kRowBcast15 = 0x142, kRowBcast31 = 0x143;
-    auto dpp = [](unsigned x, auto ctrl, auto row_mask) {
-        return (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, decltype(row_mask)::value, 0xf, false);
-    };
-    v = max(v, dpp(v, std::integral_constant<int, kRowShr + 1>{}, std::integral_constant<int, 0xf>{}));
-    v = max(v, dpp(v, std::integral_constant<int, kRowShr + 2>{}, std::integral_constant<int, 0xf>{}));
-    v = max(v, dpp(v, std::integral_constant<int, kRowShr + 4>{}, std::integral_constant<int, 0xf>{}));
-    v = max(v, dpp(v, std::integral_constant<int, kRowShr + 8>{}, std::integral_constant<int, 0xf>{}));
-    v = max(v, dpp(v, std::integral_constant<int, kRowBcast15>{}, std::integral_constant<int, 0xa>{}));
-    return max(v, dpp(v, std::integral_constant<int, kRowBcast31>{}, std::integral_constant<int, 0xc>{}));
-}
-
 // Running sum along each row of 16 lanes (lane 15 of a row ends with the row's total).
 __device__ __forceinline__ float row_sum(float v)
 {

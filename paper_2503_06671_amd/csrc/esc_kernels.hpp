@@ -76,6 +76,7 @@
 
 #include "esc_convattn.h"
 #include "esc_estimator.hpp"
+#include "esc_terms.hpp"
 
 namespace esc {
 
@@ -1032,37 +1033,6 @@ __device__ __forceinline__ ConvWhere conv_where(ParamsPtr p, unsigned item)
     return w;
 }
 
-// v = h + l / 4096 (SplitGeom), two values at a time
-constexpr float kLowTerm = 4096.f;
-__device__ __forceinline__ void split_f16(float v0, float v1, uint32_t &h, uint32_t &l)
-{
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-    const f16x2 a = __builtin_convertvector(f32x2{v0, v1}, f16x2);
-    h = __builtin_bit_cast(uint32_t, a);
-    l = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{(v0 - (float)a.x) * kLowTerm, (v1 - (float)a.y) * kLowTerm}, f16x2));
-}
-// The range of some values: their largest magnitude (NaN if there is one) and the smallest apart from zeros, its sign shifted
-// out and one subtracted, so that a zero is beyond all.  Two instructions a value.
-struct Range {
-    float large = 0.f;
-    unsigned small = 0xffffffffu;
-    __device__ __forceinline__ void look(float a, float b)
-    {
-        large = __builtin_elementwise_maximum(__builtin_elementwise_maximum(large, __builtin_fabsf(a)), __builtin_fabsf(b));
-        small = min(min(small, (__float_as_uint(a) << 1) - 1u), (__float_as_uint(b) << 1) - 1u);
-    }
-};
-// the same of a block's values: bits of the largest, and 2^32 - 1 less what Range keeps of the smallest, as maxima
-struct BlockRange {
-    unsigned large, small;
-    __device__ __forceinline__ bool finite() const { return large < 0x7f800000u; }
-    __device__ __forceinline__ int exponent() const { return (int)(large >> 23); }
-    // Brought to 2^14 ... 2^15 at the largest, the smallest is still 2^-14 at least (or all are zeros): two terms hold every
-    // value to a unit of fp32's last place.  (Values below fp32's smallest normal one have fewer bits than that.)
-    __device__ __forceinline__ bool narrow() const { return (int)(large >> 23) - (int)((0u - small) >> 24) <= 28; }
-};
-
 template <int KS, int RY, typename T, bool ADD, bool ANY>
 __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
 {
@@ -1461,39 +1431,38 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
                 rw.look(w[k][0], w[k][1]);
             }
         }
-        const u32x4 mine{wave_max(__float_as_uint(rx.large) & 0x7fffffffu), wave_max(~rx.small),
-                         wave_max(__float_as_uint(rw.large) & 0x7fffffffu), wave_max(~rw.small)};
+        const BlockRange bx(rx), bw(rw);
+        const u32x4 mine{wave_max(bx.large), wave_max(bx.small), wave_max(bw.large), wave_max(bw.small)};
         if ((tid2 & 63) == 63) g_range[tid2 >> 6] = mine;
         __syncthreads();  // also: everyone has read what is now written over
-        const u32x4 wave0 = g_range[0], wave1 = g_range[1], wave2 = g_range[2], wave3 = g_range[3];
-        auto all = [&](int k) {
-            unsigned m = wave0[k];
-            for (const unsigned o : {wave1[k], wave2[k], wave3[k]}) m = o > m ? o : m;
-            return m;
-        };
-        const BlockRange mx{all(0), all(1)}, mw{all(2), all(3)};
+        BlockRange mx, mw;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const u32x4 theirs = g_range[k];
+            mx.merge(theirs[0], theirs[1]);
+            mw.merge(theirs[2], theirs[3]);
+        }
         split = mx.finite() && mw.finite() && mx.narrow() && mw.narrow();
         if (split) {
-            // powers of two that bring the largest to 2^14 ... 2^15 (as far as fp32 reaches)
-            const int ex = min(14 + 127 - mx.exponent(), 126), ew = min(14 + 127 - mw.exponent(), 126);
-            const float fx = __uint_as_float((unsigned)(127 + ex) << 23), fw = __uint_as_float((unsigned)(127 + ew) << 23);
-            back = -ex - ew, xback = __uint_as_float((unsigned)(127 - ex) << 23);
+            const int ex = mx.up(), ew = mw.up();
+            const float fx = power_of_two(ex), fw = power_of_two(ew);
+            back = -ex - ew, xback = power_of_two(-ex);
             uint32_t *dst = tile_d + ((tc >> 2) * SG::HRP + tr) * 4 + (tc & 3);
             uint32_t *sw = reinterpret_cast<uint32_t *>(g_wl) + wr * SG::WROW + wc;
 #pragma unroll
             for (int k = 0; k < KU; ++k) {
-                uint32_t h, l;
-                split_f16(v[k][0] * fx, v[k][1] * fx, h, l);
+                uint32_t t[2];
+                split_f16(v[k][0] * fx, v[k][1] * fx, t);
                 if (tc < SG::COLS / 2 && (4 * k + 3 < SG::HRP || 4 * k + tr < SG::HRP)) {
-                    dst[16 * k] = h;
-                    if (TX > 1) dst[SG::TERM_WORDS + 16 * k] = l;
+                    dst[16 * k] = t[0];
+                    if (TX > 1) dst[SG::TERM_WORDS + 16 * k] = t[1];
                 }
             }
 #pragma unroll
             for (int k = 0; k < KWU; ++k) {
-                uint32_t h, l;
-                split_f16(w[k][0] * fw, w[k][1] * fw, h, l);
-                if (wc < SG::WROW && 8 * k + wr < KS + 1) sw[8 * k * SG::WROW] = h, sw[8 * k * SG::WROW + SG::WTERM] = l;
+                uint32_t t[2];
+                split_f16(w[k][0] * fw, w[k][1] * fw, t);
+                if (wc < SG::WROW && 8 * k + wr < KS + 1) sw[8 * k * SG::WROW] = t[0], sw[8 * k * SG::WROW + SG::WTERM] = t[1];
             }
             __syncthreads();
         }

@@ -203,6 +203,41 @@ def test_dense_fp32_at_any_scale(oracle, N, H, W, Ca, Ks):
             assert np.sqrt(((got - ref)[:, c][ok] ** 2).mean()) <= bound * rms, (what, c)
 
 
+@pytest.mark.parametrize("N,H,W,Ca,Ks", [(1, 9, 40, 16, 13), (2, 5, 45, 13, 7), (1, 33, 32, 16, 3), (1, 30, 70, 16, 11), (1, 4, 33, 5, 1)])
+def test_dense_fp32_of_wide_range(oracle, N, H, W, Ca, Ks):
+    # magnitudes far apart in a tile, between its channels, or in a kernel.  Every output lies within its own terms' bound: its K + 9
+    # products and additions within 2^-23 each of the magnitudes summed, eight more for the factors' terms.  A kernel of a single
+    # one moves the values as they are.
+    base = wk.make_random(970 + Ks, N, Ca + 1, H, W, Ca, Ks, dtype=F32)
+    lk0 = dense_kernel(971, Ca, Ks)
+    rng = np.random.default_rng(972)
+    dk = rng.standard_normal((N, Ca, 3, 3)).astype(np.float32)
+    sparse = np.where(rng.random(base.x.shape) < 0.02, 1.0, 0.0)
+    channels = np.ones((1, Ca + 1, 1, 1))
+    channels[:, 1] = 2.0 ** -45
+    eye = np.zeros((Ca, Ca, Ks, Ks))
+    eye[np.arange(Ca), np.arange(Ca), Ks // 2, Ks // 2] = 1.0
+    own = np.where(np.arange(Ca)[:, None, None, None] == 1, np.where(np.arange(Ca)[:, None, None] == 1, 1.0, 0.0), 1.0)  # channel 1 of itself alone
+    for what, large, fx, fw, fd in (("1e8", 1e8, 1.0, 1.0, 1.0), ("1e12", 1e12, 1.0, 1.0, 1.0), ("1e30", 1e30, 1.0, 1.0, 1.0), ("channels", 1.0, channels, own, 2.0 ** -45),
+                                    ("any size", 1.0, 2.0 ** rng.integers(-40, 40, base.x.shape), 1.0, 1.0),
+                                    ("weights 2^-45", 1.0, sparse, eye + 2.0 ** -45 * (1 - eye), 2.0 ** -45)):
+        print(f"[case] {what} Ca={Ca} Ks={Ks}", flush=True)
+        wl = wk.make_random(970 + Ks, N, Ca + 1, H, W, Ca, Ks, dtype=F32)
+        wl.x = (base.x * fx).astype(np.float32)
+        if large != 1.0:
+            wl.x[0, 1, 1, 1] = large
+            wl.x[N - 1, Ca - 1, H - 1, W - 1] = -large
+        lk, d = (lk0 * fw).astype(np.float32), (dk * fd).astype(np.float32)
+        ref = oracle.convattn_dense_forward(wl.x, Ca, lk, F32, dk_in=d, want_out=False)[0]
+        mags = oracle.convattn_dense_forward(np.abs(wl.x), Ca, np.abs(lk), F32, dk_in=np.abs(d), want_out=False)[0]
+        got = run_dense(wl, lk, use_gen=False, dk_in=d)[:, :Ca].astype(np.float64)
+        bound = (Ca * Ks * Ks + 17) * 2.0 ** -23 * mags
+        assert (np.abs(got - ref) <= bound).all(), (what, (np.abs(got - ref) / bound).max())
+    for fx in (1.0, 2.0 ** rng.integers(-12, 12, base.x.shape), 2.0 ** rng.integers(-40, 40, base.x.shape)):
+        wl.x = (base.x * fx).astype(np.float32)
+        assert np.array_equal(run_dense(wl, eye.astype(np.float32), use_gen=False)[:, :Ca], wl.x[:, :Ca])
+
+
 @pytest.mark.parametrize("idx", [0, 1, 2, 3])
 def test_dense_benchmark_shapes_full_size(oracle, idx):
     wl = wk.make_config(idx)
