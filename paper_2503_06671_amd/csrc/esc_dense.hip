@@ -1022,10 +1022,11 @@ __global__ __launch_bounds__(kDnThreads, 2) void dense_bf16_kernel(const DensePa
                                 if constexpr (decltype(kind)::value) {
                                     xv[2 * u] = __uint_as_float(hb << 16) + (__uint_as_float(lb << 16) + __uint_as_float(tb << 16));
                                     xv[2 * u + 1] = __uint_as_float(hb & 0xffff0000u) + (__uint_as_float(lb & 0xffff0000u) + __uint_as_float(tb & 0xffff0000u));
-                                } else {   // (exact: the terms' bits do not overlap)
+                                } else {   // (exact: the terms' bits do not overlap, and at the values' own size: DK may be of any)
+                                    const float f = power_of_two(-xexp);
                                     const f16x2 h = __builtin_bit_cast(f16x2, hb), l = __builtin_bit_cast(f16x2, lb), e = __builtin_bit_cast(f16x2, tb);
-                                    xv[2 * u] = fmaf((float)l.x + (float)e.x, 1.f / kLowTerm, (float)h.x);
-                                    xv[2 * u + 1] = fmaf((float)l.y + (float)e.y, 1.f / kLowTerm, (float)h.y);
+                                    xv[2 * u] = fmaf((float)l.x + (float)e.x, f / kLowTerm, (float)h.x * f);
+                                    xv[2 * u + 1] = fmaf((float)l.y + (float)e.y, f / kLowTerm, (float)h.y * f);
                                 }
                             }
                         } else {
@@ -1046,10 +1047,6 @@ __global__ __launch_bounds__(kDnThreads, 2) void dense_bf16_kernel(const DensePa
     if constexpr (kF32) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) back[r] = __shfl(wexp, 4 * kq + r);
-#pragma unroll
-        for (int m = 0; m < NT; ++m)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[m][r] = __builtin_amdgcn_ldexpf(acc[m][r], -xexp);
     }
 
     // ---- the four wavefronts' partial results: run nt goes to wavefront nt / NT ----

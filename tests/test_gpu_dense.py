@@ -238,6 +238,19 @@ def test_dense_fp32_of_wide_range(oracle, N, H, W, Ca, Ks):
         assert np.array_equal(run_dense(wl, eye.astype(np.float32), use_gen=False)[:, :Ca], wl.x[:, :Ca])
 
 
+@pytest.mark.parametrize("Ks", [3, 7, 13])
+def test_dense_fp32_with_dk_of_any_size(oracle, Ks):
+    # DK of up to 2^120 and weights of up to 2^125 on values whose products are ordinary numbers, and the other way round
+    wl = wk.make_random(985 + Ks, 1, 17, 9, 45, 16, Ks, dtype=F32)
+    x0, lk0 = wl.x.copy(), dense_kernel(986, 16, Ks)
+    dk = np.random.default_rng(987).standard_normal((1, 16, 3, 3)).astype(np.float32)
+    for what, fx, fw, fd in (("dk", 2.0 ** -100, 1.0, 2.0 ** 120), ("weights", 2.0 ** -100, 2.0 ** 122, 2.0 ** 100), ("large x", 2.0 ** 100, 2.0 ** -120, 2.0 ** -110)):
+        print(f"[case] {what} Ks={Ks}", flush=True)
+        wl.x, lk, d = (x0 * fx).astype(np.float32), (lk0 * fw).astype(np.float32), (dk * fd).astype(np.float32)
+        ref = oracle.convattn_dense_forward(wl.x, 16, lk, F32, dk_in=d, want_out=False)[0]
+        gu.assert_att_close(run_dense(wl, lk, use_gen=False, dk_in=d)[:, :16].astype(np.float64), ref, F32, what)
+
+
 @pytest.mark.parametrize("idx", [0, 1, 2, 3])
 def test_dense_benchmark_shapes_full_size(oracle, idx):
     wl = wk.make_config(idx)
