@@ -59,7 +59,8 @@ extern __shared__ __align__(16) float bw_lds[];
 // instructions per tile row; two by two blocks beyond, 12.  With bf16 storage the stored values are the operands
 // (products exact, fp32 accumulation).  fp32 values are taken apart into two fp16 terms behind a power of two that brings the
 // tile's largest to 2^14 ... 2^15 (within a unit of fp32's last place), kept as two tiles, and three of the four
-// products of terms are accumulated (the fourth is below 2^-22 of a product).
+// products of terms are accumulated (the fourth is below 2^-22 of a product).  A tile whose magnitudes lie further apart than that
+// reaches (BlockRange), or with infinities or NaN in it, is summed in fp32 by the vector units (plain_sums).
 // A operand: lane (i, kg) reads 16 bytes of halo row y + i - the halo tile is laid out from the
 // aligned column x0 - 8 (x0 - 16), so every read is aligned.  B operand: lane (j, kg) wants eight
 // consecutive values of the row starting j elements to the left - a start that is odd for
@@ -70,7 +71,8 @@ extern __shared__ __align__(16) float bw_lds[];
 // tile end with it.  Bound by LDS reads.
 // 64 x 64 x 64, the whole backward: 17 x 17 bf16 79 us -> 43, fp32 98 -> 80 (31 x 31 196 -> 71 and 223 -> 101), by a vector kernel
 // with the window's rows in registers until then; 13 x 13 fp32 71 -> 61 and 16 x 64 x 64 28.6 -> 26.8, with three bf16 terms and nine
-// products until then, error against float64 5.0e-7 -> 1.7e-7 (products with a low term summed apart; together 5.0e-7).  Widths off the pieces, all loads of a thread
+// products until then, error against float64 4.8e-7 -> 1.6e-7 (products with a low term summed apart; together 5.0e-7).
+// With a value of 1e10 in every tile 13 x 13 88 us, 17 x 17 142, 31 x 31 266 (by the kernels before 74, 98 and 210).  Widths off the pieces, all loads of a thread
 // at once instead of one after the other: 8 x 63 x 63 fp32 29 -> 25 us, 64 x 63 x 63 bf16 47 -> 39.
 // ---------------------------------------------------------------------------
 constexpr int kCmXP = 104;  // halo tile: elements per row (96 columns are read; 13 x 16 bytes: rows fall on different banks)
@@ -89,8 +91,16 @@ struct CorrGeom {
     static constexpr size_t G0 = (size_t)XR * kCmXP * 2, G1 = G0 + (size_t)kCorrTileH * GP * 2 + 64;
     static constexpr size_t TERM = G1 + (size_t)kCorrTileH * GP * 2;  // bytes per term
     static constexpr size_t RED = NB == 1 ? (size_t)4 * SH * 256 * 4 + 64 : (size_t)4 * 1024 * 4 + 64;
-    static constexpr size_t tiles(int terms) { return terms * TERM > RED ? terms * TERM : RED; }
-    static constexpr size_t lds() { return tiles(F32 ? 2 : 1) + 8 * sizeof(unsigned); }
+    // special tiles (below): x's halo from column -P on and grad_out, fp32, rows of whole runs of four
+    static constexpr int JG = (KC + 3) / 4, IG = (KC + 1) / 2, XF = kCorrTileW + 4 * JG + 4, XFR = kCorrTileH + 2 * IG;
+    static constexpr int SPLIT = 256 / (JG * IG) < 8 ? 256 / (JG * IG) : 8;   // threads that share two rows and four columns of the window, by tile rows
+    static constexpr size_t PLAIN = F32 || NB == 2 ? ((size_t)XFR * XF + kCorrTileH * kCorrTileW) * 4 : 0;
+    static constexpr size_t tiles(int terms)
+    {
+        const size_t a = terms * TERM > RED ? terms * TERM : RED;
+        return a > PLAIN ? a : PLAIN;
+    }
+    static constexpr size_t lds() { return tiles(F32 ? 2 : 1) + 4 * sizeof(uint4); }
 };
 
 // eight consecutive bf16 values to row[q ...]: whole words where the parity of q allows
@@ -128,7 +138,7 @@ __global__ __launch_bounds__(kBwThreads, (CorrGeom<KC, std::is_same<T, float>::v
     auto xs = [&](int t) { return reinterpret_cast<uint16_t *>(lds + t * CG::TERM); };
     auto g0 = [&](int t) { return reinterpret_cast<uint16_t *>(lds + t * CG::TERM + CG::G0); };
     auto g1 = [&](int t) { return reinterpret_cast<uint16_t *>(lds + t * CG::TERM + CG::G1); };
-    unsigned *s_max = reinterpret_cast<unsigned *>(lds + CG::tiles(NT));   // [wavefront][x, grad_out]
+    u32x4 *s_range = reinterpret_cast<u32x4 *>(lds + CG::tiles(NT));   // of each wavefront's values of x and of grad_out
 
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int H = p.H, W = p.W;
@@ -140,34 +150,38 @@ __global__ __launch_bounds__(kBwThreads, (CorrGeom<KC, std::is_same<T, float>::v
     const size_t plane = ((size_t)n * p.C + c) * (size_t)H * W;
     const T *xp = (const T *)p.x + plane, *gp = (const T *)p.go + plane;
 
-    // Up to 15 x 15 in bf16 storage a value that is not finite makes what its instructions touch NaN.  Otherwise the largest
-    // magnitudes of the two tiles are looked for: finite ones give fp32 storage its powers of two, and larger windows
-    // with others among them are summed plainly.
+    // Up to 15 x 15 in bf16 storage a value that is not finite makes what its instructions touch NaN.  Otherwise the ranges of
+    // the two tiles are looked for: they give fp32 storage its powers of two, and tiles that reach further than two terms do, or
+    // that have infinities or NaN in them, are special.
     constexpr bool kLook = kF32 || NB == 2;
-    unsigned mx = 0, mg = 0;
-    auto magnitude = [](float v) {
-        const unsigned b = __float_as_uint(v) & 0x7fffffffu;
-        return NB == 1 && b >= 0x7f800000u ? 0u : b;
-    };
+    Range rx, rg;
+    BlockRange mx, mg;
     auto agree = [&](bool barrier) {
         if constexpr (kLook) {
-            mx = wave_max(mx), mg = wave_max(mg);
-            if (lane == 63) s_max[2 * wave] = mx, s_max[2 * wave + 1] = mg;
+            const BlockRange x(rx), g(rg);
+            const u32x4 mine{wave_max(x.large), wave_max(x.small), wave_max(g.large), wave_max(g.small)};
+            if (lane == 63) s_range[wave] = mine;
         }
         if (kLook || barrier) __syncthreads();
         if constexpr (kLook) {
-            mx = max(max(s_max[0], s_max[2]), max(s_max[4], s_max[6]));
-            mg = max(max(s_max[1], s_max[3]), max(s_max[5], s_max[7]));
+#pragma unroll
+            for (int k = 0; k < kBwThreads / 64; ++k) {
+                const u32x4 theirs = s_range[k];
+                mx.merge(theirs[0], theirs[1]);
+                mg.merge(theirs[2], theirs[3]);
+            }
         }
+        return kLook && !(mx.finite() && mg.finite() && (!kF32 || (mx.narrow() && mg.narrow())));   // block-uniform
     };
-    // the power of two that brings the largest to 2^14 ... 2^15, as far as fp32 reaches
-    auto exponent = [](unsigned m) { return min(14 + 127 - (int)(m >> 23), 126); };
-    auto power = [](int e) { return __uint_as_float((unsigned)(127 + e) << 23); };
-    // a value as NT terms: bf16 storage itself; fp32 the nearest fp16 and the nearest to what is left, within a unit
-    // of fp32's last place from the largest down to 2^-15 of it
+    float *plain_x = bw_lds, *plain_g = bw_lds + CG::XFR * CG::XF;
+    auto plain_put = [&](int r, int cc, float v) {   // x, halo row r and column cc (from -BASE)
+        const int at = cc - CG::BASE + P;
+        if (at >= 0 && at < CG::XF) plain_x[r * CG::XF + at] = v;
+    };
+    // a value as NT terms: bf16 storage itself; fp32 the nearest fp16 and the nearest to 4096 times what is left
     auto split = [](float v, uint16_t (&t)[NT]) {
         if constexpr (kF32) {
-            const _Float16 h = (_Float16)v, l = (_Float16)(v - (float)h);
+            const _Float16 h = (_Float16)v, l = (_Float16)((v - (float)h) * kLowTerm);
             t[0] = __builtin_bit_cast(uint16_t, h), t[NT - 1] = __builtin_bit_cast(uint16_t, l);
         } else {
             t[0] = (uint16_t)(__float_as_uint(v) >> 16);
@@ -200,6 +214,67 @@ __global__ __launch_bounds__(kBwThreads, (CorrGeom<KC, std::is_same<T, float>::v
     };
 
     float sx = 0.f;
+    bool special = false;
+    float *dst = p.partial + ((size_t)nc * tiles + tile) * (KC * KC + 1);
+    // A special tile, in fp32: a thread has two rows and four columns of the window, for every SPLIT-th row of the tile.  Per four
+    // pixels one read of grad_out and two of x (sixteen bytes each) feed 32 multiply-adds, which bound it.  (grad_out beyond the image is not
+    // multiplied: x may be infinite there.)
+    auto plain_sums = [&]() {
+        if constexpr (kLook) {
+            typedef float f4 __attribute__((ext_vector_type(4)));
+            constexpr int JG = CG::JG, IG = CG::IG, XF = CG::XF, SPLIT = CG::SPLIT, TASKS = JG * IG;
+            const float sxr = row16_sum(sx);
+            __syncthreads();
+            const int q = tid / TASKS, task = tid - q * TASKS, i0 = 2 * (task / JG), j0 = 4 * (task % JG);
+            const int rows = min(kCorrTileH, H - ty0), cols = min(kCorrTileW, W - tx0);
+            float s[2][4] = {};
+            if (q < SPLIT) {
+                for (int y = q; y < rows; y += SPLIT) {
+                    const float *gs = plain_g + y * kCorrTileW, *xs0 = plain_x + (y + i0) * XF + j0;
+                    f4 xa[2] = {*reinterpret_cast<const f4 *>(xs0), *reinterpret_cast<const f4 *>(xs0 + XF)};
+#pragma unroll 1
+                    for (int x = 0; x < cols; x += 4) {
+                        const f4 g = *reinterpret_cast<const f4 *>(gs + x);
+#pragma unroll
+                        for (int w = 0; w < 2; ++w) {
+                            const f4 xb = *reinterpret_cast<const f4 *>(xs0 + w * XF + x + 4);
+                            const float v[8] = {xa[w][0], xa[w][1], xa[w][2], xa[w][3], xb[0], xb[1], xb[2], xb[3]};
+                            if (x + 4 <= cols) {
+#pragma unroll
+                                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                                    for (int j = 0; j < 4; ++j) s[w][j] = fmaf(g[k], v[k + j], s[w][j]);
+                            } else {
+#pragma unroll
+                                for (int k = 0; k < 3; ++k)
+#pragma unroll
+                                    for (int j = 0; j < 4; ++j) s[w][j] = x + k < cols ? fmaf(g[k], v[k + j], s[w][j]) : s[w][j];
+                            }
+                            xa[w] = xb;
+                        }
+                    }
+                }
+            }
+            __syncthreads();  // the tiles are no longer read
+            float *red = bw_lds, *sxs = bw_lds + SPLIT * 4 * IG * 2 * JG;   // [SPLIT][2 IG][4 JG], [16 rows of lanes]
+            if (q < SPLIT)
+#pragma unroll
+                for (int w = 0; w < 2; ++w)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) red[(q * 2 * IG + i0 + w) * 4 * JG + j0 + j] = s[w][j];
+            if ((lane & 15) == 15) sxs[tid >> 4] = sxr;
+            __syncthreads();
+            for (int o = tid; o < KC * KC + 1; o += kBwThreads) {
+                float sum = 0.f;
+                if (o == KC * KC) {
+                    for (int k = 0; k < 16; ++k) sum += sxs[k];
+                } else {
+                    for (int k = 0; k < SPLIT; ++k) sum += red[(k * 2 * IG + o / KC) * 4 * JG + o % KC];
+                }
+                dst[o] = sum;
+            }
+        }
+    };
     if (p.corr_vec) {
         // whole pieces of eight columns, each entirely inside or outside the image; the loads
         // travel while the LDS is cleared
@@ -223,12 +298,28 @@ __global__ __launch_bounds__(kBwThreads, (CorrGeom<KC, std::is_same<T, float>::v
 #pragma unroll
             for (int k = 0; k < XK; ++k)
 #pragma unroll
-                for (int e = 0; e < 8; ++e) mx = max(mx, magnitude(value8(xv[k], e)));
+                for (int e = 0; e < 8; e += 2) rx.look(value8(xv[k], e), value8(xv[k], e + 1));
 #pragma unroll
-            for (int e = 0; e < 8; ++e) mg = max(mg, magnitude(value8(gv, e)));
+            for (int e = 0; e < 8; e += 2) rg.look(value8(gv, e), value8(gv, e + 1));
         }
-        agree(true);
-        const float fx = kF32 ? power(exponent(mx)) : 1.f, fg = kF32 ? power(exponent(mg)) : 1.f;
+        special = agree(true);
+        if (kLook && special) {
+#pragma unroll
+            for (int k = 0; k < XK; ++k) {
+                const int t = k * kBwThreads + tid, r = t / PC, pc = t - r * PC;
+                if (t >= XT) continue;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float v = value8(xv[k], e);
+                    plain_put(r, 8 * pc + e, v);
+                    if (r >= P && r < P + kCorrTileH && pc >= NB && pc < NB + 8) sx += v;
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) plain_g[(tid >> 3) * kCorrTileW + 8 * (tid & 7) + e] = value8(gv, e);
+            return plain_sums();
+        }
+        const float fx = kF32 ? power_of_two(mx.up()) : 1.f, fg = kF32 ? power_of_two(mg.up()) : 1.f;
 #pragma unroll
         for (int k = 0; k < XK; ++k) {
             const int t = k * kBwThreads + tid, r = t / PC, pc = t - r * PC;
@@ -294,12 +385,25 @@ __global__ __launch_bounds__(kBwThreads, (CorrGeom<KC, std::is_same<T, float>::v
         }
         if constexpr (kLook) {
 #pragma unroll
-            for (int k = 0; k < STEP; ++k) mx = max(mx, magnitude(xv[k]));
+            for (int k = 0; k < STEP; k += 2) rx.look(xv[k], k + 1 < STEP ? xv[k + 1] : 0.f);
 #pragma unroll
-            for (int k = 0; k < GK; ++k) mg = max(mg, magnitude(gv[k]));
+            for (int k = 0; k < GK; k += 2) rg.look(gv[k], gv[k + 1]);
         }
-        agree(true);
-        const float fx = kF32 ? power(exponent(mx)) : 1.f, fg = kF32 ? power(exponent(mg)) : 1.f;
+        special = agree(true);
+        if (kLook && special) {
+#pragma unroll
+            for (int k = 0; k < XK; ++k) {
+                const int t = k * kBwThreads + t0, r = t / (8 * PC), cc = t - r * (8 * PC);
+                if (t >= XT) continue;
+                const float v = xv[k < STEP ? k : 0];
+                plain_put(r, cc, v);
+                if (r >= P && r < P + kCorrTileH && cc >= CG::BASE && cc < CG::BASE + kCorrTileW) sx += v;
+            }
+#pragma unroll
+            for (int k = 0; k < GK; ++k) plain_g[k * kBwThreads + t0] = gv[k];
+            return plain_sums();
+        }
+        const float fx = kF32 ? power_of_two(mx.up()) : 1.f, fg = kF32 ? power_of_two(mg.up()) : 1.f;
         put_x(0, fx);
 #pragma unroll
         for (int k = 0; k < GK; ++k) {
@@ -396,7 +500,9 @@ __global__ __launch_bounds__(kBwThreads, (CorrGeom<KC, std::is_same<T, float>::v
 #pragma unroll
                 for (int jb = 0; jb < NB; ++jb)
 #pragma unroll
-                    for (int b = 0; b < NC; ++b) acc[sft][ib][jb][b] += low[sft][ib][jb][b];
+                    for (int b = 0; b < NC; ++b)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) acc[sft][ib][jb][b][r] = fmaf(low[sft][ib][jb][b][r], 1.f / kLowTerm, acc[sft][ib][jb][b][r]);
     }
     const float sxr = row16_sum(sx);
     __syncthreads();  // the tiles are no longer read: their LDS takes the wavefronts' results
@@ -430,10 +536,7 @@ __global__ __launch_bounds__(kBwThreads, (CorrGeom<KC, std::is_same<T, float>::v
     }
     if (l16 == 15) sxs[tid >> 4] = sxr;
     __syncthreads();
-    const int back = kF32 ? -exponent(mx) - exponent(mg) : 0;
-    // values that are not finite, in a window beyond 15 x 15: every sum plainly, so that those they do not reach stay finite
-    const bool plain = NB == 2 && (mx >= 0x7f800000u || mg >= 0x7f800000u);
-    float *dst = p.partial + ((size_t)nc * tiles + tile) * (KC * KC + 1);
+    const int back = kF32 ? -mx.up() - mg.up() : 0;
     for (int o = tid; o < KC * KC + 1; o += kBwThreads) {
         float s2 = 0.f;
         if (o == KC * KC) {
@@ -441,25 +544,16 @@ __global__ __launch_bounds__(kBwThreads, (CorrGeom<KC, std::is_same<T, float>::v
             for (int k = 0; k < 16; ++k) s2 += sxs[k];
         } else {
             const int i = o / KC, j = o - i * KC;
-            if (NB == 2 && plain) {
-                for (int y = ty0; y < min(ty0 + kCorrTileH, H); ++y)
-                    for (int x = tx0; x < min(tx0 + kCorrTileW, W); ++x) {
-                        const int sy = y + i - P, sx2 = x + j - P;
-                        const bool in = sy >= 0 && sy < H && sx2 >= 0 && sx2 < W;
-                        s2 = fmaf(bw_load(gp + (size_t)y * W + x), in ? bw_load(xp + (size_t)sy * W + sx2) : 0.f, s2);
-                    }
-            } else {
 #pragma unroll
-                for (int w = 0; w < 4; ++w) {
-                    if constexpr (NB == 2) {
-                        s2 += red[w * 1024 + i * 32 + j];
-                    } else {
+            for (int w = 0; w < 4; ++w) {
+                if constexpr (NB == 2) {
+                    s2 += red[w * 1024 + i * 32 + j];
+                } else {
 #pragma unroll
-                        for (int sft = 0; sft < SH; ++sft) s2 += red[(w * SH + sft) * 256 + (i + sft) * 16 + j];
-                    }
+                    for (int sft = 0; sft < SH; ++sft) s2 += red[(w * SH + sft) * 256 + (i + sft) * 16 + j];
                 }
-                if (kF32) s2 = __builtin_amdgcn_ldexpf(s2, back);
             }
+            if (kF32) s2 = __builtin_amdgcn_ldexpf(s2, back);
         }
         dst[o] = s2;
     }

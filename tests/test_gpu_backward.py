@@ -227,3 +227,47 @@ def test_sums_at_any_scale_and_of_special_values(oracle, dtype, Ks, N, H, W):
         ok = np.isfinite(ref)
         bound = (np.sqrt(2 * H * W * N) + 8) * 2.0 ** -24
         assert np.linalg.norm(got[ok] - ref[ok]) <= bound * np.linalg.norm(ref[ok]), what
+
+
+@pytest.mark.parametrize("dtype,Ks,N,H,W", [(F32, 3, 2, 33, 72), (F32, 7, 1, 40, 67), (F32, 13, 1, 33, 72), (F32, 13, 3, 7, 5), (F32, 15, 2, 20, 37), (F32, 17, 1, 32, 64),
+                                            (F32, 17, 2, 63, 63), (F32, 29, 1, 40, 67), (F32, 31, 1, 33, 72), (BF16, 17, 2, 33, 64), (BF16, 31, 1, 31, 65)])
+def test_sums_of_wide_range(oracle, dtype, Ks, N, H, W):
+    # magnitudes far apart in x or in grad_out, infinities and NaN: every sum within its own terms' bound, special values where the
+    # definition has them (their tiles are summed in fp32: a chain of a tile's 2048 multiply-adds, one addition per tile)
+    base = wk.make_random(1600 + Ks, N, 4, H, W, 3, Ks, dtype=dtype)
+    go = grad_out_for(base, 1601)
+    g0 = (wk.bf16_bits_to_f32(go) if dtype == BF16 else go).astype(np.float64)
+    rng = np.random.default_rng(1602)
+    for what in ("x 1e8", "x 1e12", "g 1e12", "any size", "small x", "inf", "nan", "g inf"):
+        if what == "g inf" and min(H // 2, W // 2, H - 1 - H // 2, W - 1 - W // 2) < Ks // 2:
+            continue   # (its window reaches beyond the image, where zeros are multiplied)
+        print(f"[case] {what} {dtype} Ks={Ks}", flush=True)
+        xf, gf = base.x_as_f32().astype(np.float64), g0.copy()
+        if what in ("x 1e8", "x 1e12"):
+            xf[0, 1, 0, W - 1] = float(what[2:])        # a corner: a quarter of the window reaches it
+        elif what == "g 1e12":
+            gf[0, 1, H - 1, 0] = 1e12
+        elif what == "any size":
+            xf, gf = xf * 2.0 ** rng.integers(-40, 40, xf.shape), gf * 2.0 ** rng.integers(-40, 40, gf.shape)
+        elif what == "small x":
+            xf[:, 1] *= 2.0 ** -40
+            xf[0, 1, H // 2, W // 2] = 1.0
+            gf[:, 1] *= 2.0 ** -20
+        elif what in ("inf", "nan"):
+            xf[0, 1, 0, W - 1] = np.inf if what == "inf" else np.nan
+        else:
+            gf[0, 1, H // 2, W // 2] = np.inf
+        xf, gf = xf.astype(np.float32), gf.astype(np.float32)
+        wl = wk.make_random(1600 + Ks, N, 4, H, W, 3, Ks, dtype=dtype)
+        conv = (lambda a: wk.f32_to_bf16_bits(a)) if dtype == BF16 else (lambda a: a)
+        wl.x, g = conv(xf), conv(gf)
+        back = (lambda a: wk.bf16_bits_to_f32(a)) if dtype == BF16 else (lambda a: a)
+        with np.errstate(invalid="ignore"):
+            ref = oracle.convattn_backward(wl.x, g, 3, wl.lk, dtype)["dlk"]
+            mags = oracle.convattn_backward(conv(np.abs(back(wl.x)).astype(np.float32)), conv(np.abs(back(g)).astype(np.float32)), 3, wl.lk, dtype)["dlk"]
+        got = run_backward(wl, g, use_gen=False)["grad_lk"].cpu().numpy().astype(np.float64)
+        assert np.array_equal(np.isfinite(ref), np.isfinite(got)), what
+        ok = np.isfinite(ref)
+        bound = (2048 + 64) * 2.0 ** -24 * mags
+        err = np.abs(got[ok] - ref[ok])
+        assert (err <= bound[ok]).all(), (what, (err / bound[ok]).max())
