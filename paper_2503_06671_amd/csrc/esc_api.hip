@@ -204,8 +204,9 @@ Plan plan_items(FwdParams &p, int Ks, int blocks_per_cu, int carry_grains)
     // copy items there are to a conv item (and with that how small they are): 1, 2 or 3,
     // thresholds from sweeps at 540 x 960 with Ks = 7 ... 31
     const double pix = (double)p.N * p.Ca * p.H * p.W;
-    // (what a conv item sustains, its loads included; large kernels run on the matrix cores in fp32)
-    const double t_valu = 2.0 * Ks * Ks * pix / (Ks >= 15 ? 200e12 : 50e12);
+    // (what a conv item sustains, its loads included; those of SplitGeom, conv_splits, four times as much)
+    const bool splits = p.elem_bytes == 4 ? Ks >= 15 : Ks >= 19;
+    const double t_valu = 2.0 * Ks * Ks * pix / (splits ? 200e12 : 50e12);
     const double t_copy = 2.0 * (double)p.N * (double)rest_len / 4.5e12;
     unsigned a = 1, b = 1;
     if (t_valu > 0 && t_copy > 0) {
