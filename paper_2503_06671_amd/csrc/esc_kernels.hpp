@@ -973,7 +973,7 @@ struct MatrixGeom {
 // instructions, where the vector loop was bound by its multiply-adds.  A tile's values, brought to
 // at most 2^15 by a power of two, are taken apart into two fp16 terms, v = h + l / 4096, h the nearest fp16
 // to v and l the nearest to 4096 times what is left: to a unit of fp32's last place at most (a quarter of the values), from
-// 2^15 down to 2^-14 (Range; a tile with magnitudes further apart keeps the vector loop).  So are the weights, and three of the four products of terms
+// 2^15 down to 2^-13 (BlockRange; a tile with magnitudes further apart keeps the vector loop).  So are the weights, and three of the four products of terms
 // are accumulated in fp32 (the fourth is below 2^-22 of a product), the two with a low term in sums
 // of their own; bf16 values are a term each.  K of an instruction is sixteen columns of two
 // neighbouring tile rows, i.e. two kernel rows at once: sixteen outputs need NQ = 2 or 3 runs of

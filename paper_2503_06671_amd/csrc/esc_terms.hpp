@@ -51,13 +51,13 @@ struct BlockRange {
     __device__ __forceinline__ bool finite() const { return large < 0x7f800000u; }
     // the exponent of the power of two that brings the largest to 2^14 ... 2^15 (as far as fp32 reaches)
     __device__ __forceinline__ int up() const { return min(14 + 127 - (int)(large >> 23), 126); }
-    // There, the smallest is still 2^-14 at least (or all are zeros): two terms hold every value to a unit of fp32's last
+    // There, the smallest is still 2^-13 at least (or all are zeros): three terms hold every value, two to a unit of fp32's last
     // place.  (Values below fp32's smallest normal one have fewer bits than that.)
-    __device__ __forceinline__ bool narrow() const { return (int)(large >> 23) - (int)((0u - small) >> 24) <= 28; }
+    __device__ __forceinline__ bool narrow() const { return (int)(large >> 23) - (int)((0u - small) >> 24) <= 27; }
 };
 
 // N fp16 terms of two values at a time, of magnitudes up to 2^15: v = t0 + (t1 + t2) / 4096, t0 the nearest fp16 to v, t1 the nearest to
-// 4096 times what is left, t2 to what that leaves.  From 2^-14 up two terms are within a unit of fp32's last place (and
+// 4096 times what is left, t2 to what that leaves.  From 2^-13 up (below, fp16 runs out of bits) two terms are within a unit of fp32's last place (and
 // miss it in a quarter of the values), three are exact.
 constexpr float kLowTerm = 4096.f;
 template <int N>

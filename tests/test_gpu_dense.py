@@ -233,8 +233,9 @@ def test_dense_fp32_of_wide_range(oracle, N, H, W, Ca, Ks):
         got = run_dense(wl, lk, use_gen=False, dk_in=d)[:, :Ca].astype(np.float64)
         bound = (Ca * Ks * Ks + 17) * 2.0 ** -23 * mags
         assert (np.abs(got - ref) <= bound).all(), (what, (np.abs(got - ref) / bound).max())
-    for fx in (1.0, 2.0 ** rng.integers(-12, 12, base.x.shape), 2.0 ** rng.integers(-40, 40, base.x.shape)):
-        wl.x = (base.x * fx).astype(np.float32)
+    ones = np.sign(base.x) * (1.0 + rng.random(base.x.shape))   # times 2^-13 ... 2^14: the widest range the fp16 terms are used for
+    for x in (base.x, ones * 2.0 ** rng.integers(-13, 15, base.x.shape), base.x * 2.0 ** rng.integers(-40, 40, base.x.shape)):
+        wl.x = x.astype(np.float32)
         assert np.array_equal(run_dense(wl, eye.astype(np.float32), use_gen=False)[:, :Ca], wl.x[:, :Ca])
 
 

@@ -476,7 +476,7 @@ def test_large_kernels_of_wide_range(oracle, dtype, Ks, N, H, W):
     centre = np.zeros((Ks, Ks))
     centre[Ks // 2, Ks // 2] = 1.0
     sparse = np.where(rng.random(base.x.shape) < 0.01, 1.0, 0.0)
-    for what, large, fx, fw in (("1e8", 1e8, 1.0, 1.0), ("1e12", 1e12, 1.0, 1.0), ("1e30", 1e30, 1.0, 1.0), ("2^28 apart", 2.0 ** 27, 1.0, 1.0),
+    for what, large, fx, fw in (("1e8", 1e8, 1.0, 1.0), ("1e12", 1e12, 1.0, 1.0), ("1e30", 1e30, 1.0, 1.0), ("2^27 apart", 2.0 ** 27, 1.0, 1.0),
                                 ("any size", 1.0, 2.0 ** rng.integers(-60, 60, base.x.shape), 1.0),
                                 ("weights 2^-45", 1.0, sparse, centre + 2.0 ** -45 * (1 - centre)),
                                 ("weights 2^-30", 1.0, sparse, centre + 2.0 ** -30 * (1 - centre))):
@@ -494,6 +494,12 @@ def test_large_kernels_of_wide_range(oracle, dtype, Ks, N, H, W):
         got = gu.att_as_f64(gu.run_forward(wl, use_gen=False, dk_in=d), wl)
         bound = (Ks * Ks + 17) * 2.0 ** -23 * mags + (2.0 ** -8 * np.abs(ref) if dtype == BF16 else 0.0)
         assert (np.abs(got - ref) <= bound).all(), (what, (np.abs(got - ref) / bound).max())
+    # a kernel of a single one, times 2^-13 ... 2^14 (the widest range the terms are used for): the values to a unit of their last place
+    xf = np.sign(base.x_as_f32()) * (1.0 + rng.random(base.x.shape)) * 2.0 ** rng.integers(-13, 15, base.x.shape)
+    wl.x = wk.f32_to_bf16_bits(xf.astype(np.float32)) if dtype == BF16 else xf.astype(np.float32)
+    wl.lk = np.broadcast_to(centre, base.lk.shape).astype(np.float32)
+    got, want = gu.att_as_f64(gu.run_forward(wl, use_gen=False), wl), wl.x_as_f32()[:, :4].astype(np.float64)
+    assert (np.abs(got - want) <= 2.0 ** -23 * np.abs(want)).all()
 
 
 @pytest.mark.parametrize("dtype,Ks", [(F32, 15), (F32, 17), (F32, 31), (BF16, 19), (BF16, 31)])
