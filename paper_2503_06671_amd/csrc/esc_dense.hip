@@ -1025,8 +1025,8 @@ __global__ __launch_bounds__(kDnThreads, 2) void dense_bf16_kernel(const DensePa
                                 } else {   // (exact: the terms' bits do not overlap, and at the values' own size: DK may be of any)
                                     const float f = power_of_two(-xexp);
                                     const f16x2 h = __builtin_bit_cast(f16x2, hb), l = __builtin_bit_cast(f16x2, lb), e = __builtin_bit_cast(f16x2, tb);
-                                    xv[2 * u] = fmaf((float)l.x + (float)e.x, f / kLowTerm, (float)h.x * f);
-                                    xv[2 * u + 1] = fmaf((float)l.y + (float)e.y, f / kLowTerm, (float)h.y * f);
+                                    xv[2 * u] = fmaf((float)l.x, f / kLowTerm, fmaf((float)e.x, f / kLowTerm, fmaf((float)h.x, f, 0.f)));
+                                    xv[2 * u + 1] = fmaf((float)l.y, f / kLowTerm, fmaf((float)e.y, f / kLowTerm, fmaf((float)h.y, f, 0.f)));
                                 }
                             }
                         } else {

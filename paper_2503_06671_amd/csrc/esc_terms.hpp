@@ -69,8 +69,9 @@ __device__ __forceinline__ void split_f16(float v0, float v1, uint32_t (&t)[N])
     for (int q = 0; q < N; ++q) {
         const f16x2 h = __builtin_convertvector(f32x2{v0, v1}, f16x2);
         t[q] = __builtin_bit_cast(uint32_t, h);
-        v0 -= (float)h.x, v1 -= (float)h.y;
-        if (q == 0) v0 *= kLowTerm, v1 *= kLowTerm;
+        // (all exact)
+        const float f = q == 0 ? kLowTerm : 1.f;
+        v0 = __builtin_fmaf(-f, (float)h.x, v0 * f), v1 = __builtin_fmaf(-f, (float)h.y, v1 * f);
     }
 }
 
