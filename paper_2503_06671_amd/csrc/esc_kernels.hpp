@@ -1787,9 +1787,11 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) acc[t][q] = __builtin_amdgcn_ldexpf(fmaf(lo[t][q], 1.f / kLowTerm, hi[t][q]), back);
         }
-    } else if (G::UNROLL) {
-        // (with the kernel rows re-read instead, as below, tiles that SplitGeom leaves to this loop take longer: 540 x 960
-        // fp32, each with a value of 1e10, Ks = 17 83.7 us a call, so 77.4, Ks = 15 73.6 and 68.5; ordinary ones alike)
+    } else if (G::UNROLL && !(kSplit && RY == 2)) {
+        // (Tiles that SplitGeom leaves to the vector units: 540 x 960 fp32 with a value of 1e10 in every tile, Ks = 17 79 us a call, by
+        // the loop below 84; 15 69 and 74.  With two-row blocking, short calls, that one is taken: written out as well, this
+        // one makes the kernel larger than the instruction cache, and calls without such tiles pay for it, 64 x 64 Ks = 17
+        // 9.3 us, so 8.9; with a value of 1e10 10.4 and 12.1.)
 #pragma unroll
         for (int r0 = 0; r0 < G::ROWS; r0 += RY)
 #pragma unroll
@@ -1816,6 +1818,7 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
             }
             __builtin_amdgcn_sched_barrier(0);  // one row's loads at a time: the registers are few
         }
+        if (G::UNROLL) ask_again();
     }
     __builtin_amdgcn_s_setprio(kPrioHigh);
 
@@ -1906,7 +1909,7 @@ __device__ __forceinline__ Ctx conv_item(ParamsPtr p, Ctx ctx, unsigned item_in)
                         for (int k = 0; k < 4; ++k) {
                             const int w = wi - 1 + k, at = ((w >> 2) * SG::HRP + row) * 4 + (w & 3);
                             const f16x2 h = __builtin_bit_cast(f16x2, tile_d[at]);
-                            v[2 * k] = (float)h.x * xback, v[2 * k + 1] = (float)h.y * xback;
+                            v[2 * k] = fmaf((float)h.x, xback, 0.f), v[2 * k + 1] = fmaf((float)h.y, xback, 0.f);   // (one instruction, where a product takes two)
                             if constexpr (TX > 1) {
                                 const f16x2 l = __builtin_bit_cast(f16x2, tile_d[SG::TERM_WORDS + at]);
                                 v[2 * k] = fmaf((float)l.x, xback / kLowTerm, v[2 * k]), v[2 * k + 1] = fmaf((float)l.y, xback / kLowTerm, v[2 * k + 1]);
