@@ -178,10 +178,9 @@ FP32_MFMA_PEAK_TFLOPS = 157.3         # dense fp32 matrix-core peak
 
 
 def terms_per_product(wl) -> float:
-    """Matrix instructions the point-wise layers issue per block of products: fp32 storage has every
-    value and weight in two fp16 terms and multiplies three of the four pairs (ConvFFN in one launch and channels
-    that are not whole runs of sixteen: six of nine of bf16 terms), bf16 storage has every weight in two."""
-    return 2.0 if wl.elem_bytes == 2 else 3.0
+    """bf16 matrix instructions the point-wise layers issue per block of products: fp32 storage has every
+    value and weight in three bf16 terms and multiplies six of the nine pairs, bf16 storage has every weight in two."""
+    return 2.0 if wl.elem_bytes == 2 else 6.0
 
 
 def fused_roofline_of(wl, sec, lkc, residual):
@@ -258,8 +257,7 @@ def backward_roofline_of(wl, sec):
 
 def ffn_roofline_of(wl, sec, with_module):
     """ConvFFN (hidden width 2 C): x read once, out written once; the two point-wise layers on the
-    bf16 matrix cores (`achieved` counts the instructions issued: fp32 storage six of the nine products of three bf16
-    terms each, bf16 storage two), the 3 x 3 branch and the two GELUs per hidden element on the vector units.  with_module: the whole residual step, the fused module's work and bytes added
+    bf16 matrix cores (`achieved` counts the instructions issued, `terms_per_product` per block of products), the 3 x 3 branch and the two GELUs per hidden element on the vector units.  with_module: the whole residual step, the fused module's work and bytes added
     (the tensor between the two calls is written and read once more: it is an output and an input)."""
     P = wl.N * wl.H * wl.W
     Ch = 2 * wl.C
@@ -275,7 +273,7 @@ def ffn_roofline_of(wl, sec, with_module):
         f_taps = 2.0 * wl.Ks * wl.Ks * P * wl.Ca
     else:
         f_taps = 0.0
-    issued = 2.0 if wl.elem_bytes == 2 else 6.0   # (ConvFFN in one launch; Conv_fuse is priced as its layers are)
+    issued = terms_per_product(wl)
     taps_peak = BF16_MFMA_PEAK_TFLOPS if taps_on_matrix_cores(wl) else FP32_VECTOR_PEAK_TFLOPS
     t = {"hbm": b_alg / (HBM_PEAK_GBS * 1e9), "mfma": issued * f_mat / (BF16_MFMA_PEAK_TFLOPS * 1e12),
          "alu": f_vec / (FP32_VECTOR_PEAK_TFLOPS * 1e12) + f_taps / (taps_peak * 1e12)}

@@ -128,6 +128,12 @@ esc_status esc_dynkernel_gen(const void *x, esc_dtype dt, int N, int C, int H, i
  *   out    [N,C,H,W] storage type dt (written, every element)
  * With gen != NULL the result equals esc_dynkernel_gen followed by this call
  * with dk_in, bit for bit.
+ * fp32 storage up to Ks = 13: fp32 arithmetic.  bf16 storage up to Ks = 17: the stored values and
+ * the weights rounded to bf16, on the matrix cores, fp32 accumulation.  Larger kernels: values and
+ * weights as two fp16 terms each (scaled by powers of two; within a unit of fp32's last place, bf16
+ * values exact), three of the four products of terms accumulated in fp32 (what is left out lies
+ * below 2^-22 of a product); where the magnitudes in a tile (64 x 32 or 64 x 64 outputs and the halo) or
+ * in a channel's kernel lie more than 2^27 apart, or are not all finite, fp32 arithmetic.
  */
 esc_status esc_convattn_forward(const void *x, esc_dtype dt, int N, int C, int H, int W, int C_a,
                                 const float *lk, int Ks, long lk_channel_stride,
@@ -241,8 +247,10 @@ esc_status esc_residual_step_forward(const void *f_in, esc_dtype dt, int N, int 
  * bf16 storage on the stored values, each fp32 weight applied as the sum of two bf16 terms
  * (w = hi + lo to 16 mantissa bits; products exact); fp32 storage with Ks <= 13 on values
  * split exactly into three fp16 terms and weights into two (to a unit of fp32's last place; both scaled
- * first), four products of terms accumulated (what is left out lies below 2^-22 of a product: fp32
- * accuracy).  Otherwise fp32 instructions (bf16 storage widened exactly).  Limits:
+ * by powers of two first), four products of terms accumulated (what is left out lies below 2^-22 of a
+ * product: fp32 accuracy) - where the magnitudes in a tile (4 x 32 outputs and the halo, all channels) or
+ * in the kernel of an output channel lie more than 2^27 apart, or are not all finite, on three exact bf16
+ * terms of both and six products (2^-24).  Otherwise fp32 instructions (bf16 storage widened exactly).  Limits:
  * C_a <= 64, Ks odd <= 17.
  * The workspace is esc_dense_workspace_bytes large (the forward's workspace, DK and the
  * rearranged weights), prepared with esc_workspace_init.  Two launches on `stream`; with an
@@ -270,10 +278,13 @@ esc_status esc_convattn_dense_forward(const void *x, esc_dtype dt, int N, int C,
  *   accumulate != 0: the parameter gradients (grad_lk, grad_gen) are ADDED to the buffers'
  *            contents - the way a kernel shared by many modules collects its gradient
  * x, lk, gen and dk_in are the forward's inputs.  fp32 accumulation throughout; every sum
- * has a fixed order.  grad_lk's correlation of grad_out with x runs, for Ks <= 15, on the
- * bf16 matrix instructions with exact products: bf16 values as they are, fp32 values each
- * split into three bf16 terms (exactly, but for values below 2^-102), all nine products of
- * terms accumulated.  The workspace is esc_backward_workspace_bytes large, prepared with
+ * has a fixed order.  grad_lk's correlation of grad_out with x runs on the 16-bit matrix
+ * instructions: bf16 values as they are (products exact), fp32 values each as two fp16 terms
+ * (scaled by powers of two; within a unit of fp32's last place), three of the four products of
+ * terms accumulated (what is left out lies below 2^-22 of a product).  fp32 tiles (64 x 32) whose
+ * magnitudes, of x or of grad_out, lie more than 2^27 apart, and with fp32 storage or Ks > 15 those with
+ * infinities or NaN, are summed in fp32 arithmetic.  The input gradient's convolution is
+ * esc_convattn_forward's.  The workspace is esc_backward_workspace_bytes large, prepared with
  * esc_workspace_init.  Four launches on `stream`.
  */
 typedef struct esc_gen_grads {

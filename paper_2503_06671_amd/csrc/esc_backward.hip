@@ -68,7 +68,8 @@ extern __shared__ __align__(16) float bw_lds[];
 // moved by one element; a lane reads four whole words from the copy of its parity.  The four
 // wavefronts take eight rows each (neighbouring rows share their A operands, see there) and add
 // their results through LDS; the sum of x (for the GAP) comes from the halo tile's loads.  The partial sums of a
-// tile end with it.  Bound by LDS reads.
+// tile end with it.  Bound by no unit alone (16 x 64 x 64 fp32 13 x 13: the LDS at work in 47 % of the clocks, vector instructions 37 %, matrix
+// cores 15 %): one tile a block, its loads, its range and its sums one behind the other.
 // 64 x 64 x 64, the whole backward: 17 x 17 bf16 79 us -> 43, fp32 98 -> 80 (31 x 31 196 -> 71 and 223 -> 101), by a vector kernel
 // with the window's rows in registers until then; 13 x 13 fp32 71 -> 61 and 16 x 64 x 64 28.6 -> 26.8, with three bf16 terms and nine
 // products until then, error against float64 4.8e-7 -> 1.6e-7 (products with a low term summed apart; together 5.0e-7).

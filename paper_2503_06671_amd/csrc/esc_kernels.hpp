@@ -3,10 +3,11 @@
 // kernel for one kernel size per translation unit) and by esc_api.hip (host side, C ABI).
 //
 // The operation is Eq. 4 of the ESC paper with the depth-wise large kernel of
-// the paragraph around Eq. 5.  With fp32 storage everything is plain fp32 vector
+// the paragraph around Eq. 5.  With fp32 storage and Ks <= 13 everything is plain fp32 vector
 // arithmetic (a depth-wise convolution has no reduction shared between outputs); with
 // bf16 storage and Ks <= 17 the tap loop multiplies bf16 tile rows with the kernel rows'
-// Toeplitz matrices on the matrix cores, fp32 accumulation (MatrixGeom).
+// Toeplitz matrices on the matrix cores, fp32 accumulation (MatrixGeom); larger kernels do the same
+// with fp16 terms of values and weights (SplitGeom).
 //
 // One launch does the whole forward.  The work is cut into items, in this order in
 // every die's list:
@@ -978,11 +979,12 @@ struct MatrixGeom {
 // of their own; bf16 values are a term each.  K of an instruction is sixteen columns of two
 // neighbouring tile rows, i.e. two kernel rows at once: sixteen outputs need NQ = 2 or 3 runs of
 // sixteen columns, and a B operand serves every block of outputs that needs its run.
-// Error against float64: 540 x 960, Ks = 31 4.3e-7 -> 1.6e-7, Ks = 17 2.7e-7 -> 1.6e-7.
+// Error against float64 of the attention channels: 540 x 960, Ks = 31 4.3e-7 -> 1.6e-7, Ks = 17 2.7e-7 -> 1.6e-7.
 //
-// Bound by LDS reads (per pair of kernel rows 60 clocks for the A operands, 8 for a B operand's term, against 16 a
-// product).  540 x 960 fp32 Ks = 31 193 -> 97 us a call, Ks = 17 78.6 -> 63.5 (the copy alone takes 52), bf16
-// Ks = 31 176 -> 72, 64 x 64 fp32 Ks = 31 24.0 -> 12.3, Ks = 17 9.5 -> 8.6.  Smaller kernels keep the
+// Bound by no unit alone: at 540 x 960 with Ks = 31 the LDS is at work in 61 % of the clocks (a third of them bank conflicts), vector
+// instructions issue in 61 % (most in front of the loop and behind it: looking the range through, splitting, DK's taps), the matrix cores work in 39 %.
+// 540 x 960 fp32 Ks = 31 174 -> 98 us a call, Ks = 17 81 -> 65 (the copy alone takes 52), bf16
+// Ks = 31 174 -> 74, 64 x 64 fp32 Ks = 31 23.7 -> 12.8, Ks = 17 9.7 -> 8.9.  Smaller kernels keep the
 // vector loop: with Ks = 13 this one takes 8.3 us at 64 x 64, so 8.1, 10.8 and 10.35 at 180 x 320, 30.6 and 25.7 at 339 x 511.
 //
 // LDS: the terms' tiles, each laid out as in MatrixGeom, and the weights as rows of fp16 terms with
@@ -1001,7 +1003,7 @@ struct SplitGeom {
     static constexpr int WTERM = (KS + 1) * WROW;
     static constexpr int PAIRS = (KS + 1) / 2;
     // Two-row blocking, three runs: two wavefronts share sixteen rows by pairs of kernel rows, not by columns, so that a B
-    // operand serves three blocks and an A operand four (otherwise two; the loop is bound by LDS reads), and add up through LDS.
+    // operand serves three blocks and an A operand four (otherwise two), and add up through LDS.
     static constexpr bool HALVES = RY == 2 && NQ == 3;
     static constexpr int NT = HALVES ? 4 : RY;   // blocks of 16 x 16 outputs a wavefront works on
     static_assert(KS < 3 || (G::HR % 2 == 0 && G::HC + A <= COLS), "the halo does not fit");
