@@ -133,7 +133,8 @@ esc_status esc_dynkernel_gen(const void *x, esc_dtype dt, int N, int C, int H, i
  * weights as two fp16 terms each (scaled by powers of two; within a unit of fp32's last place, bf16
  * values exact), three of the four products of terms accumulated in fp32 (what is left out lies
  * below 2^-22 of a product); where the magnitudes in a tile (64 x 32 or 64 x 64 outputs and the halo) or
- * in a channel's kernel lie more than 2^27 apart, or are not all finite, fp32 arithmetic.
+ * in a channel's kernel lie more than 2^27 apart, or are not all finite, or where such a kernel has fewer
+ * than sixteen taps that are not zero, fp32 arithmetic.
  */
 esc_status esc_convattn_forward(const void *x, esc_dtype dt, int N, int C, int H, int W, int C_a,
                                 const float *lk, int Ks, long lk_channel_stride,

@@ -494,12 +494,20 @@ def test_large_kernels_of_wide_range(oracle, dtype, Ks, N, H, W):
         got = gu.att_as_f64(gu.run_forward(wl, use_gen=False, dk_in=d), wl)
         bound = (Ks * Ks + 17) * 2.0 ** -23 * mags + (2.0 ** -8 * np.abs(ref) if dtype == BF16 else 0.0)
         assert (np.abs(got - ref) <= bound).all(), (what, (np.abs(got - ref) / bound).max())
-    # a kernel of a single one, times 2^-13 ... 2^14 (the widest range the terms are used for): the values to a unit of their last place
-    xf = np.sign(base.x_as_f32()) * (1.0 + rng.random(base.x.shape)) * 2.0 ** rng.integers(-13, 15, base.x.shape)
-    wl.x = wk.f32_to_bf16_bits(xf.astype(np.float32)) if dtype == BF16 else xf.astype(np.float32)
-    wl.lk = np.broadcast_to(centre, base.lk.shape).astype(np.float32)
-    got, want = gu.att_as_f64(gu.run_forward(wl, use_gen=False), wl), wl.x_as_f32()[:, :4].astype(np.float64)
-    assert (np.abs(got - want) <= 2.0 ** -23 * np.abs(want)).all()
+    # a kernel of a single one moves the values as they are
+    xf = np.sign(base.x_as_f32()) * (1.0 + rng.random(base.x.shape))
+    mixed = (xf * 2.0 ** rng.integers(-13, 15, xf.shape)).astype(np.float32)
+    wl.x = wk.f32_to_bf16_bits(mixed) if dtype == BF16 else mixed
+    wl.lk = np.array(np.broadcast_to(centre, base.lk.shape), np.float32)
+    assert np.array_equal(gu.run_forward(wl, use_gen=False)[:, :4], wl.x[:, :4])
+    # five by four taps; values of 2^-13 in the left half and of 2^14 in the right: the widest range the terms are used for
+    xf = (xf * np.where(np.arange(W) < W // 2, 2.0 ** -13, 2.0 ** 14)).astype(np.float32)
+    wl.x = wk.f32_to_bf16_bits(xf) if dtype == BF16 else xf
+    wl.lk[:, Ks // 2 - 2:Ks // 2 + 3, Ks // 2 - 2:Ks // 2 + 2] = rng.standard_normal((4, 5, 4))
+    ref, _, _ = oracle.convattn_forward(wl.x, 4, wl.lk, dtype, want_out=False)
+    mags, _, _ = oracle.convattn_forward(wl.x & 0x7fff if dtype == BF16 else np.abs(wl.x), 4, np.abs(wl.lk), dtype, want_out=False)
+    got = gu.att_as_f64(gu.run_forward(wl, use_gen=False), wl)
+    assert (np.abs(got - ref) <= (20 + 8) * 2.0 ** -23 * mags + (2.0 ** -8 * np.abs(ref) if dtype == BF16 else 0.0)).all()
 
 
 @pytest.mark.parametrize("dtype,Ks", [(F32, 15), (F32, 17), (F32, 31), (BF16, 19), (BF16, 31)])
